@@ -15,7 +15,7 @@ _ROOT = os.path.dirname(_HERE)
 LIB_PATH = os.path.join(_HERE, "libefficientnav.so")
 _CSRC = os.path.join(_HERE, "csrc")
 SOURCES = [os.path.join(_CSRC, f) for f in
-           ("en_host.cpp", "en_tier.cpp", "en_gather.hip", "en_attn_prefill.hip", "en_attn_decode.hip",
+           ("en_host.cpp", "en_knapsack.cpp", "en_tier.cpp", "en_gather.hip", "en_attn_prefill.hip", "en_attn_decode.hip",
             "en_merge_mass.hip", "en_static_scratch.hip", "en_ceilings.hip")]
 HEADERS = [os.path.join(_CSRC, "en_internal.h"), os.path.join(_CSRC, "en_device.h"),
            os.path.join(_ROOT, "include", "efficientnav.h")]

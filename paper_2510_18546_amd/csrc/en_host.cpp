@@ -403,93 +403,6 @@ extern "C" int segment_select(const en_pool *pool, int32_t n_agents, const int32
     EN_GUARDED("segment_select", segment_select_impl(pool, n_agents, sel_host, sel_ptr_host, n_new, out));
 }
 
-// Eq. (1) as an exact 0/1 knapsack over token capacity: the groups with
-// p > threshold whose lengths fit the budget and whose summed (p - threshold) is
-// largest; among those the fewest tokens, then the lowest ids.
-// (the file is compiled without NaN semantics: finiteness is read from the bits)
-static inline bool finite_bits(float x)
-{
-    uint32_t u;
-    std::memcpy(&u, &x, sizeof u);
-    return (u & 0x7f800000u) != 0x7f800000u;
-}
-
-int en_knapsack(const float *p_host, const int32_t *len, int G, float threshold, int64_t budget_tokens,
-                std::vector<int32_t> &chosen)
-{
-    chosen.clear();
-    if (!finite_bits(threshold))
-        return fail(EN_ERR_INVALID_ARG, "retrieval knapsack: the threshold is not finite");
-    struct Item { int id; int64_t v; int w; };
-    std::vector<Item> items;
-    int64_t wsum = 0;
-    for (int g = 0; g < G; ++g) {
-        if (len[g] < 0)
-            continue;                       // not a candidate (a store group never put)
-        if (!finite_bits(p_host[g]))
-            return fail(EN_ERR_INVALID_ARG, "retrieval knapsack: score of group %d is not finite", g);
-        const double d = double(p_host[g]) - double(threshold);
-        const int64_t v = (int64_t)std::nearbyint(d * 4294967296.0);   // ties to even
-        if (v > 0) {
-            items.push_back({g, v, len[g]});
-            wsum += len[g];
-        }
-    }
-    const int m = int(items.size());
-    const int64_t W = std::min<int64_t>(budget_tokens, wsum);
-    if (wsum <= budget_tokens) {
-        for (auto &it : items)
-            chosen.push_back(it.id);
-        return EN_OK;
-    }
-    // best[a][w] over items a.. with capacity w: maximal value, then minimal
-    // tokens (two rolling rows). take[a][w] records whether taking item a is
-    // optimal at that state, ties included, so that the walk from item 0
-    // prefers the lowest ids (lexicographically smallest sorted list).
-    const size_t cols = size_t(W) + 1;
-    {
-        // one bit per (item, capacity) plus four rows of the capacity: refused beyond a stated size
-        const size_t need = size_t(m) * ((cols + 63) / 64) * 8 + cols * 24;
-        if (need > EN_KNAPSACK_MAX_BYTES)
-            return fail(EN_ERR_CAPACITY, "retrieval knapsack: %d candidates x %lld tokens of budget need a table of "
-                        "%zu bytes (limit %zu)", m, (long long)W, need, EN_KNAPSACK_MAX_BYTES);
-    }
-    std::vector<int64_t> vcur(cols, 0), vnext(cols, 0);
-    std::vector<int32_t> tcur(cols, 0), tnext(cols, 0);
-    const size_t words = (cols + 63) / 64;
-    std::vector<uint64_t> take(size_t(m) * words, 0);
-    for (int a = m - 1; a >= 0; --a) {
-        const int64_t vi = items[a].v;
-        const int wi = items[a].w;
-        uint64_t *tk = &take[size_t(a) * words];
-        for (int64_t w = 0; w <= W; ++w) {
-            int64_t bv = vnext[w];
-            int32_t bt = tnext[w];
-            if (wi <= w) {
-                const int64_t tv = vnext[w - wi] + vi;
-                const int32_t tt = tnext[w - wi] + wi;
-                if (tv > bv || (tv == bv && tt <= bt)) {
-                    bv = tv;
-                    bt = tt;
-                    tk[w >> 6] |= uint64_t(1) << (w & 63);
-                }
-            }
-            vcur[w] = bv;
-            tcur[w] = bt;
-        }
-        vcur.swap(vnext);
-        tcur.swap(tnext);
-    }
-    int64_t w = W;
-    for (int a = 0; a < m; ++a) {
-        if (take[size_t(a) * words + (w >> 6)] >> (w & 63) & 1) {
-            chosen.push_back(items[a].id);
-            w -= items[a].w;
-        }
-    }
-    return EN_OK;
-}
-
 static int segment_select_scored_impl(const en_pool *pool, const float *p_host, float threshold,
                                      int64_t budget_tokens, int32_t n_new, int32_t *sel_out_host,
                                      int32_t *n_sel_out, en_plan **out)
