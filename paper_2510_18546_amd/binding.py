@@ -72,14 +72,15 @@ def load(path: Optional[str] = None) -> C.CDLL:
     if not os.path.exists(path):
         _build.build()
     lib = C.CDLL(path)
-    vp, i32p = C.c_void_p, C.POINTER(C.c_int32)
+    # arrays of the host are passed by address (see _ip): a typed pointer object costs a microsecond to make
+    vp = i32p = f32p = C.c_void_p
     lib.kv_pool_create.argtypes = [C.POINTER(PoolDesc), vp, vp, i32p, C.POINTER(vp)]
     lib.kv_pool_set_scales.argtypes = [vp, vp, vp]
     lib.kv_pool_set_len.argtypes = [vp, C.c_int32, C.c_int32]
     lib.kv_pool_append.argtypes = [vp, C.c_int32, vp, vp, C.c_int32, vp]
     lib.kv_pool_destroy.argtypes = [vp]
     lib.segment_select.argtypes = [vp, C.c_int32, i32p, i32p, C.c_int32, C.POINTER(vp)]
-    lib.segment_select_scored.argtypes = [vp, C.POINTER(C.c_float), C.c_float, C.c_int64, C.c_int32,
+    lib.segment_select_scored.argtypes = [vp, f32p, C.c_float, C.c_int64, C.c_int32,
                                           i32p, i32p, C.POINTER(vp)]
     lib.en_plan_get_info.argtypes = [vp, C.POINTER(PlanInfo)]
     lib.en_plan_query.argtypes = [vp, C.c_int32, i32p, i32p]
@@ -105,7 +106,7 @@ def load(path: Optional[str] = None) -> C.CDLL:
                                           C.c_size_t, vp]
     lib.segmented_decode_step_static.argtypes = [vp, vp, C.c_int32, C.c_int32, vp, vp, vp, vp, vp, vp, vp, vp]
     lib.en_timing_enable.argtypes = [vp, C.c_int32]
-    lib.en_timing_collect.argtypes = [vp, C.POINTER(C.c_float), C.c_int32, i32p]
+    lib.en_timing_collect.argtypes = [vp, f32p, C.c_int32, i32p]
     lib.en_last_error.restype = C.c_char_p
     lib.en_ceiling_mfma_bf16.argtypes = [vp, C.c_size_t, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_double), vp]
     lib.en_ceiling_read_stream.argtypes = [vp, C.c_size_t, vp, C.c_size_t, C.c_int32, vp]
@@ -116,7 +117,7 @@ def load(path: Optional[str] = None) -> C.CDLL:
     lib.kv_tier_pool.restype = vp
     lib.kv_tier_put.argtypes = [vp, C.c_int32, vp, vp, C.c_int32]
     lib.kv_tier_append.argtypes = [vp, C.c_int32, vp, vp, C.c_int32, vp]
-    lib.kv_tier_select_scored.argtypes = [vp, C.POINTER(C.c_float), C.c_float, C.c_int64, i32p, i32p]
+    lib.kv_tier_select_scored.argtypes = [vp, f32p, C.c_float, C.c_int64, i32p, i32p]
     lib.kv_tier_fetch.argtypes = [vp, i32p, C.c_int32, i32p, vp]
     lib.kv_tier_fence.argtypes = [vp, vp]
     lib.kv_tier_prefetch.argtypes = [vp, i32p, C.c_int32, i32p]
@@ -140,15 +141,32 @@ def _i32(a) -> np.ndarray:
     return np.ascontiguousarray(a, dtype=np.int32)
 
 
-def _ip(a: np.ndarray):
-    return a.ctypes.data_as(C.POINTER(C.c_int32))
+def _ip(a: np.ndarray) -> int:
+    """Address of a contiguous array, which the caller keeps alive over the call."""
+    return a.ctypes.data
 
 
-def _stream(stream) -> C.c_void_p:
-    if stream is None:
-        import torch
-        stream = torch.cuda.current_stream().cuda_stream
-    return C.c_void_p(int(stream))
+_current_stream = None
+
+
+def _find_current_stream():
+    """The function that returns the handle of torch's current stream. torch.cuda.current_stream() makes a
+    stream object on the way, 2.9 us of every call into the library; the handle alone takes 0.1 us."""
+    import torch
+    torch.cuda.current_stream()          # sets the device up if nothing has yet
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw is None or device is None:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    return lambda: raw(device())
+
+
+def _stream(stream) -> int:
+    global _current_stream
+    if stream is not None:
+        return int(stream)
+    if _current_stream is None:
+        _current_stream = _find_current_stream()
+    return _current_stream()
 
 
 class Pool:
@@ -281,7 +299,7 @@ def segment_select_scored(pool: Pool, p, threshold: float, budget_tokens: int, n
     out = np.zeros(pool.desc.n_groups, dtype=np.int32)
     n = C.c_int32()
     h = C.c_void_p()
-    _check(load().segment_select_scored(pool.handle, p.ctypes.data_as(C.POINTER(C.c_float)),
+    _check(load().segment_select_scored(pool.handle, _ip(p),
                                         C.c_float(threshold), C.c_int64(int(budget_tokens)), n_new,
                                         _ip(out), C.byref(n), C.byref(h) if want_plan else None))
     return out[:n.value].copy(), (Plan(h, pool) if want_plan else None)
@@ -488,7 +506,7 @@ def kv_tier_select_scored(tier: Tier, p, threshold: float, budget_tokens: int) -
     assert p.shape == (tier.n_groups_total,)
     out = np.zeros(tier.n_groups_total, dtype=np.int32)
     n = C.c_int32()
-    _check(load().kv_tier_select_scored(tier.handle, p.ctypes.data_as(C.POINTER(C.c_float)), C.c_float(threshold),
+    _check(load().kv_tier_select_scored(tier.handle, _ip(p), C.c_float(threshold),
                                         C.c_int64(int(budget_tokens)), _ip(out), C.byref(n)))
     return out[:n.value].copy()
 
@@ -523,7 +541,7 @@ def timing_collect(pool: Pool, cap: int) -> np.ndarray:
     the last collect."""
     ms = np.zeros(cap, dtype=np.float32)
     n = C.c_int32()
-    _check(load().en_timing_collect(pool.handle, ms.ctypes.data_as(C.POINTER(C.c_float)), cap, C.byref(n)))
+    _check(load().en_timing_collect(pool.handle, _ip(ms), cap, C.byref(n)))
     return ms[:n.value].copy()
 
 
