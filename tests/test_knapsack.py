@@ -19,7 +19,7 @@ def instance(kind, rng):
     elif kind == "divisor":                    # around a multiple of 64 columns once divided
         lens, p = rng.integers(1, 9, n) * 24, rng.standard_normal(n)
     elif kind == "large values":
-        p = rng.standard_normal(n) * 2.0 ** 28
+        p = rng.standard_normal(n) * 2.0 ** 20
     return lens.astype(np.int32), p.astype(np.float32)
 
 
