@@ -471,118 +471,287 @@ __global__ __launch_bounds__(64 * SUB) void attn_decode_kernel(EnAttnArgs a)
 }
 
 // ---------------------------------------------------------------------------
-// attn_f32: one wave per (agent, head, query) row and KV split. Lanes stride
-// over the keys with a private online softmax; lanes are merged at each bucket
-// end (for the mass) and at the end of the row.
-// grid: (ceil(rows/4), n_splits), 256 threads.
+// attn_f32: attention in single precision on the fp32 matrix instruction (16 x 16 x 4, exact products,
+// fp32 sums), for small layers and short steps, which are bound by latency: the chain of a wave's trips
+// to memory and of its dependent products, not by bytes or operations.
+//
+// A workgroup takes 16 of the r * N_q query rows of a KV head and one KV split, and its eight waves share
+// the split's keys: each a contiguous run of 16-key blocks, with a softmax state of its own; they merge
+// through LDS, so a step of few keys needs no launch behind this one. (One wave per row, the lanes 64 keys
+// apart with a row of K and of V each, took 34 us for 4 heads x 64 rows over 192 keys.)
+//
+// S^T = K Q^T: lane l holds key l % 16, dimensions 4 (l / 16) .. + 3 of every 16: one 16-byte load each, and
+// its four numbers are the operands of four instructions (K and Q agree on which dimension is which k). The
+// result, keys 4 (l / 16) + e of query l % 16, is the B operand of O^T += V^T P^T as it is: instruction e
+// takes the keys 4 k + e. Row l % 16 of V^T block d is dimension (l % 16) * D / 16 + d, so that a lane's
+// values of a key are contiguous. No operand goes through LDS.
 // ---------------------------------------------------------------------------
+constexpr int F32_WAVES = 8;
+constexpr int F32_ROWS = EN_F32_ROWS;
+constexpr int F32_KEYS = 16;
+
 template <int D>
-__global__ __launch_bounds__(256) void attn_f32_kernel(EnAttnArgs a)
+__global__ __launch_bounds__(64 * F32_WAVES) void attn_f32_kernel(EnAttnArgs a)
 {
-    __shared__ float qs[4][D];
-    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-    const size_t rows = (size_t)a.B * a.Hq * a.Nq;
-    const size_t row = (size_t)blockIdx.x * 4 + wave;
-    const int sp = blockIdx.y;
-    const bool valid = row < rows;
-    // row = (b*Hq + hq)*Nq + i
-    const int i = valid ? (int)(row % a.Nq) : 0;
-    const int hq = valid ? (int)((row / a.Nq) % a.Hq) : 0;
-    const int b = valid ? (int)(row / ((size_t)a.Nq * a.Hq)) : 0;
+    constexpr int NJ = D / 16;                   // 16-byte loads per key row and lane; blocks of O^T
+    constexpr int NV = D / 64;                   // 16-byte loads per value row and lane
+    constexpr int OSTR = D + 4;                  // floats per merged row in LDS
+    __shared__ __attribute__((aligned(16))) float so[F32_WAVES][F32_ROWS][OSTR];
+    __shared__ f32x2 sml[F32_WAVES][F32_ROWS];           // (reference, sum) of a wave's rows
+    __shared__ f32x2 sfirst[F32_WAVES][F32_ROWS];        // (sum, reference) of the bucket that a wave entered midway
+    __shared__ int sspan[F32_WAVES];                     // 1: ... and that it did not leave
+
+    int t = blockIdx.x;
+    const int rg = t % a.n_ptiles;
+    t /= a.n_ptiles;
+    const int sp = t % a.n_splits;
+    t /= a.n_splits;
+    const int kvh = t % a.Hkv;
+    const int b = t / a.Hkv;
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+    const int lane = tid % 64;
+    const int col = lane % 16, grp = lane / 16;
     const int r = a.Hq / a.Hkv;
-    const int kvh = hq / r;
-    const int S = a.nseg[b];
-    const int32_t *bnd = a.bnd + (size_t)b * (a.Smax + 2);
-    const int Lc = bnd[S] + a.q_first;       // rows are new tokens q_first .. q_first+Nq-1
+
+    const en_table_ptr hdr = as_table(a.hdr + 4 * (size_t)b);
+    const en_table_ptr bnd = as_table(a.bnd + (size_t)b * (a.Smax + 2));
+    const int S = hdr[0];
+    const int Lc = hdr[1] + a.q_first;       // rows are new tokens q_first .. q_first+Nq-1
     const int Ltot = Lc + a.Nq;
     const int ntiles = (Ltot + EN_KEY_TILE - 1) / EN_KEY_TILE;
     const int kbeg = (int)split_first_tile(sp, ntiles, a.n_splits) * EN_KEY_TILE;
-    const int kend_split = min((int)split_first_tile(sp + 1, ntiles, a.n_splits) * EN_KEY_TILE, Ltot);
-    const int kend = min(kend_split, Lc + i + 1);       // causal limit
+    const int kend = min((int)split_first_tile(sp + 1, ntiles, a.n_splits) * EN_KEY_TILE, Ltot);
 
-    // rotated, scaled query in LDS
-    if (valid && lane < D / 2) {
-        const float *qp = (const float *)a.q + (((size_t)b * a.Nq + i) * a.Hq + hq) * D;
-        const int pos = Lc + i;
-        const float cs = a.cos_tab[(size_t)pos * (D / 2) + lane];
-        const float sn = a.sin_tab[(size_t)pos * (D / 2) + lane];
-        const float x1 = qp[lane], x2 = qp[lane + D / 2];
-        qs[wave][lane] = (x1 * cs - x2 * sn) * a.scale_log2e;
-        qs[wave][lane + D / 2] = (x2 * cs + x1 * sn) * a.scale_log2e;
-    }
-    __syncthreads();
-    if (!valid)
-        return;
+    // the workgroup's rows, head by head: row rr is new token rr % Nq of head rr / Nq
+    const int n_rows = r * a.Nq;
+    const int r0 = rg * F32_ROWS, r1 = min(r0 + F32_ROWS, n_rows) - 1;
+    const int i_hi = r0 / a.Nq == r1 / a.Nq ? r1 % a.Nq : a.Nq - 1;
+    const bool row_valid = r0 + col <= r1;
+    const int rr = min(r0 + col, r1);
+    const int hq = kvh * r + rr / a.Nq, i_row = rr % a.Nq;
+    const int kvis = min(kend, Lc + i_hi + 1);           // keys that any of the rows may see
+    const int n_blk = kvis > kbeg ? (kvis - kbeg + F32_KEYS - 1) / F32_KEYS : 0;
+    const int per = (n_blk + F32_WAVES - 1) / F32_WAVES;
+    const int n_used = per > 0 ? (n_blk + per - 1) / per : 0;          // waves with keys
+    const int wb = kbeg + min(wave * per, n_blk) * F32_KEYS;           // this wave's keys
+    const int we = min(kbeg + min((wave + 1) * per, n_blk) * F32_KEYS, kvis);
 
     const float *K = (const float *)a.kc + ((size_t)b * a.Hkv + kvh) * (size_t)a.T * D;
     const float *V = (const float *)a.vt + ((size_t)b * a.Hkv + kvh) * (size_t)a.T * D;
-    float m = EN_NEG_INF, l = 0.f;
-    float o[D];
+    // (context rows are zero up to a multiple of 64 keys: whole blocks can be read)
+    f32x4 kf[NJ], vf[4][NV];
+    auto load_block = [&](int kb) {
+        const float *kr = K + (size_t)(kb + col) * D + 4 * grp;
 #pragma unroll
-    for (int d = 0; d < D; ++d)
-        o[d] = 0.f;
-    float *seg_base = a.ws_seg ? a.ws_seg + ((((size_t)sp * a.B + b) * a.Hq + hq) * (a.Smax + 1)) * a.Nq * 2
-                               : nullptr;
+        for (int j = 0; j < NJ; ++j)
+            kf[j] = *reinterpret_cast<const f32x4 *>(kr + 16 * j);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float *vr = V + (size_t)(kb + 4 * grp + e) * D + col * NJ;
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+                vf[e][v] = *reinterpret_cast<const f32x4 *>(vr + 4 * v);
+        }
+    };
+    if (wb < we)
+        load_block(wb);
 
-    for (int bucket = 0; bucket <= S; ++bucket) {
-        const int lo = max(bnd[bucket], kbeg);
-        const int hi = min(bnd[bucket + 1], kend);
-        const bool touches = bnd[bucket + 1] > bnd[bucket] && max(bnd[bucket], kbeg) < min(bnd[bucket + 1], kend_split);
-        float seg = 0.f, seg_m = m;
-        for (int j = lo + lane; j < hi; j += 64) {
-            const float *kr = K + (size_t)j * D;
-            float acc = 0.f;
+    // ---- the query, rotated at L_c + i and scaled ----
+    f32x4 qf[NJ];
+    {
+        const float *qp = (const float *)a.q + (((size_t)b * a.Nq + i_row) * a.Hq + hq) * D + 4 * grp;
+        const size_t trow = (size_t)(Lc + i_row) * (D / 2) + 4 * grp;
 #pragma unroll
-            for (int d = 0; d < D; d += 4) {
-                const f32x4 kv = *reinterpret_cast<const f32x4 *>(kr + d);
-                acc += qs[wave][d] * kv[0] + qs[wave][d + 1] * kv[1] + qs[wave][d + 2] * kv[2] +
-                       qs[wave][d + 3] * kv[3];
-            }
-            const float mn = fmaxf(m, acc);
-            const float alpha = exp2f(m - mn);      // m = -inf -> 0
-            const float p = exp2f(acc - mn);
-            l = l * alpha + p;
-            seg = seg * alpha + p;
-            const float *vr = V + (size_t)j * D;
+        for (int j = 0; j < NJ; ++j)
+            qf[j] = *reinterpret_cast<const f32x4 *>(qp + 16 * j);
 #pragma unroll
-            for (int d = 0; d < D; d += 4) {
-                const f32x4 vv = *reinterpret_cast<const f32x4 *>(vr + d);
-                o[d] = o[d] * alpha + p * vv[0];
-                o[d + 1] = o[d + 1] * alpha + p * vv[1];
-                o[d + 2] = o[d + 2] * alpha + p * vv[2];
-                o[d + 3] = o[d + 3] * alpha + p * vv[3];
-            }
-            m = mn;
-        }
-        seg_m = m;
-        if (touches && seg_base) {
-            // merge the lanes' partial sums of this bucket
-            const float M = wave_max(seg_m);
-            const float w = (seg_m == EN_NEG_INF) ? 0.f : exp2f(seg_m - M);
-            const float tot = wave_sum(seg * w);
-            if (lane == 0) {
-                f32x2 v = {tot, M};
-                *reinterpret_cast<f32x2 *>(seg_base + ((size_t)bucket * a.Nq + i) * 2) = v;
-            }
+        for (int j = 0; j < NJ / 2; ++j) {
+            const f32x4 cs = *reinterpret_cast<const f32x4 *>(a.cos_tab + trow + 16 * j);
+            const f32x4 sn = *reinterpret_cast<const f32x4 *>(a.sin_tab + trow + 16 * j);
+            const f32x4 x1 = qf[j], x2 = qf[j + NJ / 2];
+            qf[j] = (x1 * cs - x2 * sn) * a.scale_log2e;
+            qf[j + NJ / 2] = (x2 * cs + x1 * sn) * a.scale_log2e;
         }
     }
-    // merge lanes
-    const float M = wave_max(m);
-    const float w = (m == EN_NEG_INF) ? 0.f : exp2f(m - M);
-    const float l_tot = wave_sum(l * w);
-    if (a.ws_ml && lane == 0) {
-        f32x2 v = {M, l_tot};
-        *reinterpret_cast<f32x2 *>(a.ws_ml + ((size_t)sp * rows + row) * 2) = v;
-    }
-    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-    float *op = (a.n_splits == 1) ? (float *)a.out + (((size_t)b * a.Nq + i) * a.Hq + hq) * D
-                                  : (float *)a.ws_opart + ((size_t)sp * rows + row) * D;
+
+    f32x4 o[NJ];
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-        const float tot = wave_sum(o[d] * w);
-        if (lane == (d & 63))
-            op[d] = tot * inv;
+    for (int j = 0; j < NJ; ++j)
+        o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m = EN_NEG_INF, l = 0.f, seg = 0.f;            // l, seg: this lane's share
+    auto row_sum = [](float v) {                         // over the four lanes of a row
+        v += __shfl_xor(v, 16, 64);
+        return v + xor32(v);
+    };
+    float *seg_row = a.ws_seg ? a.ws_seg + ((((size_t)sp * a.B + b) * a.Hq + hq) * (a.Smax + 1)) * a.Nq * 2
+                              : nullptr;
+    auto write_bucket = [&](int s, float tot, float ref) {
+        if (seg_row && row_valid && grp == 0) {
+            f32x2 v = {tot, ref};
+            *reinterpret_cast<f32x2 *>(seg_row + ((size_t)s * a.Nq + i_row) * 2) = v;
+        }
+    };
+    // The bucket the wave is in. One that an earlier wave began is handed over through sfirst, one that a
+    // later wave goes on with stays open; the others are complete here.
+    int cur = wb < we ? find_bucket(bnd, S, wb) : 0;
+    int cur_end = wb < we ? bnd[cur + 1] : 0;
+    const bool entered = wb < we && wb > kbeg && bnd[cur] < wb;
+    bool first = entered, open = false;
+    auto leave_bucket = [&]() {
+        const float tot = row_sum(seg);
+        if (first)
+            sfirst[wave][col] = f32x2{tot, m};
+        else
+            write_bucket(cur, tot, m);
+        first = false;
+        seg = 0.f;
+    };
+
+    for (int kb = wb; kb < we; kb += F32_KEYS) {
+        // ---- scores; two chains of products ----
+        f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
+#pragma unroll
+        for (int j = 0; j < NJ; j += 2)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j][e], qf[j][e], s0, 0, 0, 0);
+                s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j + 1][e], qf[j + 1][e], s1, 0, 0, 0);
+            }
+        f32x4 vc[4][NV];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+                vc[e][v] = vf[e][v];
+        if (kb + F32_KEYS < we)
+            load_block(kb + F32_KEYS);
+        f32x4 p = s0 + s1;
+        // causal mask; keys of a later wave or split do not occur: ranges are whole blocks up to kvis
+        const int rel = min(Lc + i_row, we - 1) - kb - 4 * grp;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (e > rel)
+                p[e] = EN_NEG_INF;
+        float mn = fmaxf(fmaxf(p[0], p[1]), fmaxf(p[2], p[3]));
+        mn = fmaxf(mn, __shfl_xor(mn, 16, 64));
+        mn = fmaxf(m, pair_max(mn));
+        const float ref = mn == EN_NEG_INF ? 0.f : mn;   // nothing seen yet: all exponentials are 0
+        const float alpha = fast_exp2(m - ref);
+        m = mn;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            p[e] = fast_exp2(p[e] - ref);
+        l = l * alpha + ((p[0] + p[1]) + (p[2] + p[3]));
+        // ---- per-bucket sums ----
+        seg *= alpha;
+        const int ke = min(kb + F32_KEYS, we);
+        if (cur_end > ke) {
+            seg += (p[0] + p[1]) + (p[2] + p[3]);
+        } else {
+            int lo = kb;
+            while (true) {
+                const int hi = min(cur_end, ke);
+                const int rlo = lo - kb - 4 * grp, rhi = hi - kb - 4 * grp;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    seg += (e >= rlo && e < rhi) ? p[e] : 0.f;
+                if (cur_end > ke || cur > S)
+                    break;
+                if (cur_end > bnd[cur])      // (an empty bucket has no entry)
+                    leave_bucket();
+                ++cur;
+                cur_end = cur <= S ? bnd[cur + 1] : 0x7fffffff;
+                lo = hi;
+            }
+        }
+        // ---- O^T += V^T P^T ----
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+            o[j] *= alpha;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+                o[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(vc[e][j / 4][j % 4], p[e], o[j], 0, 0, 0);
     }
+
+    // ---- the waves meet ----
+    float open_sum = 0.f;
+    if (wb < we) {
+        open = cur <= S && cur_end > we && bnd[cur] < we && we < kvis;
+        if (open) {
+            open_sum = row_sum(seg);
+            if (first && grp == 0)
+                sfirst[wave][col] = f32x2{open_sum, m};
+        } else if (cur <= S && bnd[cur] < we && cur_end > we) {
+            leave_bucket();                  // the split, or what the rows may see, ends in it
+        }
+        const float lt = row_sum(l);
+        if (grp == 0)
+            sml[wave][col] = f32x2{m, lt};
+        if (lane == 0)
+            sspan[wave] = open && first;
+    } else if (n_used == 0 && wave == 0) {
+        write_bucket(S, 0.f, EN_NEG_INF);    // a split beyond the rows' causal limit: only new tokens
+    }
+    __syncthreads();
+    float M = EN_NEG_INF;
+    for (int w = 0; w < n_used; ++w)
+        M = fmaxf(M, sml[w][col][0]);
+    if (wb < we) {
+        const float keep = m == EN_NEG_INF ? 0.f : fast_exp2(m - M);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                f32x4 x;
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    x[j] = o[4 * v + j][e] * keep;
+                *reinterpret_cast<f32x4 *>(&so[wave][col][(4 * grp + e) * NJ + 4 * v]) = x;
+            }
+        if (open && !first) {
+            // the bucket began here and goes on in the next waves: their shares join, as far as it reaches
+            float tot = open_sum, ref = m;
+            for (int w = wave + 1; w < n_used; ++w) {
+                const f32x2 x = sfirst[w][col];
+                const float both = fmaxf(ref, x[1]);
+                const float to = both == EN_NEG_INF ? 0.f : both;
+                tot = tot * fast_exp2(ref - to) + x[0] * fast_exp2(x[1] - to);
+                ref = both;
+                if (!sspan[w])
+                    break;
+            }
+            write_bucket(cur, tot, ref);
+        }
+    }
+    __syncthreads();
+    // ---- one 16-byte piece of the output per thread ----
+    constexpr int CPR = D / 4;
+    const int row = tid / CPR, c4 = tid % CPR * 4;
+    if (tid >= F32_ROWS * CPR || r0 + row > r1)
+        return;
+    float Mr = EN_NEG_INF, L = 0.f;
+    for (int w = 0; w < n_used; ++w)
+        Mr = fmaxf(Mr, sml[w][row][0]);
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int w = 0; w < n_used; ++w) {
+        const f32x2 x = sml[w][row];
+        L += x[0] == EN_NEG_INF ? 0.f : x[1] * fast_exp2(x[0] - Mr);
+        acc += *reinterpret_cast<const f32x4 *>(&so[w][row][c4]);
+    }
+    const int h = kvh * r + (r0 + row) / a.Nq, i = (r0 + row) % a.Nq;
+    const size_t rows = (size_t)a.B * a.Hq * a.Nq;
+    const size_t out_row = ((size_t)b * a.Hq + h) * a.Nq + i;
+    const float inv = L > 0.f ? 1.f / L : 0.f;
+    if (a.ws_ml && c4 == 0) {
+        f32x2 v = {Mr, L};
+        *reinterpret_cast<f32x2 *>(a.ws_ml + ((size_t)sp * rows + out_row) * 2) = v;
+    }
+    float *op = (a.n_splits == 1) ? (float *)a.out + (((size_t)b * a.Nq + i) * a.Hq + h) * D
+                                  : (float *)a.ws_opart + ((size_t)sp * rows + out_row) * D;
+    *reinterpret_cast<f32x4 *>(op + c4) = acc * inv;
 }
 
 // ---------------------------------------------------------------------------
@@ -593,8 +762,7 @@ int en_launch_attention(const en_pool *pool, const EnAttnArgs &a, void *stream)
     hipStream_t st = (hipStream_t)stream;
     const int D = pool->d.head_dim;
     if (pool->d.dtype == EN_F32) {
-        const size_t rows = (size_t)a.B * a.Hq * a.Nq;
-        const dim3 grid((unsigned)((rows + 3) / 4), a.n_splits), blk(256);
+        const dim3 grid(a.total_wgs), blk(64 * F32_WAVES);
         if (D == 64)
             hipLaunchKernelGGL((attn_f32_kernel<64>), grid, blk, 0, st, a);
         else

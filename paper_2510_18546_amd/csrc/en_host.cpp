@@ -299,6 +299,24 @@ static int choose_splits(const en_pool *pool, const en_plan *pl)
             want = (tiles + longest - 1) / longest;
         return int(want);
     }
+    if (!computes_bf16(pool->d.dtype)) {
+        // fp32: a workgroup takes 16 rows, its eight waves share the split's keys 16 at a time, one block
+        // after the other; a second split costs the merge launch (about six blocks)
+        const long base = long(pl->B) * pool->d.n_kv_heads * ((r * pl->Nq + EN_F32_ROWS - 1) / EN_F32_ROWS);
+        const int tiles = std::max(1, (pl->max_ctx_len + EN_KEY_TILE - 1) / EN_KEY_TILE);
+        int best = 1;
+        long best_cost = -1;
+        for (int n = 1; n <= std::min(tiles, EN_MAX_SPLITS); ++n) {
+            const long rounds = (base * n + pool->n_cu - 1) / pool->n_cu;
+            const long blocks = ((tiles + n - 1) / n * (EN_KEY_TILE / 16) + EN_WAVES - 1) / EN_WAVES;
+            const long cost = rounds * (blocks + 3) + (n > 1 ? 6 : 0);
+            if (best_cost < 0 || cost < best_cost) {
+                best_cost = cost;
+                best = n;
+            }
+        }
+        return best;
+    }
     const int nqb = (pl->Nq + EN_ROWS_PER_WAVE - 1) / EN_ROWS_PER_WAVE;
     const int n_ptiles = (r * nqb + EN_WAVES - 1) / EN_WAVES;
     const long base = long(pl->B) * pool->d.n_kv_heads * n_ptiles;
@@ -942,6 +960,8 @@ static int run_attention(en_pool *pool, en_plan *plan, const void *q_dev, const 
     a.decode = decode_kernel_fits(pool, n_rows) ? 1 : 0;
     if (a.decode)
         a.n_ptiles = 1;
+    if (!computes_bf16(pool->d.dtype))
+        a.n_ptiles = (pool->r * n_rows + EN_F32_ROWS - 1) / EN_F32_ROWS;
     a.total_wgs = plan->B * pool->d.n_kv_heads * n_splits * a.n_ptiles;
     a.scale_log2e = softmax_scale_log2e(pool);
     a.app_k = a.decode ? app_k_dev : nullptr;

@@ -1,0 +1,25 @@
+"""The fp32 attention kernel where its pieces meet: eight waves share a split's keys in runs of 16-key
+blocks, a segment can lie inside one wave, cross one or many of their borders or fill several waves, and the
+16 rows of a workgroup can span heads. Against the oracle, to the fp32 tolerance of test_gpu_parity."""
+import pytest
+
+from paper_2510_18546_amd import inputs as I
+from test_gpu_parity import run_case, small, step_mod  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,kv,ratio,n_new,seg,n_sel,splits", [
+    (64, 1, 1, 1, 15, 1, None),        # one row, one block, seven idle waves
+    (64, 2, 3, 5, 16, 7, 1),           # rows of three heads in one workgroup; segments of one block
+    (128, 1, 4, 17, 1, 11, 1),         # sixteen rows and one; many segments inside a block
+    (128, 2, 1, 33, 127, 2, 1),        # segments over several waves, none on a border
+    (64, 1, 2, 64, 130, 9, 3),         # waves that lie whole inside a segment; three splits
+    (128, 1, 1, 129, 40, 3, 5),        # new tokens over the last splits: rows that see nothing of one
+    (64, 1, 7, 3, 0, 4, 2),            # empty segments
+])
+def test_fp32_waves_and_segments(step_mod, oracle, d, kv, ratio, n_new, seg, n_sel, splits):
+    cfg = small(f"f32-waves-{d}-{n_new}-{seg}", 700 + n_new, dtype=I.F32, head_dim=d, n_q_heads=kv * ratio,
+                n_kv_heads=kv, n_agents=2, capacity=max(seg, 1), len_lo=max(0, seg - 3), len_hi=seg, n_sel=n_sel,
+                n_new=n_new, rope_base=1e4)
+    run_case(step_mod, oracle, cfg, n_splits=splits)
