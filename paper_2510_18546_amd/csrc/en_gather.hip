@@ -39,6 +39,21 @@ __device__ __forceinline__ EnGatherTables stage_tables(const EnGatherArgs &a, in
     return t;
 }
 
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// A piece of the context goes out. STREAM: past the caches, for contexts that the last-level cache
+// cannot hold until the attention kernel reads them (see EnGatherArgs::stream; a template parameter: the
+// choice made at run time between two kinds of store cost 150 us of 1440).
+template <bool STREAM, typename P, typename V>
+__device__ __forceinline__ void store_context(P *dst, V v)
+{
+    V *p = reinterpret_cast<V *>(dst);
+    if constexpr (STREAM)
+        __builtin_nontemporal_store(v, p);
+    else
+        *p = v;
+}
+
 // Source row of context token `tok` for (agent b, KV head kvh); nullptr for
 // padding rows at or beyond L_c + N_q. `bnd` and `sel` are the agent's tables
 // (global or staged), S its number of segments.
@@ -68,7 +83,7 @@ __device__ __forceinline__ const T *context_src(const EnGatherArgs &a, P bnd, P 
 // per head, 0.73 ms without the table, which is what the value half takes).
 // 256 threads, 32 rows per pass.
 // ---------------------------------------------------------------------------
-template <typename T, int D, bool COPY_V, int HPB, typename P>
+template <typename T, int D, bool COPY_V, int HPB, bool STREAM, typename P>
 __device__ __forceinline__ void gather_k_rows(const EnGatherArgs &a, int tok, int kv0, P bnd, P sel, int S)
 {
     constexpr int E = D / 16;
@@ -86,28 +101,37 @@ __device__ __forceinline__ void gather_k_rows(const EnGatherArgs &a, int tok, in
     if constexpr (COPY_V)
         vsrc = context_src<T, D>(a, bnd, sel, S, (const T *)a.v_pool, (const T *)a.v_new, b, kv0, tok);
     const size_t hstride = tok >= bnd[S] ? (size_t)D : (size_t)a.C * D;      // new tokens [.., Hkv, D], pool [.., Hkv, C, D]
-    tvec x1[HPB], x2[HPB];
     fvec cs = 0.f, sn = 0.f;
     if (ksrc) {
-#pragma unroll
-        for (int h = 0; h < HPB; ++h) {
-            x1[h] = *reinterpret_cast<const tvec *>(ksrc + h * hstride + c * E);
-            x2[h] = *reinterpret_cast<const tvec *>(ksrc + h * hstride + D / 2 + c * E);
-        }
         cs = *reinterpret_cast<const fvec *>(a.cos_tab + (size_t)tok * (D / 2) + c * E);
         sn = *reinterpret_cast<const fvec *>(a.sin_tab + (size_t)tok * (D / 2) + c * E);
     }
-#pragma unroll
-    for (int h = 0; h < HPB; ++h) {
-        T *dst = (T *)a.kc + (((size_t)b * a.Hkv + kv0 + h) * a.T + tok) * D;
-        fvec y1 = 0.f, y2 = 0.f;
+    // Two heads at a time: the loads of all eight at once took 150 registers, three waves per SIMD for the
+    // value units of the launch too (64 agents x 16 K tokens: 1690 us, 1470 with two heads' loads in flight
+    // per wave and five waves).
+    constexpr int HU = HPB < 2 ? HPB : 2;
+#pragma unroll 1
+    for (int h0 = 0; h0 < HPB; h0 += HU) {
+        tvec x1[HU], x2[HU];
         if (ksrc) {
-            const fvec f1 = __builtin_convertvector(x1[h], fvec), f2 = __builtin_convertvector(x2[h], fvec);
-            y1 = f1 * cs - f2 * sn;
-            y2 = f2 * cs + f1 * sn;
+#pragma unroll
+            for (int h = 0; h < HU; ++h) {
+                x1[h] = *reinterpret_cast<const tvec *>(ksrc + (h0 + h) * hstride + c * E);
+                x2[h] = *reinterpret_cast<const tvec *>(ksrc + (h0 + h) * hstride + D / 2 + c * E);
+            }
         }
-        *reinterpret_cast<tvec *>(dst + c * E) = __builtin_convertvector(y1, tvec);
-        *reinterpret_cast<tvec *>(dst + D / 2 + c * E) = __builtin_convertvector(y2, tvec);
+#pragma unroll
+        for (int h = 0; h < HU; ++h) {
+            T *dst = (T *)a.kc + (((size_t)b * a.Hkv + kv0 + h0 + h) * a.T + tok) * D;
+            fvec y1 = 0.f, y2 = 0.f;
+            if (ksrc) {
+                const fvec f1 = __builtin_convertvector(x1[h], fvec), f2 = __builtin_convertvector(x2[h], fvec);
+                y1 = f1 * cs - f2 * sn;
+                y2 = f2 * cs + f1 * sn;
+            }
+            store_context<STREAM>(dst + c * E, __builtin_convertvector(y1, tvec));
+            store_context<STREAM>(dst + D / 2 + c * E, __builtin_convertvector(y2, tvec));
+        }
     }
     if constexpr (COPY_V) {
 #pragma unroll
@@ -126,7 +150,7 @@ __device__ __forceinline__ void gather_k_rows(const EnGatherArgs &a, int tok, in
 
 // The key rows of 64-token tile `tile` for the heads kv0 .. kv0 + HPB - 1, 32 rows at a time:
 // the halves first .. last of the tile.
-template <typename T, int D, bool COPY_V, int HPB>
+template <typename T, int D, bool COPY_V, int HPB, bool STREAM>
 __device__ __forceinline__ void gather_k_block(const EnGatherArgs &a, int tile, int first, int last, int kv0,
                                                int32_t *lbnd)
 {
@@ -137,10 +161,10 @@ __device__ __forceinline__ void gather_k_block(const EnGatherArgs &a, int tile, 
     for (int half = first; half <= last; ++half) {
         const int tok = tile * EN_KEY_TILE + half * 32 + threadIdx.x / 8;
         if (t.staged)
-            gather_k_rows<T, D, COPY_V, HPB>(a, tok, kv0, (const int32_t *)lbnd,
+            gather_k_rows<T, D, COPY_V, HPB, STREAM>(a, tok, kv0, (const int32_t *)lbnd,
                                              (const int32_t *)lbnd + EN_GATHER_TAB_LDS, S);
         else
-            gather_k_rows<T, D, COPY_V, HPB>(a, tok, kv0, t.bnd, t.sel, S);
+            gather_k_rows<T, D, COPY_V, HPB, STREAM>(a, tok, kv0, t.bnd, t.sel, S);
     }
 }
 
@@ -149,7 +173,7 @@ __device__ __forceinline__ void gather_k_block(const EnGatherArgs &a, int tile, 
 // transposed, vt[d][column], where token j sits at column j with bits 2 and 3
 // exchanged. 256 threads; bx = number of the 64-token tile.
 // ---------------------------------------------------------------------------
-template <int D>
+template <int D, bool STREAM>
 __device__ __forceinline__ void gather_vt_block(const EnGatherArgs &a, int bx, int kvh, int32_t *lbnd)
 {
     constexpr int STR = D + 2;                 // LDS row stride in elements
@@ -212,12 +236,12 @@ __device__ __forceinline__ void gather_vt_block(const EnGatherArgs &a, int bx, i
             const int tk = 16 * g16 + 8 * (e >> 2) + 4 * hf + (e & 3);
             v[e] = tile[tk * STR + d];
         }
-        uint4 o;
-        o.x = v[0] | ((uint32_t)v[1] << 16);
-        o.y = v[2] | ((uint32_t)v[3] << 16);
-        o.z = v[4] | ((uint32_t)v[5] << 16);
-        o.w = v[6] | ((uint32_t)v[7] << 16);
-        *reinterpret_cast<uint4 *>(vt + (size_t)d * a.T + ch * 8) = o;
+        u32x4 o;
+        o[0] = v[0] | ((uint32_t)v[1] << 16);
+        o[1] = v[2] | ((uint32_t)v[3] << 16);
+        o[2] = v[4] | ((uint32_t)v[5] << 16);
+        o[3] = v[6] | ((uint32_t)v[7] << 16);
+        store_context<STREAM>(reinterpret_cast<u32x4 *>(vt + (size_t)d * a.T + ch * 8), o);
     }
 }
 
@@ -278,7 +302,7 @@ __device__ __forceinline__ void prepare_queries(const EnGatherArgs &a, int part,
     }
 }
 
-template <typename T, int D, int HPB>
+template <typename T, int D, int HPB, bool STREAM>
 __global__ __launch_bounds__(256) void gather_kernel(EnGatherLaunch g)
 {
     EnGatherArgs a = g.a;
@@ -314,9 +338,9 @@ __global__ __launch_bounds__(256) void gather_kernel(EnGatherLaunch g)
     }
     const int hg = unit / PER, r = unit % PER;
     if (r < KU)
-        gather_k_block<T, D, sizeof(T) == 4, HPB>(a, tile, KU == 2 ? r : 0, KU == 2 ? r : 1, hg * HPB, lbnd);
+        gather_k_block<T, D, sizeof(T) == 4, HPB, STREAM>(a, tile, KU == 2 ? r : 0, KU == 2 ? r : 1, hg * HPB, lbnd);
     else if constexpr (sizeof(T) == 2)
-        gather_vt_block<D>(a, tile, hg * HPB + r - KU, lbnd);
+        gather_vt_block<D, STREAM>(a, tile, hg * HPB + r - KU, lbnd);
 }
 
 // ---------------------------------------------------------------------------
@@ -639,18 +663,27 @@ static int gather_heads_per_unit(const en_pool *pool, const EnGatherArgs &a, int
     return 1;
 }
 
-template <typename T, int D>
-static void launch_gather_kernel(int hpb, dim3 grid, hipStream_t st, const EnGatherLaunch &g)
+template <typename T, int D, bool STREAM>
+static void launch_gather_hpb(int hpb, dim3 grid, hipStream_t st, const EnGatherLaunch &g)
 {
     const dim3 blk(256);
     if (hpb == 8)
-        hipLaunchKernelGGL((gather_kernel<T, D, 8>), grid, blk, 0, st, g);
+        hipLaunchKernelGGL((gather_kernel<T, D, 8, STREAM>), grid, blk, 0, st, g);
     else if (hpb == 4)
-        hipLaunchKernelGGL((gather_kernel<T, D, 4>), grid, blk, 0, st, g);
+        hipLaunchKernelGGL((gather_kernel<T, D, 4, STREAM>), grid, blk, 0, st, g);
     else if (hpb == 2)
-        hipLaunchKernelGGL((gather_kernel<T, D, 2>), grid, blk, 0, st, g);
+        hipLaunchKernelGGL((gather_kernel<T, D, 2, STREAM>), grid, blk, 0, st, g);
     else
-        hipLaunchKernelGGL((gather_kernel<T, D, 1>), grid, blk, 0, st, g);
+        hipLaunchKernelGGL((gather_kernel<T, D, 1, STREAM>), grid, blk, 0, st, g);
+}
+
+template <typename T, int D>
+static void launch_gather_kernel(int hpb, dim3 grid, hipStream_t st, const EnGatherLaunch &g)
+{
+    if (g.a.stream)
+        launch_gather_hpb<T, D, true>(hpb, grid, st, g);
+    else
+        launch_gather_hpb<T, D, false>(hpb, grid, st, g);
 }
 
 int en_launch_gather(const en_pool *pool, EnGatherLaunch &g, int max_ctx_len, void *stream)

@@ -301,7 +301,11 @@ static int choose_splits(const en_pool *pool, const en_plan *pl)
     }
     if (!computes_bf16(pool->d.dtype)) {
         // fp32: a workgroup takes 16 rows, its eight waves share the split's keys 16 at a time, one block
-        // after the other; a second split costs the merge launch (about six blocks)
+        // after the other (1.6 us each with D = 64, 3.4 with 128: two waves share a matrix core), and starts
+        // and ends in the time of about two; splits cost the merge launch, about 3 us (16 rows of one head
+        // over 512 keys, D = 64: 13.0 us whole, 9.8 in nine splits; 4 heads x 64 rows over 192 keys: 8.9
+        // whole, 11.3 in three)
+        const int merge = 128 / pool->d.head_dim;
         const long base = long(pl->B) * pool->d.n_kv_heads * ((r * pl->Nq + EN_F32_ROWS - 1) / EN_F32_ROWS);
         const int tiles = std::max(1, (pl->max_ctx_len + EN_KEY_TILE - 1) / EN_KEY_TILE);
         int best = 1;
@@ -309,7 +313,7 @@ static int choose_splits(const en_pool *pool, const en_plan *pl)
         for (int n = 1; n <= std::min(tiles, EN_MAX_SPLITS); ++n) {
             const long rounds = (base * n + pool->n_cu - 1) / pool->n_cu;
             const long blocks = ((tiles + n - 1) / n * (EN_KEY_TILE / 16) + EN_WAVES - 1) / EN_WAVES;
-            const long cost = rounds * (blocks + 3) + (n > 1 ? 6 : 0);
+            const long cost = rounds * (blocks + 2) + (n > 1 ? merge : 0);
             if (best_cost < 0 || cost < best_cost) {
                 best_cost = cost;
                 best = n;
@@ -828,6 +832,7 @@ static int gather_common(en_pool *pool, en_plan *plan, const void *k_new_dev, co
     }
     a.scale_log2e = softmax_scale_log2e(pool);
     a.v_rows = plan->values_from_pool ? 1 : 0;
+    a.stream = 2 * en_context_bytes(pool, plan) > EN_LAST_LEVEL_CACHE_BYTES ? 1 : 0;
     if (a.v_rows && (reinterpret_cast<uintptr_t>(v_new_dev) & uintptr_t(2 * pool->d.head_dim - 1)))
         return fail(EN_ERR_INVALID_ARG, "gather_rope: with the values taken from where they are "
                     "(en_plan_values_from_pool) the new tokens' values must be aligned to a row (%d bytes)",

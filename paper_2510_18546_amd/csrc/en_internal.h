@@ -12,6 +12,7 @@
 
 #include "efficientnav.h"
 
+constexpr size_t EN_LAST_LEVEL_CACHE_BYTES = size_t(256) << 20;
 constexpr int EN_KEY_TILE = 64;    // keys per attention tile; context rows are padded to it
 constexpr int EN_ROWS_PER_WAVE = 32;
 constexpr int EN_WAVES = 8;          // waves per attention workgroup
@@ -86,6 +87,12 @@ struct EnGatherArgs {
     // pool or the new tokens, [B, Hkv, T], and behind that table one row of zeros, which the
     // padding rows of an agent's last tile point at.
     int v_rows;
+    // 1: the context is written past the caches (non-temporal stores). Contexts beyond the 256 MB of the
+    // last-level cache are not there any more when the attention kernel comes to read them, and its lines
+    // in the way cost the gather 3 % (64 agents x 16 K tokens, 4.3 GB: 1473 -> 1438 us); a smaller one is
+    // read back from the cache (16 agents x 2 K tokens, 133 MB: the gather gains 13 us that way, the
+    // attention kernel loses 12; one agent's 36 MB: the step gets 2.5 us longer).
+    int stream;
 };
 
 // Bytes of the row-address table of EnGatherArgs::v_rows (the row of zeros follows it).
