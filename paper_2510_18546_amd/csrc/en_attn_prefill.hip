@@ -25,13 +25,13 @@
 // What limits a wave here is the number of instructions it issues per matrix
 // instruction (a wave issues in order; scalar instructions cost it about seven
 // cycles each), so the loop is kept free of scalar address arithmetic: it is
-// unrolled over the three LDS stages, which turns every LDS address into a
+// unrolled over the four LDS stages, which turns every LDS address into a
 // per-lane base plus an immediate, the loader issues unconditionally (tiles
 // past the end are clamped to the last one and land in a dead stage), and the
 // common case of a block is decided by one scalar and one vector comparison.
 //
 // K tiles [64][D] and V^T tiles [D][64] go from global memory straight into
-// LDS (global_load_lds_dwordx4: 64 lanes x 16 bytes land contiguously), three
+// LDS (global_load_lds_dwordx4: 64 lanes x 16 bytes land contiguously), four
 // stages each, one workgroup barrier per 64-key tile; the loads of a tile are
 // spread over the steps of the two phases before it is needed. Inside a tile
 // the 16-byte chunks of a row are rotated by the number of the row's 256-byte
@@ -73,7 +73,7 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_bf16_kernel(EnAttnArgs a)
     constexpr int KBYTES = KT * ROWB;
     constexpr int VROWB = KT * 2;                // bytes per V^T row of a tile
     constexpr int VBYTES = D * VROWB;
-    constexpr int NST = 3;                       // LDS stages of K and of V^T
+    constexpr int NST = 4;                       // LDS stages of K and of V^T
     constexpr int VBASE = NST * KBYTES;
     constexpr int NBK = KBYTES / 1024, NBV = VBYTES / 1024;   // 1 KB loader blocks per tile
     constexpr int KJ = NBK / ATT_WAVES, VJ = NBV / ATT_WAVES; // blocks per wave
@@ -224,15 +224,15 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_bf16_kernel(EnAttnArgs a)
     };
 
     // ---- first loads, issued before the queries are prepared so that both are in
-    // flight together. The loop is unrolled over the three stages; the nt % 3
+    // flight together. The loop is unrolled over the four stages; the nt % 4
     // tiles that do not fill a round come first, so the first tile's stage s0
-    // is chosen such that the last tile always sits in stage 2. ----
+    // is chosen such that the last tile always sits in stage 3. ----
     const int rem = nt % NST;
     const int s0 = (NST - rem) % NST;
-    const int s1 = (s0 + 1) % NST, s2 = (s0 + 2) % NST;
+    const int s1 = (s0 + 1) % NST, s2 = (s0 + 2) % NST, s3 = (s0 + 3) % NST;
     if (nt > 0) {
         vrow_request(t_begin);       // (VPOOL) the first V tile waits for these: asked for first, loaded first
-        char *vz = smem + VBASE + s2 * VBYTES;     // the first product reads a zero V^T stage
+        char *vz = smem + VBASE + s3 * VBYTES;     // the first product reads a zero V^T stage
         for (int i = tid * 16; i < VBYTES; i += 64 * ATT_WAVES * 16)
             *reinterpret_cast<uint4 *>(vz + i) = make_uint4(0, 0, 0, 0);
         if constexpr (VPOOL) {
@@ -551,6 +551,9 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_bf16_kernel(EnAttnArgs a)
         static_for<NSTEP>([&](auto k_tag) {
             constexpr int k = decltype(k_tag)::value;
             constexpr int i = k / 2;
+            // The two waves of a SIMD take turns at the matrix core: a wave is preferred while it has a score
+            // product and its exponentials to issue, the other one then issues its V^T product beside them.
+            __builtin_amdgcn_s_setprio(k % 2 == 0 ? 1 : 0);
             const bf16x8 cur_fr = fr[k % PD];
             if constexpr (k + PD < NSTEP)
                 fr[k % PD] = operand(par_tag, st_tag, std::integral_constant<int, (k + PD) % NSTEP>{});
@@ -589,9 +592,9 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_bf16_kernel(EnAttnArgs a)
             if constexpr (k == 2 || k == NSTEP / 2 + 1) {
                 using j_tag = std::integral_constant<int, (k == 2) ? 0 : 1>;
                 if constexpr (PAR == 0)
-                    dma_k(j_tag{}, std::integral_constant<int, (ST + 2) % NST>{});
+                    dma_k(j_tag{}, std::integral_constant<int, (ST + 3) % NST>{});
                 else
-                    dma_v(j_tag{}, std::integral_constant<int, (ST + 1) % NST>{});
+                    dma_v(j_tag{}, std::integral_constant<int, (ST + 2) % NST>{});
             }
             __builtin_amdgcn_sched_barrier(0);
         });
@@ -699,30 +702,52 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_bf16_kernel(EnAttnArgs a)
         calm = calm_limit();
     };
 
-    // ---- main loop: one barrier per tile. Tile t_begin + n lives in stage n % 3.
-    // At the barrier of tile t everything issued so far has landed: K up to
-    // tile t+1, V^T up to tile t. The two phases of tile t then issue K of tile
-    // t+2 and V^T of tile t+1 into stages whose last readers finished before the
-    // barrier. The first product uses a zero P^T with a zero-filled V^T stage. ----
+    // ---- main loop: one barrier per tile. Tile t_begin + n lives in stage n % 4.
+    // The two phases of tile t read K of tiles t and t+1 and V^T of tiles t-1 and t, and issue K of tile
+    // t+3 and V^T of tile t+2 into stages whose last readers finished before the barrier. What tile t
+    // reads was issued two tiles before: at its barrier the loads of tile t-1 may still be on their way
+    // (with three stages they had to have landed, some of them half a tile after they were issued).
+    // The first product uses a zero P^T with a zero-filled V^T stage. ----
     auto tile_body = [&](auto st_tag, int tile) {
-        wait_all_memory();
+        if constexpr (VPOOL)
+            wait_all_memory();        // the row addresses below are loads of the last tile
+        else
+            __builtin_amdgcn_s_waitcnt(0x0f70 | (KJ + VJ));      // vmcnt(KJ + VJ)
         __builtin_amdgcn_s_barrier();
         lds_data_ready();
-        vrow_take();                  // (VPOOL) rows of V tile + 1, asked for a tile ago
-        vrow_request(tile + 2);
+        vrow_take();                  // (VPOOL) rows of V tile + 2, asked for a tile ago
+        vrow_request(tile + 3);
         write_pending();
-        job_k(tile + 2);
+        job_k(tile + 3);
         phase(std::integral_constant<int, 0>{}, st_tag, tile);
-        job_v(tile + 1);
+        job_v(tile + 2);
         phase(std::integral_constant<int, 1>{}, st_tag, tile);
     };
     using c0 = std::integral_constant<int, 0>;
     using c1 = std::integral_constant<int, 1>;
     using c2 = std::integral_constant<int, 2>;
+    using c3 = std::integral_constant<int, 3>;
     if (nt > 0) {
         wait_all_memory();
         __builtin_amdgcn_s_barrier();
         lds_data_ready();
+        // K of the third tile and V^T of the second go out behind everything that the first one waited for
+        job_k(t_begin + 2);
+#pragma unroll
+        for (int j = 0; j < KJ; ++j)
+            dma16(kg, koff[j] + job_goff, lds_w + s2 * KBYTES + j * ATT_WAVES * 1024);
+        job_v(t_begin + 1);
+        if constexpr (VPOOL) {
+            vrow_take();
+#pragma unroll
+            for (int j = 0; j < VJ; ++j)
+                dma16_addr(vrow[j], lds_w + VBASE + s1 * VBYTES + j * ATT_WAVES * 1024);
+            vrow_request(t_begin + 2);
+        } else {
+#pragma unroll
+            for (int j = 0; j < VJ; ++j)
+                dma16(vg, voff[j] + job_goff, lds_w + VBASE + s1 * VBYTES + j * ATT_WAVES * 1024);
+        }
         // scores of the first block
         block_scores(s0 * KBYTES, sbuf[0]);
         mask_block(t_begin * KT, sbuf[0]);
@@ -734,35 +759,40 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_bf16_kernel(EnAttnArgs a)
             } else {
                 const int i = k / 2, kk = i / NDB, d = i % NDB;
                 if constexpr (VPOOL)
-                    fr[k] = v_operand(d, s2 * VBYTES, 32 + 16 * kk);
+                    fr[k] = v_operand(d, s3 * VBYTES, 32 + 16 * kk);
                 else
-                    fr[k] = *reinterpret_cast<const bf16x8 *>(smem + vaddr[1][kk] + s2 * VBYTES + d * 32 * VROWB);
+                    fr[k] = *reinterpret_cast<const bf16x8 *>(smem + vaddr[1][kk] + s3 * VBYTES + d * 32 * VROWB);
             }
         }
         int tile = t_begin;
-        if (rem == 2) {
+        if (rem == 3) {
             tile_body(c1{}, tile);
             ++tile;
         }
-        if (rem >= 1) {
+        if (rem >= 2) {
             tile_body(c2{}, tile);
+            ++tile;
+        }
+        if (rem >= 1) {
+            tile_body(c3{}, tile);
             ++tile;
         }
         for (; tile < t_end; tile += NST) {
             tile_body(c0{}, tile);
             tile_body(c1{}, tile + 1);
             tile_body(c2{}, tile + 2);
+            tile_body(c3{}, tile + 3);
         }
-        // the last pending product: keys 32..63 of the last tile (stage 2)
+        // the last pending product: keys 32..63 of the last tile (stage 3)
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
             for (int d = 0; d < NDB; ++d) {
                 bf16x8 av;
                 if constexpr (VPOOL)
-                    av = v_operand(d, 2 * VBYTES, 32 + 16 * kk);
+                    av = v_operand(d, 3 * VBYTES, 32 + 16 * kk);
                 else
-                    av = *reinterpret_cast<const bf16x8 *>(smem + vaddr[1][kk] + 2 * VBYTES + d * 32 * VROWB);
+                    av = *reinterpret_cast<const bf16x8 *>(smem + vaddr[1][kk] + 3 * VBYTES + d * 32 * VROWB);
                 o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, pbuf[1][kk], o[d], 0, 0, 0);
             }
         // loads of the clamped tiles may still be in flight
