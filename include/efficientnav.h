@@ -290,8 +290,8 @@ int segmented_prefill_attention(en_pool *pool, en_plan *plan, const void *q_dev,
  *                      the plan, so calls on one plan must not overlap), so the
  *                      result does not depend on the order in which they arrive
  *                      and is the same from run to run; it may differ from what
- *                      segment_attention_mass(reduce = 1) gives (a float sum in
- *                      a fixed order) in the last bits. That call may still
+ *                      segment_attention_mass(reduce = 1) gives (the rows in
+ *                      other groups) in the last bits. That call may still
  *                      follow, with either reduce mode. At most 1023 query
  *                      heads.
  * Plans whose steps have enough query rows for the matrix-core prefill kernel
@@ -371,7 +371,7 @@ int segmented_decode_step_static(en_pool *pool, en_plan *plan, int32_t q_first, 
  *                block, entries beyond are 0; each row sums to 1.
  *   reduce = 1 : mass_out_dev float [B, Smax+1], the above summed over heads
  *                and query tokens (divide by Hq*N_q for the average).
- * The reduced form also writes a small part of the scratch (per-head partial
+ * The reduced form also writes a small part of the scratch (accumulators of the
  * sums): two reduced calls on one scratch must not overlap in time.
  * Errors: INVALID_ARG, DEVICE.
  */

@@ -501,6 +501,9 @@ __global__ __launch_bounds__(64 * F32_WAVES) void attn_f32_kernel(EnAttnArgs a)
     __shared__ f32x2 sfirst[F32_WAVES][F32_ROWS];        // (sum, reference) of the bucket that a wave entered midway
     __shared__ int sspan[F32_WAVES];                     // 1: ... and that it did not leave
 
+    if (blockIdx.x == 0 && a.red_zero)
+        for (int i = threadIdx.x; i < a.n_red_zero; i += 64 * F32_WAVES)
+            a.red_zero[i] = 0ull;
     int t = blockIdx.x;
     const int rg = t % a.n_ptiles;
     t /= a.n_ptiles;

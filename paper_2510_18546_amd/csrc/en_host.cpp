@@ -652,8 +652,7 @@ EnWsLayout en_ws_layout_for(const en_pool *pool, const en_plan *pl, int n_rows, 
     const size_t rows = size_t(pl->B) * pool->d.n_q_heads * n_rows;
     L.ml_off = 0;
     L.seg_off = align256(L.ml_off + size_t(n_splits) * rows * 2 * sizeof(float));
-    L.red_off = align256(L.seg_off + size_t(n_splits) * rows * (pl->Smax + 1) * 2 * sizeof(float));
-    L.redacc_off = align256(L.red_off + size_t(pl->B) * (pl->Smax + 1) * pool->d.n_q_heads * sizeof(float));
+    L.redacc_off = align256(L.seg_off + size_t(n_splits) * rows * (pl->Smax + 1) * 2 * sizeof(float));
     L.mlfin_off = align256(L.redacc_off + size_t(pl->B) * (pl->Smax + 1) * sizeof(unsigned long long));
     L.opart_off = align256(L.mlfin_off + (n_splits > 1 ? rows * 2 * sizeof(float) : 0));
     L.total = L.opart_off;
@@ -880,6 +879,20 @@ extern "C" int gather_rope_queries(en_pool *pool, en_plan *plan, const void *k_n
                gather_rope_queries_impl(pool, plan, k_new_dev, v_new_dev, q_dev, kc_dev, vt_dev, q_prep_dev, stream));
 }
 
+static int bits_for(uint64_t n)
+{
+    int bits = 0;
+    while ((uint64_t(1) << bits) <= n)
+        ++bits;
+    return bits;
+}
+// Fixed point of the reduced masses: a sum is at most Hq * n_rows, and sum << (shift + count bits) must fit
+// 63 bits; 2^-40 is far below the rounding of the float that the sum becomes.
+static int fixed_point_shift(const en_pool *pool, int n_rows, int count_bits)
+{
+    return std::max(0, std::min(40, 62 - count_bits - bits_for(uint64_t(pool->d.n_q_heads) * uint64_t(n_rows))));
+}
+
 // For the rows q_first .. q_first + n_rows - 1 of the plan's new tokens, attended with n_splits KV splits.
 static EnMassArgs mass_args(const en_pool *pool, const en_plan *plan, char *ws, const EnWsLayout &L, int n_rows,
                             int n_splits, int q_first)
@@ -888,16 +901,11 @@ static EnMassArgs mass_args(const en_pool *pool, const en_plan *plan, char *ws, 
     a.ws_ml = reinterpret_cast<const float *>(ws + L.ml_off);
     a.ws_seg = reinterpret_cast<const float *>(ws + L.seg_off);
     a.ws_mlfin = reinterpret_cast<const float *>(ws + L.mlfin_off);
-    a.ws_red = reinterpret_cast<float *>(ws + L.red_off);
     a.red_out = nullptr;
     a.red_acc = reinterpret_cast<unsigned long long *>(ws + L.redacc_off);
-    {
-        // fixed point of the reduced masses: a sum is at most Hq * n_rows, and sum << (shift + 10) must fit 63 bits
-        int bits = 0;
-        while ((uint64_t(1) << bits) < uint64_t(pool->d.n_q_heads) * uint64_t(n_rows))
-            ++bits;
-        a.red_shift = std::max(0, std::min(30, 52 - bits));
-    }
+    a.red_target = pool->d.n_q_heads * ((n_rows + EN_MASS_ROWS - 1) / EN_MASS_ROWS);
+    a.red_count_bits = bits_for(a.red_target);
+    a.red_shift = fixed_point_shift(pool, n_rows, a.red_count_bits);
     a.nseg = d_nseg(plan);
     a.bnd = d_bnd(plan);
     a.hdr = d_hdr(plan);
@@ -979,7 +987,8 @@ static int run_attention(en_pool *pool, en_plan *plan, const void *q_dev, const 
     if (plan->gathered_values_from_pool >= 0 && plan->gathered_values_from_pool != a.v_rows)
         return fail(EN_ERR_INVALID_ARG, "%s: en_plan_values_from_pool was changed after the plan's last gather; "
                     "gather again", who);
-    a.red_zero = (mass_red_out_dev && ws) ? reinterpret_cast<unsigned long long *>(ws + L.redacc_off) : nullptr;
+    // (zero also when this call is not asked for masses: segment_attention_mass may follow)
+    a.red_zero = (ws && n_rows >= EN_MASS_FEW_ROWS) ? reinterpret_cast<unsigned long long *>(ws + L.redacc_off) : nullptr;
     a.n_red_zero = a.red_zero ? plan->B * (plan->Smax + 1) : 0;
     // One partial result per row in the matrix-core kernel: its workgroups add the reduced masses up
     // themselves, in the plan's own accumulators (every workgroup arrives once per bucket; the
@@ -993,10 +1002,8 @@ static int run_attention(en_pool *pool, en_plan *plan, const void *q_dev, const 
     if (red_direct) {
         a.red_direct = reinterpret_cast<unsigned long long *>(plan->d_desc + plan->acc_off);
         a.red_direct_out = mass_red_out_dev;
-        a.red_shift = mass_args(pool, plan, ws, L, n_rows, n_splits, q_first).red_shift;
+        a.red_shift = fixed_point_shift(pool, n_rows, 10);
         a.red_target = arrivals;
-        a.red_zero = nullptr;
-        a.n_red_zero = 0;
     }
     const bool timed = pool->ev_used < (int)pool->ev_start.size();
     if (timed)
@@ -1007,7 +1014,7 @@ static int run_attention(en_pool *pool, en_plan *plan, const void *q_dev, const 
     if (e != 0)
         return hip_fail((hipError_t)e, who);
     if (n_partials > 1) {
-        // the same launch also leaves the per-head partial sums of the segment masses
+        // the same launch also adds the reduced masses up, if they are wanted
         EnMassArgs m = mass_args(pool, plan, ws, L, n_rows, n_splits, q_first);
         m.red_out = mass_red_out_dev;
         EnAttnArgs c = a;
@@ -1016,12 +1023,11 @@ static int run_attention(en_pool *pool, en_plan *plan, const void *q_dev, const 
         if (e != 0)
             return hip_fail((hipError_t)e, "split combine launch");
     }
-    if (mass_red_out_dev && !red_direct) {
-        // stage 1 of the reduced masses as a launch of its own where no merge launch carried it (one
-        // partial result per row, or few rows per head): en_launch_mass launches nothing otherwise
+    if (mass_red_out_dev && !red_direct && (n_partials == 1 || n_rows < EN_MASS_FEW_ROWS)) {
+        // no merge launch carried the reduced masses: one partial result per row, or few rows per head
         EnMassArgs m = mass_args(pool, plan, ws, L, n_rows, n_splits, q_first);
         m.red_out = mass_red_out_dev;
-        e = en_launch_mass(pool, m, 2, stream);
+        e = en_launch_mass(pool, m, 1, stream);
         if (e != 0)
             return hip_fail((hipError_t)e, "reduced masses launch");
     }
@@ -1243,7 +1249,7 @@ static int segment_attention_mass_impl(en_pool *pool, en_plan *plan, void *ws_de
     const EnWsLayout L = en_ws_layout(pool, plan);
     char *ws = static_cast<char *>(ws_dev);
     EnMassArgs a = mass_args(pool, plan, ws, L, plan->Nq, plan->n_splits, 0);
-    a.out = mass_out_dev;
+    a.out = a.red_out = mass_out_dev;
     const int e = en_launch_mass(pool, a, reduce, stream);
     if (e != 0)
         return hip_fail((hipError_t)e, "segment_attention_mass launch");

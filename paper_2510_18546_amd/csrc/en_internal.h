@@ -136,8 +136,8 @@ struct EnAttnArgs {
     int q_prepared;    // prefill kernel: q holds prepared queries (rotated, scaled, bf16: see EnGatherArgs)
     int v_rows;        // prefill kernel: vt holds no values but the address of every context row's values
                        // (see EnGatherArgs::v_rows)
-    // prefill kernel, or null: n_red_zero accumulator words that its first workgroup sets to zero
-    // (EnMassArgs::red_acc, which the launches after it add to)
+    // prefill and fp32 kernels, or null: n_red_zero accumulator words that their first workgroup sets to
+    // zero (EnMassArgs::red_acc, which the launches after it add to)
     unsigned long long *red_zero;
     int n_red_zero;
     // prefill kernel with one KV split, or null: the reduced masses [B, Smax+1] without any further
@@ -154,14 +154,13 @@ struct EnAttnArgs {
 
 struct EnMassArgs {
     const float *ws_ml, *ws_seg, *ws_mlfin;
-    float *ws_red;          // [B, Smax+1, Hq] per-head partial sums of the reduced masses
-    // Reduced masses without a launch of their own, or null: every per-head partial sum is also added,
-    // as a fixed-point integer (2^-red_shift; integer sums do not depend on the order of the
-    // additions), to red_acc [B, Smax+1], whose low 10 bits count the heads that have arrived; the
-    // head that arrives last writes the sum to red_out [B, Smax+1].
+    // Reduced masses [B, Smax+1], or null. With EN_MASS_FEW_ROWS query rows per head or more they are added up,
+    // as fixed-point integers (2^-red_shift; integer sums do not depend on the order of the additions), in
+    // red_acc [B, Smax+1], whose low red_count_bits bits count the red_target workgroups (heads x chunks of
+    // EN_MASS_ROWS rows) that arrive; the last one writes the sum and sets the word back to zero.
     float *red_out;
     unsigned long long *red_acc;
-    int red_shift;
+    int red_shift, red_count_bits, red_target;
     const int32_t *nseg, *bnd;
     const int32_t *hdr;     // as in EnAttnArgs
     float *out;
@@ -185,6 +184,8 @@ struct EnAppendQ8Args {
 
 
 constexpr int EN_RED_DIRECT_MAX_BUCKETS = 256;   // EnAttnArgs::red_direct: buckets whose sums a workgroup keeps in LDS
+constexpr int EN_MASS_FEW_ROWS = 64;    // below this many query rows per head the reduced masses need no accumulators
+constexpr int EN_MASS_ROWS = 256;       // query rows per workgroup of the reduced masses
 constexpr int EN_MAX_SPLITS = 64;       // KV splits of a plan: the mass kernels hold one split per lane
 constexpr int EN_MAX_OBJECTS = 255;    // per segment_cluster_assign call (spans travel in the kernel arguments)
 struct EnClusterArgs {
@@ -218,7 +219,7 @@ struct EnCtxAppendArgs {
 
 // Workspace layout helper (bytes, every part 256-byte aligned).
 struct EnWsLayout {
-    size_t ml_off, seg_off, red_off, redacc_off, mlfin_off, opart_off, total;
+    size_t ml_off, seg_off, redacc_off, mlfin_off, opart_off, total;
 };
 EnWsLayout en_ws_layout(const en_pool *pool, const en_plan *plan);
 EnWsLayout en_ws_layout_for(const en_pool *pool, const en_plan *plan, int n_rows, int n_splits);

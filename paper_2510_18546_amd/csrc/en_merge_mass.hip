@@ -9,25 +9,24 @@
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void mass_partial_block(const EnMassArgs &a, int blk, float *red);
 
-// The reduced masses without a launch of their own: a head's sum for (agent, bucket) `idx` joins the
-// others in ONE atomic addition on a 64-bit word that holds the sum in fixed point (so that it does
-// not depend on the order in which the heads arrive) above a 10-bit count of arrivals; whoever
-// arrives last (sees Hq in the count) has the complete sum in hand, from the atomic's own return
-// value, and writes it out. The word was set to zero by the attention launch before.
-__device__ __forceinline__ void add_reduced_mass(const EnMassArgs &a, size_t idx, float head_sum)
+// The reduced masses: a workgroup's sum for (agent, bucket) `idx` joins the others in ONE atomic addition
+// on a 64-bit word that holds the sum in fixed point (so that it does not depend on the order in which
+// the workgroups arrive) above a count of arrivals; whoever arrives last has the complete sum in hand,
+// from the atomic's own return value, writes it out and sets the word back to zero. The words were set
+// to zero by the attention launch before.
+__device__ __forceinline__ void add_reduced_mass(const EnMassArgs &a, size_t idx, float part)
 {
-    if (!a.red_out)
-        return;
-    const long long q = __float2ll_rn(ldexpf(head_sum, a.red_shift));
-    const unsigned long long add = ((unsigned long long)q << 10) + 1ull;
+    const long long q = __float2ll_rn(ldexpf(part, a.red_shift));
+    const unsigned long long add = ((unsigned long long)q << a.red_count_bits) + 1ull;
     const unsigned long long now = atomicAdd(a.red_acc + idx, add) + add;
-    if ((int)(now & 1023ull) == a.Hq)
-        a.red_out[idx] = ldexpf((float)((long long)(now - (unsigned long long)a.Hq) >> 10), -a.red_shift);
+    if ((now & ((1ull << a.red_count_bits) - 1ull)) == (unsigned long long)a.red_target) {
+        a.red_out[idx] = ldexpf((float)((long long)(now - (unsigned long long)a.red_target) >> a.red_count_bits), -a.red_shift);
+        a.red_acc[idx] = 0ull;
+    }
 }
 
-constexpr int EN_MASS_FEW_ROWS = 64;      // below this many query rows per head the partial sums go thread-wise
-// Stage 1 of the reduced masses: a workgroup takes EN_MASS_BG consecutive buckets of one
-// (agent, head) over all query rows (see mass_partial_block).
+// A workgroup of the reduced masses takes EN_MASS_BG consecutive buckets of one (agent, head) over
+// EN_MASS_ROWS query rows, one row per thread (see mass_partial_block).
 constexpr int EN_MASS_BG = 8;
 __host__ __device__ inline int mass_bucket_groups(const EnMassArgs &m)
 {
@@ -35,7 +34,7 @@ __host__ __device__ inline int mass_bucket_groups(const EnMassArgs &m)
 }
 __host__ inline int mass_partial_blocks(const EnMassArgs &m)
 {
-    return mass_bucket_groups(m) * m.Hq * m.B;
+    return mass_bucket_groups(m) * m.red_target * m.B;       // red_target: heads x row chunks
 }
 
 // With many splits (decode over a long context by few agents) G = 4, 16 or 32 neighbouring lanes
@@ -46,8 +45,8 @@ __host__ inline int mass_partial_blocks(const EnMassArgs &m)
 template <typename T, int D, int G>
 __global__ __launch_bounds__(256) void combine_kernel(EnAttnArgs a, EnMassArgs m, int n_comb)
 {
-    // head of the grid (these workgroups take longest: they start first): per-head partial sums
-    // of the segment masses
+    // head of the grid (these workgroups take longest: they start first): the reduced masses, where
+    // the attention call was asked for them (without: 10.1 -> 6.1 us on the 8K-context step)
     const int n_part = (int)gridDim.x - n_comb;
     if ((int)blockIdx.x < n_part) {
         __shared__ float red[4 * EN_MASS_BG];
@@ -256,61 +255,132 @@ __device__ __forceinline__ float row_bucket_mass(const EnMassArgs &a, int b, int
     return acc / L;
 }
 
-// reduce = 0. grid: (ceil(Nq/64), Hq, B), 256 threads: the block takes 64 queries of one head.
-// The scratch is laid out query-fastest, the result bucket-fastest: each wave computes the
-// masses of its share of the buckets for the 64 queries (coalesced reads), the block transposes
-// them through LDS, 64 buckets at a time, and writes whole runs of buckets per query.
+// reduce = 0. grid: (ceil(Nq/64), Hq, B * chunks of EN_MASS_RB buckets), 256 threads: the block takes 64
+// queries of one head and one chunk of buckets. The scratch is laid out query-fastest, the result
+// bucket-fastest: each wave computes the masses of four buckets for the 64 queries (coalesced reads), the
+// block transposes them through LDS and writes runs of 64 bytes per query. A trip to memory takes about a
+// microsecond and each wave makes one for its four buckets: a block that walked all buckets of its rows
+// made nine (4 agents x 129 rows x 32 heads x 33 buckets: 10.4 us against 5.9).
+constexpr int EN_MASS_RB = 16;
 __global__ __launch_bounds__(256) void mass_rows_kernel(EnMassArgs a)
 {
-    constexpr int SB = 64;                       // buckets per pass
-    __shared__ float tile[64][SB + 1];
+    constexpr int PER = EN_MASS_RB / 4;          // buckets per wave
+    __shared__ float tile[64][EN_MASS_RB + 1];
     const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
     const int i = blockIdx.x * 64 + lane;
-    const int hq = blockIdx.y, b = blockIdx.z;
+    const int n_chunks = (a.Smax + EN_MASS_RB) / EN_MASS_RB;
+    const int hq = blockIdx.y, b = blockIdx.z / n_chunks;
+    const int s0 = blockIdx.z % n_chunks * EN_MASS_RB;
     const bool valid = i < a.Nq;
     const size_t rows = (size_t)a.B * a.Hq * a.Nq;
     const size_t row = ((size_t)b * a.Hq + hq) * a.Nq + (valid ? i : 0);
-    const int S = a.nseg[b];
-    const int32_t *bnd = a.bnd + (size_t)b * (a.Smax + 2);
-    const int Ltot = bnd[S] + a.q_first + a.Nq;     // end of what the rows could see
-    const int ntiles = (Ltot + EN_KEY_TILE - 1) / EN_KEY_TILE;
-    const EnSplitMap map = split_map(a.n_splits, ntiles);
     float M, L;
     row_final_ml(a, rows, row, M, L);
-    for (int s0 = 0; s0 <= a.Smax; s0 += SB) {
-        const int n = min(SB, a.Smax + 1 - s0);
-        for (int c = wave; c < n; c += 4) {
-            const int s = s0 + c;                 // the same for the whole wave
-            float v = 0.f;
-            if (s <= S && bnd[s + 1] > bnd[s]) {
-                int lo, hi;
-                bucket_splits(map, a.n_splits, Ltot, bnd[s], bnd[s + 1], lo, hi);
-                if (valid)
-                    v = row_bucket_mass(a, b, hq, i, s, lo, hi, M, L, map.keys);
-            }
-            tile[lane][c] = v;
+    const en_table_ptr hdr = as_table(a.hdr + 4 * (size_t)b);
+    const int S = hdr[0];
+    const int Ltot = hdr[1] + a.q_first + a.Nq;     // end of what the rows could see
+    const int ntiles = (Ltot + EN_KEY_TILE - 1) / EN_KEY_TILE;
+    const EnSplitMap map = split_map(a.n_splits, ntiles);
+    const int32_t *bnd = a.bnd + (size_t)b * (a.Smax + 2);
+    int lo[PER], hi[PER];
+    bool live[PER], simple = a.sub == 1;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int s = min(s0 + wave * PER + j, a.Smax);              // the same for the whole wave
+        const int blo = bnd[s], bhi = bnd[s + 1];
+        live[j] = s0 + wave * PER + j <= S && bhi > blo;
+        bucket_splits(map, a.n_splits, Ltot, blo, bhi, lo[j], hi[j]);
+        live[j] = live[j] && hi[j] >= lo[j];
+        simple = simple && (!live[j] || hi[j] - lo[j] <= 1);
+    }
+    float v[PER];
+    if (simple) {
+        // one split covers the bucket or two neighbours do: both entries of every bucket in one batch of loads
+        f32x2 e0[PER], e1[PER];
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const int s = min(s0 + wave * PER + j, a.Smax);
+            const int sp = live[j] ? lo[j] : 0, sp1 = live[j] ? hi[j] : 0;
+            const f32x2 *p = reinterpret_cast<const f32x2 *>(a.ws_seg) +
+                             (((size_t)b * a.Hq + hq) * (a.Smax + 1) + s) * a.Nq + (valid ? i : 0);
+            const size_t per_split = (size_t)a.B * a.Hq * (a.Smax + 1) * a.Nq;
+            e0[j] = p[sp * per_split];
+            e1[j] = p[sp1 * per_split];
         }
-        __syncthreads();
-        for (int r = wave; r < 64; r += 4) {
-            const int ir = blockIdx.x * 64 + r;
-            if (ir < a.Nq && lane < n)
-                a.out[(((size_t)b * a.Nq + ir) * a.Hq + hq) * (a.Smax + 1) + s0 + lane] = tile[r][lane];
+        const float inv = 1.f / L;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            float acc = 0.f;
+            // (an agent with fewer key tiles than the plan has splits leaves some splits without keys: nothing was
+            // written for them)
+            if (live[j] && ((map.keys >> lo[j]) & 1) && e0[j][1] != EN_NEG_INF)
+                acc += e0[j][0] * fast_exp2(e0[j][1] - M);
+            if (live[j] && hi[j] > lo[j] && ((map.keys >> hi[j]) & 1) && e1[j][1] != EN_NEG_INF)
+                acc += e1[j][0] * fast_exp2(e1[j][1] - M);
+            v[j] = acc * inv;
         }
-        __syncthreads();
+    } else {
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            v[j] = 0.f;
+            if (live[j] && valid)
+                v[j] = row_bucket_mass(a, b, hq, i, s0 + wave * PER + j, lo[j], hi[j], M, L, map.keys);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < PER; ++j)
+        tile[lane][wave * PER + j] = v[j];
+    __syncthreads();
+    const int c = threadIdx.x % EN_MASS_RB;
+#pragma unroll
+    for (int k = 0; k < 64 * EN_MASS_RB / 256; ++k) {
+        const int r = threadIdx.x / EN_MASS_RB + k * (256 / EN_MASS_RB);
+        const int ir = blockIdx.x * 64 + r;
+        if (ir < a.Nq && s0 + c <= a.Smax)
+            a.out[(((size_t)b * a.Nq + ir) * a.Hq + hq) * (a.Smax + 1) + s0 + c] = tile[r][c];
     }
 }
 
-// reduce = 1, stage 1: workgroup blk = (b * Hq + hq) * n_groups + group sums EN_MASS_BG buckets
-// of one head over the queries into partial[b][s][hq]. With several KV splits this runs in the
-// first workgroups of the combine launch (the partial sums are a by-product of the attention call, whatever
-// the caller asks of the mass call later) and merges the splits' (reference, sum) pairs itself;
-// with one split it is a launch of its own.
+// reduce = 0 for few rows per head (decode steps): a thread per result, buckets fastest. grid: (ceil(Hq (Smax+1)
+// / 256), Nq, B). One row of 64 queries' width per (agent, head) left 63 lanes of 64 idle in each of a
+// bucket's trips to memory (64 agents x 32 heads x 65 buckets, one token: 25.8 us against 4.8).
+__global__ __launch_bounds__(256) void mass_rows_few_kernel(EnMassArgs a)
+{
+    const unsigned nb = a.Smax + 1;
+    const unsigned idx = blockIdx.x * 256u + threadIdx.x;
+    if (idx >= a.Hq * nb)
+        return;
+    const int hq = idx / nb, s = idx - hq * nb;
+    const int i = blockIdx.y, b = blockIdx.z;
+    const size_t rows = (size_t)a.B * a.Hq * a.Nq;
+    float M, L;
+    row_final_ml(a, rows, ((size_t)b * a.Hq + hq) * a.Nq + i, M, L);
+    const int32_t *bnd = a.bnd + (size_t)b * (a.Smax + 2);
+    const int blo = bnd[s], bhi = bnd[s + 1];
+    const en_table_ptr hdr = as_table(a.hdr + 4 * (size_t)b);
+    const int S = hdr[0];
+    const int Ltot = hdr[1] + a.q_first + a.Nq;
+    const int ntiles = (Ltot + EN_KEY_TILE - 1) / EN_KEY_TILE;
+    float v = 0.f;
+    if (s <= S && bhi > blo) {
+        int lo, hi;
+        unsigned long long keys;
+        bucket_splits_thread(a.n_splits, ntiles, Ltot, blo, bhi, lo, hi, keys);
+        v = row_bucket_mass(a, b, hq, i, s, lo, hi, M, L, keys);
+    }
+    a.out[((size_t)b * a.Nq + i) * a.Hq * nb + idx] = v;
+}
+
+// The reduced masses: workgroup blk sums EN_MASS_BG buckets of one head over EN_MASS_ROWS queries. As part
+// of an attention call with several KV splits this runs in the first workgroups of the combine launch and
+// merges the splits' (reference, sum) pairs itself; otherwise it is a launch of its own.
 //
 // What this costs is instructions per (row, bucket) and dependent trips to memory (about a
-// microsecond each), not bytes. So lanes are rows: a row's merged (reference, sum) pair is made
-// once for the group's buckets; everything that is the same for all rows (which splits cover a
-// bucket, whether they hold keys) is decided from the agent's header and bounds in scalar
-// registers before the rows start; and a row's loads for all buckets go out together: a bucket
+// microsecond each), not bytes. So lanes are rows, a thread has one (a second round of rows per thread
+// is a second trip: 512 rows in one workgroup took 1.5 us more than in two): a row's merged (reference,
+// sum) pair is made once for the group's buckets; everything that is the same for all rows (which splits
+// cover a bucket, whether they hold keys) is decided from the agent's header and bounds before the rows
+// start; and a row's loads for all buckets go out together: a bucket
 // is covered by one split or by two neighbours unless it is longer than a split, so two entries
 // per bucket are fetched whether or not the second one counts (it lies inside the scratch either
 // way). A group with a bucket over more than two splits takes them one after the other.
@@ -325,13 +395,15 @@ __device__ __forceinline__ void mass_partial_block(const EnMassArgs &a, int blk,
     const int ng = mass_bucket_groups(a);
     const int s0 = (blk % ng) * BG;
     const int hq = (blk / ng) % a.Hq;
-    const int b = blk / (ng * a.Hq);
+    const int n_chunks = a.red_target / a.Hq;
+    const int i = (blk / (ng * a.Hq)) % n_chunks * EN_MASS_ROWS + threadIdx.x;
+    const int b = blk / (ng * a.red_target);
     const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
     float acc[BG];
 #pragma unroll
     for (int j = 0; j < BG; ++j)
         acc[j] = 0.f;
-    if (wave * 64 < a.Nq) {                        // a wave without rows has nothing to set up
+    if (i - lane < a.Nq) {                         // a wave without rows has nothing to set up
         const size_t rows = (size_t)a.B * a.Hq * a.Nq;
         const en_table_ptr hdr = as_table(a.hdr + 4 * (size_t)b);
         const int S = hdr[0];
@@ -380,7 +452,7 @@ __device__ __forceinline__ void mass_partial_block(const EnMassArgs &a, int blk,
                 p0[j] = (const char *)a.ws_seg + readlane64(off0_v, j);
                 p1[j] = (const char *)a.ws_seg + readlane64(off1_v, j);
             }
-            for (int i = threadIdx.x; i < a.Nq; i += 256) {
+            if (i < a.Nq) {
                 const size_t row = ((size_t)b * a.Hq + hq) * a.Nq + i;
                 f32x2 v0[BG], v1[BG];
 #pragma unroll
@@ -407,7 +479,7 @@ __device__ __forceinline__ void mass_partial_block(const EnMassArgs &a, int blk,
 #pragma unroll
             for (int j = 0; j < BG; ++j)
                 hi[j] = __builtin_amdgcn_readlane(hi_v, j);
-            for (int i = threadIdx.x; i < a.Nq; i += 256) {
+            if (i < a.Nq) {
                 const size_t row = ((size_t)b * a.Hq + hq) * a.Nq + i;
                 float M, L;
                 merged_ml(a, rows, row, M, L);
@@ -427,67 +499,52 @@ __device__ __forceinline__ void mass_partial_block(const EnMassArgs &a, int blk,
     __syncthreads();
     if (threadIdx.x < BG && s0 + (int)threadIdx.x <= a.Smax) {
         const int j = threadIdx.x;
-        const float tot = red[j] + red[BG + j] + red[2 * BG + j] + red[3 * BG + j];
-        a.ws_red[((size_t)b * (a.Smax + 1) + s0 + j) * a.Hq + hq] = tot;
-        add_reduced_mass(a, (size_t)b * (a.Smax + 1) + s0 + j, tot);
+        add_reduced_mass(a, (size_t)b * (a.Smax + 1) + s0 + j, red[j] + red[BG + j] + red[2 * BG + j] + red[3 * BG + j]);
     }
 }
 
-// The same for few query rows per head (decode steps): one THREAD per (agent, bucket, head) walks
-// the rows, so that a step of one token does not launch a workgroup per (bucket, head). This form
-// is a launch of its own in the mass call, whatever the number of splits: a decode step that asks
-// for no masses then does no work for them.
-__device__ __forceinline__ void mass_partial_few_rows(const EnMassArgs &a, size_t pair)
+__global__ __launch_bounds__(256) void mass_partial_kernel(EnMassArgs a)
 {
-    if (pair >= (size_t)a.B * (a.Smax + 1) * a.Hq)
-        return;
-    const int hq = (int)(pair % a.Hq);
-    const int s = (int)((pair / a.Hq) % (a.Smax + 1));
-    const int b = (int)(pair / ((size_t)a.Hq * (a.Smax + 1)));
+    __shared__ float red[4 * EN_MASS_BG];
+    mass_partial_block(a, blockIdx.x, red);
+}
+
+// The reduced masses of few query rows per head (decode steps): a workgroup of G threads per (agent,
+// bucket) walks the bucket's (head, row) pairs and writes the sum, nothing to meet and no second launch.
+template <int G>
+__global__ __launch_bounds__(256) void mass_few_rows_kernel(EnMassArgs a)
+{
+    __shared__ float red[4];
+    const int pair = blockIdx.x * (256 / G) + threadIdx.x / G;
+    const bool on = pair < a.B * (a.Smax + 1);
+    const int s = on ? pair % (a.Smax + 1) : 0;
+    const int b = on ? pair / (a.Smax + 1) : 0;
     const size_t rows = (size_t)a.B * a.Hq * a.Nq;
     const int S = a.nseg[b];
     const int32_t *bnd = a.bnd + (size_t)b * (a.Smax + 2);
     const int Ltot = bnd[S] + a.q_first + a.Nq;
     const int ntiles = (Ltot + EN_KEY_TILE - 1) / EN_KEY_TILE;
     float acc = 0.f;
-    if (s <= S && bnd[s + 1] > bnd[s]) {
+    if (on && s <= S && bnd[s + 1] > bnd[s]) {
         int lo, hi;
         unsigned long long keys;
         bucket_splits_thread(a.n_splits, ntiles, Ltot, bnd[s], bnd[s + 1], lo, hi, keys);
-        for (int i = 0; i < a.Nq; ++i) {
-            const size_t row = ((size_t)b * a.Hq + hq) * a.Nq + i;
+        for (int idx = threadIdx.x % G; idx < a.Hq * a.Nq; idx += G) {
+            const int hq = idx / a.Nq, i = idx - hq * a.Nq;
             float M, L;
-            row_final_ml(a, rows, row, M, L);      // runs after the combine launch: the merged pair is there
+            row_final_ml(a, rows, (size_t)b * a.Hq * a.Nq + idx, M, L);      // runs after the combine launch
             acc += row_bucket_mass(a, b, hq, i, s, lo, hi, M, L, keys);
         }
     }
-    a.ws_red[pair] = acc;              // [b][s][hq]
-    add_reduced_mass(a, (size_t)b * (a.Smax + 1) + s, acc);
-}
-
-// grid: mass_partial_blocks(a), or ceil(B (Smax+1) Hq / 256) blocks when Nq < EN_MASS_FEW_ROWS
-__global__ __launch_bounds__(256) void mass_partial_kernel(EnMassArgs a)
-{
-    __shared__ float red[4 * EN_MASS_BG];
-    if (a.Nq < EN_MASS_FEW_ROWS)
-        mass_partial_few_rows(a, (size_t)blockIdx.x * 256 + threadIdx.x);
-    else
-        mass_partial_block(a, blockIdx.x, red);
-}
-
-// reduce = 1, stage 2. One wave per (agent, bucket) adds up the heads.
-__global__ __launch_bounds__(256) void mass_final_kernel(EnMassArgs a)
-{
-    const int pair = blockIdx.x * 4 + threadIdx.x / 64;
-    if (pair >= a.B * (a.Smax + 1))
-        return;
-    const float *p = a.ws_red + (size_t)pair * a.Hq;
-    float acc = 0.f;
-    for (int h = threadIdx.x % 64; h < a.Hq; h += 64)
-        acc += p[h];
     acc = wave_sum(acc);
-    if (threadIdx.x % 64 == 0)
-        a.out[pair] = acc;
+    if constexpr (G > 64) {
+        if (threadIdx.x % 64 == 0)
+            red[threadIdx.x / 64] = acc;
+        __syncthreads();
+        acc = red[0] + red[1] + red[2] + red[3];
+    }
+    if (on && threadIdx.x % G == 0)
+        a.red_out[pair] = acc;
 }
 
 // ---------------------------------------------------------------------------
@@ -582,7 +639,7 @@ int en_launch_combine(const en_pool *pool, const EnAttnArgs &a, const EnMassArgs
         G = a.n_splits > 64 ? 32 : (a.n_splits > 16 ? 16 : (a.n_splits > 4 ? 4 : 1));
     const size_t n = (size_t)a.B * a.Hq * a.Nq * (D / vec) * G;
     const int n_comb = (int)((n + 255) / 256);
-    const int n_part = m.Nq < EN_MASS_FEW_ROWS ? 0 : mass_partial_blocks(m);
+    const int n_part = m.red_out && m.Nq >= EN_MASS_FEW_ROWS ? mass_partial_blocks(m) : 0;
     const dim3 grid((unsigned)(n_comb + n_part)), blk(256);
 #define EN_COMBINE(T, DD)                                                                             \
     do {                                                                                              \
@@ -627,19 +684,23 @@ int en_launch_mass(const en_pool *pool, const EnMassArgs &a, int reduce, void *s
     (void)pool;
     hipStream_t st = (hipStream_t)stream;
     if (reduce == 0) {
-        const dim3 grid((a.Nq + 63) / 64, a.Hq, a.B), blk(256);
-        hipLaunchKernelGGL(mass_rows_kernel, grid, blk, 0, st, a);
-    } else {
-        // with several splits and many rows stage 1 has already run in the combine launch
         const dim3 blk(256);
-        const dim3 grid = a.Nq < EN_MASS_FEW_ROWS ? dim3(((a.Smax + 1) * a.Hq * a.B + 255) / 256)
-                                                  : dim3(mass_partial_blocks(a));
-        if (a.n_splits * a.sub == 1 || a.Nq < EN_MASS_FEW_ROWS)
-            hipLaunchKernelGGL(mass_partial_kernel, grid, blk, 0, st, a);
-        if (reduce == 1) {           // reduce == 2: stage 1 only, which adds into a.red_out
-            const dim3 grid2((a.B * (a.Smax + 1) + 3) / 4);
-            hipLaunchKernelGGL(mass_final_kernel, grid2, blk, 0, st, a);
+        if (a.Nq < 16) {
+            const dim3 grid((a.Hq * (a.Smax + 1) + 255) / 256, a.Nq, a.B);
+            hipLaunchKernelGGL(mass_rows_few_kernel, grid, blk, 0, st, a);
+        } else {
+            const dim3 grid((a.Nq + 63) / 64, a.Hq, a.B * ((a.Smax + EN_MASS_RB) / EN_MASS_RB));
+            hipLaunchKernelGGL(mass_rows_kernel, grid, blk, 0, st, a);
         }
+    } else {
+        const dim3 blk(256);
+        const int pairs = a.B * (a.Smax + 1);
+        if (a.Nq >= EN_MASS_FEW_ROWS)
+            hipLaunchKernelGGL(mass_partial_kernel, dim3(mass_partial_blocks(a)), blk, 0, st, a);
+        else if (a.Hq * a.Nq <= 128)
+            hipLaunchKernelGGL((mass_few_rows_kernel<64>), dim3((pairs + 3) / 4), blk, 0, st, a);
+        else
+            hipLaunchKernelGGL((mass_few_rows_kernel<256>), dim3(pairs), blk, 0, st, a);
     }
     return (int)hipGetLastError();
 }
