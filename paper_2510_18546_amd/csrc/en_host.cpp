@@ -893,6 +893,13 @@ static int fixed_point_shift(const en_pool *pool, int n_rows, int count_bits)
     return std::max(0, std::min(40, 62 - count_bits - bits_for(uint64_t(pool->d.n_q_heads) * uint64_t(n_rows))));
 }
 
+// Whether the reduced masses of n_rows query rows per head are summed by mass_few_rows_kernel in a launch of
+// its own, not beside the merge.
+static bool mass_few_rows(const en_pool *pool, int n_rows)
+{
+    return n_rows < EN_MASS_FEW_ROWS || decode_kernel_fits(pool, n_rows);
+}
+
 // For the rows q_first .. q_first + n_rows - 1 of the plan's new tokens, attended with n_splits KV splits.
 static EnMassArgs mass_args(const en_pool *pool, const en_plan *plan, char *ws, const EnWsLayout &L, int n_rows,
                             int n_splits, int q_first)
@@ -903,7 +910,8 @@ static EnMassArgs mass_args(const en_pool *pool, const en_plan *plan, char *ws, 
     a.ws_mlfin = reinterpret_cast<const float *>(ws + L.mlfin_off);
     a.red_out = nullptr;
     a.red_acc = reinterpret_cast<unsigned long long *>(ws + L.redacc_off);
-    a.red_target = pool->d.n_q_heads * ((n_rows + EN_MASS_ROWS - 1) / EN_MASS_ROWS);
+    a.few = mass_few_rows(pool, n_rows) ? 1 : 0;
+    a.red_target = (pool->d.n_q_heads * ((n_rows + 63) / 64) + EN_MASS_UNITS - 1) / EN_MASS_UNITS;
     a.red_count_bits = bits_for(a.red_target);
     a.red_shift = fixed_point_shift(pool, n_rows, a.red_count_bits);
     a.nseg = d_nseg(plan);
@@ -988,7 +996,7 @@ static int run_attention(en_pool *pool, en_plan *plan, const void *q_dev, const 
         return fail(EN_ERR_INVALID_ARG, "%s: en_plan_values_from_pool was changed after the plan's last gather; "
                     "gather again", who);
     // (zero also when this call is not asked for masses: segment_attention_mass may follow)
-    a.red_zero = (ws && n_rows >= EN_MASS_FEW_ROWS) ? reinterpret_cast<unsigned long long *>(ws + L.redacc_off) : nullptr;
+    a.red_zero = (ws && !mass_few_rows(pool, n_rows)) ? reinterpret_cast<unsigned long long *>(ws + L.redacc_off) : nullptr;
     a.n_red_zero = a.red_zero ? plan->B * (plan->Smax + 1) : 0;
     // One partial result per row in the matrix-core kernel: its workgroups add the reduced masses up
     // themselves, in the plan's own accumulators (every workgroup arrives once per bucket; the
@@ -1023,7 +1031,7 @@ static int run_attention(en_pool *pool, en_plan *plan, const void *q_dev, const 
         if (e != 0)
             return hip_fail((hipError_t)e, "split combine launch");
     }
-    if (mass_red_out_dev && !red_direct && (n_partials == 1 || n_rows < EN_MASS_FEW_ROWS)) {
+    if (mass_red_out_dev && !red_direct && (n_partials == 1 || mass_few_rows(pool, n_rows))) {
         // no merge launch carried the reduced masses: one partial result per row, or few rows per head
         EnMassArgs m = mass_args(pool, plan, ws, L, n_rows, n_splits, q_first);
         m.red_out = mass_red_out_dev;

@@ -154,10 +154,10 @@ struct EnAttnArgs {
 
 struct EnMassArgs {
     const float *ws_ml, *ws_seg, *ws_mlfin;
-    // Reduced masses [B, Smax+1], or null. With EN_MASS_FEW_ROWS query rows per head or more they are added up,
-    // as fixed-point integers (2^-red_shift; integer sums do not depend on the order of the additions), in
-    // red_acc [B, Smax+1], whose low red_count_bits bits count the red_target workgroups (heads x chunks of
-    // EN_MASS_ROWS rows) that arrive; the last one writes the sum and sets the word back to zero.
+    // Reduced masses [B, Smax+1], or null. Unless the step has few rows (`few`, en_mass_few_rows) they are added
+    // up, as fixed-point integers (2^-red_shift; integer sums do not depend on the order of the additions), in
+    // red_acc [B, Smax+1], whose low red_count_bits bits count the red_target workgroups (of EN_MASS_UNITS
+    // units of 64 rows of a head) that arrive; the last one writes the sum and sets the word back to zero.
     float *red_out;
     unsigned long long *red_acc;
     int red_shift, red_count_bits, red_target;
@@ -167,6 +167,7 @@ struct EnMassArgs {
     int B, Hq, Nq, Smax, n_splits;
     int sub;                // as in EnAttnArgs: n_splits * sub partial results per row, the sub of a split side by side
     int q_first;            // as in EnAttnArgs
+    int few;                // 1: the reduced masses go through the kernel for few rows per head
 };
 
 struct EnAppendArgs {
@@ -184,8 +185,8 @@ struct EnAppendQ8Args {
 
 
 constexpr int EN_RED_DIRECT_MAX_BUCKETS = 256;   // EnAttnArgs::red_direct: buckets whose sums a workgroup keeps in LDS
-constexpr int EN_MASS_FEW_ROWS = 64;    // below this many query rows per head the reduced masses need no accumulators
-constexpr int EN_MASS_ROWS = 256;       // query rows per workgroup of the reduced masses
+constexpr int EN_MASS_FEW_ROWS = 8;     // below this many query rows per head the reduced masses need no accumulators
+constexpr int EN_MASS_UNITS = 4;        // units of 64 query rows of a head per workgroup of the reduced masses, one per wave
 constexpr int EN_MAX_SPLITS = 64;       // KV splits of a plan: the mass kernels hold one split per lane
 constexpr int EN_MAX_OBJECTS = 255;    // per segment_cluster_assign call (spans travel in the kernel arguments)
 struct EnClusterArgs {

@@ -25,8 +25,8 @@ __device__ __forceinline__ void add_reduced_mass(const EnMassArgs &a, size_t idx
     }
 }
 
-// A workgroup of the reduced masses takes EN_MASS_BG consecutive buckets of one (agent, head) over
-// EN_MASS_ROWS query rows, one row per thread (see mass_partial_block).
+// A workgroup of the reduced masses takes EN_MASS_BG consecutive buckets of one agent over EN_MASS_UNITS
+// units of 64 query rows (see mass_partial_block).
 constexpr int EN_MASS_BG = 8;
 __host__ __device__ inline int mass_bucket_groups(const EnMassArgs &m)
 {
@@ -34,7 +34,7 @@ __host__ __device__ inline int mass_bucket_groups(const EnMassArgs &m)
 }
 __host__ inline int mass_partial_blocks(const EnMassArgs &m)
 {
-    return mass_bucket_groups(m) * m.red_target * m.B;       // red_target: heads x row chunks
+    return mass_bucket_groups(m) * m.red_target * m.B;       // red_target: workgroups per agent and bucket group
 }
 
 // With many splits (decode over a long context by few agents) G = 4, 16 or 32 neighbouring lanes
@@ -371,13 +371,15 @@ __global__ __launch_bounds__(256) void mass_rows_few_kernel(EnMassArgs a)
     a.out[((size_t)b * a.Nq + i) * a.Hq * nb + idx] = v;
 }
 
-// The reduced masses: workgroup blk sums EN_MASS_BG buckets of one head over EN_MASS_ROWS queries. As part
-// of an attention call with several KV splits this runs in the first workgroups of the combine launch and
-// merges the splits' (reference, sum) pairs itself; otherwise it is a launch of its own.
+// The reduced masses: workgroup blk sums EN_MASS_BG buckets over EN_MASS_UNITS units, one per wave, a unit
+// being 64 query rows of one head: a step of few rows per head fills its workgroups with heads (32 heads x 48
+// rows over 1.6 K tokens, attention call: 29.3 us with a launch behind the merge that walked the rows of a
+// bucket one trip to memory after the other, 22.8 like this; without masses 20.7). As part of an attention call with several KV splits this runs in the first
+// workgroups of the combine launch and merges the splits' (reference, sum) pairs itself; otherwise it is a
+// launch of its own.
 //
 // What this costs is instructions per (row, bucket) and dependent trips to memory (about a
-// microsecond each), not bytes. So lanes are rows, a thread has one (a second round of rows per thread
-// is a second trip: 512 rows in one workgroup took 1.5 us more than in two): a row's merged (reference,
+// microsecond each), not bytes. So lanes are rows: a row's merged (reference,
 // sum) pair is made once for the group's buckets; everything that is the same for all rows (which splits
 // cover a bucket, whether they hold keys) is decided from the agent's header and bounds before the rows
 // start; and a row's loads for all buckets go out together: a bucket
@@ -388,22 +390,24 @@ __global__ __launch_bounds__(256) void mass_rows_few_kernel(EnMassArgs a)
 // 8K-context merge: one workgroup per (bucket, head), all of the above per row: 23 us / 6 us;
 // the same buckets in one workgroup with loads as they are needed: 27 us / 13 us; one launch that
 // lets the last workgroup finish (a device-scope release per workgroup, which writes the L2
-// back): 25 us; one workgroup per bucket: 14 us.)
+// back): 25 us; one workgroup per bucket: 14 us; two units per wave and four buckets, four and four, which
+// halve and quarter the arrivals at an accumulator: 0.3 and 4 us more than one and eight.)
 __device__ __forceinline__ void mass_partial_block(const EnMassArgs &a, int blk, float *red)
 {
     constexpr int BG = EN_MASS_BG;
     const int ng = mass_bucket_groups(a);
     const int s0 = (blk % ng) * BG;
-    const int hq = (blk / ng) % a.Hq;
-    const int n_chunks = a.red_target / a.Hq;
-    const int i = (blk / (ng * a.Hq)) % n_chunks * EN_MASS_ROWS + threadIdx.x;
+    const int wg = (blk / ng) % a.red_target;          // workgroup among those of the agent's bucket group
     const int b = blk / (ng * a.red_target);
-    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
+    const int n_chunks = (a.Nq + 63) / 64;
+    const int n_units = a.Hq * n_chunks;
+    const int unit = wg * EN_MASS_UNITS + wave;
     float acc[BG];
 #pragma unroll
     for (int j = 0; j < BG; ++j)
         acc[j] = 0.f;
-    if (i - lane < a.Nq) {                         // a wave without rows has nothing to set up
+    if (unit < n_units) {                         // a wave without rows has nothing to set up
         const size_t rows = (size_t)a.B * a.Hq * a.Nq;
         const en_table_ptr hdr = as_table(a.hdr + 4 * (size_t)b);
         const int S = hdr[0];
@@ -416,8 +420,9 @@ __device__ __forceinline__ void mass_partial_block(const EnMassArgs &a, int blk,
         // kernel's time: the scalar unit is shared by all waves of a compute unit.
         int lo_v, hi_v;
         bool live_v, use0_v, use1_v, next_v;
-        size_t off0_v, off1_v;                          // byte offsets of the bucket's two entries of row 0
+        size_t off0_v, off1_v;                          // byte offsets of the bucket's two entries of row 0, head 0
         const size_t per_split = (size_t)a.B * a.Hq * (a.Smax + 1) * a.Nq * 8;      // bytes
+        const size_t per_head = (size_t)(a.Smax + 1) * a.Nq * 8;
         {
             const int jl = lane % BG;
             const int s = min(s0 + jl, a.Smax);
@@ -435,58 +440,51 @@ __device__ __forceinline__ void mass_partial_block(const EnMassArgs &a, int blk,
             use1_v = live_v && h > l && next_v && e1 != e2;
             lo_v = (int)l;
             hi_v = (int)h;
-            off0_v = l * per_split + (((size_t)b * a.Hq + hq) * (a.Smax + 1) + s) * a.Nq * 8;
+            off0_v = l * per_split + (size_t)b * a.Hq * per_head + (size_t)s * a.Nq * 8;
             off1_v = off0_v + (next_v ? per_split : 0);
         }
         const unsigned use0 = (unsigned)__ballot(use0_v), use1 = (unsigned)__ballot(use1_v);
         const unsigned live = (unsigned)__ballot(live_v);
         const bool simple = a.sub == 1 && __ballot(live_v && hi_v - lo_v > 1) == 0;
-        int lo[BG];
-#pragma unroll
-        for (int j = 0; j < BG; ++j)
-            lo[j] = __builtin_amdgcn_readlane(lo_v, j);
+        const int hq = unit / n_chunks;
+        const int row_i = (unit - hq * n_chunks) * 64 + lane;
+        const bool on = row_i < a.Nq;
+        const int i = on ? row_i : 0;
+        float M, L;
         if (simple) {
-            const char *p0[BG], *p1[BG];
+            f32x2 v0[BG], v1[BG];
 #pragma unroll
             for (int j = 0; j < BG; ++j) {
-                p0[j] = (const char *)a.ws_seg + readlane64(off0_v, j);
-                p1[j] = (const char *)a.ws_seg + readlane64(off1_v, j);
+                const char *p0 = (const char *)a.ws_seg + readlane64(off0_v, j) + hq * per_head;
+                const char *p1 = (const char *)a.ws_seg + readlane64(off1_v, j) + hq * per_head;
+                v0[j] = *reinterpret_cast<const f32x2 *>(p0 + (unsigned)i * 8u);
+                v1[j] = *reinterpret_cast<const f32x2 *>(p1 + (unsigned)i * 8u);
             }
-            if (i < a.Nq) {
-                const size_t row = ((size_t)b * a.Hq + hq) * a.Nq + i;
-                f32x2 v0[BG], v1[BG];
+            merged_ml(a, rows, ((size_t)b * a.Hq + hq) * a.Nq + i, M, L);
+            const float inv = on ? 1.f / L : 0.f;
 #pragma unroll
-                for (int j = 0; j < BG; ++j) {
-                    v0[j] = *reinterpret_cast<const f32x2 *>(p0[j] + (unsigned)i * 8u);
-                    v1[j] = *reinterpret_cast<const f32x2 *>(p1[j] + (unsigned)i * 8u);
-                }
-                float M, L;
-                merged_ml(a, rows, row, M, L);
-                const float inv = 1.f / L;
-#pragma unroll
-                for (int j = 0; j < BG; ++j) {
-                    float part = 0.f;
-                    if (((use0 >> j) & 1) && v0[j][1] != EN_NEG_INF)
-                        part += v0[j][0] * fast_exp2(v0[j][1] - M);
-                    if (((use1 >> j) & 1) && v1[j][1] != EN_NEG_INF)
-                        part += v1[j][0] * fast_exp2(v1[j][1] - M);
-                    acc[j] += part * inv;
-                }
+            for (int j = 0; j < BG; ++j) {
+                float part = 0.f;
+                if (((use0 >> j) & 1) && v0[j][1] != EN_NEG_INF)
+                    part += v0[j][0] * fast_exp2(v0[j][1] - M);
+                if (((use1 >> j) & 1) && v1[j][1] != EN_NEG_INF)
+                    part += v1[j][0] * fast_exp2(v1[j][1] - M);
+                acc[j] = part * inv;
             }
         } else {
             const EnSplitMap map = split_map(a.n_splits, (int)ntiles);
-            int hi[BG];
+            int lo[BG], hi[BG];
 #pragma unroll
-            for (int j = 0; j < BG; ++j)
+            for (int j = 0; j < BG; ++j) {
+                lo[j] = __builtin_amdgcn_readlane(lo_v, j);
                 hi[j] = __builtin_amdgcn_readlane(hi_v, j);
-            if (i < a.Nq) {
-                const size_t row = ((size_t)b * a.Hq + hq) * a.Nq + i;
-                float M, L;
-                merged_ml(a, rows, row, M, L);
+            }
+            if (on) {
+                merged_ml(a, rows, ((size_t)b * a.Hq + hq) * a.Nq + i, M, L);
 #pragma unroll
                 for (int j = 0; j < BG; ++j)
                     if ((live >> j) & 1)
-                        acc[j] += row_bucket_mass(a, b, hq, i, s0 + j, lo[j], hi[j], M, L, map.keys);
+                        acc[j] = row_bucket_mass(a, b, hq, i, s0 + j, lo[j], hi[j], M, L, map.keys);
             }
         }
     }
@@ -639,7 +637,7 @@ int en_launch_combine(const en_pool *pool, const EnAttnArgs &a, const EnMassArgs
         G = a.n_splits > 64 ? 32 : (a.n_splits > 16 ? 16 : (a.n_splits > 4 ? 4 : 1));
     const size_t n = (size_t)a.B * a.Hq * a.Nq * (D / vec) * G;
     const int n_comb = (int)((n + 255) / 256);
-    const int n_part = m.red_out && m.Nq >= EN_MASS_FEW_ROWS ? mass_partial_blocks(m) : 0;
+    const int n_part = m.red_out && !m.few ? mass_partial_blocks(m) : 0;
     const dim3 grid((unsigned)(n_comb + n_part)), blk(256);
 #define EN_COMBINE(T, DD)                                                                             \
     do {                                                                                              \
@@ -695,7 +693,7 @@ int en_launch_mass(const en_pool *pool, const EnMassArgs &a, int reduce, void *s
     } else {
         const dim3 blk(256);
         const int pairs = a.B * (a.Smax + 1);
-        if (a.Nq >= EN_MASS_FEW_ROWS)
+        if (!a.few)
             hipLaunchKernelGGL(mass_partial_kernel, dim3(mass_partial_blocks(a)), blk, 0, st, a);
         else if (a.Hq * a.Nq <= 128)
             hipLaunchKernelGGL((mass_few_rows_kernel<64>), dim3((pairs + 3) / 4), blk, 0, st, a);

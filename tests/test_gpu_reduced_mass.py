@@ -1,0 +1,33 @@
+"""The reduced masses where their pieces meet: units of 64 query rows of a head, four to a workgroup, eight
+buckets each; steps of few rows, whose workgroups hold several heads; heads and buckets that do not fill the last
+workgroup; buckets within one split, over two and over more. Against the oracle, to the tolerances of
+test_gpu_parity, as part of the attention call and as a call of its own."""
+import numpy as np
+import pytest
+
+from paper_2510_18546_amd import inputs as I
+from test_gpu_parity import run_case, small, step_mod  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,heads,kv,n_new,n_sel,splits", [
+    (I.BF16, 10, 2, 7, 6, 2),        # the last step that the kernel for few rows takes
+    (I.BF16, 10, 2, 8, 8, 2),        # the first that is added up beside the merge: two idle waves, one bucket more than a group
+    (I.BF16, 7, 1, 63, 7, 3),        # units of 63 rows; eight buckets exactly
+    (I.BF16, 5, 1, 64, 5, 7),        # buckets over more than two splits
+    (I.BF16, 6, 2, 65, 9, 2),        # a second unit of one row per head
+    (I.BF16, 6, 2, 40, 3, 1),        # one split: no merge launch
+    (I.F32, 3, 1, 8, 9, 2),
+    (I.F32, 3, 3, 66, 2, 1),
+])
+def test_reduced_masses_of_few_rows(step_mod, oracle, dtype, heads, kv, n_new, n_sel, splits):
+    cfg = small(f"reduced-{n_new}-{n_sel}", 800 + n_new, dtype=dtype, n_agents=2, n_q_heads=heads, n_kv_heads=kv,
+                head_dim=64, len_lo=0, n_sel=n_sel, n_new=n_new, rope_base=1e4)
+    st, _, _, _ = run_case(step_mod, oracle, cfg, n_splits=splits)
+    red = st.mass_red_host()
+    st.mass_red.fill_(float("nan"))
+    st.masses(1)                     # the same sums once more, from the scratch that the attention call left
+    # both are sums of the same masses in float32, in another order: the sum of n numbers of one sign is off by at
+    # most n 2^-24 of itself (at most 128 terms per float sum, the rest is added up exactly)
+    np.testing.assert_allclose(st.mass_red_host(), red, rtol=2.0 ** -16, atol=2.0 ** -30)
