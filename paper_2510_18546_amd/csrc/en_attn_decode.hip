@@ -672,11 +672,38 @@ __global__ __launch_bounds__(64 * F32_WAVES) void attn_f32_kernel(EnAttnArgs a)
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
             o[j] *= alpha;
+        // A product sums over the block's keys, the hidden ones with probability 0. That is no contribution
+        // unless such a key's value is infinite or NaN, which a row that does not see the key must not take:
+        // then the keys go one by one, and a row keeps its sums where it does not see the key.
+        bool by_key = false;
+        if (kb + F32_KEYS - 1 > min(Lc, we - 1)) {           // some key may be hidden from some row
+            uint32_t top = 0;                                // (by the bits: this library is built without NaN compares)
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
+            for (int e = 0; e < 4; ++e)
 #pragma unroll
-            for (int j = 0; j < NJ; ++j)
-                o[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(vc[e][j / 4][j % 4], p[e], o[j], 0, 0, 0);
+                for (int j = 0; j < NJ; ++j)
+                    top = max(top, __float_as_uint(vc[e][j / 4][j % 4]) & 0x7f800000u);
+            by_key = __any(top == 0x7f800000u);
+        }
+        if (!by_key) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+                    o[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(vc[e][j / 4][j % 4], p[e], o[j], 0, 0, 0);
+        } else {
+            const int last = min(Lc + i_row, we - 1) - kb;   // the row's last visible key of the block
+#pragma unroll 1
+            for (int g = 0; g < 4; ++g)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j) {
+                        const f32x4 with = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                            grp == g ? vc[e][j / 4][j % 4] : 0.f, grp == g ? p[e] : 0.f, o[j], 0, 0, 0);
+                        o[j] = 4 * g + e <= last ? with : o[j];
+                    }
+        }
     }
 
     // ---- the waves meet ----

@@ -1,6 +1,7 @@
 """The fp32 attention kernel where its pieces meet: eight waves share a split's keys in runs of 16-key
 blocks, a segment can lie inside one wave, cross one or many of their borders or fill several waves, and the
 16 rows of a workgroup can span heads. Against the oracle, to the fp32 tolerance of test_gpu_parity."""
+import numpy as np
 import pytest
 
 from paper_2510_18546_amd import inputs as I
@@ -23,3 +24,21 @@ def test_fp32_waves_and_segments(step_mod, oracle, d, kv, ratio, n_new, seg, n_s
                 n_kv_heads=kv, n_agents=2, capacity=max(seg, 1), len_lo=max(0, seg - 3), len_hi=seg, n_sel=n_sel,
                 n_new=n_new, rope_base=1e4)
     run_case(step_mod, oracle, cfg, n_splits=splits)
+
+
+@pytest.mark.parametrize("d,n_new,splits", [(64, 1, 1), (64, 20, 1), (128, 33, 3)])
+def test_fp32_values_of_hidden_tokens(step_mod, d, n_new, splits):
+    """The value of the last new token is no number: the rows before it, which do not see it, are what they were."""
+    cfg = small(f"f32-hidden-{d}-{n_new}", 760 + n_new, dtype=I.F32, head_dim=d, n_q_heads=4, rope_base=1e4,
+                n_new=n_new)
+    st = step_mod.PlanningStep(I.make_workload(cfg), n_splits=splits)
+    st.run()
+    out, mass = st.out_host(), st.mass_host()
+    for x in (float("nan"), float("inf")):
+        st.v_new[:, -1] = x
+        st.run()
+        got = st.out_host()
+        # (the same products, at the last block's keys one by one: sums of at most 16 terms in another order)
+        np.testing.assert_allclose(got[:, :-1], out[:, :-1], rtol=0, atol=16 * 2.0 ** -24 * np.abs(out).max())
+        assert not np.isfinite(got[:, -1]).any()
+        np.testing.assert_array_equal(st.mass_host(), mass)
