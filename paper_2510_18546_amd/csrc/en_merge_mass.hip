@@ -255,8 +255,8 @@ __device__ __forceinline__ float row_bucket_mass(const EnMassArgs &a, int b, int
     return acc / L;
 }
 
-// reduce = 0. grid: (ceil(Nq/64), Hq, B * chunks of EN_MASS_RB buckets), 256 threads: the block takes 64
-// queries of one head and one chunk of buckets. The scratch is laid out query-fastest, the result
+// reduce = 0. grid: (ceil(Nq/64) * chunks of EN_MASS_RB buckets, Hq, B), 256 threads: the block takes 64
+// queries of one head and one chunk of buckets (both in x: the other dimensions of a grid end at 65535). The scratch is laid out query-fastest, the result
 // bucket-fastest: each wave computes the masses of four buckets for the 64 queries (coalesced reads), the
 // block transposes them through LDS and writes runs of 64 bytes per query. A trip to memory takes about a
 // microsecond and each wave makes one for its four buckets: a block that walked all buckets of its rows
@@ -267,10 +267,10 @@ __global__ __launch_bounds__(256) void mass_rows_kernel(EnMassArgs a)
     constexpr int PER = EN_MASS_RB / 4;          // buckets per wave
     __shared__ float tile[64][EN_MASS_RB + 1];
     const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-    const int i = blockIdx.x * 64 + lane;
     const int n_chunks = (a.Smax + EN_MASS_RB) / EN_MASS_RB;
-    const int hq = blockIdx.y, b = blockIdx.z / n_chunks;
-    const int s0 = blockIdx.z % n_chunks * EN_MASS_RB;
+    const int i0 = blockIdx.x / n_chunks * 64, i = i0 + lane;
+    const int hq = blockIdx.y, b = blockIdx.z;
+    const int s0 = blockIdx.x % n_chunks * EN_MASS_RB;
     const bool valid = i < a.Nq;
     const size_t rows = (size_t)a.B * a.Hq * a.Nq;
     const size_t row = ((size_t)b * a.Hq + hq) * a.Nq + (valid ? i : 0);
@@ -335,7 +335,7 @@ __global__ __launch_bounds__(256) void mass_rows_kernel(EnMassArgs a)
 #pragma unroll
     for (int k = 0; k < 64 * EN_MASS_RB / 256; ++k) {
         const int r = threadIdx.x / EN_MASS_RB + k * (256 / EN_MASS_RB);
-        const int ir = blockIdx.x * 64 + r;
+        const int ir = i0 + r;
         if (ir < a.Nq && s0 + c <= a.Smax)
             a.out[(((size_t)b * a.Nq + ir) * a.Hq + hq) * (a.Smax + 1) + s0 + c] = tile[r][c];
     }
@@ -687,7 +687,7 @@ int en_launch_mass(const en_pool *pool, const EnMassArgs &a, int reduce, void *s
             const dim3 grid((a.Hq * (a.Smax + 1) + 255) / 256, a.Nq, a.B);
             hipLaunchKernelGGL(mass_rows_few_kernel, grid, blk, 0, st, a);
         } else {
-            const dim3 grid((a.Nq + 63) / 64, a.Hq, a.B * ((a.Smax + EN_MASS_RB) / EN_MASS_RB));
+            const dim3 grid((a.Nq + 63) / 64 * ((a.Smax + EN_MASS_RB) / EN_MASS_RB), a.Hq, a.B);
             hipLaunchKernelGGL(mass_rows_kernel, grid, blk, 0, st, a);
         }
     } else {

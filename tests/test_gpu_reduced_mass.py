@@ -31,3 +31,11 @@ def test_reduced_masses_of_few_rows(step_mod, oracle, dtype, heads, kv, n_new, n
     # both are sums of the same masses in float32, in another order: the sum of n numbers of one sign is off by at
     # most n 2^-24 of itself (at most 128 terms per float sum, the rest is added up exactly)
     np.testing.assert_allclose(st.mass_red_host(), red, rtol=2.0 ** -16, atol=2.0 ** -30)
+
+
+def test_masses_of_many_agents_and_segments(step_mod, oracle):
+    # agents x chunks of 16 buckets: 4100 x 16, more than a grid's second and third dimensions hold
+    cfg = small("many-agents-segments", 860, dtype=I.F32, n_agents=4100, n_q_heads=1, n_kv_heads=1, head_dim=64,
+                n_groups=256, capacity=1, len_lo=0, len_hi=1, n_sel=240, n_new=16, rope_base=1e4)
+    rows = np.array([(b, i, 0) for b in (0, 2049, 4095, 4096, 4099) for i in range(16)], dtype=np.int32)
+    run_case(step_mod, oracle, cfg, rows=rows)
