@@ -39,3 +39,28 @@ def test_masses_of_many_agents_and_segments(step_mod, oracle):
                 n_groups=256, capacity=1, len_lo=0, len_hi=1, n_sel=240, n_new=16, rope_base=1e4)
     rows = np.array([(b, i, 0) for b in (0, 2049, 4095, 4096, 4099) for i in range(16)], dtype=np.int32)
     run_case(step_mod, oracle, cfg, rows=rows)
+
+
+@pytest.mark.parametrize("dtype,n_new,splits", [(I.BF16, 7, 2), (I.BF16, 40, 2), (I.BF16, 65, 7), (I.F32, 9, 1)])
+def test_reduced_masses_of_a_query_that_is_no_number(step_mod, dtype, n_new, splits):
+    """The sums that hold its masses are NaN too, the other agent's are as before; the next call, without it, is
+    free of it."""
+    cfg = small(f"nan-{n_new}", 870 + n_new, dtype=dtype, n_agents=2, n_q_heads=6, head_dim=64, len_lo=8, n_new=n_new,
+                rope_base=1e4)
+    st = step_mod.PlanningStep(I.make_workload(cfg), n_splits=splits)
+
+    def reduced():
+        st.gather()
+        st.attention()
+        st.masses(1)
+        return st.mass_red_host()
+
+    clean = reduced()
+    assert np.isfinite(clean).all()
+    q = st.q.clone()
+    st.q[1, n_new // 2, 3] = float("nan")
+    dirty = reduced()
+    assert np.isnan(dirty[1]).all()
+    np.testing.assert_array_equal(dirty[0], clean[0])
+    st.q.copy_(q)
+    np.testing.assert_array_equal(reduced(), clean)
