@@ -143,7 +143,6 @@ __global__ __launch_bounds__(256) void combine_kernel(EnAttnArgs a, EnMassArgs m
 }
 
 // ---------------------------------------------------------------------------
-// ---------------------------------------------------------------------------
 // mass: probability mass per (row, bucket) from the raw partial sums.
 //   mass = sum over splits touching the bucket of seg * 2^(m_seg - M) / L
 // with (M, L) the row's final reference maximum and sum.
