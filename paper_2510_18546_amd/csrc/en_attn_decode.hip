@@ -178,8 +178,10 @@ __global__ __launch_bounds__(64 * SUB) void attn_decode_kernel(EnAttnArgs a)
         for (int j = 0; j < APP_J; ++j) {
             const int c = lane + 64 * j;
             if (c < D / 2) {
-                kd[c] = (bf16_t)(app_x1[j] * app_cs[j] - app_x2[j] * app_sn[j]);
-                kd[c + D / 2] = (bf16_t)(app_x2[j] * app_cs[j] + app_x1[j] * app_sn[j]);
+                float y1, y2;
+                rope_key_pair(app_x1[j], app_x2[j], app_cs[j], app_sn[j], y1, y2);
+                kd[c] = (bf16_t)y1;
+                kd[c + D / 2] = (bf16_t)y2;
                 vd[(size_t)c * a.T] = app_v1[j];
                 vd[(size_t)(c + D / 2) * a.T] = app_v2[j];
             }

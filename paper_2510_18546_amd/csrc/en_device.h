@@ -40,6 +40,20 @@ __device__ __forceinline__ void rope_scale_pair(float x1, float x2, float c, flo
     y2 = (x2 * c + x1 * s) * scale;
 }
 
+// A key's rotary pair turned by its position's angle: of the two products of each half one is rounded and the
+// other goes into a fused multiply-add. Which one is said here: left to the compiler, the choice changed with
+// the loop around the expression, and the last bits of the context with it. The second half rounds x2's
+// product; in the 8-bit gather (X1_ROUNDED) x1's: the bits that these contexts have always had.
+template <bool X1_ROUNDED = false, typename F>
+__device__ __forceinline__ void rope_key_pair(F x1, F x2, F c, F s, F &y1, F &y2)
+{
+#pragma clang fp contract(off)
+    const F a = x2 * s;
+    y1 = __builtin_elementwise_fma(x1, c, -a);
+    const F r = X1_ROUNDED ? x1 * s : x2 * c;
+    y2 = X1_ROUNDED ? __builtin_elementwise_fma(x2, c, r) : __builtin_elementwise_fma(x1, s, r);
+}
+
 // Exchange a value with the lane 32 positions away.
 __device__ __forceinline__ float xor32(float v)
 {

@@ -126,8 +126,7 @@ __device__ __forceinline__ void gather_k_rows(const EnGatherArgs &a, int tok, in
             fvec y1 = 0.f, y2 = 0.f;
             if (ksrc) {
                 const fvec f1 = __builtin_convertvector(x1[h], fvec), f2 = __builtin_convertvector(x2[h], fvec);
-                y1 = f1 * cs - f2 * sn;
-                y2 = f2 * cs + f1 * sn;
+                rope_key_pair(f1, f2, cs, sn, y1, y2);
             }
             store_context<STREAM>(dst + c * E, __builtin_convertvector(y1, tvec));
             store_context<STREAM>(dst + D / 2 + c * E, __builtin_convertvector(y2, tvec));
@@ -408,8 +407,7 @@ __device__ __forceinline__ void gather_q8_k_rows(const EnGatherArgs &a, const En
     if (loc.kind != 0) {
         const fvec cs = *reinterpret_cast<const fvec *>(a.cos_tab + (size_t)tok * (D / 2) + c * E);
         const fvec sn = *reinterpret_cast<const fvec *>(a.sin_tab + (size_t)tok * (D / 2) + c * E);
-        y1 = x1 * cs - x2 * sn;
-        y2 = x2 * cs + x1 * sn;
+        rope_key_pair<true>(x1, x2, cs, sn, y1, y2);
     }
     *reinterpret_cast<tvec *>(dst + c * E) = __builtin_convertvector(y1, tvec);
     *reinterpret_cast<tvec *>(dst + D / 2 + c * E) = __builtin_convertvector(y2, tvec);
@@ -545,8 +543,10 @@ __global__ __launch_bounds__(D / 2) void ctx_append_kernel(EnCtxAppendArgs a)
     const float cs = a.cos_tab[(size_t)pos * (D / 2) + c], sn = a.sin_tab[(size_t)pos * (D / 2) + c];
     const float x1 = (float)kr[c], x2 = (float)kr[c + D / 2];
     T *kd = (T *)a.kc + (((size_t)b * a.Hkv + h) * a.T + pos) * D;
-    kd[c] = (T)(x1 * cs - x2 * sn);
-    kd[c + D / 2] = (T)(x2 * cs + x1 * sn);
+    float y1, y2;
+    rope_key_pair(x1, x2, cs, sn, y1, y2);
+    kd[c] = (T)y1;
+    kd[c + D / 2] = (T)y2;
     if constexpr (sizeof(T) == 4) {
         T *vd = (T *)a.vt + (((size_t)b * a.Hkv + h) * a.T + pos) * D;
         vd[c] = vr[c];
