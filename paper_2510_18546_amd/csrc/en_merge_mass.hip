@@ -314,7 +314,6 @@ __global__ __launch_bounds__(256) void mass_rows_kernel(EnMassArgs a)
             e0[j] = p[sp * per_split];
             e1[j] = p[sp1 * per_split];
         }
-        const float inv = 1.f / L;
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
             float acc = 0.f;
@@ -324,7 +323,7 @@ __global__ __launch_bounds__(256) void mass_rows_kernel(EnMassArgs a)
                 acc += e0[j][0] * fast_exp2(e0[j][1] - M);
             if (live[j] && hi[j] > lo[j] && ((map.keys >> hi[j]) & 1) && e1[j][1] != EN_NEG_INF)
                 acc += e1[j][0] * fast_exp2(e1[j][1] - M);
-            v[j] = acc * inv;
+            v[j] = acc / L;              // (as row_bucket_mass: one rounding, not two)
         }
     } else {
 #pragma unroll

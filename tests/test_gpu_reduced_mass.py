@@ -1,7 +1,8 @@
 """The reduced masses where their pieces meet: units of 64 query rows of a head, four to a workgroup, eight
 buckets each; steps of few rows, whose workgroups hold several heads; heads and buckets that do not fill the last
 workgroup; buckets within one split, over two and over more. Against the oracle, to the tolerances of
-test_gpu_parity, as part of the attention call and as a call of its own."""
+test_gpu_parity, as part of the attention call and as a call of its own. And the masses of every row, whose sums
+are exact where all scores are 0."""
 import numpy as np
 import pytest
 
@@ -31,6 +32,26 @@ def test_reduced_masses_of_few_rows(step_mod, oracle, dtype, heads, kv, n_new, n
     # both are sums of the same masses in float32, in another order: the sum of n numbers of one sign is off by at
     # most n 2^-24 of itself (at most 128 terms per float sum, the rest is added up exactly)
     np.testing.assert_allclose(st.mass_red_host(), red, rtol=2.0 ** -16, atol=2.0 ** -30)
+
+
+@pytest.mark.parametrize("dtype,n_new,n_sel,splits", [
+    (I.F32, 15, 5, 1), (I.F32, 16, 5, 1), (I.F32, 70, 18, 2), (I.BF16, 40, 5, 1), (I.BF16, 65, 16, 2),
+    (I.BF16, 130, 3, 7)])
+def test_masses_of_queries_without_direction(step_mod, dtype, n_new, n_sel, splits):
+    """All scores are 0, every exponential is 1, the sums count keys: a mass is the one quotient of the segment's
+    keys and the row's, rounded once. (15 and 16 rows per head: either side of the border between the two kernels.)"""
+    cfg = small(f"even-{n_new}-{n_sel}", 830 + n_new, dtype=dtype, n_agents=2, n_q_heads=4, head_dim=64, n_groups=24,
+                len_lo=0, n_sel=n_sel, n_new=n_new, rope_base=1e4)
+    st = step_mod.PlanningStep(I.make_workload(cfg), n_splits=splits)
+    st.q.zero_()
+    st.run()
+    mass = st.mass_host()
+    for b in range(cfg.n_agents):
+        off = st.plan.offsets(b)
+        for i in range(n_new):
+            keys = np.append(np.diff(off), i + 1).astype(np.float32)
+            want = keys / np.float32(off[-1] + i + 1)
+            np.testing.assert_array_equal(mass[b, i], np.broadcast_to(want.astype(np.float64), mass[b, i].shape))
 
 
 def test_masses_of_many_agents_and_segments(step_mod, oracle):
