@@ -256,9 +256,9 @@ int gather_rope(en_pool *pool, en_plan *plan, const void *k_new_dev, const void 
 int gather_rope_queries(en_pool *pool, en_plan *plan, const void *k_new_dev, const void *v_new_dev,
                         const void *q_dev, void *kc_dev, void *vt_dev, void *q_prep_dev, void *stream);
 
-/* Bytes of scratch the attention call needs for this plan: per-split running
- * (max, sum), per-(row, segment) partial sums, and, when n_splits > 1, partial
- * outputs (a step of few rows and few agents keeps two partial results per
+/* Bytes of scratch the attention call and the mass calls behind it need for this
+ * plan: per-split running (max, sum), per-(row, segment) partial sums, parts of
+ * the reduced masses, and, when n_splits > 1, partial outputs (a step of few rows and few agents keeps two partial results per
  * split: the size accounts for it). */
 size_t en_workspace_bytes(const en_pool *pool, const en_plan *plan);
 
@@ -289,9 +289,10 @@ int segmented_prefill_attention(en_pool *pool, en_plan *plan, const void *q_dev,
  *                      by the attention kernel itself in words that belong to
  *                      the plan, so calls on one plan must not overlap), so the
  *                      result does not depend on the order in which they arrive
- *                      and is the same from run to run; it may differ from what
- *                      segment_attention_mass(reduce = 1) gives (the rows in
- *                      other groups) in the last bits. That call may still
+ *                      and is the same from run to run, in steps of 2^-40 (of
+ *                      2^-30 at worst up to 4 M heads x rows), where
+ *                      segment_attention_mass(reduce = 1) adds up floats: small
+ *                      sums have fewer digits here. That call may still
  *                      follow, with either reduce mode. At most 1023 query
  *                      heads.
  * Plans whose steps have enough query rows for the matrix-core prefill kernel
@@ -371,7 +372,7 @@ int segmented_decode_step_static(en_pool *pool, en_plan *plan, int32_t q_first, 
  *                block, entries beyond are 0; each row sums to 1.
  *   reduce = 1 : mass_out_dev float [B, Smax+1], the above summed over heads
  *                and query tokens (divide by Hq*N_q for the average).
- * The reduced form also writes a small part of the scratch (accumulators of the
+ * The reduced form also writes a small part of the scratch (the parts of the
  * sums): two reduced calls on one scratch must not overlap in time.
  * Errors: INVALID_ARG, DEVICE.
  */

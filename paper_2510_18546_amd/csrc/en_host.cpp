@@ -644,6 +644,19 @@ int en_attn_sub(const en_pool *pool, const en_plan *pl, int n_rows, int n_splits
     return long(pl->B) * pool->d.n_kv_heads * n_splits <= 2L * pool->n_cu ? 2 : 1;
 }
 
+// Whether the reduced masses of n_rows query rows per head are summed by mass_few_rows_kernel in a launch of
+// its own, not beside the merge.
+static bool mass_few_rows(const en_pool *pool, int n_rows)
+{
+    return n_rows < EN_MASS_FEW_ROWS || decode_kernel_fits(pool, n_rows);
+}
+
+// Workgroups per agent and bucket group of the others.
+static int mass_workgroups(const en_pool *pool, int n_rows)
+{
+    return (pool->d.n_q_heads * ((n_rows + 63) / 64) + EN_MASS_UNITS - 1) / EN_MASS_UNITS;
+}
+
 // Scratch layout for n_rows query rows per agent and n_splits KV splits.
 EnWsLayout en_ws_layout_for(const en_pool *pool, const en_plan *pl, int n_rows, int n_splits_plan)
 {
@@ -658,6 +671,10 @@ EnWsLayout en_ws_layout_for(const en_pool *pool, const en_plan *pl, int n_rows, 
     L.total = L.opart_off;
     if (n_splits > 1)
         L.total = align256(L.opart_off + size_t(n_splits) * rows * pool->d.head_dim * elem_size(pool->d.dtype));
+    // last, since only segment_attention_mass uses it, which does not follow a decode step
+    L.parts_off = L.total;
+    if (!mass_few_rows(pool, n_rows))
+        L.total = align256(L.parts_off + size_t(pl->B) * (pl->Smax + 1) * mass_workgroups(pool, n_rows) * sizeof(float));
     return L;
 }
 
@@ -886,23 +903,18 @@ static int bits_for(uint64_t n)
         ++bits;
     return bits;
 }
-// Fixed point of the reduced masses: a sum is at most Hq * n_rows, and sum << (shift + count bits) must fit
-// 63 bits; 2^-40 is far below the rounding of the float that the sum becomes.
+// Fixed point of the reduced masses of an attention call: a sum is at most Hq * n_rows, and above the count's bits
+// (ten at most, EN_MASS_ARRIVALS) all of it must stay below the word's top bit, which marks a sum that is no number.
+// Steps of 2^-40 up to 4096 heads x rows at least, of 2^-30 up to 4 M.
 static int fixed_point_shift(const en_pool *pool, int n_rows, int count_bits)
 {
-    return std::max(0, std::min(40, 62 - count_bits - bits_for(uint64_t(pool->d.n_q_heads) * uint64_t(n_rows))));
-}
-
-// Whether the reduced masses of n_rows query rows per head are summed by mass_few_rows_kernel in a launch of
-// its own, not beside the merge.
-static bool mass_few_rows(const en_pool *pool, int n_rows)
-{
-    return n_rows < EN_MASS_FEW_ROWS || decode_kernel_fits(pool, n_rows);
+    return std::max(0, std::min(40, 62 - count_bits - bits_for(uint64_t(pool->d.n_q_heads) * uint64_t(n_rows) - 1)));
 }
 
 // For the rows q_first .. q_first + n_rows - 1 of the plan's new tokens, attended with n_splits KV splits.
+// fixed_point: how the reduced masses' parts meet (see EnMassArgs::red_out).
 static EnMassArgs mass_args(const en_pool *pool, const en_plan *plan, char *ws, const EnWsLayout &L, int n_rows,
-                            int n_splits, int q_first)
+                            int n_splits, int q_first, bool fixed_point)
 {
     EnMassArgs a;
     a.ws_ml = reinterpret_cast<const float *>(ws + L.ml_off);
@@ -911,7 +923,8 @@ static EnMassArgs mass_args(const en_pool *pool, const en_plan *plan, char *ws, 
     a.red_out = nullptr;
     a.red_acc = reinterpret_cast<unsigned long long *>(ws + L.redacc_off);
     a.few = mass_few_rows(pool, n_rows) ? 1 : 0;
-    a.red_target = (pool->d.n_q_heads * ((n_rows + 63) / 64) + EN_MASS_UNITS - 1) / EN_MASS_UNITS;
+    a.parts = fixed_point ? nullptr : reinterpret_cast<float *>(ws + L.parts_off);
+    a.red_target = mass_workgroups(pool, n_rows);
     a.red_count_bits = bits_for(a.red_target);
     a.red_shift = fixed_point_shift(pool, n_rows, a.red_count_bits);
     a.nseg = d_nseg(plan);
@@ -929,10 +942,11 @@ static EnMassArgs mass_args(const en_pool *pool, const en_plan *plan, char *ws, 
 }
 
 // Attention of n_rows query rows per agent (new tokens q_first .. q_first+n_rows-1 of the plan)
-// with n_splits KV splits; the scratch is laid out for exactly these.
+// with n_splits KV splits; the scratch is laid out for exactly these. is_step: a decode step, which no
+// segment_attention_mass follows.
 static int run_attention(en_pool *pool, en_plan *plan, const void *q_dev, const void *kc_dev,
                          const void *vt_dev, void *out_dev, void *ws_dev, size_t ws_bytes, void *stream,
-                         int q_first, int n_rows, int n_splits, const char *who,
+                         int q_first, int n_rows, int n_splits, bool is_step, const char *who,
                          const void *app_k_dev = nullptr, const void *app_v_dev = nullptr,
                          bool q_prepared = false, float *mass_red_out_dev = nullptr)
 {
@@ -945,8 +959,9 @@ static int run_attention(en_pool *pool, en_plan *plan, const void *q_dev, const 
     const int n_partials = n_splits * sub;
     if (!ws_dev && n_partials > 1)
         return fail(EN_ERR_INVALID_ARG, "%s: workspace required with %d partial results per row", who, n_partials);
-    if (ws_dev && ws_bytes < L.total)
-        return fail(EN_ERR_CAPACITY, "%s: workspace %zu < %zu bytes", who, ws_bytes, L.total);
+    const size_t need = is_step ? L.parts_off : L.total;
+    if (ws_dev && ws_bytes < need)
+        return fail(EN_ERR_CAPACITY, "%s: workspace %zu < %zu bytes", who, ws_bytes, need);
     if (ws_dev && (reinterpret_cast<uintptr_t>(ws_dev) & 15))
         return fail(EN_ERR_INVALID_ARG, "%s: workspace must be 16-byte aligned", who);
     int rc;
@@ -995,9 +1010,6 @@ static int run_attention(en_pool *pool, en_plan *plan, const void *q_dev, const 
     if (plan->gathered_values_from_pool >= 0 && plan->gathered_values_from_pool != a.v_rows)
         return fail(EN_ERR_INVALID_ARG, "%s: en_plan_values_from_pool was changed after the plan's last gather; "
                     "gather again", who);
-    // (zero also when this call is not asked for masses: segment_attention_mass may follow)
-    a.red_zero = (ws && !mass_few_rows(pool, n_rows)) ? reinterpret_cast<unsigned long long *>(ws + L.redacc_off) : nullptr;
-    a.n_red_zero = a.red_zero ? plan->B * (plan->Smax + 1) : 0;
     // One partial result per row in the matrix-core kernel: its workgroups add the reduced masses up
     // themselves, in the plan's own accumulators (every workgroup arrives once per bucket; the
     // kernel keeps its eight waves' sums of the buckets in LDS).
@@ -1006,13 +1018,19 @@ static int run_attention(en_pool *pool, en_plan *plan, const void *q_dev, const 
     a.red_shift = a.red_target = 0;
     const int arrivals = pool->d.n_kv_heads * a.n_ptiles;        // workgroups per agent
     const bool red_direct = mass_red_out_dev && ws && n_partials == 1 && !a.decode && computes_bf16(pool->d.dtype) &&
-                            q_first == 0 && n_rows == plan->Nq && arrivals <= 1023 && plan->Smax + 1 <= EN_RED_DIRECT_MAX_BUCKETS;
+                            q_first == 0 && n_rows == plan->Nq && arrivals <= EN_MASS_ARRIVALS && plan->Smax + 1 <= EN_RED_DIRECT_MAX_BUCKETS;
     if (red_direct) {
         a.red_direct = reinterpret_cast<unsigned long long *>(plan->d_desc + plan->acc_off);
         a.red_direct_out = mass_red_out_dev;
         a.red_shift = fixed_point_shift(pool, n_rows, 10);
         a.red_target = arrivals;
     }
+    // Otherwise in accumulators of the scratch, which this launch sets to zero, as long as their count can tell the
+    // workgroups apart (4092 units of 64 rows of a head: steps beyond take milliseconds).
+    const bool few = mass_few_rows(pool, n_rows);
+    const bool fixed_point = mass_red_out_dev && ws && !red_direct && !few && mass_workgroups(pool, n_rows) <= EN_MASS_ARRIVALS;
+    a.red_zero = fixed_point ? reinterpret_cast<unsigned long long *>(ws + L.redacc_off) : nullptr;
+    a.n_red_zero = fixed_point ? plan->B * (plan->Smax + 1) : 0;
     const bool timed = pool->ev_used < (int)pool->ev_start.size();
     if (timed)
         (void)hipEventRecord(pool->ev_start[pool->ev_used], (hipStream_t)stream);
@@ -1023,17 +1041,17 @@ static int run_attention(en_pool *pool, en_plan *plan, const void *q_dev, const 
         return hip_fail((hipError_t)e, who);
     if (n_partials > 1) {
         // the same launch also adds the reduced masses up, if they are wanted
-        EnMassArgs m = mass_args(pool, plan, ws, L, n_rows, n_splits, q_first);
-        m.red_out = mass_red_out_dev;
+        EnMassArgs m = mass_args(pool, plan, ws, L, n_rows, n_splits, q_first, true);
+        m.red_out = fixed_point ? mass_red_out_dev : nullptr;
         EnAttnArgs c = a;
         c.n_splits = n_partials;              // the merge only counts partial results
         e = en_launch_combine(pool, c, m, stream);
         if (e != 0)
             return hip_fail((hipError_t)e, "split combine launch");
     }
-    if (mass_red_out_dev && !red_direct && (n_partials == 1 || mass_few_rows(pool, n_rows))) {
-        // no merge launch carried the reduced masses: one partial result per row, or few rows per head
-        EnMassArgs m = mass_args(pool, plan, ws, L, n_rows, n_splits, q_first);
+    if (mass_red_out_dev && !red_direct && !(fixed_point && n_partials > 1)) {
+        // no merge launch carried the reduced masses: one partial result per row, few rows per head, or very many
+        EnMassArgs m = mass_args(pool, plan, ws, L, n_rows, n_splits, q_first, fixed_point);
         m.red_out = mass_red_out_dev;
         e = en_launch_mass(pool, m, 1, stream);
         if (e != 0)
@@ -1051,7 +1069,7 @@ static int segmented_prefill_attention_impl(en_pool *pool, en_plan *plan, const 
     if (plan->pool != pool)
         return fail(EN_ERR_INVALID_ARG, "segmented_prefill_attention: plan belongs to another pool");
     return run_attention(pool, plan, q_dev, kc_dev, vt_dev, out_dev, ws_dev, ws_bytes, stream, 0, plan->Nq,
-                         plan->n_splits, "segmented_prefill_attention");
+                         plan->n_splits, false, "segmented_prefill_attention");
 }
 extern "C" int segmented_prefill_attention(en_pool *pool, en_plan *plan, const void *q_dev,
                                            const void *kc_dev, const void *vt_dev, void *out_dev,
@@ -1081,7 +1099,7 @@ static int segmented_prefill_attention_prepared_impl(en_pool *pool, en_plan *pla
         return fail(EN_ERR_UNSUPPORTED, "segmented_prefill_attention_prepared: reduced masses in the attention call "
                     "count at most 1023 query heads; use segment_attention_mass");
     return run_attention(pool, plan, q_prep_dev, kc_dev, vt_dev, out_dev, ws_dev, ws_bytes, stream, 0, plan->Nq,
-                         plan->n_splits, "segmented_prefill_attention_prepared", nullptr, nullptr, true,
+                         plan->n_splits, false, "segmented_prefill_attention_prepared", nullptr, nullptr, true,
                          mass_red_out_dev);
 }
 extern "C" int segmented_prefill_attention_prepared(en_pool *pool, en_plan *plan, const void *q_prep_dev,
@@ -1161,13 +1179,13 @@ static int segmented_decode_step_impl(en_pool *pool, en_plan *plan, int32_t q_fi
     // 2. attention of the step's rows over everything before and including them
     const int n_splits = step_splits(pool, plan, n_rows);
     if ((rc = run_attention(pool, plan, q_dev, kc_dev, vt_dev, out_dev, ws_dev, ws_bytes, stream, q_first, n_rows,
-                            n_splits, "segmented_decode_step", fused ? k_rows_dev : nullptr,
+                            n_splits, true, "segmented_decode_step", fused ? k_rows_dev : nullptr,
                             fused ? v_rows_dev : nullptr)) != EN_OK)
         return rc;
     // 3. per-row masses, if wanted
     if (mass_out_dev) {
         const EnWsLayout L = en_ws_layout_for(pool, plan, n_rows, n_splits);
-        EnMassArgs m = mass_args(pool, plan, static_cast<char *>(ws_dev), L, n_rows, n_splits, q_first);
+        EnMassArgs m = mass_args(pool, plan, static_cast<char *>(ws_dev), L, n_rows, n_splits, q_first, false);
         m.out = mass_out_dev;
         e = en_launch_mass(pool, m, 0, stream);
         if (e != 0)
@@ -1196,7 +1214,7 @@ static int segmented_decode_step_static_impl(en_pool *pool, en_plan *plan, int32
         return fail(EN_ERR_INVALID_ARG, "segmented_decode_step_static: plan belongs to another pool");
     if (n_rows <= 0)
         return fail(EN_ERR_OUT_OF_RANGE, "segmented_decode_step_static: n_rows = %d", n_rows);
-    const size_t need = en_ws_layout_for(pool, plan, n_rows, step_splits(pool, plan, n_rows)).total;
+    const size_t need = en_ws_layout_for(pool, plan, n_rows, step_splits(pool, plan, n_rows)).parts_off;
     if (need > EN_STATIC_SCRATCH_BYTES)
         return fail(EN_ERR_CAPACITY, "segmented_decode_step_static: the step needs %zu bytes of scratch, the static "
                     "scratch holds %zu; use segmented_decode_step with a workspace of the caller's", need,
@@ -1256,7 +1274,7 @@ static int segment_attention_mass_impl(en_pool *pool, en_plan *plan, void *ws_de
         return rc;
     const EnWsLayout L = en_ws_layout(pool, plan);
     char *ws = static_cast<char *>(ws_dev);
-    EnMassArgs a = mass_args(pool, plan, ws, L, plan->Nq, plan->n_splits, 0);
+    EnMassArgs a = mass_args(pool, plan, ws, L, plan->Nq, plan->n_splits, 0, false);
     a.out = a.red_out = mass_out_dev;
     const int e = en_launch_mass(pool, a, reduce, stream);
     if (e != 0)
@@ -1292,7 +1310,7 @@ static int cluster_assign(en_pool *pool, en_plan *plan, int q_first, int n_rows,
         return rc;
     const EnWsLayout L = en_ws_layout_for(pool, plan, n_rows, n_splits);
     EnClusterArgs a;
-    a.m = mass_args(pool, plan, static_cast<char *>(ws_dev), L, n_rows, n_splits, q_first);
+    a.m = mass_args(pool, plan, static_cast<char *>(ws_dev), L, n_rows, n_splits, q_first, false);
     a.score = score_dev;
     a.assign = assign_dev;
     a.n_obj = n_obj;

@@ -154,11 +154,17 @@ struct EnAttnArgs {
 
 struct EnMassArgs {
     const float *ws_ml, *ws_seg, *ws_mlfin;
-    // Reduced masses [B, Smax+1], or null. Unless the step has few rows (`few`, en_mass_few_rows) they are added
-    // up, as fixed-point integers (2^-red_shift; integer sums do not depend on the order of the additions), in
-    // red_acc [B, Smax+1], whose low red_count_bits bits count the red_target workgroups (of EN_MASS_UNITS
-    // units of 64 rows of a head) that arrive; the last one writes the sum and sets the word back to zero.
+    // Reduced masses [B, Smax+1], or null. Unless the step has few rows (`few`, mass_few_rows in en_host.cpp)
+    // red_target workgroups, of EN_MASS_UNITS units of 64 rows of a head each, sum a bucket's rows in fp32.
+    // Their sums meet in one of two ways. With `parts` null, as part of an attention call and without a
+    // launch behind it: as fixed-point integers (2^-red_shift; integer sums do not depend on the order of
+    // the additions) in red_acc [B, Smax+1], whose low red_count_bits bits count the arrivals; the last one
+    // writes the sum and sets the word back to zero. Else in parts [B, Smax+1, red_target], which a second
+    // launch adds up, fp32 all the way: in steps of 2^-40 a sum of 1e-9 has ten bits. (32 heads x 512 rows
+    // over 8 K tokens: 8.1 us, 6.7 in fixed point; x 2048 rows: 11.2, 10.8; x 4096: 12.6, 14.7. One launch
+    // whose last workgroup adds up the parts, behind a release of each: 11.8, 28.5 and 31.5.)
     float *red_out;
+    float *parts;
     unsigned long long *red_acc;
     int red_shift, red_count_bits, red_target;
     const int32_t *nseg, *bnd;
@@ -187,6 +193,7 @@ struct EnAppendQ8Args {
 constexpr int EN_RED_DIRECT_MAX_BUCKETS = 256;   // EnAttnArgs::red_direct: buckets whose sums a workgroup keeps in LDS
 constexpr int EN_MASS_FEW_ROWS = 8;     // below this many query rows per head the reduced masses need no accumulators
 constexpr int EN_MASS_UNITS = 4;        // units of 64 query rows of a head per workgroup of the reduced masses, one per wave
+constexpr int EN_MASS_ARRIVALS = 1023;  // workgroups that may meet in one accumulator of the reduced masses (10 bits)
 constexpr int EN_MAX_SPLITS = 64;       // KV splits of a plan: the mass kernels hold one split per lane
 constexpr int EN_MAX_OBJECTS = 255;    // per segment_cluster_assign call (spans travel in the kernel arguments)
 struct EnClusterArgs {
@@ -220,7 +227,7 @@ struct EnCtxAppendArgs {
 
 // Workspace layout helper (bytes, every part 256-byte aligned).
 struct EnWsLayout {
-    size_t ml_off, seg_off, redacc_off, mlfin_off, opart_off, total;
+    size_t ml_off, seg_off, redacc_off, mlfin_off, opart_off, parts_off, total;
 };
 EnWsLayout en_ws_layout(const en_pool *pool, const en_plan *plan);
 EnWsLayout en_ws_layout_for(const en_pool *pool, const en_plan *plan, int n_rows, int n_splits);

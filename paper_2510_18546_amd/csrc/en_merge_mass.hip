@@ -503,7 +503,12 @@ __device__ __forceinline__ void mass_partial_block(const EnMassArgs &a, int blk,
     __syncthreads();
     if (threadIdx.x < BG && s0 + (int)threadIdx.x <= a.Smax) {
         const int j = threadIdx.x;
-        add_reduced_mass(a, (size_t)b * (a.Smax + 1) + s0 + j, red[j] + red[BG + j] + red[2 * BG + j] + red[3 * BG + j]);
+        const size_t idx = (size_t)b * (a.Smax + 1) + s0 + j;
+        const float part = red[j] + red[BG + j] + red[2 * BG + j] + red[3 * BG + j];
+        if (a.parts)
+            a.parts[idx * a.red_target + wg] = part;
+        else
+            add_reduced_mass(a, idx, part);
     }
 }
 
@@ -511,6 +516,21 @@ __global__ __launch_bounds__(256) void mass_partial_kernel(EnMassArgs a)
 {
     __shared__ float red[4 * EN_MASS_BG];
     mass_partial_block(a, blockIdx.x, red);
+}
+
+// The parts of a sum, added up by one wave per (agent, bucket) in an order of its own: fp32 all the way.
+__global__ __launch_bounds__(256) void mass_final_kernel(EnMassArgs a)
+{
+    const int pair = blockIdx.x * 4 + threadIdx.x / 64;
+    if (pair >= a.B * (a.Smax + 1))
+        return;
+    const float *p = a.parts + (size_t)pair * a.red_target;
+    float acc = 0.f;
+    for (int k = threadIdx.x % 64; k < a.red_target; k += 64)
+        acc += p[k];
+    acc = wave_sum(acc);
+    if (threadIdx.x % 64 == 0)
+        a.red_out[pair] = acc;
 }
 
 // The reduced masses of few query rows per head (decode steps): a workgroup of G threads per (agent,
@@ -699,9 +719,11 @@ int en_launch_mass(const en_pool *pool, const EnMassArgs &a, int reduce, void *s
     } else {
         const dim3 blk(256);
         const int pairs = a.B * (a.Smax + 1);
-        if (!a.few)
+        if (!a.few) {
             hipLaunchKernelGGL(mass_partial_kernel, dim3(mass_partial_blocks(a)), blk, 0, st, a);
-        else if (a.Hq * a.Nq <= 128)
+            if (a.parts)
+                hipLaunchKernelGGL(mass_final_kernel, dim3((pairs + 3) / 4), blk, 0, st, a);
+        } else if (a.Hq * a.Nq <= 128)
             hipLaunchKernelGGL((mass_few_rows_kernel<64>), dim3((pairs + 3) / 4), blk, 0, st, a);
         else
             hipLaunchKernelGGL((mass_few_rows_kernel<256>), dim3(pairs), blk, 0, st, a);

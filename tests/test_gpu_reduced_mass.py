@@ -62,6 +62,59 @@ def test_masses_of_many_agents_and_segments(step_mod, oracle):
     run_case(step_mod, oracle, cfg, rows=rows)
 
 
+@pytest.mark.parametrize("dtype,n_new,splits", [
+    (I.F32, 3, 1), (I.F32, 9, 1), (I.F32, 70, 3), (I.BF16, 8, 2), (I.BF16, 40, 1), (I.BF16, 130, 2), (I.BF16, 257, 2)])
+def test_reduced_masses_of_a_segment_far_off(step_mod, dtype, n_new, splits):
+    """A segment whose scores lie 30 below the others, masses of about 1e-14 a row: their sum is as exact as that of
+    the large ones."""
+    cfg = small(f"far-{n_new}", 890 + n_new, dtype=dtype, n_agents=2, n_q_heads=6, head_dim=64, n_new=n_new)
+    w = I.make_workload(cfg)
+    far, slow = int(w.sel[2]), cfg.head_dim // 2 - 1       # (that pair turns by 3e-6 a token)
+    lean = np.float32((30.0 * 8.0) ** 0.5)
+    for x, along in ((w.q, lean), (w.k_new, 0), (w.k_pool, 0), (w.k_pool[far], -lean)):
+        x[..., slow], x[..., -1] = along, 0
+    st = step_mod.PlanningStep(w, n_splits=splits)
+    st.gather()
+    st.attention()
+    st.masses(0)
+    st.masses(1)
+    red, rows = st.mass_red_host(), st.mass_host().sum(axis=(1, 2))
+    assert 1e-16 < rows[0, 2] < 1e-9
+    # row masses in float32 (three roundings each, two in the sums), added up in a tree of at most 6 + 2 + 3 levels
+    # of a row, then at most four in a line: below 32 roundings
+    np.testing.assert_allclose(red, rows, rtol=32 * 2.0 ** -24, atol=0)
+
+
+@pytest.mark.parametrize("rows,step", [(4032, 2.0 ** -34), (4160, 0.0)])
+def test_reduced_masses_of_a_long_step(step_mod, rows, step):
+    """64 heads: as many units as an accumulator's count can tell apart (1008 workgroups; sums in steps of 2^-34), and
+    more (no accumulators). Every row gives the second segment 2^-38."""
+    import torch
+    from paper_2510_18546_amd import binding as B
+    hq, cached, d, dev = 64, 8192, 64, "cuda:0"
+    k = torch.zeros((2, 1, cached, d), dtype=torch.bfloat16, device=dev)
+    q = torch.zeros((1, rows, hq, d), dtype=torch.bfloat16, device=dev)
+    lean = (25 * np.log(2.0) * d ** 0.5) ** 0.5
+    q[..., d // 2 - 1], k[1, 0, 0, d // 2 - 1] = lean, -lean
+    pool = B.kv_pool_create(k, k.clone(), np.array([cached, 1], np.int32), hq, 500000.0, cached + 1 + rows)
+    plan = B.segment_select(pool, np.array([0, 1], np.int32), np.array([0, 2], np.int32), rows)
+    plan.set_splits(2)
+    kc, vt = B.alloc_context(pool, plan)
+    new, q_prep, out = torch.zeros((1, rows, 1, d), dtype=torch.bfloat16, device=dev), torch.empty_like(q), torch.empty_like(q)
+    ws = B.alloc_workspace(pool, plan)
+    in_call, by_itself = (torch.zeros((1, 3), device=dev) for _ in range(2))
+    of_rows = torch.zeros((1, rows, hq, 3), device=dev)
+    B.gather_rope_queries(pool, plan, new, new, q, kc, vt, q_prep)
+    B.segmented_prefill_attention_prepared(pool, plan, q_prep, kc, vt, out, ws, in_call)
+    B.segment_attention_mass(pool, plan, ws, 1, by_itself)
+    B.segment_attention_mass(pool, plan, ws, 0, of_rows)
+    want = of_rows.double().sum(dim=(1, 2)).cpu().numpy()[0]
+    assert 3e-7 < want[1] < 2e-6
+    # 1008 sums rounded to a step; sums in float32 of at most 6 + 2 + 6 levels and 17 terms in a line
+    np.testing.assert_allclose(in_call.cpu().numpy()[0], want, rtol=64 * 2.0 ** -24, atol=1008 * step / 2)
+    np.testing.assert_allclose(by_itself.cpu().numpy()[0], want, rtol=64 * 2.0 ** -24, atol=0)
+
+
 @pytest.mark.parametrize("dtype,n_new,splits", [(I.BF16, 7, 2), (I.BF16, 40, 2), (I.BF16, 65, 7), (I.F32, 9, 1)])
 def test_reduced_masses_of_a_query_that_is_no_number(step_mod, dtype, n_new, splits):
     """The sums that hold its masses are NaN too, the other agent's are as before; the next call, without it, is
