@@ -805,6 +805,7 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_bf16_kernel(EnAttnArgs a)
     if (!wave_valid && !a.red_direct)
         return;
     float inv = 0.f;
+    bool no_sum = false;         // this lane's row has no sum to divide by (NaN or infinity in the step's inputs)
     // (one split, reduced masses from this kernel: see below) the wave's pairs of 2 UB buckets
     constexpr int UB = 8;
     f32x2 pairs[UB];
@@ -847,6 +848,8 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_bf16_kernel(EnAttnArgs a)
     // when every wave does it at once). Staged through LDS, each store instruction writes whole
     // rows: 64 lanes x 16 bytes = four rows of 256 bytes.
     inv = (row_valid && l_tot > 0.f) ? 1.f / l_tot : 0.f;
+    // (by the bits: neither NaN, infinite, negative nor 0)
+    no_sum = row_valid && __float_as_uint(l_tot) - 1u >= 0x7f800000u - 1u;
     constexpr int OSTR = 2 * D + 16;             // bytes per staged row (padded: bank spread, 16-byte aligned)
     constexpr int OCPR = D / 8;                  // 16-byte chunks per row
     static_assert(ATT_WAVES * 32 * OSTR <= NST * (KBYTES + VBYTES), "staging areas must fit the tile stages");
@@ -893,7 +896,8 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_bf16_kernel(EnAttnArgs a)
     // (agent, bucket): one arrival per workgroup (arrivals at one address take about 0.1 us each). ----
     if (red_direct) {
         constexpr int OAREA = ATT_WAVES * 32 * (2 * D + 16);      // the staging areas of the output rows
-        float *red_w = reinterpret_cast<float *>(smem + OAREA);   // [waves][Smax + 1]
+        uint32_t *red_w = reinterpret_cast<uint32_t *>(smem + OAREA);   // floats' bits, [waves][Smax + 1]
+        const bool wave_no_sum = __any(no_sum);
         static_assert(OAREA + ATT_WAVES * EN_RED_DIRECT_MAX_BUCKETS * 4 <= NST * (KBYTES + VBYTES), "sums of the buckets beside the staging areas");
         const int nb = a.Smax + 1;
         for (int s0 = 0; s0 < nb; s0 += 2 * UB) {
@@ -905,24 +909,21 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_bf16_kernel(EnAttnArgs a)
                 float v = pairs[u][1] != EN_NEG_INF ? pairs[u][0] * fast_exp2(pairs[u][1] - m_ref) * inv : 0.f;
                 v = half_sum(v);
                 if (col == 0 && s < nb)
-                    red_w[wave * nb + s] = v;
+                    red_w[wave * nb + s] = wave_no_sum ? 0x7fc00000u : __float_as_uint(v);
             }
         }
         __syncthreads();
         for (int s = tid; s < nb; s += 64 * ATT_WAVES) {
             float v = 0.f;
+            bool bad = false;
 #pragma unroll
-            for (int w = 0; w < ATT_WAVES; ++w)
-                v += red_w[w * nb + s];
-            const size_t idx = (size_t)b * nb + s;
-            const long long q = __float2ll_rn(ldexpf(v, a.red_shift));
-            const unsigned long long add = ((unsigned long long)q << 10) + 1ull;
-            const unsigned long long now = atomicAdd(a.red_direct + idx, add) + add;
-            if ((int)(now & 1023ull) == a.red_target) {
-                a.red_direct_out[idx] =
-                    ldexpf((float)((long long)(now - (unsigned long long)a.red_target) >> 10), -a.red_shift);
-                a.red_direct[idx] = 0ull;           // nobody arrives after the last: ready for the next call
+            for (int w = 0; w < ATT_WAVES; ++w) {
+                const float part = __uint_as_float(red_w[w * nb + s]);
+                bad |= not_a_number(part);
+                v += part;
             }
+            const size_t idx = (size_t)b * nb + s;
+            arrive_fixed_point(a.red_direct + idx, v, bad, a.red_shift, 10, a.red_target, a.red_direct_out + idx);
         }
     }
 }

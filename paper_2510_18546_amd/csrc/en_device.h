@@ -54,6 +54,37 @@ __device__ __forceinline__ void rope_key_pair(F x1, F x2, F c, F s, F &y1, F &y2
     y2 = X1_ROUNDED ? __builtin_elementwise_fma(x2, c, r) : __builtin_elementwise_fma(x1, s, r);
 }
 
+// NaN or infinite, by the bits: the library is built without NaN compares.
+__device__ __forceinline__ bool not_a_number(float v)
+{
+    return (__float_as_uint(v) & 0x7f800000u) == 0x7f800000u;
+}
+
+// The reduced masses inside an attention call: a workgroup's part joins the others in ONE atomic addition on a
+// 64-bit word that holds the sum in fixed point (so that it does not depend on the order in which the workgroups
+// arrive) above a count of arrivals; whoever arrives last has the complete sum in hand, from the atomic's own
+// return value, writes it out and sets the word back to zero. A part that is no number (`bad`: NaN or infinity in
+// the step's inputs) has no fixed point: it marks the word in its top bit, which sums leave alone (see
+// fixed_point_shift in en_host.cpp), before it arrives, and the result is NaN.
+__device__ __forceinline__ void arrive_fixed_point(unsigned long long *word, float part, bool bad, int shift,
+                                                   int count_bits, int target, float *out)
+{
+    constexpr unsigned long long NOT_A_NUMBER = 1ull << 63;
+    long long q = 0;
+    if (!bad)
+        q = __float2ll_rn(ldexpf(part, shift));
+    else
+        atomicOr(word, NOT_A_NUMBER);
+    const unsigned long long add = ((unsigned long long)q << count_bits) + 1ull;
+    const unsigned long long now = atomicAdd(word, add) + add;
+    if ((now & ((1ull << count_bits) - 1ull)) == (unsigned long long)target) {
+        const unsigned long long sum = (now & ~NOT_A_NUMBER) >> count_bits;
+        *reinterpret_cast<uint32_t *>(out) =
+            now & NOT_A_NUMBER ? 0x7fc00000u : __float_as_uint(ldexpf((float)sum, -shift));
+        *word = 0ull;
+    }
+}
+
 // Exchange a value with the lane 32 positions away.
 __device__ __forceinline__ float xor32(float v)
 {

@@ -9,28 +9,12 @@
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void mass_partial_block(const EnMassArgs &a, int blk, float *red);
 
-// The reduced masses: a workgroup's sum for (agent, bucket) `idx` joins the others in ONE atomic addition
-// on a 64-bit word that holds the sum in fixed point (so that it does not depend on the order in which
-// the workgroups arrive) above a count of arrivals; whoever arrives last has the complete sum in hand,
-// from the atomic's own return value, writes it out and sets the word back to zero. The words were set
-// to zero by the attention launch before. A part that is no number (NaN or infinity in the step's inputs) has
-// no fixed point: it marks the word in its top bit, which sums leave alone (see fixed_point_shift in
-// en_host.cpp), before it arrives, and the result is NaN.
+// A workgroup's part of the reduced mass of (agent, bucket) `idx`; the words were set to zero by the attention
+// launch before.
 __device__ __forceinline__ void add_reduced_mass(const EnMassArgs &a, size_t idx, float part)
 {
-    constexpr unsigned long long NOT_A_NUMBER = 1ull << 63;
-    long long q = 0;
-    if ((__float_as_uint(part) & 0x7f800000u) != 0x7f800000u)        // (the library is built without NaN compares)
-        q = __float2ll_rn(ldexpf(part, a.red_shift));
-    else
-        atomicOr(a.red_acc + idx, NOT_A_NUMBER);
-    const unsigned long long add = ((unsigned long long)q << a.red_count_bits) + 1ull;
-    const unsigned long long now = atomicAdd(a.red_acc + idx, add) + add;
-    if ((now & ((1ull << a.red_count_bits) - 1ull)) == (unsigned long long)a.red_target) {
-        const uint32_t sum = __float_as_uint(ldexpf((float)(now >> a.red_count_bits), -a.red_shift));
-        reinterpret_cast<uint32_t *>(a.red_out)[idx] = now & NOT_A_NUMBER ? 0x7fc00000u : sum;
-        a.red_acc[idx] = 0ull;
-    }
+    arrive_fixed_point(a.red_acc + idx, part, not_a_number(part), a.red_shift, a.red_count_bits, a.red_target,
+                       a.red_out + idx);
 }
 
 // A workgroup of the reduced masses takes EN_MASS_BG consecutive buckets of one agent over EN_MASS_UNITS

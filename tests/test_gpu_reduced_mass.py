@@ -115,8 +115,10 @@ def test_reduced_masses_of_a_long_step(step_mod, rows, step):
     np.testing.assert_allclose(by_itself.cpu().numpy()[0], want, rtol=64 * 2.0 ** -24, atol=0)
 
 
-@pytest.mark.parametrize("dtype,n_new,splits", [(I.BF16, 7, 2), (I.BF16, 40, 2), (I.BF16, 65, 7), (I.F32, 9, 1)])
-def test_reduced_masses_of_a_query_that_is_no_number(step_mod, dtype, n_new, splits):
+@pytest.mark.parametrize("dtype,n_new,splits,in_call", [
+    (I.BF16, 7, 2, False), (I.BF16, 40, 1, False), (I.BF16, 40, 2, False), (I.BF16, 65, 7, False), (I.F32, 9, 1, False),
+    (I.BF16, 40, 2, True), (I.BF16, 40, 1, True), (I.BF16, 130, 1, True)])
+def test_reduced_masses_of_a_query_that_is_no_number(step_mod, dtype, n_new, splits, in_call):
     """The sums that hold its masses are NaN too, the other agent's are as before; the next call, without it, is
     free of it."""
     cfg = small(f"nan-{n_new}", 870 + n_new, dtype=dtype, n_agents=2, n_q_heads=6, head_dim=64, len_lo=8, n_new=n_new,
@@ -125,8 +127,9 @@ def test_reduced_masses_of_a_query_that_is_no_number(step_mod, dtype, n_new, spl
 
     def reduced():
         st.gather()
-        st.attention()
-        st.masses(1)
+        st.attention(in_call)
+        if not in_call:
+            st.masses(1)
         return st.mass_red_host()
 
     clean = reduced()
