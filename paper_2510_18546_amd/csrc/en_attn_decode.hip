@@ -477,10 +477,11 @@ __global__ __launch_bounds__(64 * SUB) void attn_decode_kernel(EnAttnArgs a)
 // fp32 sums), for small layers and short steps, which are bound by latency: the chain of a wave's trips
 // to memory and of its dependent products, not by bytes or operations.
 //
-// A workgroup takes 16 of the r * N_q query rows of a KV head and one KV split, and its eight waves share
-// the split's keys: each a contiguous run of 16-key blocks, with a softmax state of its own; they merge
-// through LDS, so a step of few keys needs no launch behind this one. (One wave per row, the lanes 64 keys
-// apart with a row of K and of V each, took 34 us for 4 heads x 64 rows over 192 keys.)
+// A workgroup takes 16 of the r * N_q query rows of a KV head and one KV split, and its eight waves (two where
+// short splits fill the chip: see EnAttnArgs::f32_waves) share the split's keys: each a contiguous run of
+// 16-key blocks, with a softmax state of its own; they merge through LDS, so a step of few keys needs no
+// launch behind this one. (One wave per row, the lanes 64 keys apart with a row of K and of V each, took
+// 34 us for 4 heads x 64 rows over 192 keys.)
 //
 // S^T = K Q^T: lane l holds key l % 16, dimensions 4 (l / 16) .. + 3 of every 16: one 16-byte load each, and
 // its four numbers are the operands of four instructions (K and Q agree on which dimension is which k). The
@@ -490,23 +491,22 @@ __global__ __launch_bounds__(64 * SUB) void attn_decode_kernel(EnAttnArgs a)
 //
 // Probabilities below 2^-126 of the row's largest count as 0 (fast_exp2).
 // ---------------------------------------------------------------------------
-constexpr int F32_WAVES = 8;
 constexpr int F32_ROWS = EN_F32_ROWS;
 constexpr int F32_KEYS = 16;
 
-template <int D>
-__global__ __launch_bounds__(64 * F32_WAVES) void attn_f32_kernel(EnAttnArgs a)
+template <int D, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void attn_f32_kernel(EnAttnArgs a)
 {
     constexpr int NJ = D / 16;                   // 16-byte loads per key row and lane; blocks of O^T
     constexpr int NV = D / 64;                   // 16-byte loads per value row and lane
     constexpr int OSTR = D + 4;                  // floats per merged row in LDS
-    __shared__ __attribute__((aligned(16))) float so[F32_WAVES][F32_ROWS][OSTR];
-    __shared__ f32x2 sml[F32_WAVES][F32_ROWS];           // (reference, sum) of a wave's rows
-    __shared__ f32x2 sfirst[F32_WAVES][F32_ROWS];        // (sum, reference) of the bucket that a wave entered midway
-    __shared__ int sspan[F32_WAVES];                     // 1: ... and that it did not leave
+    __shared__ __attribute__((aligned(16))) float so[WAVES][F32_ROWS][OSTR];
+    __shared__ f32x2 sml[WAVES][F32_ROWS];           // (reference, sum) of a wave's rows
+    __shared__ f32x2 sfirst[WAVES][F32_ROWS];        // (sum, reference) of the bucket that a wave entered midway
+    __shared__ int sspan[WAVES];                     // 1: ... and that it did not leave
 
     if (blockIdx.x == 0 && a.red_zero)
-        for (int i = threadIdx.x; i < a.n_red_zero; i += 64 * F32_WAVES)
+        for (int i = threadIdx.x; i < a.n_red_zero; i += 64 * WAVES)
             a.red_zero[i] = 0ull;
     int t = blockIdx.x;
     const int rg = t % a.n_ptiles;
@@ -539,7 +539,7 @@ __global__ __launch_bounds__(64 * F32_WAVES) void attn_f32_kernel(EnAttnArgs a)
     const int hq = kvh * r + rr / a.Nq, i_row = rr % a.Nq;
     const int kvis = min(kend, Lc + i_hi + 1);           // keys that any of the rows may see
     const int n_blk = kvis > kbeg ? (kvis - kbeg + F32_KEYS - 1) / F32_KEYS : 0;
-    const int per = (n_blk + F32_WAVES - 1) / F32_WAVES;
+    const int per = (n_blk + WAVES - 1) / WAVES;
     const int n_used = per > 0 ? (n_blk + per - 1) / per : 0;          // waves with keys
     const int wb = kbeg + min(wave * per, n_blk) * F32_KEYS;           // this wave's keys
     const int we = min(kbeg + min((wave + 1) * per, n_blk) * F32_KEYS, kvis);
@@ -772,31 +772,44 @@ __global__ __launch_bounds__(64 * F32_WAVES) void attn_f32_kernel(EnAttnArgs a)
         }
     }
     __syncthreads();
-    // ---- one 16-byte piece of the output per thread ----
+    // ---- the output, a 16-byte piece per thread at a time ----
     constexpr int CPR = D / 4;
-    const int row = tid / CPR, c4 = tid % CPR * 4;
-    if (tid >= F32_ROWS * CPR || r0 + row > r1)
-        return;
-    float Mr = EN_NEG_INF, L = 0.f;
-    for (int w = 0; w < n_used; ++w)
-        Mr = fmaxf(Mr, sml[w][row][0]);
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int w = 0; w < n_used; ++w) {
-        const f32x2 x = sml[w][row];
-        L += x[0] == EN_NEG_INF ? 0.f : x[1] * fast_exp2(x[0] - Mr);
-        acc += *reinterpret_cast<const f32x4 *>(&so[w][row][c4]);
-    }
-    const int h = kvh * r + (r0 + row) / a.Nq, i = (r0 + row) % a.Nq;
     const size_t rows = (size_t)a.B * a.Hq * a.Nq;
-    const size_t out_row = ((size_t)b * a.Hq + h) * a.Nq + i;
-    const float inv = L > 0.f ? 1.f / L : 0.f;
-    if (a.ws_ml && c4 == 0) {
-        f32x2 v = {Mr, L};
-        *reinterpret_cast<f32x2 *>(a.ws_ml + ((size_t)sp * rows + out_row) * 2) = v;
+#pragma unroll
+    for (int k = 0; k < (F32_ROWS * CPR + 64 * WAVES - 1) / (64 * WAVES); ++k) {
+        const int row = (k * 64 * WAVES + tid) / CPR, c4 = tid % CPR * 4;
+        if (row >= F32_ROWS || r0 + row > r1)
+            return;
+        float Mr = EN_NEG_INF, L = 0.f;
+        for (int w = 0; w < n_used; ++w)
+            Mr = fmaxf(Mr, sml[w][row][0]);
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int w = 0; w < n_used; ++w) {
+            const f32x2 x = sml[w][row];
+            L += x[0] == EN_NEG_INF ? 0.f : x[1] * fast_exp2(x[0] - Mr);
+            acc += *reinterpret_cast<const f32x4 *>(&so[w][row][c4]);
+        }
+        const int h = kvh * r + (r0 + row) / a.Nq, i = (r0 + row) % a.Nq;
+        const size_t out_row = ((size_t)b * a.Hq + h) * a.Nq + i;
+        const float inv = L > 0.f ? 1.f / L : 0.f;
+        if (a.ws_ml && c4 == 0) {
+            f32x2 v = {Mr, L};
+            *reinterpret_cast<f32x2 *>(a.ws_ml + ((size_t)sp * rows + out_row) * 2) = v;
+        }
+        float *op = (a.n_splits == 1) ? (float *)a.out + (((size_t)b * a.Nq + i) * a.Hq + h) * D
+                                      : (float *)a.ws_opart + ((size_t)sp * rows + out_row) * D;
+        *reinterpret_cast<f32x4 *>(op + c4) = acc * inv;
     }
-    float *op = (a.n_splits == 1) ? (float *)a.out + (((size_t)b * a.Nq + i) * a.Hq + h) * D
-                                  : (float *)a.ws_opart + ((size_t)sp * rows + out_row) * D;
-    *reinterpret_cast<f32x4 *>(op + c4) = acc * inv;
+}
+
+template <int WAVES>
+static void launch_f32_waves(int D, const EnAttnArgs &a, hipStream_t st)
+{
+    const dim3 grid(a.total_wgs), blk(64 * WAVES);
+    if (D == 64)
+        hipLaunchKernelGGL((attn_f32_kernel<64, WAVES>), grid, blk, 0, st, a);
+    else
+        hipLaunchKernelGGL((attn_f32_kernel<128, WAVES>), grid, blk, 0, st, a);
 }
 
 // ---------------------------------------------------------------------------
@@ -807,11 +820,12 @@ int en_launch_attention(const en_pool *pool, const EnAttnArgs &a, void *stream)
     hipStream_t st = (hipStream_t)stream;
     const int D = pool->d.head_dim;
     if (pool->d.dtype == EN_F32) {
-        const dim3 grid(a.total_wgs), blk(64 * F32_WAVES);
-        if (D == 64)
-            hipLaunchKernelGGL((attn_f32_kernel<64>), grid, blk, 0, st, a);
+        if (a.f32_waves == 8)
+            launch_f32_waves<8>(D, a, st);
+        else if (a.f32_waves == 2)
+            launch_f32_waves<2>(D, a, st);
         else
-            hipLaunchKernelGGL((attn_f32_kernel<128>), grid, blk, 0, st, a);
+            return (int)hipErrorInvalidValue;
     } else if (a.decode) {
         const dim3 grid((a.total_wgs + 7) / 8 * 8), blk(64 * a.sub);
         if (a.sub != 1 && a.sub != 2)

@@ -999,6 +999,7 @@ static int run_attention(en_pool *pool, en_plan *plan, const void *q_dev, const 
     if (!computes_bf16(pool->d.dtype))
         a.n_ptiles = (pool->r * n_rows + EN_F32_ROWS - 1) / EN_F32_ROWS;
     a.total_wgs = plan->B * pool->d.n_kv_heads * n_splits * a.n_ptiles;
+    a.f32_waves = a.total_wgs >= 2 * pool->n_cu && plan->max_ctx_len <= 1024 * n_splits ? 2 : 8;
     a.scale_log2e = softmax_scale_log2e(pool);
     a.app_k = a.decode ? app_k_dev : nullptr;
     a.app_v = a.decode ? app_v_dev : nullptr;

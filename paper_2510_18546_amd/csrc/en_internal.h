@@ -133,6 +133,12 @@ struct EnAttnArgs {
                        // block of the split's tiles and leaves its own partial results at index
                        // sp * sub + w of n_splits * sub
     float scale_log2e;
+    // fp32 kernel: waves per workgroup, 8 or 2. Eight share the keys of few workgroups, which wait for memory; where
+    // two and more workgroups per compute unit and at most 1 K keys per split come together, most of the eight
+    // have little or nothing to do and starting and merging them is what the launch takes (16 heads, a row each:
+    // 256 agents x 33 keys 64.6 us with eight, 31.9 with two; x 513 keys 227, 208; 64 agents x 1025 keys 103, 98;
+    // x 4097 keys 371, 372; 16 agents x 129 keys 8.1, 11.0).
+    int f32_waves;
     int q_prepared;    // prefill kernel: q holds prepared queries (rotated, scaled, bf16: see EnGatherArgs)
     int v_rows;        // prefill kernel: vt holds no values but the address of every context row's values
                        // (see EnGatherArgs::v_rows)

@@ -1,4 +1,4 @@
-"""The fp32 attention kernel where its pieces meet: eight waves share a split's keys in runs of 16-key
+"""The fp32 attention kernel where its pieces meet: eight waves (or two) share a split's keys in runs of 16-key
 blocks, a segment can lie inside one wave, cross one or many of their borders or fill several waves, and the
 16 rows of a workgroup can span heads. Against the oracle, to the fp32 tolerance of test_gpu_parity."""
 import numpy as np
@@ -24,6 +24,18 @@ def test_fp32_waves_and_segments(step_mod, oracle, d, kv, ratio, n_new, seg, n_s
                 n_kv_heads=kv, n_agents=2, capacity=max(seg, 1), len_lo=max(0, seg - 3), len_hi=seg, n_sel=n_sel,
                 n_new=n_new, rope_base=1e4)
     run_case(step_mod, oracle, cfg, n_splits=splits)
+
+
+@pytest.mark.parametrize("d,agents,kv,ratio,n_new,seg,n_sel", [
+    (64, 256, 2, 1, 1, 16, 2),         # 512 workgroups of two waves on 256 compute units
+    (128, 128, 1, 2, 26, 30, 3),       # ... four row groups a head; a segment from one wave to the other
+    (64, 64, 8, 1, 1, 96, 11),         # runs of many blocks per wave
+])
+def test_fp32_two_waves(step_mod, oracle, d, agents, kv, ratio, n_new, seg, n_sel):
+    cfg = small(f"f32-two-{d}-{n_new}-{seg}", 720 + n_new, dtype=I.F32, head_dim=d, n_q_heads=kv * ratio,
+                n_kv_heads=kv, n_agents=agents, capacity=seg, len_lo=max(0, seg - 3), len_hi=seg, n_sel=n_sel,
+                n_new=n_new, rope_base=1e4)
+    run_case(step_mod, oracle, cfg, n_splits=1)
 
 
 @pytest.mark.parametrize("agents,d,kv,hq,n_new,seg,n_sel,limit", [
