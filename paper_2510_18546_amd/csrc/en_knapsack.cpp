@@ -41,62 +41,60 @@ struct Item {
     K key;
 };
 
-// One item's row of the programme: cur[c] = the best number with capacity c, over this item and those
-// behind it (next[]); bit c of `bits`: taking it is optimal there, ties included. Columns
-// 64 * first_word .. 64 * end_word - 1.
+// One item's row of the programme, in place: row[c] held the best number with capacity c over the items behind
+// this one and gets this one too; bit c of `bits`: taking it is optimal there, ties included. Columns
+// 64 * first_word .. 64 * end_word - 1, from the last down: what a column reads lies in front of it (w > 0).
 template <typename K>
-void knapsack_row_scalar(const K *next, K *cur, uint64_t *bits, size_t first_word, size_t end_word, size_t w, K key)
+void knapsack_row_scalar(K *row, uint64_t *bits, size_t first_word, size_t end_word, size_t w, K key)
 {
-    for (size_t wd = first_word; wd < end_word; ++wd) {
+    for (size_t wd = end_word; wd-- > first_word;) {
         uint64_t m = 0;
-        for (size_t c = wd * 64; c < wd * 64 + 64; ++c) {
-            K best = next[c];
-            if (c >= w) {
-                const K with = next[c - w] + key;
-                if (with >= best) {
-                    best = with;
-                    m |= uint64_t(1) << (c & 63);
-                }
+        for (size_t c = wd * 64 + 64; c-- > wd * 64;) {
+            if (c < w)
+                break;
+            const K with = row[c - w] + key;
+            if (with >= row[c]) {
+                row[c] = with;
+                m |= uint64_t(1) << (c & 63);
             }
-            cur[c] = best;
         }
         bits[wd] = m;
     }
 }
 
 // The same on 64-bit numbers, four at a time (about 0.2 ns per cell instead of 0.6).
-__attribute__((target("avx2"))) void knapsack_row_avx2(const int64_t *next, int64_t *cur, uint64_t *bits,
-                                                        size_t first_word, size_t end_word, size_t w, int64_t key)
+__attribute__((target("avx2"))) void knapsack_row_avx2(int64_t *row, uint64_t *bits, size_t first_word,
+                                                        size_t end_word, size_t w, int64_t key)
 {
     const size_t whole = std::max(first_word, std::min(end_word, (w + 63) / 64));      // words with c >= w throughout
-    knapsack_row_scalar(next, cur, bits, first_word, whole, w, key);
     const __m256i k4 = _mm256_set1_epi64x(key);
-    for (size_t wd = whole; wd < end_word; ++wd) {
+    for (size_t wd = end_word; wd-- > whole;) {
         uint64_t skip = 0;
-        for (int i = 0; i < 16; ++i) {
+        for (int i = 15; i >= 0; --i) {
             const size_t c = wd * 64 + 4 * i;
-            const __m256i old = _mm256_loadu_si256(reinterpret_cast<const __m256i *>(next + c));
+            const __m256i old = _mm256_loadu_si256(reinterpret_cast<const __m256i *>(row + c));
             const __m256i with =
-                _mm256_add_epi64(_mm256_loadu_si256(reinterpret_cast<const __m256i *>(next + c - w)), k4);
+                _mm256_add_epi64(_mm256_loadu_si256(reinterpret_cast<const __m256i *>(row + c - w)), k4);
             const __m256i worse = _mm256_cmpgt_epi64(old, with);
-            _mm256_storeu_si256(reinterpret_cast<__m256i *>(cur + c), _mm256_blendv_epi8(with, old, worse));
+            _mm256_storeu_si256(reinterpret_cast<__m256i *>(row + c), _mm256_blendv_epi8(with, old, worse));
             skip |= uint64_t(unsigned(_mm256_movemask_pd(_mm256_castsi256_pd(worse)))) << (4 * i);
         }
         bits[wd] = ~skip;
     }
+    knapsack_row_scalar(row, bits, first_word, whole, w, key);
 }
 
-void knapsack_row(const int64_t *next, int64_t *cur, uint64_t *bits, size_t first, size_t end, size_t w, int64_t key)
+void knapsack_row(int64_t *row, uint64_t *bits, size_t first, size_t end, size_t w, int64_t key)
 {
     static const bool avx2 = __builtin_cpu_supports("avx2");
     if (avx2)
-        knapsack_row_avx2(next, cur, bits, first, end, w, key);
+        knapsack_row_avx2(row, bits, first, end, w, key);
     else
-        knapsack_row_scalar(next, cur, bits, first, end, w, key);
+        knapsack_row_scalar(row, bits, first, end, w, key);
 }
-void knapsack_row(const __int128 *next, __int128 *cur, uint64_t *bits, size_t first, size_t end, size_t w, __int128 key)
+void knapsack_row(__int128 *row, uint64_t *bits, size_t first, size_t end, size_t w, __int128 key)
 {
-    knapsack_row_scalar(next, cur, bits, first, end, w, key);
+    knapsack_row_scalar(row, bits, first, end, w, key);
 }
 
 // Best number over items[0 .. m) with capacity W. With `taken` non-null the optimal set that prefers
@@ -116,16 +114,15 @@ K solve(const Item<K> *items, int m, int64_t W, std::vector<int> *taken)
         return all_key;
     }
     const size_t words = size_t(W) / 64 + 1;
-    std::vector<K> next(words * 64, K(0)), cur(words * 64, K(0));
+    std::vector<K> row(words * 64, K(0));
     std::vector<uint64_t> bits(taken ? size_t(m) * words : words);
     int64_t before = all_w;              // tokens of the items in front of a
     for (int a = m - 1; a >= 0; --a) {
         before -= items[a].w;
         // whatever the items in front take, at least W - before is left when it is a's turn
         const size_t first = size_t(std::max<int64_t>(0, W - before)) / 64;
-        knapsack_row(next.data(), cur.data(), bits.data() + (taken ? size_t(a) * words : 0), first, words,
-                     size_t(items[a].w), items[a].key);
-        next.swap(cur);
+        knapsack_row(row.data(), bits.data() + (taken ? size_t(a) * words : 0), first, words, size_t(items[a].w),
+                     items[a].key);
     }
     if (taken) {
         int64_t c = W;
@@ -135,7 +132,7 @@ K solve(const Item<K> *items, int m, int64_t W, std::vector<int> *taken)
                 c -= items[a].w;
             }
     }
-    return next[size_t(W)];
+    return row[size_t(W)];
 }
 
 // items: positive lengths of at most W, ids ascending, together longer than W.
@@ -276,8 +273,8 @@ int en_knapsack(const float *p_host, const int32_t *len, int G, float threshold,
     }
     const int64_t W = budget_tokens;
     {
-        // what the programme over all candidates would need, one bit per (item, capacity) plus four rows of
-        // the capacity: refused beyond a stated size (no instance that is accepted can then need more)
+        // One bit per (item, capacity) and 24 bytes per capacity: refused beyond a stated size. The programme holds
+        // the bits and one row of 8 or 16 bytes per capacity, so no instance that is accepted needs more.
         const size_t cols = size_t(W) + 1;
         const size_t need = size_t(m) * ((cols + 63) / 64) * 8 + cols * 24;
         if (need > EN_KNAPSACK_MAX_BYTES) {
@@ -289,8 +286,9 @@ int en_knapsack(const float *p_host, const int32_t *len, int G, float threshold,
     int shift = 1;
     while ((int64_t(1) << shift) <= wsum)
         ++shift;
-    // 64-bit numbers wherever the sum of all values leaves room for the tokens: 256 groups of 256 tokens
-    // do up to scores of 2^5 each; other instances take 128-bit ones
+    // 64-bit numbers wherever the sum of all values leaves room for the tokens: 256 groups of 256 tokens do up to
+    // scores of 2^4 each; other instances take 128-bit ones (one cell at a time: where nothing can be fixed either,
+    // 256 groups under 7 K tokens take 2.1 ms)
     if (std::ldexp(vsum, shift) < 0x1p61)
         choose_from<int64_t>(cand, W, shift, unit, chosen);
     else

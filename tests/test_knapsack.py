@@ -1,6 +1,10 @@
 """The retrieval knapsack against the oracle's, where its parts meet: instances that the reduction decides
 almost whole, instances in which nearly everything ties and nothing can be fixed, groups without tokens,
 lengths with a common divisor, and values so large that the programme counts in 128 bits."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 
@@ -33,3 +37,24 @@ def test_knapsack_matches_oracle(oracle, kind):
         for budget in {0, 1, 63, 64, int(lens.sum()) // 3, int(rng.integers(0, lens.sum() + 2)), int(lens.sum()) - 1}:
             got = B.segment_select_scored(pool, p, 0.0, max(budget, 0), 1, want_plan=False)[0].tolist()
             assert got == oracle.knapsack_dp(p, lens, 0.0, max(budget, 0)), (kind, budget)
+
+
+def test_knapsack_stays_within_its_bound():
+    """Long candidates with values that count in 128 bits, just accepted (the bound is 1 GiB): the call takes no more
+    than the bound."""
+    code = """
+import itertools, resource
+import numpy as np
+from paper_2510_18546_amd import binding as B
+lens, p, budget = np.array([19999999, 20000003, 20000017], np.int32), np.array([1.5, 1.0, 1.25], np.float32) * 2.0 ** 20, 40000018
+pool = B.kv_pool_create(None, None, lens, n_q_heads=4, rope_base=1e4, max_ctx=1 << 20, dtype=B.EN_BF16, k_ptr=0x1000,
+                        v_ptr=0x2000, shape=(3, 1, int(lens.max()), 64))
+B.segment_select_scored(pool, p, 0.0, 1, 1, want_plan=False)
+before = resource.getrusage(resource.RUSAGE_SELF).ru_maxrss
+got = B.segment_select_scored(pool, p, 0.0, budget, 1, want_plan=False)[0].tolist()
+sets = [s for n in range(4) for s in itertools.combinations(range(3), n) if sum(int(lens[g]) for g in s) <= budget]
+assert got == list(max(sets, key=lambda s: sum(float(p[g]) for g in s))), got
+grown = resource.getrusage(resource.RUSAGE_SELF).ru_maxrss - before
+assert grown <= 1 << 20, grown
+"""
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
