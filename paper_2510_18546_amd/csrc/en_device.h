@@ -210,25 +210,6 @@ __device__ __forceinline__ float pair_max(float v)
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
-// Sum, maximum over the four lanes l % 16 + {0, 16, 32, 48}, in each of them: two exchanges in the vector ALU
-// (of rows of 16 lanes, of the halves of the wave) and no LDS crossbar.
-__device__ __forceinline__ float quad_sum(float v)
-{
-    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-    u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ __forceinline__ float quad_max(float v)
-{
-    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-    u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-
 // Sum over the 32 lanes of each half of the wave, in every lane of the half: four steps inside the
 // rows of 16 lanes in the vector ALU (data-parallel primitives), one exchange between the two rows.
 __device__ __forceinline__ float half_sum(float v)
