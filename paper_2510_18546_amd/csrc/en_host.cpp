@@ -644,11 +644,16 @@ int en_attn_sub(const en_pool *pool, const en_plan *pl, int n_rows, int n_splits
     return long(pl->B) * pool->d.n_kv_heads * n_splits <= 2L * pool->n_cu ? 2 : 1;
 }
 
-// Whether the reduced masses of n_rows query rows per head are summed by mass_few_rows_kernel in a launch of
-// its own, not beside the merge.
+// Whether the reduced masses that an attention call over n_rows query rows per head is asked for are summed by
+// mass_few_rows_kernel in a launch of its own, not beside the merge.
 static bool mass_few_rows(const en_pool *pool, int n_rows)
 {
     return n_rows < EN_MASS_FEW_ROWS || decode_kernel_fits(pool, n_rows);
+}
+// ... and those of the call for them.
+static bool mass_call_few_rows(const en_pool *pool, int n_rows)
+{
+    return mass_few_rows(pool, n_rows) || long(pool->d.n_q_heads) * n_rows <= EN_MASS_FEW_PAIRS;
 }
 
 // Workgroups per agent and bucket group of the others.
@@ -673,7 +678,7 @@ EnWsLayout en_ws_layout_for(const en_pool *pool, const en_plan *pl, int n_rows, 
         L.total = align256(L.opart_off + size_t(n_splits) * rows * pool->d.head_dim * elem_size(pool->d.dtype));
     // last, since only segment_attention_mass uses it, which does not follow a decode step
     L.parts_off = L.total;
-    if (!mass_few_rows(pool, n_rows))
+    if (!mass_call_few_rows(pool, n_rows))
         L.total = align256(L.parts_off + size_t(pl->B) * (pl->Smax + 1) * mass_workgroups(pool, n_rows) * sizeof(float));
     return L;
 }
@@ -922,7 +927,7 @@ static EnMassArgs mass_args(const en_pool *pool, const en_plan *plan, char *ws, 
     a.ws_mlfin = reinterpret_cast<const float *>(ws + L.mlfin_off);
     a.red_out = nullptr;
     a.red_acc = reinterpret_cast<unsigned long long *>(ws + L.redacc_off);
-    a.few = mass_few_rows(pool, n_rows) ? 1 : 0;
+    a.few = (fixed_point ? mass_few_rows(pool, n_rows) : mass_call_few_rows(pool, n_rows)) ? 1 : 0;
     a.parts = fixed_point ? nullptr : reinterpret_cast<float *>(ws + L.parts_off);
     a.red_target = mass_workgroups(pool, n_rows);
     a.red_count_bits = bits_for(a.red_target);

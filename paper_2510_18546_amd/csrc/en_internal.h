@@ -91,7 +91,10 @@ struct EnGatherArgs {
     // last-level cache are not there any more when the attention kernel comes to read them, and its lines
     // in the way cost the gather 3 % (64 agents x 16 K tokens, 4.3 GB: 1473 -> 1438 us); a smaller one is
     // read back from the cache (16 agents x 2 K tokens, 133 MB: the gather gains 13 us that way, the
-    // attention kernel loses 12; one agent's 36 MB: the step gets 2.5 us longer).
+    // attention kernel loses 12; one agent's 36 MB: the step gets 2.5 us longer). Plans that leave their values
+    // in the pool write half as much, but the attention kernel then reads the pool's values beside the keys: the
+    // line is the same one, twice the keys (9 agents x 8 K tokens, keys of 146 MB, gather and attention: 247 us
+    // kept in the caches, 241 past them; 12 agents 195 MB: 305, 297; 15 agents 243 MB: 337, 329).
     int stream;
 };
 
@@ -160,7 +163,7 @@ struct EnAttnArgs {
 
 struct EnMassArgs {
     const float *ws_ml, *ws_seg, *ws_mlfin;
-    // Reduced masses [B, Smax+1], or null. Unless the step has few rows (`few`, mass_few_rows in en_host.cpp)
+    // Reduced masses [B, Smax+1], or null. Unless the step has few rows (`few`, see mass_few_rows in en_host.cpp)
     // red_target workgroups, of EN_MASS_UNITS units of 64 rows of a head each, sum a bucket's rows in fp32.
     // Their sums meet in one of two ways. With `parts` null, as part of an attention call and without a
     // launch behind it: as fixed-point integers (2^-red_shift; integer sums do not depend on the order of
@@ -197,7 +200,14 @@ struct EnAppendQ8Args {
 
 
 constexpr int EN_RED_DIRECT_MAX_BUCKETS = 256;   // EnAttnArgs::red_direct: buckets whose sums a workgroup keeps in LDS
-constexpr int EN_MASS_FEW_ROWS = 8;     // below this many query rows per head the reduced masses need no accumulators
+// Reduced masses in an attention call: below this many query rows per head a launch behind the merge adds them up in
+// fp32, from here on the merge launch does, in fixed point (56 heads, 4 K tokens, behind / beside the merge: 7 rows
+// 25.1 / 23.2 us, 8 rows 25.3 / 23.4, 24 rows 32.3 / 26.0).
+constexpr int EN_MASS_FEW_ROWS = 8;
+// Reduced masses in a call of their own: up to this many (head, row) pairs one launch with a workgroup per bucket,
+// beyond it the parts of many workgroups and a second launch (17 buckets: 1024 pairs 5.0 / 7.7 us, 2048 7.1 / 7.7,
+// 3072 9.3 / 7.7; 16 agents x 25 buckets: 4.7 / 8.2, 6.2 / 8.2, 7.8 / 10.0).
+constexpr int EN_MASS_FEW_PAIRS = 2048;
 constexpr int EN_MASS_UNITS = 4;        // units of 64 query rows of a head per workgroup of the reduced masses, one per wave
 constexpr int EN_MASS_ARRIVALS = 1023;  // workgroups that may meet in one accumulator of the reduced masses (10 bits)
 constexpr int EN_MAX_SPLITS = 64;       // KV splits of a plan: the mass kernels hold one split per lane

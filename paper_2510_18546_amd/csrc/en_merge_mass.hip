@@ -693,6 +693,8 @@ int en_launch_mass(const en_pool *pool, const EnMassArgs &a, int reduce, void *s
     hipStream_t st = (hipStream_t)stream;
     if (reduce == 0) {
         const dim3 blk(256);
+        // The line: 64 agents x 32 heads x 65 buckets, a thread per result / 64 rows' width: 12 rows 17.7 / 27.5 us,
+        // 15 21.0 / 28.0, 16 22.1 / 27.6, 20 26.8 / 29.3, 32 40.6 / 30.5; a few agents 4.0 either way.
         if (a.Nq < 16) {
             const dim3 grid((a.Hq * (a.Smax + 1) + 255) / 256, a.Nq, a.B);
             hipLaunchKernelGGL(mass_rows_few_kernel, grid, blk, 0, st, a);
@@ -707,6 +709,8 @@ int en_launch_mass(const en_pool *pool, const EnMassArgs &a, int reduce, void *s
             hipLaunchKernelGGL(mass_partial_kernel, dim3(mass_partial_blocks(a)), blk, 0, st, a);
             if (a.parts)
                 hipLaunchKernelGGL(mass_final_kernel, dim3((pairs + 3) / 4), blk, 0, st, a);
+        // A wave or a workgroup per bucket: 64 agents x 65 buckets, 128 (head, row) pairs 5.1 / 9.2 us, 256 6.4 / 10.4;
+        // one agent, 33 buckets 4.0 / 3.9 and 4.4 / 3.9.
         } else if (a.Hq * a.Nq <= 128)
             hipLaunchKernelGGL((mass_few_rows_kernel<64>), dim3((pairs + 3) / 4), blk, 0, st, a);
         else

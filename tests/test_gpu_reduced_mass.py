@@ -21,6 +21,8 @@ pytestmark = pytest.mark.gpu
     (I.BF16, 6, 2, 40, 3, 1),        # one split: no merge launch
     (I.F32, 3, 1, 8, 9, 2),
     (I.F32, 3, 3, 66, 2, 1),
+    (I.BF16, 35, 5, 65, 9, 7),       # more than 2048 (head, row) pairs: the call of its own in two launches
+    (I.F32, 33, 3, 66, 8, 1),
 ])
 def test_reduced_masses_of_few_rows(step_mod, oracle, dtype, heads, kv, n_new, n_sel, splits):
     cfg = small(f"reduced-{n_new}-{n_sel}", 800 + n_new, dtype=dtype, n_agents=2, n_q_heads=heads, n_kv_heads=kv,
@@ -63,7 +65,8 @@ def test_masses_of_many_agents_and_segments(step_mod, oracle):
 
 
 @pytest.mark.parametrize("dtype,n_new,splits", [
-    (I.F32, 3, 1), (I.F32, 9, 1), (I.F32, 70, 3), (I.BF16, 8, 2), (I.BF16, 40, 1), (I.BF16, 130, 2), (I.BF16, 257, 2)])
+    (I.F32, 3, 1), (I.F32, 9, 1), (I.F32, 70, 3), (I.BF16, 8, 2), (I.BF16, 40, 1), (I.BF16, 130, 2), (I.BF16, 350, 2),
+    (I.F32, 350, 1)])
 def test_reduced_masses_of_a_segment_far_off(step_mod, dtype, n_new, splits):
     """A segment whose scores lie 30 below the others, masses of about 1e-14 a row: their sum is as exact as that of
     the large ones."""
