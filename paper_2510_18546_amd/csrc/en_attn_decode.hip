@@ -168,7 +168,7 @@ __global__ __launch_bounds__(64 * SUB) void attn_decode_kernel(EnAttnArgs a)
             app_v2[j] = vr[c + D / 2];
         }
     };
-    auto app_store = [&](int t) {
+    auto app_store = [&](auto first_tag, int t) {
         const int pos = Lc + t;
         bf16_t *kd = (bf16_t *)a.kc + (((size_t)b * a.Hkv + kvh) * a.T + pos) * D;
         // token j in column j with bits 2 and 3 exchanged
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(64 * SUB) void attn_decode_kernel(EnAttnArgs a)
             const int c = lane + 64 * j;
             if (c < D / 2) {
                 float y1, y2;
-                rope_key_pair(app_x1[j], app_x2[j], app_cs[j], app_sn[j], y1, y2);
+                rope_key_pair<decltype(first_tag)::value>(app_x1[j], app_x2[j], app_cs[j], app_sn[j], y1, y2);
                 kd[c] = (bf16_t)y1;
                 kd[c + D / 2] = (bf16_t)y2;
                 vd[(size_t)c * a.T] = app_v1[j];
@@ -217,10 +217,10 @@ __global__ __launch_bounds__(64 * SUB) void attn_decode_kernel(EnAttnArgs a)
         // them, so that their acknowledgement is under way while the queries are rotated
         if (appends) {
             int t = first_new - Lc;
-            app_store(t);
+            app_store(std::true_type{}, t);
             for (++t; t < a.Nq && Lc + t < split_key_end; ++t) {
                 app_load(t);
-                app_store(t);
+                app_store(std::false_type{}, t);
             }
         }
         if (owns_new && !first_tile_old) {

@@ -42,8 +42,10 @@ __device__ __forceinline__ void rope_scale_pair(float x1, float x2, float c, flo
 
 // A key's rotary pair turned by its position's angle: of the two products of each half one is rounded and the
 // other goes into a fused multiply-add. Which one is said here: left to the compiler, the choice changed with
-// the loop around the expression, and the last bits of the context with it. The second half rounds x2's
-// product; in the 8-bit gather (X1_ROUNDED) x1's: the bits that these contexts have always had.
+// the loop around the expression, and the last bits of the context with it. The first half rounds x2's product.
+// The second half rounds x2's too or (X1_ROUNDED) x1's; either is as exact, and who writes which are the bits
+// that these contexts have always had: x1's in the 8-bit gather, in the first row that a wave of the decode
+// kernel appends, and in all heads but the last of a gather unit of four (16-bit, of eight with D = 64).
 template <bool X1_ROUNDED = false, typename F>
 __device__ __forceinline__ void rope_key_pair(F x1, F x2, F c, F s, F &y1, F &y2)
 {

@@ -110,6 +110,7 @@ __device__ __forceinline__ void gather_k_rows(const EnGatherArgs &a, int tok, in
     // value units of the launch too (64 agents x 16 K tokens: 1690 us, 1470 with two heads' loads in flight
     // per wave and five waves).
     constexpr int HU = HPB < 2 ? HPB : 2;
+    constexpr bool X1_ROUNDED = sizeof(T) == 2 && (HPB == 4 || (HPB == 8 && D == 64));      // see rope_key_pair
 #pragma unroll 1
     for (int h0 = 0; h0 < HPB; h0 += HU) {
         tvec x1[HU], x2[HU];
@@ -126,7 +127,10 @@ __device__ __forceinline__ void gather_k_rows(const EnGatherArgs &a, int tok, in
             fvec y1 = 0.f, y2 = 0.f;
             if (ksrc) {
                 const fvec f1 = __builtin_convertvector(x1[h], fvec), f2 = __builtin_convertvector(x2[h], fvec);
-                rope_key_pair(f1, f2, cs, sn, y1, y2);
+                if (X1_ROUNDED && (h < HU - 1 || h0 + HU < HPB))
+                    rope_key_pair<true>(f1, f2, cs, sn, y1, y2);
+                else
+                    rope_key_pair(f1, f2, cs, sn, y1, y2);
             }
             store_context<STREAM>(dst + c * E, __builtin_convertvector(y1, tvec));
             store_context<STREAM>(dst + D / 2 + c * E, __builtin_convertvector(y2, tvec));
