@@ -91,10 +91,12 @@ struct EnGatherArgs {
     // last-level cache are not there any more when the attention kernel comes to read them, and its lines
     // in the way cost the gather 3 % (64 agents x 16 K tokens, 4.3 GB: 1473 -> 1438 us); a smaller one is
     // read back from the cache (16 agents x 2 K tokens, 133 MB: the gather gains 13 us that way, the
-    // attention kernel loses 12; one agent's 36 MB: the step gets 2.5 us longer). Plans that leave their values
-    // in the pool write half as much, but the attention kernel then reads the pool's values beside the keys: the
-    // line is the same one, twice the keys (9 agents x 8 K tokens, keys of 146 MB, gather and attention: 247 us
-    // kept in the caches, 241 past them; 12 agents 195 MB: 305, 297; 15 agents 243 MB: 337, 329).
+    // attention kernel loses 12; one agent's 36 MB: the step gets 2.5 us longer). With rows of 64 values the
+    // gather itself loses (64 agents x 16 K tokens, 8 heads 648 -> 674 us, 2 heads 188 -> 194), the attention
+    // behind it gains more (together 1063 -> 1028, 358 -> 314). Plans that leave their values in the pool write
+    // half as much, but the attention kernel then reads the pool's values beside the keys: the line is the same
+    // one, twice the keys (9 agents x 8 K tokens, keys of 146 MB, gather and attention: 247 us kept in the caches,
+    // 241 past them; 12 agents 195 MB: 305, 297; 15 agents 243 MB: 337, 329).
     int stream;
 };
 
