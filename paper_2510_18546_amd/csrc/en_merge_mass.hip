@@ -517,7 +517,7 @@ __global__ __launch_bounds__(256) void mass_final_kernel(EnMassArgs a)
         a.red_out[pair] = acc;
 }
 
-// The reduced masses of few query rows per head (decode steps): a workgroup of G threads per (agent,
+// The reduced masses of few (head, row) pairs (decode steps, small layers): a workgroup of G threads per (agent,
 // bucket) walks the bucket's (head, row) pairs and writes the sum, nothing to meet and no second launch.
 template <int G>
 __global__ __launch_bounds__(256) void mass_few_rows_kernel(EnMassArgs a)

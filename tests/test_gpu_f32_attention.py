@@ -73,3 +73,20 @@ def test_fp32_values_of_hidden_tokens(step_mod, d, n_new, splits):
         np.testing.assert_allclose(got[:, :-1], out[:, :-1], rtol=0, atol=16 * 2.0 ** -24 * np.abs(out).max())
         assert not np.isfinite(got[:, -1]).any()
         np.testing.assert_array_equal(st.mass_host(), mass)
+
+
+@pytest.mark.parametrize("offset", [1, 3])
+def test_fp32_queries_and_outputs_at_any_float(step_mod, offset):
+    """Queries and outputs need no more than a float's alignment; nothing around the outputs is written."""
+    import torch
+    from paper_2510_18546_amd import binding as B
+    cfg = small("f32-align", 790, dtype=I.F32, head_dim=64, n_q_heads=4, rope_base=1e4, n_new=21, n_agents=2)
+    st = step_mod.PlanningStep(I.make_workload(cfg))
+    st.run()
+    n = st.q.numel()
+    q, out = torch.zeros(n + 8, device="cuda:0"), torch.full((n + 8,), 7.0, device="cuda:0")
+    q[offset:offset + n] = st.q.flatten()
+    B.segmented_prefill_attention(st.pool, st.plan, q[offset:offset + n].view_as(st.q), st.kc, st.vt,
+                                  out[offset:offset + n].view_as(st.out), st.ws)
+    assert torch.equal(out[offset:offset + n].view_as(st.out), st.out)
+    assert (out[:offset] == 7).all() and (out[offset + n:] == 7).all()
