@@ -258,8 +258,9 @@ int gather_rope_queries(en_pool *pool, en_plan *plan, const void *k_new_dev, con
 
 /* Bytes of scratch the attention call and the mass calls behind it need for this
  * plan: per-split running (max, sum), per-(row, segment) partial sums, parts of
- * the reduced masses, and, when n_splits > 1, partial outputs (a step of few rows and few agents keeps two partial results per
- * split: the size accounts for it). */
+ * the reduced masses, and, when n_splits > 1, partial outputs (a step of few
+ * rows and few agents keeps two partial results per split: the size accounts
+ * for it). */
 size_t en_workspace_bytes(const en_pool *pool, const en_plan *plan);
 
 /* softmax(Q K^T / sqrt(D)) V (Appendix A) of the N_q new tokens over the
