@@ -54,6 +54,12 @@ __device__ __forceinline__ void store_context(P *dst, V v)
         *p = v;
 }
 
+// Units of heads whose keys, all but the last one's, are turned in the form X1_ROUNDED of rope_key_pair, or 0; `many`:
+// heads per key unit by gather_heads_many.
+__host__ __device__ constexpr int en_rope_unit(int elem, int d, int many)
+{
+    return elem == 2 && (many == 4 || (many == 8 && d == 64)) ? many : 0;
+}
 // Source row of context token `tok` for (agent b, KV head kvh); nullptr for
 // padding rows at or beyond L_c + N_q. `bnd` and `sel` are the agent's tables
 // (global or staged), S its number of segments.
@@ -83,11 +89,10 @@ __device__ __forceinline__ const T *context_src(const EnGatherArgs &a, P bnd, P 
 // per head, 0.73 ms without the table, which is what the value half takes).
 // 256 threads, 32 rows per pass.
 // ---------------------------------------------------------------------------
-template <typename T, int D, bool COPY_V, int HPB, bool STREAM, typename P>
-__device__ __forceinline__ void gather_k_rows(const EnGatherArgs &a, int tok, int kv0, P bnd, P sel, int S)
+template <typename T, int D, bool COPY_V, int HPB, bool STREAM, bool AHEAD, typename P>
+__device__ __forceinline__ void gather_k_rows(const EnGatherArgs &a, int b, int tok, int kv0, P bnd, P sel, int S)
 {
     constexpr int E = D / 16;
-    const int b = blockIdx.z;
     const int c = threadIdx.x % 8;
     const int Ltot = bnd[S + 1];
     const int Lpad = (Ltot + EN_KEY_TILE - 1) / EN_KEY_TILE * EN_KEY_TILE;
@@ -106,14 +111,16 @@ __device__ __forceinline__ void gather_k_rows(const EnGatherArgs &a, int tok, in
         cs = *reinterpret_cast<const fvec *>(a.cos_tab + (size_t)tok * (D / 2) + c * E);
         sn = *reinterpret_cast<const fvec *>(a.sin_tab + (size_t)tok * (D / 2) + c * E);
     }
-    // Two heads at a time: the loads of all eight at once took 150 registers, three waves per SIMD for the
-    // value units of the launch too (64 agents x 16 K tokens: 1690 us, 1470 with two heads' loads in flight
-    // per wave and five waves).
-    constexpr int HU = HPB < 2 ? HPB : 2;
-    constexpr bool X1_ROUNDED = sizeof(T) == 2 && (HPB == 4 || (HPB == 8 && D == 64));      // see rope_key_pair
-#pragma unroll 1
-    for (int h0 = 0; h0 < HPB; h0 += HU) {
-        tvec x1[HU], x2[HU];
+    // HU heads at a time. AHEAD (see EnGatherLaunch::ahead): the loads of the next ones go out before these are
+    // turned and stored, so that a workgroup of several heads waits for memory once and not once per HU heads.
+    // Four of eight at a time then (two: the ordered gather of 64 agents x 16 K tokens takes 1 % longer, that of 32
+    // agents 3 %).
+    constexpr int HU = AHEAD && HPB == 8 ? 4 : HPB < 2 ? HPB : 2;
+    // (without AHEAD the heads of a unit are those that en_rope_unit goes by; with it, a launch of single heads is far
+    // smaller than one that has such units)
+    const int rope_unit = !AHEAD ? en_rope_unit(sizeof(T), D, HPB) : HPB > 1 ? a.rope_unit : 0;
+    tvec x1[HU], x2[HU];
+    auto load = [&](int h0) {
         if (ksrc) {
 #pragma unroll
             for (int h = 0; h < HU; ++h) {
@@ -121,13 +128,32 @@ __device__ __forceinline__ void gather_k_rows(const EnGatherArgs &a, int tok, in
                 x2[h] = *reinterpret_cast<const tvec *>(ksrc + (h0 + h) * hstride + D / 2 + c * E);
             }
         }
+    };
+    if constexpr (AHEAD)
+        load(0);
+#pragma unroll 1
+    for (int h0 = 0; h0 < HPB; h0 += HU) {
+        if constexpr (!AHEAD)
+            load(h0);
+        tvec w1[HU], w2[HU];
 #pragma unroll
         for (int h = 0; h < HU; ++h) {
-            T *dst = (T *)a.kc + (((size_t)b * a.Hkv + kv0 + h0 + h) * a.T + tok) * D;
+            w1[h] = x1[h];
+            w2[h] = x2[h];
+        }
+        if constexpr (AHEAD) {
+            asm volatile("" ::: "memory");         // (not behind the stores)
+            if (h0 + HU < HPB)
+                load(h0 + HU);
+        }
+#pragma unroll
+        for (int h = 0; h < HU; ++h) {
+            const int kvh = kv0 + h0 + h;
+            const fvec f1 = __builtin_convertvector(w1[h], fvec), f2 = __builtin_convertvector(w2[h], fvec);
+            T *dst = (T *)a.kc + (((size_t)b * a.Hkv + kvh) * a.T + tok) * D;
             fvec y1 = 0.f, y2 = 0.f;
             if (ksrc) {
-                const fvec f1 = __builtin_convertvector(x1[h], fvec), f2 = __builtin_convertvector(x2[h], fvec);
-                if (X1_ROUNDED && (h < HU - 1 || h0 + HU < HPB))
+                if (rope_unit && (kvh + 1) % rope_unit != 0)
                     rope_key_pair<true>(f1, f2, cs, sn, y1, y2);
                 else
                     rope_key_pair(f1, f2, cs, sn, y1, y2);
@@ -153,104 +179,126 @@ __device__ __forceinline__ void gather_k_rows(const EnGatherArgs &a, int tok, in
 
 // The key rows of 64-token tile `tile` for the heads kv0 .. kv0 + HPB - 1, 32 rows at a time:
 // the halves first .. last of the tile.
-template <typename T, int D, bool COPY_V, int HPB, bool STREAM>
-__device__ __forceinline__ void gather_k_block(const EnGatherArgs &a, int tile, int first, int last, int kv0,
+template <typename T, int D, bool COPY_V, int HPB, bool STREAM, bool AHEAD>
+__device__ __forceinline__ void gather_k_block(const EnGatherArgs &a, int b, int tile, int first, int last, int kv0,
                                                int32_t *lbnd)
 {
-    const int b = blockIdx.z;
     const int S = a.nseg[b];
     const EnGatherTables t = stage_tables(a, b, lbnd);
 #pragma unroll 1
     for (int half = first; half <= last; ++half) {
         const int tok = tile * EN_KEY_TILE + half * 32 + threadIdx.x / 8;
         if (t.staged)
-            gather_k_rows<T, D, COPY_V, HPB, STREAM>(a, tok, kv0, (const int32_t *)lbnd,
-                                             (const int32_t *)lbnd + EN_GATHER_TAB_LDS, S);
+            gather_k_rows<T, D, COPY_V, HPB, STREAM, AHEAD>(a, b, tok, kv0, (const int32_t *)lbnd,
+                                                            (const int32_t *)lbnd + EN_GATHER_TAB_LDS, S);
         else
-            gather_k_rows<T, D, COPY_V, HPB, STREAM>(a, tok, kv0, t.bnd, t.sel, S);
+            gather_k_rows<T, D, COPY_V, HPB, STREAM, AHEAD>(a, b, tok, kv0, t.bnd, t.sel, S);
     }
 }
 
 // ---------------------------------------------------------------------------
 // gather_vt (bf16): values of a 64-token tile are staged in LDS and written
 // transposed, vt[d][column], where token j sits at column j with bits 2 and 3
-// exchanged. 256 threads; bx = number of the 64-token tile.
+// exchanged; the heads kv0 .. kv0 + HPB - 1 one after the other, the next head's
+// loads on their way meanwhile. 256 threads; bx = number of the 64-token tile.
 // ---------------------------------------------------------------------------
-template <int D, bool STREAM>
-__device__ __forceinline__ void gather_vt_block(const EnGatherArgs &a, int bx, int kvh, int32_t *lbnd)
+template <int D, int HPB, bool STREAM>
+__device__ __forceinline__ void gather_vt_block(const EnGatherArgs &a, int b, int bx, int kv0, int32_t *lbnd)
 {
     constexpr int STR = D + 2;                 // LDS row stride in elements
     __shared__ uint16_t tile[EN_KEY_TILE * STR];
     __shared__ const uint16_t *srcs[EN_KEY_TILE];
-    const int b = blockIdx.z;
     const int t0 = bx * EN_KEY_TILE;
     const int S = a.nseg[b];
     const EnGatherTables t = stage_tables(a, b, lbnd);
     const int32_t *lsel = lbnd + EN_GATHER_TAB_LDS;
+    const int Lc = t.staged ? lbnd[S] : t.bnd[S];
     const int Ltot = t.staged ? lbnd[S + 1] : t.bnd[S + 1];
     if (t0 >= Ltot)                            // the same for the whole block
         return;
+    // head kv0 + h is h * stride elements further: new tokens [.., Hkv, D], pool [.., Hkv, C, D]
+    auto head_stride = [&](bool fresh) { return fresh ? (size_t)D : (size_t)a.C * D; };
+    const uint16_t *src = nullptr;
+    if (threadIdx.x < EN_KEY_TILE) {
+        const uint16_t *vp = (const uint16_t *)a.v_pool, *vn = (const uint16_t *)a.v_new;
+        src = t.staged ? context_src<uint16_t, D>(a, (const int32_t *)lbnd, lsel, S, vp, vn, b, kv0, t0 + threadIdx.x)
+                       : context_src<uint16_t, D>(a, t.bnd, t.sel, S, vp, vn, b, kv0, t0 + threadIdx.x);
+    }
     if (a.v_rows) {
         // the values stay where they are: the tile's 64 row addresses instead (padding rows: the row of zeros)
         char *zero_row = (char *)a.vt + en_v_rows_table_bytes(a.B, a.Hkv, a.T);
         if (threadIdx.x < EN_KEY_TILE) {
-            const uint16_t *vp = (const uint16_t *)a.v_pool, *vn = (const uint16_t *)a.v_new;
-            const uint16_t *src =
-                t.staged ? context_src<uint16_t, D>(a, (const int32_t *)lbnd, lsel, S, vp, vn, b, kvh, t0 + threadIdx.x)
-                         : context_src<uint16_t, D>(a, t.bnd, t.sel, S, vp, vn, b, kvh, t0 + threadIdx.x);
-            unsigned long long *tab = (unsigned long long *)a.vt + ((size_t)b * a.Hkv + kvh) * (size_t)a.T + t0;
-            tab[threadIdx.x] = (unsigned long long)(uintptr_t)(src ? (const void *)src : (const void *)zero_row);
-        } else if (bx == 0 && kvh == 0 && b == 0 && threadIdx.x < EN_KEY_TILE + D * 2 / 16) {
+            unsigned long long *tab = (unsigned long long *)a.vt + ((size_t)b * a.Hkv + kv0) * (size_t)a.T + t0;
+            for (int h = 0; h < HPB; ++h)
+                tab[(size_t)h * a.T + threadIdx.x] = (unsigned long long)(uintptr_t)(
+                    src ? (const void *)(src + h * head_stride(t0 + (int)threadIdx.x >= Lc)) : (const void *)zero_row);
+        } else if (bx == 0 && kv0 == 0 && b == 0 && threadIdx.x < EN_KEY_TILE + D * 2 / 16) {
             reinterpret_cast<uint4 *>(zero_row)[threadIdx.x - EN_KEY_TILE] = make_uint4(0, 0, 0, 0);
         }
         return;
     }
-    if (threadIdx.x < EN_KEY_TILE) {
-        const uint16_t *vp = (const uint16_t *)a.v_pool, *vn = (const uint16_t *)a.v_new;
-        srcs[threadIdx.x] =
-            t.staged ? context_src<uint16_t, D>(a, (const int32_t *)lbnd, lsel, S, vp, vn, b, kvh, t0 + threadIdx.x)
-                     : context_src<uint16_t, D>(a, t.bnd, t.sel, S, vp, vn, b, kvh, t0 + threadIdx.x);
-    }
+    if (threadIdx.x < EN_KEY_TILE)
+        srcs[threadIdx.x] = src;
     __syncthreads();
-    // load: D/8 chunks of 16 bytes per token
-    constexpr int CH = D / 8;
-    for (int idx = threadIdx.x; idx < EN_KEY_TILE * CH; idx += 256) {
-        const int tk = idx / CH, ch = idx % CH;
-        const uint16_t *s = srcs[tk];
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (s)
-            v = *reinterpret_cast<const uint4 *>(s + ch * 8);
-        uint16_t *d = &tile[tk * STR + ch * 8];
-        // STR is even but not a multiple of 8: store as 4 dwords
-        reinterpret_cast<uint32_t *>(d)[0] = v.x;
-        reinterpret_cast<uint32_t *>(d)[1] = v.y;
-        reinterpret_cast<uint32_t *>(d)[2] = v.z;
-        reinterpret_cast<uint32_t *>(d)[3] = v.w;
-    }
-    __syncthreads();
-    // store: for every d, 8 chunks of 8 columns
-    uint16_t *vt = (uint16_t *)a.vt + ((size_t)b * a.Hkv + kvh) * D * (size_t)a.T + t0;
-    for (int idx = threadIdx.x; idx < D * 8; idx += 256) {
-        const int d = idx / 8, ch = idx % 8;      // columns ch*8 .. ch*8+7
-        const int g16 = ch / 2, hf = ch % 2;
-        uint16_t v[8];
+    // D/8 chunks of 16 bytes per token, NC of them per thread
+    constexpr int CH = D / 8, NC = EN_KEY_TILE * CH / 256;
+    const int tk0 = threadIdx.x / CH, ch0 = threadIdx.x % CH;
+    const uint16_t *from[NC];
+    bool fresh[NC];                              // a row of the new tokens
+    uint4 v[NC];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int tk = 16 * g16 + 8 * (e >> 2) + 4 * hf + (e & 3);
-            v[e] = tile[tk * STR + d];
+    for (int i = 0; i < NC; ++i) {
+        const int tk = tk0 + i * (256 / CH);
+        from[i] = srcs[tk];
+        fresh[i] = t0 + tk >= Lc;
+        v[i] = make_uint4(0, 0, 0, 0);
+        if (from[i])
+            v[i] = *reinterpret_cast<const uint4 *>(from[i] += ch0 * 8);
+    }
+    uint16_t *vt = (uint16_t *)a.vt + ((size_t)b * a.Hkv + kv0) * D * (size_t)a.T + t0;
+#pragma unroll 1
+    for (int h = 0; h < HPB; ++h, vt += D * (size_t)a.T) {
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            uint16_t *d = &tile[(tk0 + i * (256 / CH)) * STR + ch0 * 8];
+            // STR is even but not a multiple of 8: store as 4 dwords
+            reinterpret_cast<uint32_t *>(d)[0] = v[i].x;
+            reinterpret_cast<uint32_t *>(d)[1] = v[i].y;
+            reinterpret_cast<uint32_t *>(d)[2] = v[i].z;
+            reinterpret_cast<uint32_t *>(d)[3] = v[i].w;
         }
-        u32x4 o;
-        o[0] = v[0] | ((uint32_t)v[1] << 16);
-        o[1] = v[2] | ((uint32_t)v[3] << 16);
-        o[2] = v[4] | ((uint32_t)v[5] << 16);
-        o[3] = v[6] | ((uint32_t)v[7] << 16);
-        store_context<STREAM>(reinterpret_cast<u32x4 *>(vt + (size_t)d * a.T + ch * 8), o);
+        if (h + 1 < HPB) {
+#pragma unroll
+            for (int i = 0; i < NC; ++i)
+                if (from[i])
+                    v[i] = *reinterpret_cast<const uint4 *>(from[i] += head_stride(fresh[i]));
+        }
+        __syncthreads();
+        // store: for every d, 8 chunks of 8 columns
+        for (int idx = threadIdx.x; idx < D * 8; idx += 256) {
+            const int d = idx / 8, ch = idx % 8;      // columns ch*8 .. ch*8+7
+            const int g16 = ch / 2, hf = ch % 2;
+            uint16_t v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int tk = 16 * g16 + 8 * (e >> 2) + 4 * hf + (e & 3);
+                v[e] = tile[tk * STR + d];
+            }
+            u32x4 o;
+            o[0] = v[0] | ((uint32_t)v[1] << 16);
+            o[1] = v[2] | ((uint32_t)v[3] << 16);
+            o[2] = v[4] | ((uint32_t)v[5] << 16);
+            o[3] = v[6] | ((uint32_t)v[7] << 16);
+            store_context<STREAM>(reinterpret_cast<u32x4 *>(vt + (size_t)d * a.T + ch * 8), o);
+        }
+        if (h + 1 < HPB)
+            __syncthreads();
     }
 }
 
 // One launch for the whole gather. Grid (64-token tiles, units, agents); the units, head group
 // by head group: the key units (the tile's key rows of HPB heads, which also copy fp32 values),
-// then, for bf16, HPB value units (one head's transposed tile each). Workgroups are dispatched
+// then, for bf16, the value units (the same heads' transposed tiles: one unit with AHEAD, else one each). Workgroups are dispatched
 // tile by tile along one unit, then the next unit: each unit is a sequential stream through
 // memory (with the units of one tile side by side instead, the 8K-context gather took 18.8 us
 // against 13.5), and key and value units of several heads are in flight together: they load
@@ -305,7 +353,44 @@ __device__ __forceinline__ void prepare_queries(const EnGatherArgs &a, int part,
     }
 }
 
-template <typename T, int D, int HPB, bool STREAM>
+// n_q_units more units along y, in front of the key and value units (dispatched first, so that their short
+// chains of loads run beside the streams and not behind them): the queries to prepare. True: this was one;
+// else `unit` is the number of the key or value unit.
+template <int D, bool ORDERED>
+__device__ __forceinline__ bool query_unit(const EnGatherArgs &a, int &unit)
+{
+    if (unit >= a.n_q_units) {
+        unit -= a.n_q_units;
+        return false;
+    }
+    const int w = unit * gridDim.x + blockIdx.x, n = a.n_q_units * gridDim.x;
+    if (!ORDERED || !a.order)
+        prepare_queries<D>(a, w, n, blockIdx.z);
+    else if (w / a.B < n / a.B)              // one grid for all agents (n >= B: an agent has a tile at least)
+        prepare_queries<D>(a, w / a.B, n / a.B, w % a.B);
+    return true;
+}
+
+// Which agent's 64-token tile a workgroup of a key or value unit takes (false: none). Without an order the grid
+// says it. With one (EnGatherArgs::order) the workgroups of an XCD, every eighth of the grid, go through that XCD's
+// list of entries; an entry is up to 1 << order_shift neighbouring tiles of an agent.
+template <bool ORDERED>
+__device__ __forceinline__ bool gather_where(const EnGatherArgs &a, int &tile, int &b)
+{
+    tile = blockIdx.x;
+    b = blockIdx.z;
+    if (ORDERED && a.order) {
+        const unsigned q = blockIdx.x / EN_XCDS;
+        const en_table_ptr e = as_table(a.order) + 2 * ((size_t)(q >> a.order_shift) * EN_XCDS + blockIdx.x % EN_XCDS);
+        const int j = q & ((1 << a.order_shift) - 1);
+        b = e[0];
+        tile = (e[1] >> 2) + j;
+        return j <= (e[1] & 3) && b >= 0;
+    }
+    return true;
+}
+
+template <typename T, int D, int HPB, bool STREAM, bool AHEAD>
 __global__ __launch_bounds__(256) void gather_kernel(EnGatherLaunch g)
 {
     EnGatherArgs a = g.a;
@@ -324,26 +409,23 @@ __global__ __launch_bounds__(256) void gather_kernel(EnGatherLaunch g)
         }
     }
     __shared__ int32_t lbnd[2 * EN_GATHER_TAB_LDS];       // bucket bounds, then selected groups
-    const int tile = blockIdx.x;
+    constexpr bool ORDERED = STREAM && AHEAD;                 // may come in an order
     constexpr int KU = en_gather_key_units(HPB);
-    constexpr int PER = KU + (sizeof(T) == 2 ? HPB : 0);      // units per head group
+    constexpr int VPB = AHEAD ? HPB : 1;                      // heads per value unit
+    constexpr int PER = KU + (sizeof(T) == 2 ? HPB / VPB : 0);      // units per head group
     int unit = blockIdx.y;
     if constexpr (sizeof(T) == 2) {
-        // n_q_units more units along y, in front of the key and value units (dispatched first, so that
-        // their short chains of loads run beside the streams and not behind them): the queries to prepare
-        if (a.q) {
-            if (unit < a.n_q_units) {
-                prepare_queries<D>(a, unit * gridDim.x + tile, a.n_q_units * gridDim.x, blockIdx.z);
-                return;
-            }
-            unit -= a.n_q_units;
-        }
+        if (a.q && query_unit<D, ORDERED>(a, unit))
+            return;
     }
+    int tile, b;
+    if (!gather_where<ORDERED>(a, tile, b))
+        return;
     const int hg = unit / PER, r = unit % PER;
     if (r < KU)
-        gather_k_block<T, D, sizeof(T) == 4, HPB, STREAM>(a, tile, KU == 2 ? r : 0, KU == 2 ? r : 1, hg * HPB, lbnd);
+        gather_k_block<T, D, sizeof(T) == 4, HPB, STREAM, AHEAD>(a, b, tile, KU == 2 ? r : 0, KU == 2 ? r : 1, hg * HPB, lbnd);
     else if constexpr (sizeof(T) == 2)
-        gather_vt_block<D, STREAM>(a, tile, hg * HPB + r - KU, lbnd);
+        gather_vt_block<D, VPB, STREAM>(a, b, tile, hg * HPB + (r - KU) * VPB, lbnd);
 }
 
 // ---------------------------------------------------------------------------
@@ -516,13 +598,8 @@ __global__ __launch_bounds__(256) void gather_q8_kernel(EnGatherLaunch g)
     __shared__ int32_t ltab[2 * EN_GATHER_TAB_LDS];       // bucket bounds, then selected groups
     // the grid of gather_kernel with one head per key unit
     int unit = blockIdx.y;
-    if (a.q) {
-        if (unit < a.n_q_units) {      // the units in front: queries to prepare
-            prepare_queries<D>(a, unit * gridDim.x + blockIdx.x, a.n_q_units * gridDim.x, blockIdx.z);
-            return;
-        }
-        unit -= a.n_q_units;
-    }
+    if (a.q && query_unit<D, false>(a, unit))
+        return;
     const int tile = blockIdx.x, kvh = unit / 2;
     if (unit % 2 == 0)
         gather_q8_k_block<D>(a, tile, kvh, ltab);
@@ -656,8 +733,9 @@ __global__ __launch_bounds__(64) void append_q8_kernel(EnAppendQ8Args a)
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-// Heads per key unit: as many (8, 4, 2 that divide Hkv) as still leave 32 workgroups per compute unit.
-static int gather_heads_per_unit(const en_pool *pool, const EnGatherArgs &a, int n_tiles, bool with_value_units)
+// Heads per key unit of the forms without AHEAD: as many (8, 4, 2 that divide Hkv) as still leave 32 workgroups per
+// compute unit (counted with a value unit per head).
+static int gather_heads_many(const en_pool *pool, const EnGatherArgs &a, int n_tiles, bool with_value_units)
 {
     for (int hpb = 8; hpb > 1; hpb /= 2) {
         const long units = (long)(a.Hkv / hpb) * (en_gather_key_units(hpb) + (with_value_units ? hpb : 0));
@@ -667,27 +745,54 @@ static int gather_heads_per_unit(const en_pool *pool, const EnGatherArgs &a, int
     return 1;
 }
 
-template <typename T, int D, bool STREAM>
+// Heads per unit with AHEAD: as many as leave 1.25 workgroups per compute unit. About four fit one, so where eight
+// heads make more of them than that, a last round of long workgroups would run alone: two heads then, unless the
+// context is so long (past the caches) that many rounds follow each other. Gather and attention, us, with one / two /
+// four / eight heads: 137 tiles (of 8 heads) 88.8 / 88.6 / 88.9 / 90.3, 194: 56.7 / 55.5 / 53.0 / 50.9, 390: 85.0 /
+// 81.0 / 79.6 / 80.1, 528: 129.2 / 125.7 / 127.3 / 129.7, 784: 130.2 / 130.7 / 133.0 / 135.2; past the caches 1300
+// tiles 233 / 228 / 217 / 214, 6200: 965 / 840 / 823 / 805. With changing inputs (nothing of the pool left in the
+// last-level cache) 136 tiles, keys only, 69.5 / 68.9 / 68.8 / 72.3, 28 tiles 32.1 / 32.1 / 32.7 / 35.6, 235: 97.0 /
+// 95.5 / 93.0 / 92.7.
+static int gather_heads_ahead(const en_pool *pool, const EnGatherArgs &a, int n_tiles)
+{
+    int hpb = 8;
+    const long work = (a.v_rows ? 1L : 2L) * a.Hkv * n_tiles * a.B;                  // (tile, head), keys and values
+    if (!a.stream && work > 8 * 4L * pool->n_cu)
+        hpb = 2;
+    while (hpb > 1 && (a.Hkv % hpb || 4 * work < 5L * hpb * pool->n_cu))
+        hpb /= 2;
+    return hpb;
+}
+
+template <typename T, int D, bool STREAM, bool AHEAD>
 static void launch_gather_hpb(int hpb, dim3 grid, hipStream_t st, const EnGatherLaunch &g)
 {
     const dim3 blk(256);
     if (hpb == 8)
-        hipLaunchKernelGGL((gather_kernel<T, D, 8, STREAM>), grid, blk, 0, st, g);
+        hipLaunchKernelGGL((gather_kernel<T, D, 8, STREAM, AHEAD>), grid, blk, 0, st, g);
     else if (hpb == 4)
-        hipLaunchKernelGGL((gather_kernel<T, D, 4, STREAM>), grid, blk, 0, st, g);
+        hipLaunchKernelGGL((gather_kernel<T, D, 4, STREAM, AHEAD>), grid, blk, 0, st, g);
     else if (hpb == 2)
-        hipLaunchKernelGGL((gather_kernel<T, D, 2, STREAM>), grid, blk, 0, st, g);
+        hipLaunchKernelGGL((gather_kernel<T, D, 2, STREAM, AHEAD>), grid, blk, 0, st, g);
     else
-        hipLaunchKernelGGL((gather_kernel<T, D, 1, STREAM>), grid, blk, 0, st, g);
+        hipLaunchKernelGGL((gather_kernel<T, D, 1, STREAM, AHEAD>), grid, blk, 0, st, g);
 }
 
 template <typename T, int D>
 static void launch_gather_kernel(int hpb, dim3 grid, hipStream_t st, const EnGatherLaunch &g)
 {
+    if constexpr (sizeof(T) == 2 && D == 128)
+        if (g.ahead) {
+            if (g.a.stream)
+                launch_gather_hpb<T, D, true, true>(hpb, grid, st, g);
+            else
+                launch_gather_hpb<T, D, false, true>(hpb, grid, st, g);
+            return;
+        }
     if (g.a.stream)
-        launch_gather_hpb<T, D, true>(hpb, grid, st, g);
+        launch_gather_hpb<T, D, true, false>(hpb, grid, st, g);
     else
-        launch_gather_hpb<T, D, false>(hpb, grid, st, g);
+        launch_gather_hpb<T, D, false, false>(hpb, grid, st, g);
 }
 
 int en_launch_gather(const en_pool *pool, EnGatherLaunch &g, int max_ctx_len, void *stream)
@@ -705,9 +810,15 @@ int en_launch_gather(const en_pool *pool, EnGatherLaunch &g, int max_ctx_len, vo
         return (int)hipGetLastError();
     }
     const bool bf16 = pool->d.dtype != EN_F32;
-    const int hpb = gather_heads_per_unit(pool, a, n_tiles, bf16);
+    const int many = gather_heads_many(pool, a, n_tiles, bf16);
+    // which heads' keys are turned in which form (rope_key_pair) goes by the number of heads that this rule gives
+    g.a.rope_unit = en_rope_unit(bf16 ? 2 : 4, D, many);
+    const int hpb = g.ahead ? gather_heads_ahead(pool, a, n_tiles) : many;
+    const int value_units = !bf16 ? 0 : g.ahead ? 1 : hpb;       // per key unit's heads
     // (n_q_units more units along y when the launch also prepares the queries: bf16 contexts only)
-    const dim3 grid(n_tiles, (a.Hkv / hpb) * (en_gather_key_units(hpb) + (bf16 ? hpb : 0)) + (bf16 && a.q ? a.n_q_units : 0), a.B);
+    const dim3 grid(g.order_grid ? g.order_grid : n_tiles,
+                    (a.Hkv / hpb) * (en_gather_key_units(hpb) + value_units) + (bf16 && a.q ? a.n_q_units : 0),
+                    g.order_grid ? 1 : a.B);
     if (!bf16) {
         if (D == 64)
             launch_gather_kernel<float, 64>(hpb, grid, st, g);

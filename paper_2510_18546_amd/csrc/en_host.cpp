@@ -384,6 +384,9 @@ static int build_plan(const en_pool *pool, int32_t B, const int32_t *sel, const 
             if (seen[g] == b) {
                 return fail(EN_ERR_DUPLICATE, "segment_select: agent %d selects group %d twice", b, g);
             }
+            if (seen[g] < 0)
+                ++pl->distinct;
+            pl->max_len = std::max(pl->max_len, pool->len[g]);
             seen[g] = b;
             pl->sel[size_t(b) * sstr + s] = g;
             bnd[s] = int32_t(acc);
@@ -556,6 +559,95 @@ extern "C" int en_plan_destroy(en_plan *plan)
     EN_GUARDED("en_plan_destroy", en_plan_destroy_impl(plan));
 }
 
+// EnGatherArgs::stream
+static bool gather_past_caches(const en_pool *pool, const en_plan *pl)
+{
+    return 2 * en_context_bytes(pool, pl) > EN_LAST_LEVEL_CACHE_BYTES;
+}
+
+// Whether a plan's tiles are gathered in the order of their groups, the agents that share a group one after the other
+// on one XCD: its rows then come from memory once and from that XCD's L2 for the others, where the last-level cache
+// cannot hold the pool for them. Gather and attention, us, agent by agent / in order: 64 agents x 16 K tokens of 4.1
+// agents a group 2208 / 1806, 32 x 14 K of 4.1 935 / 858, 16 x 14 K of 2.3 488 / 466, 64 x
+// 6 K of 1.6 in groups of 96 tokens 896 / 860, 64 x 3 K of 4.1 in groups of 48 419 / 395. Not below EN_GATHER_HUGE_BYTES
+// (neighbouring tiles of an agent are then written far apart): 16 x 12 K tokens of 4 heads, 403 MB, 210 / 223; 16 x 5 K,
+// 335 MB, 201 / 208; 16 x 2 K, 134 MB, 125 / 147; where fewer than two agents share a group, only from 1 GiB on: 16 x
+// 12 K tokens of 1.6, 805 MB, 433 / 438. Nor for rows of 64 values: 791 / 896. Plans whose
+// tables travel in the launch's arguments stay as they are: the order would need a copy of its own.
+static bool gather_in_order(const en_plan *pl)
+{
+    const en_pool *pool = pl->pool;
+    size_t n_sel = 0;
+    for (int b = 0; b < pl->B; ++b)
+        n_sel += size_t(pl->nseg[b]);
+    const size_t distinct = size_t(pl->distinct), bytes = 2 * en_context_bytes(pool, pl);
+    if (pool->d.dtype != EN_BF16 || pool->d.head_dim != 128)
+        return false;
+    return n_sel >= 2 * distinct ? bytes >= EN_GATHER_HUGE_BYTES
+                                 : 2 * n_sel >= 3 * distinct && bytes >= EN_GATHER_HUGE_BYTES / 3 * 4;
+}
+
+// EnGatherArgs::order of a plan. A tile belongs to the segment of its first token. The tiles of all agents that
+// belong to the same group come one after the other, in the list of one XCD.
+static void gather_order(en_plan *pl)
+{
+    const en_pool *pool = pl->pool;
+    const int sstr = std::max(pl->Smax, 1);
+    pl->order_shift = pl->max_len > 2 * EN_KEY_TILE ? 2 : pl->max_len > EN_KEY_TILE ? 1 : 0;
+    const int most = 1 << pl->order_shift;           // tiles per entry
+    // the (agent, segment) pairs sorted by group, the new tokens (group number G) last
+    const int G = pool->d.n_groups;
+    std::vector<int32_t> first(size_t(G) + 2, 0);
+    size_t n = 0;
+    for (int b = 0; b < pl->B; ++b) {
+        for (int s = 0; s < pl->nseg[b]; ++s)
+            ++first[pl->sel[size_t(b) * sstr + s] + 1];
+        ++first[G + 1];
+        n += size_t(pl->nseg[b]) + 1;
+    }
+    for (int g = 0; g <= G; ++g)
+        first[g + 1] += first[g];
+    std::vector<std::pair<int32_t, int32_t>> by_group(n);
+    for (int b = 0; b < pl->B; ++b)
+        for (int s = 0; s <= pl->nseg[b]; ++s)
+            by_group[first[s < pl->nseg[b] ? pl->sel[size_t(b) * sstr + s] : G]++] = {b, s};
+    // (first[g] is now the end of group g)
+    std::vector<int32_t> lists[EN_XCDS];
+    size_t at = 0;
+    for (int g = 0; g <= G; ++g) {
+        int x = 0;                                   // the shortest list
+        for (int i = 1; i < EN_XCDS; ++i)
+            if (lists[i].size() < lists[x].size())
+                x = i;
+        for (int piece = 0, more = 1; more; ++piece) {
+            more = 0;
+            for (size_t i = at; i < size_t(first[g]); ++i) {
+                const int b = by_group[i].first;
+                const int32_t *bnd = &pl->bnd[size_t(b) * (pl->Smax + 2) + by_group[i].second];
+                const int t0 = (bnd[0] + EN_KEY_TILE - 1) / EN_KEY_TILE + piece * most;
+                const int t1 = (bnd[1] + EN_KEY_TILE - 1) / EN_KEY_TILE;
+                if (t0 >= t1)
+                    continue;
+                lists[x].push_back(b);
+                lists[x].push_back(t0 << 2 | (std::min(most, t1 - t0) - 1));
+                more |= t1 - t0 > most;
+            }
+            if (g == G)                              // new tokens are shared with nobody
+                x = (x + 1) % EN_XCDS;
+        }
+        at = first[g];
+    }
+    size_t longest = 0;
+    for (const auto &l : lists)
+        longest = std::max(longest, l.size() / 2);
+    pl->order.assign(longest * EN_XCDS * 2, -1);
+    for (int x = 0; x < EN_XCDS; ++x)
+        for (size_t k = 0; 2 * k < lists[x].size(); ++k) {
+            pl->order[(k * EN_XCDS + x) * 2] = lists[x][2 * k];
+            pl->order[(k * EN_XCDS + x) * 2 + 1] = lists[x][2 * k + 1];
+        }
+}
+
 // Device block of a plan (taken from the pool's cache of released blocks when
 // one fits) and its host image. With inline_ok the upload is left to the
 // gather kernel, which receives the image in its arguments, provided it is
@@ -567,7 +659,11 @@ static int plan_ensure_device(en_plan *pl, hipStream_t stream, bool inline_ok = 
         *inlined = false;
     if (pl->uploaded)
         return EN_OK;
-    const size_t n = pl->nseg.size() + pl->sel.size() + pl->bnd.size() + pl->hdr.size();
+    size_t n = pl->nseg.size() + pl->sel.size() + pl->bnd.size() + pl->hdr.size();
+    const bool inline_it = inline_ok && n <= size_t(EN_INLINE_DESC_MAX);
+    if (n > size_t(EN_INLINE_DESC_MAX) && gather_in_order(pl))
+        gather_order(pl);
+    n += pl->order.size();
     pl->acc_off = (n + 1) & ~size_t(1);                                   // 8-byte aligned
     const size_t n_all = pl->acc_off + 2 * size_t(pl->B) * (pl->Smax + 1);    // tables, then the accumulators
     const size_t bytes = n_all * sizeof(int32_t);
@@ -577,6 +673,7 @@ static int plan_ensure_device(en_plan *pl, hipStream_t stream, bool inline_ok = 
     pl->h_desc.insert(pl->h_desc.end(), pl->sel.begin(), pl->sel.end());
     pl->h_desc.insert(pl->h_desc.end(), pl->bnd.begin(), pl->bnd.end());
     pl->h_desc.insert(pl->h_desc.end(), pl->hdr.begin(), pl->hdr.end());
+    pl->h_desc.insert(pl->h_desc.end(), pl->order.begin(), pl->order.end());
     hipError_t e;
     auto &cache = pl->pool->desc_cache;
     for (size_t i = 0; i < cache.size(); ++i)
@@ -592,7 +689,7 @@ static int plan_ensure_device(en_plan *pl, hipStream_t stream, bool inline_ok = 
             return hip_fail(e, "hipMalloc(plan descriptors)");
         pl->d_desc_bytes = cap;
     }
-    if (inline_ok && n <= size_t(EN_INLINE_DESC_MAX)) {
+    if (inline_it) {
         *inlined = true;              // (the launch also sets the accumulators to zero)
     } else {
         pl->h_desc.resize(n_all, 0);
@@ -609,6 +706,7 @@ static inline const int32_t *d_nseg(const en_plan *pl) { return pl->d_desc; }
 static inline const int32_t *d_sel(const en_plan *pl) { return d_nseg(pl) + pl->nseg.size(); }
 static inline const int32_t *d_bnd(const en_plan *pl) { return d_sel(pl) + pl->sel.size(); }
 static inline const int32_t *d_hdr(const en_plan *pl) { return d_bnd(pl) + pl->bnd.size(); }
+static inline const int32_t *d_order(const en_plan *pl) { return d_hdr(pl) + pl->hdr.size(); }
 
 // ---------------------------------------------------------------------------
 // sizes
@@ -836,6 +934,11 @@ static int gather_common(en_pool *pool, en_plan *plan, const void *k_new_dev, co
     a.nseg = d_nseg(plan);
     a.sel = d_sel(plan);
     a.bnd = d_bnd(plan);
+    a.order = plan->order.empty() ? nullptr : d_order(plan);
+    a.order_shift = plan->order_shift;
+    g.ahead = computes_bf16(pool->d.dtype) && pool->d.head_dim == 128 &&
+              (a.order || 2 * en_context_bytes(pool, plan) < EN_GATHER_HUGE_BYTES);
+    g.order_grid = int(plan->order.size() / 2) << plan->order_shift;
     a.B = plan->B;
     a.Hkv = pool->d.n_kv_heads;
     a.C = pool->d.capacity;
@@ -853,7 +956,7 @@ static int gather_common(en_pool *pool, en_plan *plan, const void *k_new_dev, co
     }
     a.scale_log2e = softmax_scale_log2e(pool);
     a.v_rows = plan->values_from_pool ? 1 : 0;
-    a.stream = 2 * en_context_bytes(pool, plan) > EN_LAST_LEVEL_CACHE_BYTES ? 1 : 0;
+    a.stream = gather_past_caches(pool, plan) ? 1 : 0;
     if (a.v_rows && (reinterpret_cast<uintptr_t>(v_new_dev) & uintptr_t(2 * pool->d.head_dim - 1)))
         return fail(EN_ERR_INVALID_ARG, "gather_rope: with the values taken from where they are "
                     "(en_plan_values_from_pool) the new tokens' values must be aligned to a row (%d bytes)",

@@ -13,6 +13,8 @@
 #include "efficientnav.h"
 
 constexpr size_t EN_LAST_LEVEL_CACHE_BYTES = size_t(256) << 20;
+constexpr size_t EN_GATHER_HUGE_BYTES = 3 * EN_LAST_LEVEL_CACHE_BYTES;      // of a context's keys and values
+constexpr int EN_XCDS = 8;         // dies of the chip, each with an L2 of its own; workgroups are dealt out over them in turn
 constexpr int EN_KEY_TILE = 64;    // keys per attention tile; context rows are padded to it
 constexpr int EN_ROWS_PER_WAVE = 32;
 constexpr int EN_WAVES = 8;          // waves per attention workgroup
@@ -50,7 +52,12 @@ struct en_plan {
     std::vector<int32_t> sel;     // [B, Smax]   (-1 padded)
     std::vector<int32_t> bnd;     // [B, Smax+2] bucket bounds: offset[0..S], then L_c+N_q
     std::vector<int32_t> hdr;     // [B, 4] S, L_c, L_c+N_q, 0: what a workgroup needs first, in one load
-    // device block: nseg | sel | bnd | hdr, created on first GPU use
+    // EnGatherArgs::order, or empty; its entries are up to 1 << order_shift tiles
+    std::vector<int32_t> order;
+    int order_shift = 0;
+    int distinct = 0;             // groups that at least one agent selects
+    int max_len = 0;              // of a selected group
+    // device block: nseg | sel | bnd | hdr | order, created on first GPU use
     int32_t *d_desc = nullptr;
     size_t d_desc_bytes = 0;
     std::vector<int32_t> h_desc;  // staging copy, alive as long as the plan
@@ -87,6 +94,11 @@ struct EnGatherArgs {
     // pool or the new tokens, [B, Hkv, T], and behind that table one row of zeros, which the
     // padding rows of an agent's last tile point at.
     int v_rows;
+    // Order in which the tiles are gathered, or null (tile by tile along x, agent by agent along z): entries
+    // {agent, first tile << 2 | tiles - 1} (agent -1: none) in lists per XCD, list X at X, X + EN_XCDS, ...
+    const int32_t *order;
+    int order_shift;
+    int rope_unit;         // en_rope_unit
     // 1: the context is written past the caches (non-temporal stores). Contexts beyond the 256 MB of the
     // last-level cache are not there any more when the attention kernel comes to read them, and its lines
     // in the way cost the gather 3 % (64 agents x 16 K tokens, 4.3 GB: 1473 -> 1438 us); a smaller one is
@@ -116,6 +128,13 @@ struct EnGatherLaunch {
     int n_inline;           // ints of `desc` in use, 0: read the device block
     int n_zero;             // ints to set to zero behind them in the device block (the plan's accumulators)
     int off_nseg, off_sel, off_bnd;   // int offsets of the three tables in the block
+    int order_grid;         // with a.order: workgroups along x
+    // 1: a workgroup takes the keys, or the values, of several heads with the next heads' loads on their way (bf16 rows
+    // of 128 values). Gather and attention, us, without / with: 194 tiles of 8 heads 57.7 / 51.8, 390: 86.8 / 78.5, 528:
+    // 133 / 128. Not where a context of three times the last-level cache and more is gathered agent by agent: 16
+    // agents x 12 K tokens 433 / 445, 64 x 6 K 832 / 850, 64 x 16 K 2173 / 2217 (in order, see gather_in_order: 1806).
+    // Rows of 64 values: 64 agents x 16 K tokens 797 / 817.
+    int ahead;
     int32_t *desc_out;      // device block to fill when n_inline > 0
     int32_t desc[EN_INLINE_DESC_MAX];
 };

@@ -1,0 +1,73 @@
+"""Gathers whose workgroups take several heads one after the other, and long contexts of agents that share groups, whose
+tiles are gathered in the order of the groups: bit for bit the contexts of the agents gathered one by one."""
+import numpy as np
+import pytest
+
+from paper_2510_18546_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def make(agents, kv, groups, cap, lo, hi, picks, n_new, seed=5, ratio=8, d=128):
+    import torch
+    rng = np.random.default_rng(seed)
+    gen = torch.Generator(device="cuda:0").manual_seed(seed)
+    lens = rng.integers(lo, hi + 1, groups).astype(np.int32)
+    lens[:: 7] = 0
+    k, v = (torch.randn((groups, kv, cap, d), device="cuda:0", generator=gen).to(torch.bfloat16) for _ in range(2))
+    # agents of different numbers of groups, one of them without any
+    sel = [rng.choice(groups, 0 if b == 1 else int(rng.integers(picks // 2, picks + 1)), replace=False).astype(np.int32)
+           for b in range(agents)]
+    k_new, v_new = (torch.randn((agents, n_new, kv, d), device="cuda:0", generator=gen).to(torch.bfloat16) for _ in range(2))
+    q = torch.randn((agents, n_new, kv * ratio, d), device="cuda:0", generator=gen).to(torch.bfloat16)
+    pool = B.kv_pool_create(k, v, lens, kv * ratio, 5e5, picks * cap + n_new)
+    return pool, lens, sel, k_new, v_new, q
+
+
+def gather(pool, sel, k_new, v_new, q, from_pool):
+    import torch
+    plan = B.segment_select(pool, np.concatenate(sel), np.cumsum([0] + [len(x) for x in sel]), k_new.shape[1])
+    if from_pool:
+        plan.values_from_pool(True)
+    kc, vt = B.alloc_context(pool, plan)
+    kc, vt = kc.view(torch.int16).fill_(7), vt.view(torch.int16).fill_(7)
+    q_prep = torch.empty_like(q)
+    B.gather_rope_queries(pool, plan, k_new, v_new, q, kc, vt, q_prep)
+    return plan, kc, vt, q_prep
+
+
+# 2 x 2 bytes x 128 x heads x tokens of the agents: 900 MB and more, in order; the last three below the line
+@pytest.mark.parametrize("agents,kv,groups,cap,lo,hi,picks,n_new,from_pool", [
+    (24, 8, 60, 256, 200, 256, 50, 5, False), (24, 8, 60, 256, 200, 256, 50, 130, True),
+    (40, 3, 90, 512, 300, 512, 48, 70, False), (100, 1, 80, 1000, 500, 1000, 70, 5, False),
+    (130, 8, 130, 32, 1, 32, 120, 64, False), (25, 8, 30, 70, 30, 70, 20, 129, False),
+    (4, 8, 64, 130, 60, 130, 40, 100, False), (3, 2, 40, 64, 10, 64, 33, 17, False)])
+def test_same_contexts_as_one_by_one(agents, kv, groups, cap, lo, hi, picks, n_new, from_pool):
+    import torch
+    pool, lens, sel, k_new, v_new, q = make(agents, kv, groups, cap, lo, hi, picks, n_new)
+    plan, kc, vt, q_prep = gather(pool, sel, k_new, v_new, q, from_pool)
+    T = plan.info.ctx_stride
+    kc = kc.view(agents, kv, T, 128)
+    table = vt.view(torch.int64)[:agents * kv * T].view(agents, kv, T) if from_pool else None
+    vt = vt[:agents * kv * 128 * T].view(agents, kv, 128, T)
+    for b in range(agents):
+        p1, k1, v1, q1 = gather(pool, [sel[b]], k_new[b:b + 1], v_new[b:b + 1], q[b:b + 1], False)
+        t1 = p1.info.ctx_stride
+        k1, v1 = k1.view(kv, t1, 128), v1.view(kv, 128, t1)
+        assert torch.equal(kc[b, :, :t1], k1), b
+        assert bool((kc[b, :, t1:] == 7).all()), b
+        assert torch.equal(q_prep[b:b + 1].view(torch.int16), q1.view(torch.int16)), b
+        if not from_pool:
+            assert torch.equal(vt[b, :, :, :t1], v1), b
+            assert bool((vt[b, :, :, t1:] == 7).all()), b
+            continue
+        # the table of row addresses: the pool's rows, then the new tokens' rows, then one and the same row
+        at = [pool.v.data_ptr() + 256 * ((int(g) * kv + h) * cap + t) for h in range(kv) for g in sel[b] for t in range(lens[g])]
+        at = np.array(at, np.int64).reshape(kv, -1)
+        new = np.array([[v_new.data_ptr() + 256 * ((b * n_new + i) * kv + h) for i in range(n_new)] for h in range(kv)], np.int64)
+        want = np.concatenate([at, new], 1)
+        got = table[b, :, :t1].cpu().numpy()
+        np.testing.assert_array_equal(got[:, :want.shape[1]], want)
+        assert len(np.unique(got[:, want.shape[1]:])) <= 1
+        p1.close()
+    plan.close()
