@@ -456,7 +456,7 @@ __device__ __forceinline__ EnCtxLoc context_loc(const EnGatherArgs &a, const EnG
     return {1, ((size_t)g * a.Hkv + kvh) * a.C + (tok - bnd[s])};
 }
 
-template <int D>
+template <int D, bool STREAM>
 __device__ __forceinline__ void gather_q8_k_rows(const EnGatherArgs &a, const EnGatherTables &tabs, int tok, int kvh,
                                                  int32_t *lds)
 {
@@ -495,20 +495,20 @@ __device__ __forceinline__ void gather_q8_k_rows(const EnGatherArgs &a, const En
         const fvec sn = *reinterpret_cast<const fvec *>(a.sin_tab + (size_t)tok * (D / 2) + c * E);
         rope_key_pair<true>(x1, x2, cs, sn, y1, y2);
     }
-    *reinterpret_cast<tvec *>(dst + c * E) = __builtin_convertvector(y1, tvec);
-    *reinterpret_cast<tvec *>(dst + D / 2 + c * E) = __builtin_convertvector(y2, tvec);
+    store_context<STREAM>(dst + c * E, __builtin_convertvector(y1, tvec));
+    store_context<STREAM>(dst + D / 2 + c * E, __builtin_convertvector(y2, tvec));
 }
 
-template <int D>
+template <int D, bool STREAM>
 __device__ __forceinline__ void gather_q8_k_block(const EnGatherArgs &a, int tile, int kvh, int32_t *lds)
 {
     const EnGatherTables tabs = stage_tables(a, blockIdx.z, lds);
 #pragma unroll 1
     for (int half = 0; half < 2; ++half)
-        gather_q8_k_rows<D>(a, tabs, tile * EN_KEY_TILE + half * 32 + threadIdx.x / 8, kvh, lds);
+        gather_q8_k_rows<D, STREAM>(a, tabs, tile * EN_KEY_TILE + half * 32 + threadIdx.x / 8, kvh, lds);
 }
 
-template <int D>
+template <int D, bool STREAM>
 __device__ __forceinline__ void gather_q8_vt_block(const EnGatherArgs &a, int bx, int kvh, int32_t *lds)
 {
     constexpr int STR = D + 2;                 // LDS row stride in elements
@@ -568,16 +568,16 @@ __device__ __forceinline__ void gather_q8_vt_block(const EnGatherArgs &a, int bx
             const int tk = 16 * g16 + 8 * (e >> 2) + 4 * hf + (e & 3);
             v[e] = tile[tk * STR + d];
         }
-        uint4 o;
-        o.x = v[0] | ((uint32_t)v[1] << 16);
-        o.y = v[2] | ((uint32_t)v[3] << 16);
-        o.z = v[4] | ((uint32_t)v[5] << 16);
-        o.w = v[6] | ((uint32_t)v[7] << 16);
-        *reinterpret_cast<uint4 *>(vt + (size_t)d * a.T + ch * 8) = o;
+        u32x4 o;
+        o[0] = v[0] | ((uint32_t)v[1] << 16);
+        o[1] = v[2] | ((uint32_t)v[3] << 16);
+        o[2] = v[4] | ((uint32_t)v[5] << 16);
+        o[3] = v[6] | ((uint32_t)v[7] << 16);
+        store_context<STREAM>(reinterpret_cast<u32x4 *>(vt + (size_t)d * a.T + ch * 8), o);
     }
 }
 
-template <int D>
+template <int D, bool STREAM>
 __global__ __launch_bounds__(256) void gather_q8_kernel(EnGatherLaunch g)
 {
     EnGatherArgs a = g.a;
@@ -602,9 +602,9 @@ __global__ __launch_bounds__(256) void gather_q8_kernel(EnGatherLaunch g)
         return;
     const int tile = blockIdx.x, kvh = unit / 2;
     if (unit % 2 == 0)
-        gather_q8_k_block<D>(a, tile, kvh, ltab);
+        gather_q8_k_block<D, STREAM>(a, tile, kvh, ltab);
     else
-        gather_q8_vt_block<D>(a, tile, kvh, ltab);
+        gather_q8_vt_block<D, STREAM>(a, tile, kvh, ltab);
 }
 
 // ---------------------------------------------------------------------------
@@ -803,10 +803,14 @@ int en_launch_gather(const en_pool *pool, EnGatherLaunch &g, int max_ctx_len, vo
     const int D = pool->d.head_dim;
     if (pool->d.dtype == EN_I8) {
         const dim3 grid(n_tiles, 2 * a.Hkv + (a.q ? a.n_q_units : 0), a.B), blk(256);
-        if (D == 64)
-            hipLaunchKernelGGL((gather_q8_kernel<64>), grid, blk, 0, st, g);
+        if (D == 64 && a.stream)
+            hipLaunchKernelGGL((gather_q8_kernel<64, true>), grid, blk, 0, st, g);
+        else if (D == 64)
+            hipLaunchKernelGGL((gather_q8_kernel<64, false>), grid, blk, 0, st, g);
+        else if (a.stream)
+            hipLaunchKernelGGL((gather_q8_kernel<128, true>), grid, blk, 0, st, g);
         else
-            hipLaunchKernelGGL((gather_q8_kernel<128>), grid, blk, 0, st, g);
+            hipLaunchKernelGGL((gather_q8_kernel<128, false>), grid, blk, 0, st, g);
         return (int)hipGetLastError();
     }
     const bool bf16 = pool->d.dtype != EN_F32;

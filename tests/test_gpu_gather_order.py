@@ -71,3 +71,34 @@ def test_same_contexts_as_one_by_one(agents, kv, groups, cap, lo, hi, picks, n_n
         assert len(np.unique(got[:, want.shape[1]:])) <= 1
         p1.close()
     plan.close()
+
+
+# 8-bit pools: contexts of 300 MB go past the caches (the last one does not)
+@pytest.mark.parametrize("agents,kv,d,cap,n_new", [(9, 8, 128, 130, 70), (17, 2, 128, 256, 1), (18, 6, 64, 200, 33),
+                                                   (25, 3, 128, 130, 70), (2, 8, 128, 100, 40)])
+def test_same_contexts_from_8_bit_pools(agents, kv, d, cap, n_new):
+    import torch
+    rng = np.random.default_rng(agents)
+    gen = torch.Generator(device="cuda:0").manual_seed(agents)
+    groups, picks = 140, 90
+    lens = rng.integers(cap - 30, cap + 1, groups).astype(np.int32)
+    lens[::9] = 0
+    k, v = (torch.randint(-127, 128, (groups, kv, cap, d), dtype=torch.int8, device="cuda:0", generator=gen) for _ in range(2))
+    scales = [torch.rand((groups, kv, cap), device="cuda:0", generator=gen) + 0.01 for _ in range(2)]
+    k_new, v_new = (torch.randn((agents, n_new, kv, d), device="cuda:0", generator=gen).to(torch.bfloat16) for _ in range(2))
+    q = torch.randn((agents, n_new, kv, d), device="cuda:0", generator=gen).to(torch.bfloat16)
+    pool = B.kv_pool_create(k, v, lens, kv, 1e4, picks * cap + n_new)
+    B.kv_pool_set_scales(pool, *scales)
+    sel = [rng.choice(groups, 0 if b == 1 else picks - b % 3, replace=False).astype(np.int32) for b in range(agents)]
+    plan, kc, vt, q_prep = gather(pool, sel, k_new, v_new, q, False)
+    T = plan.info.ctx_stride
+    kc, vt = kc.view(agents, kv, T, d), vt.view(agents, kv, d, T)
+    for b in range(agents):
+        p1, k1, v1, q1 = gather(pool, [sel[b]], k_new[b:b + 1], v_new[b:b + 1], q[b:b + 1], False)
+        t1 = p1.info.ctx_stride
+        assert torch.equal(kc[b, :, :t1], k1.view(kv, t1, d)), b
+        assert torch.equal(vt[b, :, :, :t1], v1.view(kv, d, t1)), b
+        assert torch.equal(q_prep[b:b + 1].view(torch.int16), q1.view(torch.int16)), b
+        assert bool((kc[b, :, t1:] == 7).all()) and bool((vt[b, :, :, t1:] == 7).all()), b
+        p1.close()
+    plan.close()
