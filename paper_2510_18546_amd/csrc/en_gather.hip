@@ -432,7 +432,7 @@ __global__ __launch_bounds__(256) void gather_kernel(EnGatherLaunch g)
 // gather from an 8-bit pool: the same bf16 contexts as above from rows of int8
 // codes with one float scale per (group, head, token): value = code * scale in
 // float32, keys rotated, everything rounded to bf16 once. New tokens arrive in
-// bf16 as ever. grid as for the bf16 gather.
+// bf16 as ever. grid as for the bf16 gather, the units by gather_heads_q8.
 // ---------------------------------------------------------------------------
 struct EnCtxLoc {
     int kind;        // 0 padding, 1 row of the pool, 2 row of the new tokens
@@ -456,66 +456,90 @@ __device__ __forceinline__ EnCtxLoc context_loc(const EnGatherArgs &a, const EnG
     return {1, ((size_t)g * a.Hkv + kvh) * a.C + (tok - bnd[s])};
 }
 
-template <int D, bool STREAM>
-__device__ __forceinline__ void gather_q8_k_rows(const EnGatherArgs &a, const EnGatherTables &tabs, int tok, int kvh,
-                                                 int32_t *lds)
+// The key rows of HPB heads, kv0 onwards: where the row comes from, its cosines and sines once for all of them, and
+// the codes of all of them on their way before the first are turned and stored.
+template <int D, int HPB, bool STREAM>
+__device__ __forceinline__ void gather_q8_k_rows(const EnGatherArgs &a, const EnGatherTables &tabs, int b, int tok,
+                                                 int kv0, int32_t *lds)
 {
     constexpr int E = D / 16;
-    const int b = blockIdx.z;
     const int c = threadIdx.x % 8;
     const int S = a.nseg[b];
     const int Ltot = tabs.staged ? lds[S + 1] : tabs.bnd[S + 1];
     const int Lpad = (Ltot + EN_KEY_TILE - 1) / EN_KEY_TILE * EN_KEY_TILE;
     if (tok >= Lpad)
         return;
-    bf16_t *dst = (bf16_t *)a.kc + (((size_t)b * a.Hkv + kvh) * a.T + tok) * D;
     typedef bf16_t tvec __attribute__((ext_vector_type(E)));
     typedef float fvec __attribute__((ext_vector_type(E)));
-    const EnCtxLoc loc = context_loc(a, tabs, lds, b, kvh, tok);
-    fvec x1 = 0.f, x2 = 0.f;
-    if (loc.kind == 1) {
-        const int8_t *src = (const int8_t *)a.k_pool + loc.row * D;
-        const float sc = a.k_scale[loc.row];
-        int8_t c1[E], c2[E];
-        __builtin_memcpy(c1, src + c * E, E);
-        __builtin_memcpy(c2, src + D / 2 + c * E, E);
+    auto store = [&](int h, fvec y1, fvec y2) {
+        bf16_t *dst = (bf16_t *)a.kc + (((size_t)b * a.Hkv + kv0 + h) * a.T + tok) * D;
+        store_context<STREAM>(dst + c * E, __builtin_convertvector(y1, tvec));
+        store_context<STREAM>(dst + D / 2 + c * E, __builtin_convertvector(y2, tvec));
+    };
+    const EnCtxLoc loc = context_loc(a, tabs, lds, b, kv0, tok);
+    if (loc.kind == 0) {
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-            x1[e] = (float)c1[e] * sc;
-            x2[e] = (float)c2[e] * sc;
+        for (int h = 0; h < HPB; ++h)
+            store(h, 0.f, 0.f);
+        return;
+    }
+    const fvec cs = *reinterpret_cast<const fvec *>(a.cos_tab + (size_t)tok * (D / 2) + c * E);
+    const fvec sn = *reinterpret_cast<const fvec *>(a.sin_tab + (size_t)tok * (D / 2) + c * E);
+    if (loc.kind == 1) {
+        int8_t c1[HPB][E], c2[HPB][E];
+        float sc[HPB];
+#pragma unroll
+        for (int h = 0; h < HPB; ++h) {
+            const size_t row = loc.row + (size_t)h * a.C;
+            const int8_t *src = (const int8_t *)a.k_pool + row * D;
+            __builtin_memcpy(c1[h], src + c * E, E);
+            __builtin_memcpy(c2[h], src + D / 2 + c * E, E);
+            sc[h] = a.k_scale[row];
         }
-    } else if (loc.kind == 2) {
-        const bf16_t *src = (const bf16_t *)a.k_new + loc.row * D;
-        x1 = __builtin_convertvector(*reinterpret_cast<const tvec *>(src + c * E), fvec);
-        x2 = __builtin_convertvector(*reinterpret_cast<const tvec *>(src + D / 2 + c * E), fvec);
+        if constexpr (HPB > 1)
+            asm volatile("" ::: "memory");             // (not behind the stores)
+#pragma unroll
+        for (int h = 0; h < HPB; ++h) {
+            fvec x1, x2, y1, y2;
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                x1[e] = (float)c1[h][e] * sc[h];
+                x2[e] = (float)c2[h][e] * sc[h];
+            }
+            rope_key_pair<true>(x1, x2, cs, sn, y1, y2);
+            store(h, y1, y2);
+        }
+    } else {
+#pragma unroll
+        for (int h = 0; h < HPB; ++h) {
+            const bf16_t *src = (const bf16_t *)a.k_new + (loc.row + h) * D;
+            const fvec x1 = __builtin_convertvector(*reinterpret_cast<const tvec *>(src + c * E), fvec);
+            const fvec x2 = __builtin_convertvector(*reinterpret_cast<const tvec *>(src + D / 2 + c * E), fvec);
+            fvec y1, y2;
+            rope_key_pair<true>(x1, x2, cs, sn, y1, y2);
+            store(h, y1, y2);
+        }
     }
-    fvec y1 = 0.f, y2 = 0.f;
-    if (loc.kind != 0) {
-        const fvec cs = *reinterpret_cast<const fvec *>(a.cos_tab + (size_t)tok * (D / 2) + c * E);
-        const fvec sn = *reinterpret_cast<const fvec *>(a.sin_tab + (size_t)tok * (D / 2) + c * E);
-        rope_key_pair<true>(x1, x2, cs, sn, y1, y2);
-    }
-    store_context<STREAM>(dst + c * E, __builtin_convertvector(y1, tvec));
-    store_context<STREAM>(dst + D / 2 + c * E, __builtin_convertvector(y2, tvec));
 }
 
-template <int D, bool STREAM>
-__device__ __forceinline__ void gather_q8_k_block(const EnGatherArgs &a, int tile, int kvh, int32_t *lds)
+template <int D, int HPB, bool STREAM>
+__device__ __forceinline__ void gather_q8_k_block(const EnGatherArgs &a, int b, int tile, int kv0, int32_t *lds)
 {
-    const EnGatherTables tabs = stage_tables(a, blockIdx.z, lds);
+    const EnGatherTables tabs = stage_tables(a, b, lds);
 #pragma unroll 1
     for (int half = 0; half < 2; ++half)
-        gather_q8_k_rows<D, STREAM>(a, tabs, tile * EN_KEY_TILE + half * 32 + threadIdx.x / 8, kvh, lds);
+        gather_q8_k_rows<D, HPB, STREAM>(a, tabs, b, tile * EN_KEY_TILE + half * 32 + threadIdx.x / 8, kv0, lds);
 }
 
-template <int D, bool STREAM>
-__device__ __forceinline__ void gather_q8_vt_block(const EnGatherArgs &a, int bx, int kvh, int32_t *lds)
+// The transposed values of a tile for HPB heads, kv0 onwards, one after the other, the next head's loads on their way
+// meanwhile.
+template <int D, int HPB, bool STREAM>
+__device__ __forceinline__ void gather_q8_vt_block(const EnGatherArgs &a, int b, int bx, int kv0, int32_t *lds)
 {
     constexpr int STR = D + 2;                 // LDS row stride in elements
     __shared__ uint16_t tile[EN_KEY_TILE * STR];
     __shared__ size_t rows[EN_KEY_TILE];
     __shared__ int kinds[EN_KEY_TILE];
-    const int b = blockIdx.z;
     const int t0 = bx * EN_KEY_TILE;
     const int S = a.nseg[b];
     const EnGatherTables tabs = stage_tables(a, b, lds);
@@ -523,61 +547,93 @@ __device__ __forceinline__ void gather_q8_vt_block(const EnGatherArgs &a, int bx
     if (t0 >= Ltot)                            // the same for the whole block
         return;
     if (threadIdx.x < EN_KEY_TILE) {
-        const EnCtxLoc loc = context_loc(a, tabs, lds, b, kvh, t0 + threadIdx.x);
+        const EnCtxLoc loc = context_loc(a, tabs, lds, b, kv0, t0 + threadIdx.x);
         rows[threadIdx.x] = loc.row;
         kinds[threadIdx.x] = loc.kind;
     }
     __syncthreads();
     typedef bf16_t bvec __attribute__((ext_vector_type(8)));
     typedef float fvec8 __attribute__((ext_vector_type(8)));
-    constexpr int CH = D / 8;                  // chunks of 8 elements per token
-    for (int idx = threadIdx.x; idx < EN_KEY_TILE * CH; idx += 256) {
-        const int tk = idx / CH, ch = idx % CH;
-        bvec v = {0, 0, 0, 0, 0, 0, 0, 0};
-        if (kinds[tk] == 1) {
-            const int8_t *src = (const int8_t *)a.v_pool + rows[tk] * D + ch * 8;
-            const float sc = a.v_scale[rows[tk]];
-            int8_t cd[8];
-            __builtin_memcpy(cd, src, 8);
-            fvec8 f;
+    // D/8 chunks of 8 elements per token, NC of them per thread
+    constexpr int CH = D / 8, NC = EN_KEY_TILE * CH / 256;
+    const int tk0 = threadIdx.x / CH, ch0 = threadIdx.x % CH;
+    int kind[NC];
+    size_t row[NC];
+    uint4 raw[NC];                             // 8 codes, or 8 values of a new token
+    float sc[NC];
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
-                f[e] = (float)cd[e] * sc;
-            v = __builtin_convertvector(f, bvec);
-        } else if (kinds[tk] == 2) {
-            v = *reinterpret_cast<const bvec *>((const bf16_t *)a.v_new + rows[tk] * D + ch * 8);
-        }
-        uint4 raw;
-        __builtin_memcpy(&raw, &v, 16);
-        uint16_t *d = &tile[tk * STR + ch * 8];
-        // STR is even but not a multiple of 8: store as 4 dwords
-        reinterpret_cast<uint32_t *>(d)[0] = raw.x;
-        reinterpret_cast<uint32_t *>(d)[1] = raw.y;
-        reinterpret_cast<uint32_t *>(d)[2] = raw.z;
-        reinterpret_cast<uint32_t *>(d)[3] = raw.w;
+    for (int i = 0; i < NC; ++i) {
+        kind[i] = kinds[tk0 + i * (256 / CH)];
+        row[i] = rows[tk0 + i * (256 / CH)];
     }
-    __syncthreads();
-    // store: for every d, 8 chunks of 8 columns (the same order as the bf16 gather)
-    uint16_t *vt = (uint16_t *)a.vt + ((size_t)b * a.Hkv + kvh) * D * (size_t)a.T + t0;
-    for (int idx = threadIdx.x; idx < D * 8; idx += 256) {
-        const int d = idx / 8, ch = idx % 8;      // columns ch*8 .. ch*8+7
-        const int g16 = ch / 2, hf = ch % 2;
-        uint16_t v[8];
+    auto load = [&] {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int tk = 16 * g16 + 8 * (e >> 2) + 4 * hf + (e & 3);
-            v[e] = tile[tk * STR + d];
+        for (int i = 0; i < NC; ++i) {
+            if (kind[i] == 1) {
+                __builtin_memcpy(&raw[i], (const int8_t *)a.v_pool + row[i] * D + ch0 * 8, 8);
+                sc[i] = a.v_scale[row[i]];
+                row[i] += a.C;
+            } else if (kind[i] == 2) {
+                raw[i] = *reinterpret_cast<const uint4 *>((const bf16_t *)a.v_new + row[i] * D + ch0 * 8);
+                row[i] += 1;
+            }
         }
-        u32x4 o;
-        o[0] = v[0] | ((uint32_t)v[1] << 16);
-        o[1] = v[2] | ((uint32_t)v[3] << 16);
-        o[2] = v[4] | ((uint32_t)v[5] << 16);
-        o[3] = v[6] | ((uint32_t)v[7] << 16);
-        store_context<STREAM>(reinterpret_cast<u32x4 *>(vt + (size_t)d * a.T + ch * 8), o);
+    };
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+        raw[i] = make_uint4(0, 0, 0, 0);
+        sc[i] = 0.f;
+    }
+    load();
+    uint16_t *vt = (uint16_t *)a.vt + ((size_t)b * a.Hkv + kv0) * D * (size_t)a.T + t0;
+#pragma unroll 1
+    for (int h = 0; h < HPB; ++h, vt += D * (size_t)a.T) {
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            uint4 w = raw[i];
+            if (kind[i] == 1) {
+                int8_t cd[8];
+                __builtin_memcpy(cd, &raw[i], 8);
+                fvec8 f;
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    f[e] = (float)cd[e] * sc[i];
+                const bvec v = __builtin_convertvector(f, bvec);
+                __builtin_memcpy(&w, &v, 16);
+            }
+            uint16_t *d = &tile[(tk0 + i * (256 / CH)) * STR + ch0 * 8];
+            // STR is even but not a multiple of 8: store as 4 dwords
+            reinterpret_cast<uint32_t *>(d)[0] = w.x;
+            reinterpret_cast<uint32_t *>(d)[1] = w.y;
+            reinterpret_cast<uint32_t *>(d)[2] = w.z;
+            reinterpret_cast<uint32_t *>(d)[3] = w.w;
+        }
+        if (h + 1 < HPB)
+            load();
+        __syncthreads();
+        // store: for every d, 8 chunks of 8 columns (the same order as the bf16 gather)
+        for (int idx = threadIdx.x; idx < D * 8; idx += 256) {
+            const int d = idx / 8, ch = idx % 8;      // columns ch*8 .. ch*8+7
+            const int g16 = ch / 2, hf = ch % 2;
+            uint16_t v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int tk = 16 * g16 + 8 * (e >> 2) + 4 * hf + (e & 3);
+                v[e] = tile[tk * STR + d];
+            }
+            u32x4 o;
+            o[0] = v[0] | ((uint32_t)v[1] << 16);
+            o[1] = v[2] | ((uint32_t)v[3] << 16);
+            o[2] = v[4] | ((uint32_t)v[5] << 16);
+            o[3] = v[6] | ((uint32_t)v[7] << 16);
+            store_context<STREAM>(reinterpret_cast<u32x4 *>(vt + (size_t)d * a.T + ch * 8), o);
+        }
+        if (h + 1 < HPB)
+            __syncthreads();
     }
 }
 
-template <int D, bool STREAM>
+template <int D, int HPB, bool STREAM>
 __global__ __launch_bounds__(256) void gather_q8_kernel(EnGatherLaunch g)
 {
     EnGatherArgs a = g.a;
@@ -596,15 +652,16 @@ __global__ __launch_bounds__(256) void gather_q8_kernel(EnGatherLaunch g)
         }
     }
     __shared__ int32_t ltab[2 * EN_GATHER_TAB_LDS];       // bucket bounds, then selected groups
-    // the grid of gather_kernel with one head per key unit
+    // per HPB heads one key unit, one value unit
     int unit = blockIdx.y;
     if (a.q && query_unit<D, false>(a, unit))
         return;
-    const int tile = blockIdx.x, kvh = unit / 2;
+    const int tile = blockIdx.x, b = blockIdx.z;
+    const int kv0 = unit / 2 * HPB;
     if (unit % 2 == 0)
-        gather_q8_k_block<D, STREAM>(a, tile, kvh, ltab);
+        gather_q8_k_block<D, HPB, STREAM>(a, b, tile, kv0, ltab);
     else
-        gather_q8_vt_block<D, STREAM>(a, tile, kvh, ltab);
+        gather_q8_vt_block<D, HPB, STREAM>(a, b, tile, kv0, ltab);
 }
 
 // ---------------------------------------------------------------------------
@@ -795,6 +852,32 @@ static void launch_gather_kernel(int hpb, dim3 grid, hipStream_t st, const EnGat
         launch_gather_hpb<T, D, false, false>(hpb, grid, st, g);
 }
 
+// Heads per unit of the gather from 8-bit pools: four where the context goes past the caches and the launch is many
+// rounds of workgroups, two from 16 (tile, head) units per compute unit on (about two rounds), one below. Gather and
+// attention, us, with one / two / four / eight heads: 64 agents x 16 K tokens 2316 / 2116 / 1984 / 1976, rows of 64
+// values 1233 / 1101 / 1044 / 1011, 32 x 6 K 430 / 406 / 399 / 409, 16 x 14 K 532 / 502 / 486 / 491; kept in the
+// caches 16 x 2 K (5100 units) 138.4 / 136.1 / 138.2 / 145.0, rows of 64 values 84.0 / 80.9 / 82.5 / 83.9; 3600 units
+// 56.5 / 57.5 / 56.7 / 61.0, 2200: 90.4 / 90.7 / 92.9 / 98.9, 450: 38.1 / 39.1 / 42.6 / 49.4.
+static int gather_heads_q8(const en_pool *pool, const EnGatherArgs &a, int n_tiles)
+{
+    int hpb = a.stream ? 4 : 2L * a.Hkv * n_tiles * a.B >= 16L * pool->n_cu ? 2 : 1;
+    while (a.Hkv % hpb)
+        hpb /= 2;
+    return hpb;
+}
+
+template <int D, bool STREAM>
+static void launch_gather_q8(int hpb, dim3 grid, hipStream_t st, const EnGatherLaunch &g)
+{
+    const dim3 blk(256);
+    if (hpb == 4)
+        hipLaunchKernelGGL((gather_q8_kernel<D, 4, STREAM>), grid, blk, 0, st, g);
+    else if (hpb == 2)
+        hipLaunchKernelGGL((gather_q8_kernel<D, 2, STREAM>), grid, blk, 0, st, g);
+    else
+        hipLaunchKernelGGL((gather_q8_kernel<D, 1, STREAM>), grid, blk, 0, st, g);
+}
+
 int en_launch_gather(const en_pool *pool, EnGatherLaunch &g, int max_ctx_len, void *stream)
 {
     const EnGatherArgs &a = g.a;
@@ -802,15 +885,16 @@ int en_launch_gather(const en_pool *pool, EnGatherLaunch &g, int max_ctx_len, vo
     const int n_tiles = (max_ctx_len + EN_KEY_TILE - 1) / EN_KEY_TILE;
     const int D = pool->d.head_dim;
     if (pool->d.dtype == EN_I8) {
-        const dim3 grid(n_tiles, 2 * a.Hkv + (a.q ? a.n_q_units : 0), a.B), blk(256);
+        const int hpb = gather_heads_q8(pool, a, n_tiles);
+        const dim3 grid(n_tiles, 2 * (a.Hkv / hpb) + (a.q ? a.n_q_units : 0), a.B);
         if (D == 64 && a.stream)
-            hipLaunchKernelGGL((gather_q8_kernel<64, true>), grid, blk, 0, st, g);
+            launch_gather_q8<64, true>(hpb, grid, st, g);
         else if (D == 64)
-            hipLaunchKernelGGL((gather_q8_kernel<64, false>), grid, blk, 0, st, g);
+            launch_gather_q8<64, false>(hpb, grid, st, g);
         else if (a.stream)
-            hipLaunchKernelGGL((gather_q8_kernel<128, true>), grid, blk, 0, st, g);
+            launch_gather_q8<128, true>(hpb, grid, st, g);
         else
-            hipLaunchKernelGGL((gather_q8_kernel<128, false>), grid, blk, 0, st, g);
+            launch_gather_q8<128, false>(hpb, grid, st, g);
         return (int)hipGetLastError();
     }
     const bool bf16 = pool->d.dtype != EN_F32;

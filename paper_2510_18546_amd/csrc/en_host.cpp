@@ -572,7 +572,8 @@ static bool gather_past_caches(const en_pool *pool, const en_plan *pl)
 // 6 K of 1.6 in groups of 96 tokens 896 / 860, 64 x 3 K of 4.1 in groups of 48 419 / 395. Not below EN_GATHER_HUGE_BYTES
 // (neighbouring tiles of an agent are then written far apart): 16 x 12 K tokens of 4 heads, 403 MB, 210 / 223; 16 x 5 K,
 // 335 MB, 201 / 208; 16 x 2 K, 134 MB, 125 / 147; where fewer than two agents share a group, only from 1 GiB on: 16 x
-// 12 K tokens of 1.6, 805 MB, 433 / 438. Nor for rows of 64 values: 791 / 896. Plans whose
+// 12 K tokens of 1.6, 805 MB, 433 / 438. Nor for rows of 64 values: 791 / 896; nor from 8-bit pools, which are half
+// the reading: 64 x 16 K of 4.1 1984 / 2104, 16 x 14 K of 5.1 493 / 538. Plans whose
 // tables travel in the launch's arguments stay as they are: the order would need a copy of its own.
 static bool gather_in_order(const en_plan *pl)
 {
@@ -936,7 +937,7 @@ static int gather_common(en_pool *pool, en_plan *plan, const void *k_new_dev, co
     a.bnd = d_bnd(plan);
     a.order = plan->order.empty() ? nullptr : d_order(plan);
     a.order_shift = plan->order_shift;
-    g.ahead = computes_bf16(pool->d.dtype) && pool->d.head_dim == 128 &&
+    g.ahead = pool->d.dtype == EN_BF16 && pool->d.head_dim == 128 &&
               (a.order || 2 * en_context_bytes(pool, plan) < EN_GATHER_HUGE_BYTES);
     g.order_grid = int(plan->order.size() / 2) << plan->order_shift;
     a.B = plan->B;

@@ -108,7 +108,7 @@ struct EnGatherArgs {
     // behind it gains more (together 1063 -> 1028, 358 -> 314). Plans that leave their values in the pool write
     // half as much, but the attention kernel then reads the pool's values beside the keys: the line is the same
     // one, twice the keys (9 agents x 8 K tokens, keys of 146 MB, gather and attention: 247 us kept in the caches,
-    // 241 past them; 12 agents 195 MB: 305, 297; 15 agents 243 MB: 337, 329). From 8-bit pools, gather and attention:
+    // 241 past them; 12 agents 195 MB: 305, 297; 15 agents 243 MB: 337, 329). From 8-bit pools, one head a workgroup:
     // 32 agents x 6 K tokens 501 -> 417, 16 x 14 K 582 -> 516, 64 x 16 K 2319 -> 2280, rows of 64 values 1220 -> 943.
     int stream;
 };

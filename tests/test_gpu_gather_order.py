@@ -73,9 +73,11 @@ def test_same_contexts_as_one_by_one(agents, kv, groups, cap, lo, hi, picks, n_n
     plan.close()
 
 
-# 8-bit pools: contexts of 300 MB go past the caches (the last one does not)
+# 8-bit pools: contexts of 300 MB go past the caches, four, two or one heads a workgroup; the last three do not (two heads
+# for the agents together, one for each by itself)
 @pytest.mark.parametrize("agents,kv,d,cap,n_new", [(9, 8, 128, 130, 70), (17, 2, 128, 256, 1), (18, 6, 64, 200, 33),
-                                                   (25, 3, 128, 130, 70), (2, 8, 128, 100, 40)])
+                                                   (25, 3, 128, 130, 70), (20, 4, 64, 200, 130),
+                                                   (2, 8, 128, 100, 40), (3, 6, 64, 130, 129), (2, 8, 64, 130, 1)])
 def test_same_contexts_from_8_bit_pools(agents, kv, d, cap, n_new):
     import torch
     rng = np.random.default_rng(agents)
@@ -93,6 +95,13 @@ def test_same_contexts_from_8_bit_pools(agents, kv, d, cap, n_new):
     plan, kc, vt, q_prep = gather(pool, sel, k_new, v_new, q, False)
     T = plan.info.ctx_stride
     kc, vt = kc.view(agents, kv, T, d), vt.view(agents, kv, d, T)
+    # the values of agent 0 are code x scale in float32, rounded once; token j in the column with its bits 2 and 3 exchanged
+    rows = torch.from_numpy(np.concatenate([g * cap + np.arange(lens[g]) for g in sel[0]])).cuda()
+    v0 = (v.float() * scales[1][..., None]).to(torch.bfloat16).transpose(0, 1).reshape(kv, groups * cap, d)[:, rows]
+    v0 = torch.cat([v0, v_new[0].transpose(0, 1)], 1)
+    j = torch.arange(v0.shape[1], device="cuda:0")
+    col = (j & ~12) | ((j & 4) << 1) | ((j & 8) >> 1)
+    assert torch.equal(vt[0][:, :, col], v0.transpose(1, 2).contiguous().view(torch.int16))
     for b in range(agents):
         p1, k1, v1, q1 = gather(pool, [sel[b]], k_new[b:b + 1], v_new[b:b + 1], q[b:b + 1], False)
         t1 = p1.info.ctx_stride
