@@ -856,7 +856,7 @@ static void launch_gather_kernel(int hpb, dim3 grid, hipStream_t st, const EnGat
 // rounds of workgroups, two from 16 (tile, head) units per compute unit on (about two rounds), one below. Gather and
 // attention, us, with one / two / four / eight heads: 64 agents x 16 K tokens 2316 / 2116 / 1984 / 1976, rows of 64
 // values 1233 / 1101 / 1044 / 1011, 32 x 6 K 430 / 406 / 399 / 409, 16 x 14 K 532 / 502 / 486 / 491; kept in the
-// caches 16 x 2 K (5100 units) 138.4 / 136.1 / 138.2 / 145.0, rows of 64 values 84.0 / 80.9 / 82.5 / 83.9; 3600 units
+// caches 16 x 2 K (9000 units) 138.4 / 136.1 / 138.2 / 145.0, rows of 64 values 84.0 / 80.9 / 82.5 / 83.9; 3600 units
 // 56.5 / 57.5 / 56.7 / 61.0, 2200: 90.4 / 90.7 / 92.9 / 98.9, 450: 38.1 / 39.1 / 42.6 / 49.4.
 static int gather_heads_q8(const en_pool *pool, const EnGatherArgs &a, int n_tiles)
 {
