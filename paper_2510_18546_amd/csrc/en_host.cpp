@@ -575,7 +575,7 @@ static bool gather_past_caches(const en_pool *pool, const en_plan *pl)
 // 12 K tokens of 1.6, 805 MB, 433 / 438. Nor for rows of 64 values: 791 / 896; nor from 8-bit pools, which are half
 // the reading: 64 x 16 K of 4.1 1984 / 2104, 16 x 14 K of 5.1 493 / 538. Plans whose
 // tables travel in the launch's arguments stay as they are: the order would need a copy of its own.
-static bool gather_in_order(const en_plan *pl)
+bool en_gather_in_order(const en_plan *pl)
 {
     const en_pool *pool = pl->pool;
     size_t n_sel = 0;
@@ -588,22 +588,36 @@ static bool gather_in_order(const en_plan *pl)
                                  : 2 * n_sel >= 3 * distinct && bytes >= EN_GATHER_HUGE_BYTES / 3 * 4;
 }
 
-// EnGatherArgs::order of a plan. A tile belongs to the segment of its first token. The tiles of all agents that
-// belong to the same group come one after the other, in the list of one XCD.
-static void gather_order(en_plan *pl)
+// EnGatherArgs::order of a plan. A tile belongs to the segment of its first token. What agents share is the same piece
+// of a group, up to four tiles of it, one entry for each agent: those of a piece come one after the other, in the list of
+// the XCD that has the fewest entries so far. A piece of so many agents that it is more than a 32nd of all tiles goes to
+// several, so that no XCD is left with the work of another. The gather, us, agent by agent / whole groups on one XCD /
+// their pieces: 128 agents that share one group of 2 K tokens 325 / 905 / 212, two of three groups of 1 - 2 K 503 / 594 /
+// 335, 64 agents with eight of nine such groups 978 / 645 / 641.
+void en_gather_order(en_plan *pl)
 {
     const en_pool *pool = pl->pool;
     const int sstr = std::max(pl->Smax, 1);
     pl->order_shift = pl->max_len > 2 * EN_KEY_TILE ? 2 : pl->max_len > EN_KEY_TILE ? 1 : 0;
     const int most = 1 << pl->order_shift;           // tiles per entry
+    // tiles of segment s (S: the new tokens) of agent b
+    const auto tiles_of = [&](int b, int s, int &first, int &end) {
+        const int32_t *bnd = &pl->bnd[size_t(b) * (pl->Smax + 2) + s];
+        first = (bnd[0] + EN_KEY_TILE - 1) / EN_KEY_TILE;
+        end = (bnd[1] + EN_KEY_TILE - 1) / EN_KEY_TILE;
+    };
     // the (agent, segment) pairs sorted by group, the new tokens (group number G) last
     const int G = pool->d.n_groups;
     std::vector<int32_t> first(size_t(G) + 2, 0);
     size_t n = 0;
+    long all = 0;
     for (int b = 0; b < pl->B; ++b) {
-        for (int s = 0; s < pl->nseg[b]; ++s)
-            ++first[pl->sel[size_t(b) * sstr + s] + 1];
-        ++first[G + 1];
+        for (int s = 0; s <= pl->nseg[b]; ++s) {
+            int t0, t1;
+            tiles_of(b, s, t0, t1);
+            all += t1 - t0;
+            ++first[(s < pl->nseg[b] ? pl->sel[size_t(b) * sstr + s] : G) + 1];
+        }
         n += size_t(pl->nseg[b]) + 1;
     }
     for (int g = 0; g <= G; ++g)
@@ -616,25 +630,28 @@ static void gather_order(en_plan *pl)
     std::vector<int32_t> lists[EN_XCDS];
     size_t at = 0;
     for (int g = 0; g <= G; ++g) {
-        int x = 0;                                   // the shortest list
-        for (int i = 1; i < EN_XCDS; ++i)
-            if (lists[i].size() < lists[x].size())
-                x = i;
         for (int piece = 0, more = 1; more; ++piece) {
             more = 0;
+            std::vector<int32_t> *list = nullptr;
+            long run = 0;                            // tiles of the piece in this list
             for (size_t i = at; i < size_t(first[g]); ++i) {
                 const int b = by_group[i].first;
-                const int32_t *bnd = &pl->bnd[size_t(b) * (pl->Smax + 2) + by_group[i].second];
-                const int t0 = (bnd[0] + EN_KEY_TILE - 1) / EN_KEY_TILE + piece * most;
-                const int t1 = (bnd[1] + EN_KEY_TILE - 1) / EN_KEY_TILE;
+                int t0, t1;
+                tiles_of(b, by_group[i].second, t0, t1);
+                t0 += piece * most;
                 if (t0 >= t1)
                     continue;
-                lists[x].push_back(b);
-                lists[x].push_back(t0 << 2 | (std::min(most, t1 - t0) - 1));
+                const int k = std::min(most, t1 - t0);
+                if (!list || 32 * (run + k) > all) {
+                    list = std::min_element(lists, lists + EN_XCDS,
+                                            [](const auto &l, const auto &m) { return l.size() < m.size(); });
+                    run = 0;
+                }
+                run += k;
+                list->push_back(b);
+                list->push_back(t0 << 2 | (k - 1));
                 more |= t1 - t0 > most;
             }
-            if (g == G)                              // new tokens are shared with nobody
-                x = (x + 1) % EN_XCDS;
         }
         at = first[g];
     }
@@ -662,8 +679,8 @@ static int plan_ensure_device(en_plan *pl, hipStream_t stream, bool inline_ok = 
         return EN_OK;
     size_t n = pl->nseg.size() + pl->sel.size() + pl->bnd.size() + pl->hdr.size();
     const bool inline_it = inline_ok && n <= size_t(EN_INLINE_DESC_MAX);
-    if (n > size_t(EN_INLINE_DESC_MAX) && gather_in_order(pl))
-        gather_order(pl);
+    if (n > size_t(EN_INLINE_DESC_MAX) && en_gather_in_order(pl))
+        en_gather_order(pl);
     n += pl->order.size();
     pl->acc_off = (n + 1) & ~size_t(1);                                   // 8-byte aligned
     const size_t n_all = pl->acc_off + 2 * size_t(pl->B) * (pl->Smax + 1);    // tables, then the accumulators

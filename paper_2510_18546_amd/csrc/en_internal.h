@@ -133,7 +133,7 @@ struct EnGatherLaunch {
     // 1: a workgroup takes the keys, or the values, of several heads with the next heads' loads on their way (bf16 rows
     // of 128 values). Gather and attention, us, without / with: 194 tiles of 8 heads 57.7 / 51.8, 390: 86.8 / 78.5, 528:
     // 133 / 128. Not where a context of three times the last-level cache and more is gathered agent by agent: 16
-    // agents x 12 K tokens 433 / 445, 64 x 6 K 832 / 850, 64 x 16 K 2173 / 2217 (in order, see gather_in_order: 1806).
+    // agents x 12 K tokens 433 / 445, 64 x 6 K 832 / 850, 64 x 16 K 2173 / 2217 (in order, see en_gather_in_order: 1806).
     // Rows of 64 values: 64 agents x 16 K tokens 797 / 817.
     int ahead;
     int32_t *desc_out;      // device block to fill when n_inline > 0
@@ -270,6 +270,9 @@ struct EnWsLayout {
 EnWsLayout en_ws_layout(const en_pool *pool, const en_plan *plan);
 EnWsLayout en_ws_layout_for(const en_pool *pool, const en_plan *plan, int n_rows, int n_splits);
 int en_attn_sub(const en_pool *pool, const en_plan *plan, int n_rows, int n_splits);
+// Whether a plan's gather goes in the order of the groups, and that order (into the plan).
+bool en_gather_in_order(const en_plan *plan);
+void en_gather_order(en_plan *plan);
 
 // Kernel launchers (the .hip files). Return hipError_t as int.
 int en_launch_gather(const en_pool *pool, EnGatherLaunch &g, int max_ctx_len, void *stream);

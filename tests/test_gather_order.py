@@ -1,0 +1,123 @@
+"""The order in which long contexts of agents that share groups are gathered, built on the host: every tile of every agent
+once, the tiles that agents share one after the other on one XCD, and no XCD with the work of another."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2510_18546_amd import binding as B
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+XCDS, TILE = 8, 64
+
+# reads: heads, groups, agents, new tokens, capacity, tokens per group, (groups, then their numbers) per agent
+DRIVER = '''
+#include <cstdio>
+#include "en_internal.h"
+static int num() { int v = 0; if (scanf("%d", &v) != 1) v = -1; return v; }
+int main() {
+    en_pool_desc d = {};
+    d.n_kv_heads = d.n_q_heads = num();
+    d.n_groups = num();
+    const int agents = num(), n_new = num();
+    d.capacity = num();
+    d.head_dim = 128; d.dtype = EN_BF16; d.max_ctx = 1 << 26; d.rope_base = 1e4;
+    std::vector<int32_t> len(d.n_groups), sel, ptr(1, 0);
+    for (auto &v : len) v = num();
+    for (int b = 0; b < agents; ++b) {
+        for (int k = num(); k > 0; --k) sel.push_back(num());
+        ptr.push_back(int32_t(sel.size()));
+    }
+    en_pool *pool = nullptr; en_plan *plan = nullptr;
+    if (kv_pool_create(&d, (void *)256, (void *)256, len.data(), &pool) != EN_OK) return 1;
+    if (segment_select(pool, agents, sel.data(), ptr.data(), n_new, &plan) != EN_OK) return 2;
+    const bool in_order = en_gather_in_order(plan);
+    en_gather_order(plan);
+    printf("%d %d", in_order, plan->order_shift);
+    for (int v : plan->order) printf(" %d", v);
+    printf("\\n");
+    en_plan_destroy(plan); kv_pool_destroy(pool);
+    return 0;
+}
+'''
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    at = tmp_path_factory.mktemp("order")
+    src, exe = at / "order.cpp", at / "order"
+    src.write_text(DRIVER)
+    csrc, inc = os.path.join(ROOT, "paper_2510_18546_amd", "csrc"), os.path.join(ROOT, "include")
+    B.load()
+    subprocess.check_call(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", inc, "-I", csrc,
+                           str(src), "-o", str(exe), B._build.LIB_PATH,
+                           "-Wl,-rpath," + os.path.dirname(B._build.LIB_PATH)])
+    return str(exe)
+
+
+def order(driver, kv, lens, sel, n_new):
+    """(gathered in order?, tiles an entry, list of (agent, first tile, tiles) per XCD, {(agent, tile): piece it shares})"""
+    nums = [kv, len(lens), len(sel), n_new, max(1, int(max(lens)))] + [int(x) for x in lens]
+    for s in sel:
+        nums += [len(s)] + [int(x) for x in s]
+    out = subprocess.run([driver], input=" ".join(map(str, nums)), capture_output=True, text=True, check=True).stdout
+    flat = np.array(out.split(), np.int64)
+    most, e = 1 << flat[1], flat[2:].reshape(-1, XCDS, 2)
+    lists = [[(int(b), int(v) >> 2, (int(v) & 3) + 1) for b, v in e[:, x] if b >= 0] for x in range(XCDS)]
+    piece = {}
+    for b, s in enumerate(sel):
+        end = 0
+        for g in list(s) + [-1]:
+            begin, end = end, end + (int(lens[g]) if g >= 0 else n_new)
+            t0, t1 = -(-begin // TILE), -(-end // TILE)
+            piece.update({(b, t): (int(g) if g >= 0 else ("new", b), (t - t0) // most) for t in range(t0, t1)})
+    return bool(flat[0]), int(most), lists, piece
+
+
+def check_once(lists, piece, most):
+    seen = [(b, t) for l in lists for b, t0, k in l for t in range(t0, t0 + k)]
+    assert len(seen) == len(set(seen)) and set(seen) == set(piece)
+    assert all(1 <= k <= most and len({piece[b, t] for t in range(t0, t0 + k)}) == 1 for l in lists for b, t0, k in l)
+
+
+def busiest(lists):
+    tiles = [sum(k for _, _, k in l) for l in lists]
+    return max(tiles) * XCDS / sum(tiles)
+
+
+def picks(rng, groups, agents, n):
+    return [rng.choice(groups, n, replace=False) for _ in range(agents)]
+
+
+# (groups, tokens of a group, agents, groups per agent): few groups, so long or so shared that a whole group, or a piece
+# of it, is more than an XCD's share of the work
+@pytest.mark.parametrize("groups,lo,hi,agents,per", [(1, 2048, 2048, 128, 1), (3, 1024, 2048, 128, 2), (9, 1024, 2048, 64, 8),
+                                                     (20, 700, 1024, 64, 16), (1, 256, 256, 1000, 1), (2, 100, 256, 2000, 2)])
+def test_few_shared_groups_use_every_xcd(driver, groups, lo, hi, agents, per):
+    rng = np.random.default_rng(groups)
+    lens = rng.integers(lo, hi + 1, groups)
+    in_order, most, lists, piece = order(driver, 8, lens, picks(rng, groups, agents, per), 1)
+    assert in_order
+    check_once(lists, piece, most)
+    # (whole groups on one XCD: 7.8, 3.4, 1.5, 1.2, 6.4, 4.7.) A run of entries is a 32nd of the tiles at most and joined
+    # the list with the fewest entries
+    assert busiest(lists) <= 1.25
+
+
+@pytest.mark.parametrize("groups,cap,agents,per,n_new", [(60, 256, 24, 50, 5), (80, 1000, 100, 70, 5), (130, 32, 130, 120, 64),
+                                                         (40, 64, 9, 30, 130), (5, 700, 3, 4, 1)])
+def test_every_tile_once_and_shared_pieces_together(driver, groups, cap, agents, per, n_new):
+    rng = np.random.default_rng(agents)
+    lens = rng.integers(cap // 2, cap + 1, groups)
+    lens[::7] = 0
+    sel = [s[:0] if b == 1 else s[b % 3:] for b, s in enumerate(picks(rng, groups, agents, per))]
+    _, most, lists, piece = order(driver, 8, lens, sel, n_new)
+    check_once(lists, piece, most)
+    # a piece that agents share is one run of entries in one list, unless it is more than a 32nd of the tiles
+    runs = [piece[b, t0] for l in lists for i, (b, t0, _) in enumerate(l) if i == 0 or piece[b, t0] != piece[l[i - 1][0], l[i - 1][1]]]
+    size = {}
+    for p in piece.values():
+        size[p] = size.get(p, 0) + 1
+    twice = {p for p in runs if runs.count(p) > 1}
+    assert all(32 * size[p] > len(piece) for p in twice)
