@@ -606,30 +606,30 @@ void en_gather_order(en_plan *pl)
         first = (bnd[0] + EN_KEY_TILE - 1) / EN_KEY_TILE;
         end = (bnd[1] + EN_KEY_TILE - 1) / EN_KEY_TILE;
     };
-    // the (agent, segment) pairs sorted by group, the new tokens (group number G) last
+    // the (agent, segment) pairs sorted by group
     const int G = pool->d.n_groups;
-    std::vector<int32_t> first(size_t(G) + 2, 0);
+    std::vector<int32_t> first(size_t(G) + 1, 0);
     size_t n = 0;
     long all = 0;
     for (int b = 0; b < pl->B; ++b) {
-        for (int s = 0; s <= pl->nseg[b]; ++s) {
-            int t0, t1;
-            tiles_of(b, s, t0, t1);
-            all += t1 - t0;
-            ++first[(s < pl->nseg[b] ? pl->sel[size_t(b) * sstr + s] : G) + 1];
-        }
-        n += size_t(pl->nseg[b]) + 1;
+        for (int s = 0; s < pl->nseg[b]; ++s)
+            ++first[pl->sel[size_t(b) * sstr + s] + 1];
+        n += size_t(pl->nseg[b]);
+        all += (pl->hdr[size_t(b) * 4 + 2] + EN_KEY_TILE - 1) / EN_KEY_TILE;
     }
-    for (int g = 0; g <= G; ++g)
+    for (int g = 0; g < G; ++g)
         first[g + 1] += first[g];
     std::vector<std::pair<int32_t, int32_t>> by_group(n);
     for (int b = 0; b < pl->B; ++b)
-        for (int s = 0; s <= pl->nseg[b]; ++s)
-            by_group[first[s < pl->nseg[b] ? pl->sel[size_t(b) * sstr + s] : G]++] = {b, s};
+        for (int s = 0; s < pl->nseg[b]; ++s)
+            by_group[first[pl->sel[size_t(b) * sstr + s]]++] = {b, s};
     // (first[g] is now the end of group g)
     std::vector<int32_t> lists[EN_XCDS];
+    const auto emptiest = [&] {
+        return std::min_element(lists, lists + EN_XCDS, [](const auto &l, const auto &m) { return l.size() < m.size(); });
+    };
     size_t at = 0;
-    for (int g = 0; g <= G; ++g) {
+    for (int g = 0; g < G; ++g) {
         for (int piece = 0, more = 1; more; ++piece) {
             more = 0;
             std::vector<int32_t> *list = nullptr;
@@ -643,8 +643,7 @@ void en_gather_order(en_plan *pl)
                     continue;
                 const int k = std::min(most, t1 - t0);
                 if (!list || 32 * (run + k) > all) {
-                    list = std::min_element(lists, lists + EN_XCDS,
-                                            [](const auto &l, const auto &m) { return l.size() < m.size(); });
+                    list = emptiest();
                     run = 0;
                 }
                 run += k;
@@ -654,6 +653,16 @@ void en_gather_order(en_plan *pl)
             }
         }
         at = first[g];
+    }
+    // the new tokens are shared with nobody: agent after agent, to the XCDs in turn
+    for (int b = 0; b < pl->B; ++b) {
+        int t0, t1;
+        tiles_of(b, pl->nseg[b], t0, t1);
+        for (; t0 < t1; t0 += most) {
+            std::vector<int32_t> *list = emptiest();
+            list->push_back(b);
+            list->push_back(t0 << 2 | (std::min(most, t1 - t0) - 1));
+        }
     }
     size_t longest = 0;
     for (const auto &l : lists)

@@ -121,3 +121,15 @@ def test_every_tile_once_and_shared_pieces_together(driver, groups, cap, agents,
         size[p] = size.get(p, 0) + 1
     twice = {p for p in runs if runs.count(p) > 1}
     assert all(32 * size[p] > len(piece) for p in twice)
+
+
+@pytest.mark.parametrize("groups,lo,hi,agents,per,n_new", [(130, 1, 32, 130, 120, 64), (16, 32, 64, 128, 8, 512),
+                                                           (40, 100, 256, 300, 12, 200), (1, 256, 256, 1000, 1, 1)])
+def test_new_tokens_go_round_the_xcds(driver, groups, lo, hi, agents, per, n_new):
+    """New tokens are shared with nobody: their entries go to the XCDs in turn, those of an agent one after the other."""
+    rng = np.random.default_rng(groups)
+    _, most, lists, piece = order(driver, 8, rng.integers(lo, hi + 1, groups), picks(rng, groups, agents, per), n_new)
+    check_once(lists, piece, most)
+    assert busiest(lists) <= 1.25               # (as pieces of one more group: up to 1.34)
+    new = [[(b, t) for b, t, _ in l if piece[b, t][0] == ("new", b)] for l in lists]
+    assert all(x == sorted(x) for x in new)
