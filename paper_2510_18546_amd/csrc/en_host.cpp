@@ -384,8 +384,6 @@ static int build_plan(const en_pool *pool, int32_t B, const int32_t *sel, const 
             if (seen[g] == b) {
                 return fail(EN_ERR_DUPLICATE, "segment_select: agent %d selects group %d twice", b, g);
             }
-            if (seen[g] < 0)
-                ++pl->distinct;
             pl->max_len = std::max(pl->max_len, pool->len[g]);
             seen[g] = b;
             pl->sel[size_t(b) * sstr + s] = g;
@@ -571,21 +569,33 @@ static bool gather_past_caches(const en_pool *pool, const en_plan *pl)
 // agents a group 2208 / 1806, 32 x 14 K of 4.1 935 / 858, 16 x 14 K of 2.3 488 / 466, 64 x
 // 6 K of 1.6 in groups of 96 tokens 896 / 860, 64 x 3 K of 4.1 in groups of 48 419 / 395. Not below EN_GATHER_HUGE_BYTES
 // (neighbouring tiles of an agent are then written far apart): 16 x 12 K tokens of 4 heads, 403 MB, 210 / 223; 16 x 5 K,
-// 335 MB, 201 / 208; 16 x 2 K, 134 MB, 125 / 147; where fewer than two agents share a group, only from 1 GiB on: 16 x
-// 12 K tokens of 1.6, 805 MB, 433 / 438. Nor for rows of 64 values: 791 / 896; nor from 8-bit pools, which are half
+// 335 MB, 201 / 208; 16 x 2 K, 134 MB, 125 / 147; where fewer than two agents share a token, only from 1 GiB on: 16 x
+// 12 K tokens of 1.6, 805 MB, 433 / 438. Nor where more than a third of the tokens are one agent's alone, new ones among
+// them. The gather, us: 120 agents with 1 K new tokens of 2.6 K 369 / 378, with the queries to prepare 781 / 982, 60 with
+// a group of 4 K of their own and 1.4 K of shared ones 481 / 514, 100 with 2 K and 0.9 K 474 / 480; but 500 with 128 of
+// 512 789 / 591. Nor for rows of 64 values: 791 / 896; nor from 8-bit pools, which are half
 // the reading: 64 x 16 K of 4.1 1984 / 2104, 16 x 14 K of 5.1 493 / 538. Plans whose
 // tables travel in the launch's arguments stay as they are: the order would need a copy of its own.
 bool en_gather_in_order(const en_plan *pl)
 {
     const en_pool *pool = pl->pool;
-    size_t n_sel = 0;
-    for (int b = 0; b < pl->B; ++b)
-        n_sel += size_t(pl->nseg[b]);
-    const size_t distinct = size_t(pl->distinct), bytes = 2 * en_context_bytes(pool, pl);
-    if (pool->d.dtype != EN_BF16 || pool->d.head_dim != 128)
+    const size_t bytes = 2 * en_context_bytes(pool, pl);
+    if (pool->d.dtype != EN_BF16 || pool->d.head_dim != 128 || bytes < EN_GATHER_HUGE_BYTES)
         return false;
-    return n_sel >= 2 * distinct ? bytes >= EN_GATHER_HUGE_BYTES
-                                 : 2 * n_sel >= 3 * distinct && bytes >= EN_GATHER_HUGE_BYTES / 3 * 4;
+    std::vector<int32_t> agents(size_t(pool->d.n_groups), 0);     // that select a group
+    int64_t distinct = 0, own = int64_t(pl->B) * pl->Nq;          // tokens in the pool; of one agent alone
+    const int64_t cached = pl->total_cached, all = cached + own;
+    for (int b = 0; b < pl->B; ++b) {
+        const int32_t *sel = &pl->sel[size_t(b) * std::max(pl->Smax, 1)], *bnd = &pl->bnd[size_t(b) * (pl->Smax + 2)];
+        for (int s = 0; s < pl->nseg[b]; ++s) {
+            const int len = bnd[s + 1] - bnd[s], n = ++agents[sel[s]];
+            distinct += n == 1 ? len : 0;
+            own += n == 1 ? len : n == 2 ? -len : 0;
+        }
+    }
+    if (3 * own > all)
+        return false;
+    return cached >= 2 * distinct || (2 * cached >= 3 * distinct && bytes >= EN_GATHER_HUGE_BYTES / 3 * 4);
 }
 
 // EnGatherArgs::order of a plan. A tile belongs to the segment of its first token. What agents share is the same piece

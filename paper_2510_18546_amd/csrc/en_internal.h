@@ -55,7 +55,6 @@ struct en_plan {
     // EnGatherArgs::order, or empty; its entries are up to 1 << order_shift tiles
     std::vector<int32_t> order;
     int order_shift = 0;
-    int distinct = 0;             // groups that at least one agent selects
     int max_len = 0;              // of a selected group
     // device block: nseg | sel | bnd | hdr | order, created on first GPU use
     int32_t *d_desc = nullptr;

@@ -133,3 +133,16 @@ def test_new_tokens_go_round_the_xcds(driver, groups, lo, hi, agents, per, n_new
     assert busiest(lists) <= 1.25               # (as pieces of one more group: up to 1.34)
     new = [[(b, t) for b, t, _ in l if piece[b, t][0] == ("new", b)] for l in lists]
     assert all(x == sorted(x) for x in new)
+
+
+# agents, tokens of each agent's own group, shared groups, their tokens, of them per agent, new tokens
+@pytest.mark.parametrize("agents,own,groups,tokens,per,n_new,want", [
+    (60, 4096, 20, 160, 9, 1, False), (100, 2048, 20, 160, 8, 1, False), (120, 0, 32, 192, 8, 1024, False),
+    (100, 0, 32, 384, 4, 1024, False), (128, 0, 16, 48, 8, 512, False), (64, 0, 1024, 256, 64, 1, True),
+    (500, 0, 16, 48, 8, 120, True), (64, 0, 2560, 96, 64, 1, True), (64, 512, 64, 256, 16, 1, True), (16, 0, 4000, 256, 64, 1, False)])
+def test_order_goes_by_the_tokens_that_agents_share(driver, agents, own, groups, tokens, per, n_new, want):
+    rng = np.random.default_rng(groups)
+    sel = [np.r_[s, groups + b] if own else s for b, s in enumerate(picks(rng, groups, agents, per))]
+    in_order, most, lists, piece = order(driver, 8, [tokens] * groups + [own] * (agents if own else 0), sel, n_new)
+    assert in_order == want
+    check_once(lists, piece, most)
