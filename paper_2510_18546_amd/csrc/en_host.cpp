@@ -677,6 +677,10 @@ void en_gather_order(en_plan *pl)
     size_t longest = 0;
     for (const auto &l : lists)
         longest = std::max(longest, l.size() / 2);
+    if (longest * EN_XCDS * most > EN_GRID_MAX) {     // more workgroups than a launch may have: agent by agent
+        pl->order.clear();
+        return;
+    }
     pl->order.assign(longest * EN_XCDS * 2, -1);
     for (int x = 0; x < EN_XCDS; ++x)
         for (size_t k = 0; 2 * k < lists[x].size(); ++k) {

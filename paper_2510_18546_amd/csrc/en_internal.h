@@ -15,6 +15,7 @@
 constexpr size_t EN_LAST_LEVEL_CACHE_BYTES = size_t(256) << 20;
 constexpr size_t EN_GATHER_HUGE_BYTES = 3 * EN_LAST_LEVEL_CACHE_BYTES;      // of a context's keys and values
 constexpr int EN_XCDS = 8;         // dies of the chip, each with an L2 of its own; workgroups are dealt out over them in turn
+constexpr size_t EN_GRID_MAX = ((size_t(1) << 32) - 1) / 256;      // workgroups of 256 along x: a launch counts threads in 32 bits
 constexpr int EN_KEY_TILE = 64;    // keys per attention tile; context rows are padded to it
 constexpr int EN_ROWS_PER_WAVE = 32;
 constexpr int EN_WAVES = 8;          // waves per attention workgroup

@@ -11,7 +11,8 @@ from paper_2510_18546_amd import binding as B
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 XCDS, TILE = 8, 64
 
-# reads: heads, groups, agents, new tokens, capacity, tokens per group, (groups, then their numbers) per agent
+# reads: heads, groups, agents, new tokens, capacity, tokens per group, (groups, then their numbers) per agent,
+# -1: as the agent before
 DRIVER = '''
 #include <cstdio>
 #include "en_internal.h"
@@ -26,7 +27,9 @@ int main() {
     std::vector<int32_t> len(d.n_groups), sel, ptr(1, 0);
     for (auto &v : len) v = num();
     for (int b = 0; b < agents; ++b) {
-        for (int k = num(); k > 0; --k) sel.push_back(num());
+        const int n = num(), prev = b > 0 ? ptr[b - 1] : 0, end = int(sel.size());
+        for (int k = 0; k < n; ++k) sel.push_back(num());
+        for (int k = prev; n < 0 && k < end; ++k) sel.push_back(sel[k]);
         ptr.push_back(int32_t(sel.size()));
     }
     en_pool *pool = nullptr; en_plan *plan = nullptr;
@@ -59,8 +62,8 @@ def driver(tmp_path_factory):
 def order(driver, kv, lens, sel, n_new):
     """(gathered in order?, tiles an entry, list of (agent, first tile, tiles) per XCD, {(agent, tile): piece it shares})"""
     nums = [kv, len(lens), len(sel), n_new, max(1, int(max(lens)))] + [int(x) for x in lens]
-    for s in sel:
-        nums += [len(s)] + [int(x) for x in s]
+    for b, s in enumerate(sel):
+        nums += [-1] if b and s is sel[b - 1] else [len(s)] + [int(x) for x in s]
     out = subprocess.run([driver], input=" ".join(map(str, nums)), capture_output=True, text=True, check=True).stdout
     flat = np.array(out.split(), np.int64)
     most, e = 1 << flat[1], flat[2:].reshape(-1, XCDS, 2)
@@ -146,3 +149,10 @@ def test_order_goes_by_the_tokens_that_agents_share(driver, agents, own, groups,
     in_order, most, lists, piece = order(driver, 8, [tokens] * groups + [own] * (agents if own else 0), sel, n_new)
     assert in_order == want
     check_once(lists, piece, most)
+
+
+def test_no_order_of_more_workgroups_than_a_launch_may_have(driver):
+    """4.4 million entries of one tile where an entry is four tiles' workgroups: 17.6 million of them, 2^24 - 1 fit."""
+    nums = [1, 4000, 1100, 1, 256] + [64] * 3999 + [256] + [4000] + list(range(4000)) + [-1] * 1099
+    out = subprocess.run([driver], input=" ".join(map(str, nums)), capture_output=True, text=True, check=True).stdout
+    assert out.split()[0] == "1" and len(out.split()) == 2
