@@ -384,7 +384,10 @@ static int build_plan(const en_pool *pool, int32_t B, const int32_t *sel, const 
             if (seen[g] == b) {
                 return fail(EN_ERR_DUPLICATE, "segment_select: agent %d selects group %d twice", b, g);
             }
-            pl->max_len = std::max(pl->max_len, pool->len[g]);
+            if (seen[g] < 0) {
+                ++pl->selected;
+                pl->distinct += pool->len[g];
+            }
             seen[g] = b;
             pl->sel[size_t(b) * sstr + s] = g;
             bnd[s] = int32_t(acc);
@@ -563,130 +566,159 @@ static bool gather_past_caches(const en_pool *pool, const en_plan *pl)
     return 2 * en_context_bytes(pool, pl) > EN_LAST_LEVEL_CACHE_BYTES;
 }
 
+struct EnGroupUse {
+    int32_t len = 0, agents = 0;       // tokens, agents of the plan that select it
+    uint32_t first = 0;                // number of its first piece, see en_gather_order
+};
 // Whether a plan's tiles are gathered in the order of their groups, the agents that share a group one after the other
 // on one XCD: its rows then come from memory once and from that XCD's L2 for the others, where the last-level cache
 // cannot hold the pool for them. Gather and attention, us, agent by agent / in order: 64 agents x 16 K tokens of 4.1
-// agents a group 2208 / 1806, 32 x 14 K of 4.1 935 / 858, 16 x 14 K of 2.3 488 / 466, 64 x
-// 6 K of 1.6 in groups of 96 tokens 896 / 860, 64 x 3 K of 4.1 in groups of 48 419 / 395. Not below EN_GATHER_HUGE_BYTES
-// (neighbouring tiles of an agent are then written far apart): 16 x 12 K tokens of 4 heads, 403 MB, 210 / 223; 16 x 5 K,
-// 335 MB, 201 / 208; 16 x 2 K, 134 MB, 125 / 147; where fewer than two agents share a token, only from 1 GiB on: 16 x
-// 12 K tokens of 1.6, 805 MB, 433 / 438. Nor where more than a third of the tokens are one agent's alone, new ones among
-// them. The gather, us: 120 agents with 1 K new tokens of 2.6 K 369 / 378, with the queries to prepare 781 / 982, 60 with
-// a group of 4 K of their own and 1.4 K of shared ones 481 / 514, 100 with 2 K and 0.9 K 474 / 480; but 500 with 128 of
-// 512 789 / 591. Nor for rows of 64 values: 791 / 896; nor from 8-bit pools, which are half
-// the reading: 64 x 16 K of 4.1 1984 / 2104, 16 x 14 K of 5.1 493 / 538. Plans whose
-// tables travel in the launch's arguments stay as they are: the order would need a copy of its own.
-bool en_gather_in_order(const en_plan *pl)
+// agents a group 2208 / 1806, 32 x 14 K of 4.1 935 / 858, 16 x 14 K of 2.3 488 / 466, 64 x 3 K of 4.1 in groups of 48
+// 419 / 395. Not below EN_GATHER_HUGE_BYTES (neighbouring tiles of an agent are then written far apart): 16 x 12 K tokens
+// of 4 heads, 403 MB, 210 / 223; 16 x 5 K, 335 MB, 201 / 208; 16 x 2 K, 134 MB, 125 / 147; where fewer than two agents
+// share a token, only from 1 GiB on: 16 x 12 K tokens of 1.6, 805 MB, 433 / 438.
+// Nor where more than a third of the tokens are one agent's alone, new ones among them. The gather, us: 120 agents with
+// 1 K new tokens of 2.6 K 369 / 378, with the queries to prepare 781 / 982, 60 with a group of 4 K of their own and 1.4 K
+// of shared ones 481 / 514, 100 with 2 K and 0.9 K 474 / 480; but 500 with 128 of 512 789 / 591.
+// Nor where a group's rows read fewer times are less than EN_ORDER_MIN_SAVED bytes: the order takes host time for every
+// segment, which a step by itself waits for. Selection and gather, us, contexts of 0.8 - 1.1 GB: 2 heads, groups of 48
+// tokens, 6 agents a group (246 KB) 384 / 453, 4 heads, 96 tokens, 2.2 (236 KB) 379 / 403, 8 heads, 96 tokens, 1.9 (354
+// KB) 547 / 552, 4 heads, 96 tokens, 3 (393 KB) 382 / 408; 1 head, 256 tokens, 4.2 (419 KB) 410 / 343, 8 heads, 96 tokens,
+// 2.2 (472 KB) 360 / 358 and 298 / 294, 4 heads, 48 tokens, 6 (491 KB) 382 / 376, 8 heads, 256 tokens, 2.2 352 / 332.
+// Nor for rows of 64 values: 791 / 896; nor from 8-bit pools, which are half the reading: 64 x 16 K of 4.1 1984 / 2104,
+// 16 x 14 K of 5.1 493 / 538. Plans whose tables travel in the launch's arguments stay as they are: the order would need a
+// copy of its own.
+constexpr int64_t EN_ORDER_MIN_SAVED = 400000;
+static bool gather_in_order(const en_plan *pl, std::vector<EnGroupUse> &groups)
 {
     const en_pool *pool = pl->pool;
     const size_t bytes = 2 * en_context_bytes(pool, pl);
-    if (pool->d.dtype != EN_BF16 || pool->d.head_dim != 128 || bytes < EN_GATHER_HUGE_BYTES)
+    const int64_t cached = pl->total_cached, all = cached + int64_t(pl->B) * pl->Nq;      // tokens
+    const int64_t saved = (cached - pl->distinct) * pool->d.n_kv_heads * 2 * 256;         // bytes of keys and values
+    if (pool->d.dtype != EN_BF16 || pool->d.head_dim != 128 || bytes < EN_GATHER_HUGE_BYTES ||
+        2 * cached < (bytes < EN_GATHER_HUGE_BYTES / 3 * 4 ? 4 : 3) * pl->distinct || saved < pl->selected * EN_ORDER_MIN_SAVED)
         return false;
-    std::vector<int32_t> agents(size_t(pool->d.n_groups), 0);     // that select a group
-    int64_t distinct = 0, own = int64_t(pl->B) * pl->Nq;          // tokens in the pool; of one agent alone
-    const int64_t cached = pl->total_cached, all = cached + own;
+    groups.assign(size_t(pool->d.n_groups), EnGroupUse());
     for (int b = 0; b < pl->B; ++b) {
         const int32_t *sel = &pl->sel[size_t(b) * std::max(pl->Smax, 1)], *bnd = &pl->bnd[size_t(b) * (pl->Smax + 2)];
         for (int s = 0; s < pl->nseg[b]; ++s) {
-            const int len = bnd[s + 1] - bnd[s], n = ++agents[sel[s]];
-            distinct += n == 1 ? len : 0;
-            own += n == 1 ? len : n == 2 ? -len : 0;
+            EnGroupUse &g = groups[sel[s]];
+            g.len = bnd[s + 1] - bnd[s];
+            ++g.agents;
         }
     }
-    if (3 * own > all)
-        return false;
-    return cached >= 2 * distinct || (2 * cached >= 3 * distinct && bytes >= EN_GATHER_HUGE_BYTES / 3 * 4);
+    int64_t own = int64_t(pl->B) * pl->Nq;
+    for (const EnGroupUse &g : groups)
+        own += g.agents == 1 ? g.len : 0;
+    return 3 * own <= all;
 }
 
-// EnGatherArgs::order of a plan. A tile belongs to the segment of its first token. What agents share is the same piece
-// of a group, up to four tiles of it, one entry for each agent: those of a piece come one after the other, in the list of
-// the XCD that has the fewest entries so far. A piece of so many agents that it is more than a 32nd of all tiles goes to
-// several, so that no XCD is left with the work of another. The gather, us, agent by agent / whole groups on one XCD /
-// their pieces: 128 agents that share one group of 2 K tokens 325 / 905 / 212, two of three groups of 1 - 2 K 503 / 594 /
-// 335, 64 agents with eight of nine such groups 978 / 645 / 641.
+// EnGatherArgs::order of a plan, or none, behind the tables in its host image. A tile belongs to the segment of its
+// first token. What agents share is the same piece of a group, up to four tiles of it, one entry for each agent: those of
+// a piece come one after the other, in the list of the XCD that has the fewest entries so far. A piece of so many agents
+// that it is more than a 32nd of all tiles goes to several, so that no XCD is left with the work of another. The gather,
+// us, agent by agent / whole groups on one XCD / their pieces: 128 agents that share one group of 2 K tokens 325 / 905 /
+// 212, two of three groups of 1 - 2 K 503 / 594 / 335, 64 agents with eight of nine such groups 978 / 645 / 641.
+// These loops stand in front of the launch. They and the longer tables add to a step by itself, us: 64 agents x 64 groups
+// 18 (segments sorted, lists that grew entry by entry: 29), 130 x 120 42 (67), 512 x 60 of 1 head 138 (180).
 void en_gather_order(en_plan *pl)
 {
-    const en_pool *pool = pl->pool;
+    std::vector<EnGroupUse> groups;
+    pl->order_ints = 0;
+    if (!gather_in_order(pl, groups))
+        return;
     const int sstr = std::max(pl->Smax, 1);
-    pl->order_shift = pl->max_len > 2 * EN_KEY_TILE ? 2 : pl->max_len > EN_KEY_TILE ? 1 : 0;
-    const int most = 1 << pl->order_shift;           // tiles per entry
-    // tiles of segment s (S: the new tokens) of agent b
-    const auto tiles_of = [&](int b, int s, int &first, int &end) {
-        const int32_t *bnd = &pl->bnd[size_t(b) * (pl->Smax + 2) + s];
-        first = (bnd[0] + EN_KEY_TILE - 1) / EN_KEY_TILE;
-        end = (bnd[1] + EN_KEY_TILE - 1) / EN_KEY_TILE;
-    };
-    // the (agent, segment) pairs sorted by group
-    const int G = pool->d.n_groups;
-    std::vector<int32_t> first(size_t(G) + 1, 0);
-    size_t n = 0;
-    long all = 0;
-    for (int b = 0; b < pl->B; ++b) {
-        for (int s = 0; s < pl->nseg[b]; ++s)
-            ++first[pl->sel[size_t(b) * sstr + s] + 1];
-        n += size_t(pl->nseg[b]);
-        all += (pl->hdr[size_t(b) * 4 + 2] + EN_KEY_TILE - 1) / EN_KEY_TILE;
+    int max_len = 0;
+    for (const EnGroupUse &g : groups)
+        max_len = std::max(max_len, g.len);
+    const int shift = max_len > 2 * EN_KEY_TILE ? 2 : max_len > EN_KEY_TILE ? 1 : 0;
+    const uint32_t most = 1u << shift;               // tiles per entry
+    const auto tile_at = [](int32_t token) { return uint32_t(token + EN_KEY_TILE - 1) / EN_KEY_TILE; };   // first one from there on
+    uint32_t n_pieces = 0;
+    for (EnGroupUse &g : groups) {
+        g.first = n_pieces;
+        n_pieces += (g.len / EN_KEY_TILE + most) >> shift;        // (a segment has a tile more at most than fit in it)
     }
-    for (int g = 0; g < G; ++g)
-        first[g + 1] += first[g];
-    std::vector<std::pair<int32_t, int32_t>> by_group(n);
-    for (int b = 0; b < pl->B; ++b)
-        for (int s = 0; s < pl->nseg[b]; ++s)
-            by_group[first[pl->sel[size_t(b) * sstr + s]]++] = {b, s};
-    // (first[g] is now the end of group g)
-    std::vector<int32_t> lists[EN_XCDS];
-    const auto emptiest = [&] {
-        return std::min_element(lists, lists + EN_XCDS, [](const auto &l, const auto &m) { return l.size() < m.size(); });
+    // entries per piece, then its first run
+    std::vector<uint32_t> piece(n_pieces, 0);
+    size_t entries = 0, fresh = 0, tiles = 0;        // fresh: of new tokens
+    for (int b = 0; b < pl->B; ++b) {
+        const int32_t *sel = &pl->sel[size_t(b) * sstr], *bnd = &pl->bnd[size_t(b) * (pl->Smax + 2)];
+        uint32_t t0 = 0;
+        for (int s = 0; s < pl->nseg[b]; ++s) {
+            const uint32_t t1 = tile_at(bnd[s + 1]);
+            for (uint32_t p = groups[sel[s]].first; t0 < t1; t0 += std::min(most, t1 - t0), ++p, ++entries)
+                ++piece[p];
+        }
+        const uint32_t end = tile_at(bnd[pl->nseg[b] + 1]);
+        fresh += (end - t0 + most - 1) >> shift;
+        tiles += end;
+    }
+    struct Run {
+        uint32_t at, left;                           // next entry's place in the order; entries to come
     };
-    size_t at = 0;
-    for (int g = 0; g < G; ++g) {
-        for (int piece = 0, more = 1; more; ++piece) {
-            more = 0;
-            std::vector<int32_t> *list = nullptr;
-            long run = 0;                            // tiles of the piece in this list
-            for (size_t i = at; i < size_t(first[g]); ++i) {
-                const int b = by_group[i].first;
-                int t0, t1;
-                tiles_of(b, by_group[i].second, t0, t1);
-                t0 += piece * most;
-                if (t0 >= t1)
-                    continue;
-                const int k = std::min(most, t1 - t0);
-                if (!list || 32 * (run + k) > all) {
-                    list = emptiest();
-                    run = 0;
-                }
-                run += k;
-                list->push_back(b);
-                list->push_back(t0 << 2 | (k - 1));
-                more |= t1 - t0 > most;
+    std::vector<Run> runs;
+    runs.reserve(n_pieces);
+    // per list its next entry's place in the order, a multiple of EN_XCDS and the list's number: the least is the
+    // emptiest list's (no branches: which it is cannot be foretold)
+    uint32_t next[EN_XCDS];
+    for (uint32_t x = 0; x < EN_XCDS; ++x)
+        next[x] = x;
+    const auto emptiest = [&next] {
+        uint32_t least = next[0];
+        for (int x = 1; x < EN_XCDS; ++x)
+            least = std::min(least, next[x]);
+        return least;
+    };
+    const uint32_t longest_run = uint32_t(std::max<size_t>(1, tiles / (32 * most)));
+    for (uint32_t &n : piece) {
+        const uint32_t first = uint32_t(runs.size());
+        for (uint32_t left = n; left > 0;) {
+            const uint32_t at = emptiest(), k = std::min(left, longest_run);
+            runs.push_back({at, k});
+            next[at % EN_XCDS] += k * EN_XCDS;
+            left -= k;
+        }
+        n = first;
+    }
+    // (the new tokens, to the emptiest list one by one, level the lists)
+    const size_t longest = std::max<size_t>(*std::max_element(next, next + EN_XCDS) / EN_XCDS, (entries + fresh + EN_XCDS - 1) / EN_XCDS);
+    if (longest * EN_XCDS * most > EN_GRID_MAX)       // more workgroups than a launch may have: agent by agent
+        return;
+    pl->order_shift = shift;
+    pl->order_ints = longest * EN_XCDS * 2;
+    pl->h_desc.resize(pl->h_desc.size() + pl->order_ints, -1);
+    int32_t *const out = pl->h_desc.data() + pl->h_desc.size() - pl->order_ints;
+    Run *const run = runs.data();
+    uint32_t *const run_of = piece.data();
+    const EnGroupUse *const use = groups.data();
+    const auto put = [out](uint32_t at, int b, uint32_t t0, uint32_t k) {
+        out[size_t(at) * 2] = b;
+        out[size_t(at) * 2 + 1] = int32_t(t0 << 2 | (k - 1));
+    };
+    for (int b = 0; b < pl->B; ++b) {
+        const int32_t *sel = &pl->sel[size_t(b) * sstr], *bnd = &pl->bnd[size_t(b) * (pl->Smax + 2)];
+        const int S = pl->nseg[b];
+        uint32_t t0 = 0;
+        for (int s = 0; s < S; ++s) {
+            const uint32_t t1 = tile_at(bnd[s + 1]);
+            for (uint32_t p = use[sel[s]].first; t0 < t1; ++p) {
+                run_of[p] += run[run_of[p]].left == 0;
+                Run &r = run[run_of[p]];
+                const uint32_t k = std::min(most, t1 - t0);
+                put(r.at, b, t0, k);
+                r.at += EN_XCDS;
+                --r.left;
+                t0 += k;
             }
         }
-        at = first[g];
-    }
-    // the new tokens are shared with nobody: agent after agent, to the XCDs in turn
-    for (int b = 0; b < pl->B; ++b) {
-        int t0, t1;
-        tiles_of(b, pl->nseg[b], t0, t1);
-        for (; t0 < t1; t0 += most) {
-            std::vector<int32_t> *list = emptiest();
-            list->push_back(b);
-            list->push_back(t0 << 2 | (std::min(most, t1 - t0) - 1));
+        // new tokens are shared with nobody: agent after agent, to the XCDs in turn
+        for (const uint32_t t1 = tile_at(bnd[S + 1]); t0 < t1; t0 += most) {
+            const uint32_t at = emptiest();
+            next[at % EN_XCDS] += EN_XCDS;
+            put(at, b, t0, std::min(most, t1 - t0));
         }
     }
-    size_t longest = 0;
-    for (const auto &l : lists)
-        longest = std::max(longest, l.size() / 2);
-    if (longest * EN_XCDS * most > EN_GRID_MAX) {     // more workgroups than a launch may have: agent by agent
-        pl->order.clear();
-        return;
-    }
-    pl->order.assign(longest * EN_XCDS * 2, -1);
-    for (int x = 0; x < EN_XCDS; ++x)
-        for (size_t k = 0; 2 * k < lists[x].size(); ++k) {
-            pl->order[(k * EN_XCDS + x) * 2] = lists[x][2 * k];
-            pl->order[(k * EN_XCDS + x) * 2 + 1] = lists[x][2 * k + 1];
-        }
 }
 
 // Device block of a plan (taken from the pool's cache of released blocks when
@@ -700,21 +732,19 @@ static int plan_ensure_device(en_plan *pl, hipStream_t stream, bool inline_ok = 
         *inlined = false;
     if (pl->uploaded)
         return EN_OK;
-    size_t n = pl->nseg.size() + pl->sel.size() + pl->bnd.size() + pl->hdr.size();
-    const bool inline_it = inline_ok && n <= size_t(EN_INLINE_DESC_MAX);
-    if (n > size_t(EN_INLINE_DESC_MAX) && en_gather_in_order(pl))
-        en_gather_order(pl);
-    n += pl->order.size();
-    pl->acc_off = (n + 1) & ~size_t(1);                                   // 8-byte aligned
-    const size_t n_all = pl->acc_off + 2 * size_t(pl->B) * (pl->Smax + 1);    // tables, then the accumulators
-    const size_t bytes = n_all * sizeof(int32_t);
     pl->h_desc.clear();
-    pl->h_desc.reserve(n_all);
+    pl->h_desc.reserve(pl->nseg.size() + pl->sel.size() + pl->bnd.size() + pl->hdr.size());
     pl->h_desc.insert(pl->h_desc.end(), pl->nseg.begin(), pl->nseg.end());
     pl->h_desc.insert(pl->h_desc.end(), pl->sel.begin(), pl->sel.end());
     pl->h_desc.insert(pl->h_desc.end(), pl->bnd.begin(), pl->bnd.end());
     pl->h_desc.insert(pl->h_desc.end(), pl->hdr.begin(), pl->hdr.end());
-    pl->h_desc.insert(pl->h_desc.end(), pl->order.begin(), pl->order.end());
+    const bool small = pl->h_desc.size() <= size_t(EN_INLINE_DESC_MAX), inline_it = inline_ok && small;
+    pl->order_ints = 0;
+    if (!small)
+        en_gather_order(pl);
+    pl->acc_off = (pl->h_desc.size() + 1) & ~size_t(1);                   // 8-byte aligned
+    const size_t n_all = pl->acc_off + 2 * size_t(pl->B) * (pl->Smax + 1);    // tables, then the accumulators
+    const size_t bytes = n_all * sizeof(int32_t);
     hipError_t e;
     auto &cache = pl->pool->desc_cache;
     for (size_t i = 0; i < cache.size(); ++i)
@@ -975,11 +1005,11 @@ static int gather_common(en_pool *pool, en_plan *plan, const void *k_new_dev, co
     a.nseg = d_nseg(plan);
     a.sel = d_sel(plan);
     a.bnd = d_bnd(plan);
-    a.order = plan->order.empty() ? nullptr : d_order(plan);
+    a.order = plan->order_ints ? d_order(plan) : nullptr;
     a.order_shift = plan->order_shift;
     g.ahead = pool->d.dtype == EN_BF16 && pool->d.head_dim == 128 &&
               (a.order || 2 * en_context_bytes(pool, plan) < EN_GATHER_HUGE_BYTES);
-    g.order_grid = int(plan->order.size() / 2) << plan->order_shift;
+    g.order_grid = int(plan->order_ints / 2) << plan->order_shift;
     a.B = plan->B;
     a.Hkv = pool->d.n_kv_heads;
     a.C = pool->d.capacity;

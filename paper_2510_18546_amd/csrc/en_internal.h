@@ -48,15 +48,15 @@ struct en_plan {
     int B = 0, Nq = 0, Smax = 0;
     int ctx_stride = 0, max_ctx_len = 0, n_splits = 1;
     int64_t total_pairs = 0, total_cached = 0;
+    int64_t selected = 0, distinct = 0;      // groups that at least one agent selects, their tokens
     // host descriptors (uniform stride per agent)
     std::vector<int32_t> nseg;    // [B]
     std::vector<int32_t> sel;     // [B, Smax]   (-1 padded)
     std::vector<int32_t> bnd;     // [B, Smax+2] bucket bounds: offset[0..S], then L_c+N_q
     std::vector<int32_t> hdr;     // [B, 4] S, L_c, L_c+N_q, 0: what a workgroup needs first, in one load
-    // EnGatherArgs::order, or empty; its entries are up to 1 << order_shift tiles
-    std::vector<int32_t> order;
+    // length of EnGatherArgs::order, or 0; its entries are up to 1 << order_shift tiles
+    size_t order_ints = 0;
     int order_shift = 0;
-    int max_len = 0;              // of a selected group
     // device block: nseg | sel | bnd | hdr | order, created on first GPU use
     int32_t *d_desc = nullptr;
     size_t d_desc_bytes = 0;
@@ -133,7 +133,7 @@ struct EnGatherLaunch {
     // 1: a workgroup takes the keys, or the values, of several heads with the next heads' loads on their way (bf16 rows
     // of 128 values). Gather and attention, us, without / with: 194 tiles of 8 heads 57.7 / 51.8, 390: 86.8 / 78.5, 528:
     // 133 / 128. Not where a context of three times the last-level cache and more is gathered agent by agent: 16
-    // agents x 12 K tokens 433 / 445, 64 x 6 K 832 / 850, 64 x 16 K 2173 / 2217 (in order, see en_gather_in_order: 1806).
+    // agents x 12 K tokens 433 / 445, 64 x 6 K 832 / 850, 64 x 16 K 2173 / 2217 (in order, see en_gather_order: 1806).
     // Rows of 64 values: 64 agents x 16 K tokens 797 / 817.
     int ahead;
     int32_t *desc_out;      // device block to fill when n_inline > 0
@@ -270,8 +270,7 @@ struct EnWsLayout {
 EnWsLayout en_ws_layout(const en_pool *pool, const en_plan *plan);
 EnWsLayout en_ws_layout_for(const en_pool *pool, const en_plan *plan, int n_rows, int n_splits);
 int en_attn_sub(const en_pool *pool, const en_plan *plan, int n_rows, int n_splits);
-// Whether a plan's gather goes in the order of the groups, and that order (into the plan).
-bool en_gather_in_order(const en_plan *plan);
+// The order of a plan's gather, to the end of en_plan::h_desc.
 void en_gather_order(en_plan *plan);
 
 // Kernel launchers (the .hip files). Return hipError_t as int.
