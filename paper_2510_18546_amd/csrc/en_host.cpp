@@ -721,6 +721,18 @@ void en_gather_order(en_plan *pl)
     }
 }
 
+// Bytes to allocate for a plan's device block of `bytes`. The length of an order differs a little from one selection to
+// the next, so that a block made to measure would often be too small for the next plan of the same kind and the step
+// would wait for another allocation: powers of two there.
+size_t en_plan_block_bytes(const en_plan *pl, size_t bytes)
+{
+    size_t cap = std::max<size_t>(align256(bytes), 4096);
+    if (pl->order_ints)
+        for (cap = 4096; cap < bytes;)
+            cap *= 2;
+    return cap;
+}
+
 // Device block of a plan (taken from the pool's cache of released blocks when
 // one fits) and its host image. With inline_ok the upload is left to the
 // gather kernel, which receives the image in its arguments, provided it is
@@ -755,7 +767,7 @@ static int plan_ensure_device(en_plan *pl, hipStream_t stream, bool inline_ok = 
             break;
         }
     if (!pl->d_desc) {
-        const size_t cap = std::max<size_t>(align256(bytes), 4096);
+        const size_t cap = en_plan_block_bytes(pl, bytes);
         if ((e = hipMalloc((void **)&pl->d_desc, cap)) != hipSuccess)
             return hip_fail(e, "hipMalloc(plan descriptors)");
         pl->d_desc_bytes = cap;

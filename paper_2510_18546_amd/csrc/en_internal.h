@@ -272,6 +272,7 @@ EnWsLayout en_ws_layout_for(const en_pool *pool, const en_plan *plan, int n_rows
 int en_attn_sub(const en_pool *pool, const en_plan *plan, int n_rows, int n_splits);
 // The order of a plan's gather, to the end of en_plan::h_desc.
 void en_gather_order(en_plan *plan);
+size_t en_plan_block_bytes(const en_plan *plan, size_t bytes);
 
 // Kernel launchers (the .hip files). Return hipError_t as int.
 int en_launch_gather(const en_pool *pool, EnGatherLaunch &g, int max_ctx_len, void *stream);

@@ -37,7 +37,8 @@ int main() {
     if (segment_select(pool, agents, sel.data(), ptr.data(), n_new, &plan) != EN_OK) return 2;
     en_gather_order(plan);
     if (plan->order_ints != plan->h_desc.size()) return 3;
-    printf("%d %d", plan->order_ints > 0, plan->order_shift);
+    const size_t tables = plan->nseg.size() + plan->sel.size() + plan->bnd.size() + plan->hdr.size();
+    printf("%d %d %zu", plan->order_ints > 0, plan->order_shift, en_plan_block_bytes(plan, 4 * (tables + plan->order_ints)));
     for (int v : plan->h_desc) printf(" %d", v);
     printf("\\n");
     en_plan_destroy(plan); kv_pool_destroy(pool);
@@ -59,14 +60,18 @@ def driver(tmp_path_factory):
     return str(exe)
 
 
-def order(driver, kv, lens, sel, n_new):
-    """(gathered in order?, tiles an entry, list of (agent, first tile, tiles) per XCD, {(agent, tile): piece it shares})"""
+def run(driver, kv, lens, sel, n_new):
     nums = [kv, len(lens), len(sel), n_new, max(1, int(max(lens)))] + [int(x) for x in lens]
     for b, s in enumerate(sel):
         nums += [-1] if b and s is sel[b - 1] else [len(s)] + [int(x) for x in s]
     out = subprocess.run([driver], input=" ".join(map(str, nums)), capture_output=True, text=True, check=True).stdout
-    flat = np.array(out.split(), np.int64)
-    most, e = 1 << flat[1], flat[2:].reshape(-1, XCDS, 2)
+    return np.array(out.split(), np.int64)
+
+
+def order(driver, kv, lens, sel, n_new):
+    """(gathered in order?, tiles an entry, list of (agent, first tile, tiles) per XCD, {(agent, tile): piece it shares})"""
+    flat = run(driver, kv, lens, sel, n_new)
+    most, e = 1 << flat[1], flat[3:].reshape(-1, XCDS, 2)
     lists = [[(int(b), int(v) >> 2, (int(v) & 3) + 1) for b, v in e[:, x] if b >= 0] for x in range(XCDS)]
     piece = {}
     for b, s in enumerate(sel):
@@ -159,4 +164,13 @@ def test_no_order_of_more_workgroups_than_a_launch_may_have(driver):
     """4.4 million entries of one tile where an entry is four tiles' workgroups: 17.6 million of them, 2^24 - 1 fit."""
     nums = [1, 4000, 1100, 1, 256] + [64] * 3999 + [256] + [4000] + list(range(4000)) + [-1] * 1099
     out = subprocess.run([driver], input=" ".join(map(str, nums)), capture_output=True, text=True, check=True).stdout
-    assert out.split()[0] == "0" and len(out.split()) == 2
+    assert out.split()[0] == "0" and len(out.split()) == 3
+
+
+def test_a_planner_of_one_kind_of_step_allocates_its_device_block_once(driver):
+    """The order's length differs between selections of the same agents and groups; the block's size does not follow it."""
+    rng = np.random.default_rng(3)
+    lens = rng.integers(150, 257, 200)
+    out = [run(driver, 8, lens, picks(rng, 200, 48, 30), 1) for _ in range(12)]
+    assert all(o[0] for o in out) and len({len(o) for o in out}) > 3
+    assert len({int(o[2]) for o in out}) == 1
