@@ -39,6 +39,14 @@ __device__ __forceinline__ EnGatherTables stage_tables(const EnGatherArgs &a, in
     return t;
 }
 
+// The tables of a descriptor block, one behind the other.
+__device__ __forceinline__ void tables_in(EnGatherArgs &a, const int32_t *block)
+{
+    a.nseg = block;
+    a.sel = a.nseg + a.B;
+    a.bnd = a.sel + a.B * (a.Smax > 0 ? a.Smax : 1);
+}
+
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // A piece of the context goes out. STREAM: past the caches, for contexts that the last-level cache
@@ -111,7 +119,7 @@ __device__ __forceinline__ void gather_k_rows(const EnGatherArgs &a, int b, int 
         cs = *reinterpret_cast<const fvec *>(a.cos_tab + (size_t)tok * (D / 2) + c * E);
         sn = *reinterpret_cast<const fvec *>(a.sin_tab + (size_t)tok * (D / 2) + c * E);
     }
-    // HU heads at a time. AHEAD (see EnGatherLaunch::ahead): the loads of the next ones go out before these are
+    // HU heads at a time. AHEAD (see EnGatherForm::ahead): the loads of the next ones go out before these are
     // turned and stored, so that a workgroup of several heads waits for memory once and not once per HU heads.
     // Four of eight at a time then (two: the ordered gather of 64 agents x 16 K tokens takes 1 % longer, that of 32
     // agents 3 %).
@@ -397,9 +405,7 @@ __global__ __launch_bounds__(256) void gather_kernel(EnGatherLaunch g)
     if (g.n_inline > 0) {
         const int32_t *img = reinterpret_cast<const int32_t *>(
             reinterpret_cast<uintptr_t>(__builtin_amdgcn_kernarg_segment_ptr()) + offsetof(EnGatherLaunch, desc));
-        a.nseg = img + g.off_nseg;
-        a.sel = img + g.off_sel;
-        a.bnd = img + g.off_bnd;
+        tables_in(a, img);
         if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0)
         {
             for (int i = threadIdx.x; i < g.n_inline; i += 256)
@@ -640,9 +646,7 @@ __global__ __launch_bounds__(256) void gather_q8_kernel(EnGatherLaunch g)
     if (g.n_inline > 0) {
         const int32_t *img = reinterpret_cast<const int32_t *>(
             reinterpret_cast<uintptr_t>(__builtin_amdgcn_kernarg_segment_ptr()) + offsetof(EnGatherLaunch, desc));
-        a.nseg = img + g.off_nseg;
-        a.sel = img + g.off_sel;
-        a.bnd = img + g.off_bnd;
+        tables_in(a, img);
         if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0)
         {
             for (int i = threadIdx.x; i < g.n_inline; i += 256)
@@ -836,10 +840,10 @@ static void launch_gather_hpb(int hpb, dim3 grid, hipStream_t st, const EnGather
 }
 
 template <typename T, int D>
-static void launch_gather_kernel(int hpb, dim3 grid, hipStream_t st, const EnGatherLaunch &g)
+static void launch_gather_kernel(bool ahead, int hpb, dim3 grid, hipStream_t st, const EnGatherLaunch &g)
 {
     if constexpr (sizeof(T) == 2 && D == 128)
-        if (g.ahead) {
+        if (ahead) {
             if (g.a.stream)
                 launch_gather_hpb<T, D, true, true>(hpb, grid, st, g);
             else
@@ -878,7 +882,7 @@ static void launch_gather_q8(int hpb, dim3 grid, hipStream_t st, const EnGatherL
         hipLaunchKernelGGL((gather_q8_kernel<D, 1, STREAM>), grid, blk, 0, st, g);
 }
 
-int en_launch_gather(const en_pool *pool, EnGatherLaunch &g, int max_ctx_len, void *stream)
+int en_launch_gather(const en_pool *pool, EnGatherLaunch &g, const EnGatherForm &form, int max_ctx_len, void *stream)
 {
     const EnGatherArgs &a = g.a;
     hipStream_t st = (hipStream_t)stream;
@@ -901,22 +905,22 @@ int en_launch_gather(const en_pool *pool, EnGatherLaunch &g, int max_ctx_len, vo
     const int many = gather_heads_many(pool, a, n_tiles, bf16);
     // which heads' keys are turned in which form (rope_key_pair) goes by the number of heads that this rule gives
     g.a.rope_unit = en_rope_unit(bf16 ? 2 : 4, D, many);
-    const int hpb = g.ahead ? gather_heads_ahead(pool, a, n_tiles) : many;
-    const int value_units = !bf16 ? 0 : g.ahead ? 1 : hpb;       // per key unit's heads
+    const int hpb = form.ahead ? gather_heads_ahead(pool, a, n_tiles) : many;
+    const int value_units = !bf16 ? 0 : form.ahead ? 1 : hpb;       // per key unit's heads
     // (n_q_units more units along y when the launch also prepares the queries: bf16 contexts only)
-    const dim3 grid(g.order_grid ? g.order_grid : n_tiles,
+    const dim3 grid(form.order_grid ? form.order_grid : n_tiles,
                     (a.Hkv / hpb) * (en_gather_key_units(hpb) + value_units) + (bf16 && a.q ? a.n_q_units : 0),
-                    g.order_grid ? 1 : a.B);
+                    form.order_grid ? 1 : a.B);
     if (!bf16) {
         if (D == 64)
-            launch_gather_kernel<float, 64>(hpb, grid, st, g);
+            launch_gather_kernel<float, 64>(form.ahead, hpb, grid, st, g);
         else
-            launch_gather_kernel<float, 128>(hpb, grid, st, g);
+            launch_gather_kernel<float, 128>(form.ahead, hpb, grid, st, g);
     } else {
         if (D == 64)
-            launch_gather_kernel<bf16_t, 64>(hpb, grid, st, g);
+            launch_gather_kernel<bf16_t, 64>(form.ahead, hpb, grid, st, g);
         else
-            launch_gather_kernel<bf16_t, 128>(hpb, grid, st, g);
+            launch_gather_kernel<bf16_t, 128>(form.ahead, hpb, grid, st, g);
     }
     return (int)hipGetLastError();
 }

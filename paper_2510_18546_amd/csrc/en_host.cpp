@@ -1019,9 +1019,10 @@ static int gather_common(en_pool *pool, en_plan *plan, const void *k_new_dev, co
     a.bnd = d_bnd(plan);
     a.order = plan->order_ints ? d_order(plan) : nullptr;
     a.order_shift = plan->order_shift;
-    g.ahead = pool->d.dtype == EN_BF16 && pool->d.head_dim == 128 &&
+    EnGatherForm form;
+    form.ahead = pool->d.dtype == EN_BF16 && pool->d.head_dim == 128 &&
               (a.order || 2 * en_context_bytes(pool, plan) < EN_GATHER_HUGE_BYTES);
-    g.order_grid = int(plan->order_ints / 2) << plan->order_shift;
+    form.order_grid = int(plan->order_ints / 2) << plan->order_shift;
     a.B = plan->B;
     a.Hkv = pool->d.n_kv_heads;
     a.C = pool->d.capacity;
@@ -1045,9 +1046,6 @@ static int gather_common(en_pool *pool, en_plan *plan, const void *k_new_dev, co
                     "(en_plan_values_from_pool) the new tokens' values must be aligned to a row (%d bytes)",
                     2 * pool->d.head_dim);
     g.n_inline = 0;
-    g.off_nseg = 0;
-    g.off_sel = g.off_nseg + int(plan->nseg.size());
-    g.off_bnd = g.off_sel + int(plan->sel.size());
     g.desc_out = plan->d_desc;
     g.n_zero = 0;
     if (inlined) {
@@ -1055,7 +1053,7 @@ static int gather_common(en_pool *pool, en_plan *plan, const void *k_new_dev, co
         g.n_zero = int(plan->acc_off + 2 * size_t(plan->B) * (plan->Smax + 1)) - g.n_inline;
         std::memcpy(g.desc, plan->h_desc.data(), plan->h_desc.size() * sizeof(int32_t));
     }
-    const int e = en_launch_gather(pool, g, plan->max_ctx_len, stream);
+    const int e = en_launch_gather(pool, g, form, plan->max_ctx_len, stream);
     if (e != 0) {
         if (inlined)
             plan->uploaded = false;       // the block was to be filled by this launch
