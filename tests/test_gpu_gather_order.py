@@ -36,11 +36,13 @@ def gather(pool, sel, k_new, v_new, q, from_pool):
     return plan, kc, vt, q_prep
 
 
-# 2 x 2 bytes x 128 x heads x tokens of the agents: 900 MB and more, in order; the last three below the line
+# 2 x 2 bytes x 128 x heads x tokens of the agents: 900 MB and more, in order; two that share too little, agent by agent;
+# the last three below the line
 @pytest.mark.parametrize("agents,kv,groups,cap,lo,hi,picks,n_new,from_pool", [
     (24, 8, 60, 256, 200, 256, 50, 5, False), (24, 8, 60, 256, 200, 256, 50, 130, True),
     (40, 3, 90, 512, 300, 512, 48, 70, False), (100, 1, 80, 1000, 500, 1000, 70, 5, False),
-    (130, 8, 130, 32, 1, 32, 120, 64, False), (25, 8, 30, 70, 30, 70, 20, 129, False),
+    (130, 8, 130, 32, 1, 32, 120, 64, False),
+    (14, 8, 700, 512, 300, 512, 42, 5, False), (60, 2, 3000, 512, 300, 512, 42, 33, True), (25, 8, 30, 70, 30, 70, 20, 129, False),
     (4, 8, 64, 130, 60, 130, 40, 100, False), (3, 2, 40, 64, 10, 64, 33, 17, False)])
 def test_same_contexts_as_one_by_one(agents, kv, groups, cap, lo, hi, picks, n_new, from_pool):
     import torch
