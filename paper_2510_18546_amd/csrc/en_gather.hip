@@ -119,7 +119,7 @@ __device__ __forceinline__ void gather_k_rows(const EnGatherArgs &a, int b, int 
         cs = *reinterpret_cast<const fvec *>(a.cos_tab + (size_t)tok * (D / 2) + c * E);
         sn = *reinterpret_cast<const fvec *>(a.sin_tab + (size_t)tok * (D / 2) + c * E);
     }
-    // HU heads at a time. AHEAD (see EnGatherForm::ahead): the loads of the next ones go out before these are
+    // HU heads at a time. AHEAD (see gather_ahead): the loads of the next ones go out before these are
     // turned and stored, so that a workgroup of several heads waits for memory once and not once per HU heads.
     // Four of eight at a time then (two: the ordered gather of 64 agents x 16 K tokens takes 1 % longer, that of 32
     // agents 3 %).
@@ -823,23 +823,52 @@ static int gather_heads_many(const en_pool *pool, const EnGatherArgs &a, int n_t
     return 1;
 }
 
-// Heads per unit with AHEAD: as many as leave 1.25 workgroups per compute unit. About four fit one, so where eight
-// heads make more of them than that, a last round of long workgroups would run alone: two heads then, unless the
-// context is so long (past the caches) that many rounds follow each other. Gather and attention, us, with one / two /
-// four / eight heads: 137 tiles (of 8 heads) 88.8 / 88.6 / 88.9 / 90.3, 194: 56.7 / 55.5 / 53.0 / 50.9, 390: 85.0 /
+// Rows of a gather: query rows to prepare, rows of keys and values.
+struct EnGatherRows {
+    long queries, keys_values;
+};
+
+// Heads per unit with AHEAD: as many as leave 1.25 workgroups per compute unit. Three (of eight heads) to five fit one, so
+// where eight heads make more of them than four each, a last round of long workgroups would run alone: two heads then,
+// unless the context is so long (past the caches) that many rounds follow each other. Gather and attention, us, with one /
+// two / four / eight heads: 137 tiles (of 8 heads) 88.8 / 88.6 / 88.9 / 90.3, 194: 56.7 / 55.5 / 53.0 / 50.9, 390: 85.0 /
 // 81.0 / 79.6 / 80.1, 528: 129.2 / 125.7 / 127.3 / 129.7, 784: 130.2 / 130.7 / 133.0 / 135.2; past the caches 1300
 // tiles 233 / 228 / 217 / 214, 6200: 965 / 840 / 823 / 805. With changing inputs (nothing of the pool left in the
 // last-level cache) 136 tiles, keys only, 69.5 / 68.9 / 68.8 / 72.3, 28 tiles 32.1 / 32.1 / 32.7 / 35.6, 235: 97.0 /
 // 95.5 / 93.0 / 92.7.
-static int gather_heads_ahead(const en_pool *pool, const EnGatherArgs &a, int n_tiles)
+// With one query row to six of keys and values and more, at most four: eight heads are 132 registers, three workgroups to
+// a compute unit, four are 96 and five, and queries prepared beside them want the more. The gather, us, with eight / four:
+// 64 agents with 512 new tokens of 2.3 K, keys only (0.44 to 1) 228 / 209, with values (0.22) 318 / 310, 16 of 4.1 K, keys
+// only (0.25) 78 / 72; but 2 with 512 of 7.7 K (0.13) 26.3 / 26.7, 24 with 130 of 11 K, keys only (0.05) 139 / 144, though
+// 130 with 64 of 2 K (0.06) 252 / 243.
+static int gather_heads_ahead(const en_pool *pool, const EnGatherArgs &a, const EnGatherRows &rows, int n_tiles)
 {
-    int hpb = 8;
+    int hpb = 6 * rows.queries < rows.keys_values ? 8 : 4;
     const long work = (a.v_rows ? 1L : 2L) * a.Hkv * n_tiles * a.B;                  // (tile, head), keys and values
     if (!a.stream && work > 8 * 4L * pool->n_cu)
         hpb = 2;
     while (hpb > 1 && (a.Hkv % hpb || 4 * work < 5L * hpb * pool->n_cu))
         hpb /= 2;
     return hpb;
+}
+
+// AHEAD: a workgroup takes the keys, or the values, of several heads with the next heads' loads on their way (bf16 rows
+// of 128 values). Gather and attention, us, without / with: 194 tiles of 8 heads 57.7 / 51.8, 390: 86.8 / 78.5, 528:
+// 133 / 128. Not where a context of three times the last-level cache and more is gathered agent by agent: 16
+// agents x 12 K tokens 433 / 445, 64 x 6 K 832 / 850, 64 x 16 K 2173 / 2217 (in order, see en_gather_order: 1806).
+// Rows of 64 values: 64 agents x 16 K tokens 797 / 817.
+// Nor where queries to prepare are most of a launch of several heads a workgroup, whose registers leave them fewer waves:
+// from three query rows to two of keys and values on, in the caches from as many on. The gather, us: 16 agents with 512
+// new tokens of 1 K (1.1 to 1) 45.8 / 48.9, with 1 K of 1.4 K (1.5) 86.5 / 87.2, keys only 16 with 512 of 1 K (2.1)
+// 38.7 / 44.9 and 128 with 512 of 0.9 K (2.3) 291 / 321; but past the caches 128 with 512 of 0.9 K (1.1) 363 / 344, 64 with
+// 512 of 1.4 K, keys only (1.5), 186 / 175. Of one head: 2 agents with 512 of 1 K (1.1) 7.98 / 7.58.
+static bool gather_ahead(const en_plan *plan, const EnGatherArgs &a, const EnGatherRows &rows, int heads)
+{
+    const en_pool *pool = plan->pool;
+    if (pool->d.dtype != EN_BF16 || pool->d.head_dim != 128 ||
+        (!a.order && 2 * en_context_bytes(pool, plan) >= EN_GATHER_HUGE_BYTES))
+        return false;
+    return heads == 1 || 2 * rows.queries < (a.stream ? 3 : 2) * rows.keys_values;
 }
 
 template <typename T, int D, bool STREAM, bool AHEAD>
@@ -899,11 +928,12 @@ static void launch_gather_q8(int hpb, dim3 grid, hipStream_t st, const EnGatherL
         hipLaunchKernelGGL((gather_q8_kernel<D, 1, STREAM>), grid, blk, 0, st, g);
 }
 
-int en_launch_gather(const en_pool *pool, EnGatherLaunch &g, const EnGatherForm &form, int max_ctx_len, void *stream)
+int en_launch_gather(const en_plan *plan, EnGatherLaunch &g, void *stream)
 {
+    const en_pool *pool = plan->pool;
     const EnGatherArgs &a = g.a;
     hipStream_t st = (hipStream_t)stream;
-    const int n_tiles = (max_ctx_len + EN_KEY_TILE - 1) / EN_KEY_TILE;
+    const int n_tiles = (plan->max_ctx_len + EN_KEY_TILE - 1) / EN_KEY_TILE;
     const int D = pool->d.head_dim;
     if (pool->d.dtype == EN_I8) {
         const int hpb = gather_heads_q8(pool, a, n_tiles);
@@ -922,22 +952,28 @@ int en_launch_gather(const en_pool *pool, EnGatherLaunch &g, const EnGatherForm 
     const int many = gather_heads_many(pool, a, n_tiles, bf16);
     // which heads' keys are turned in which form (rope_key_pair) goes by the number of heads that this rule gives
     g.a.rope_unit = en_rope_unit(bf16 ? 2 : 4, D, many);
-    const int hpb = form.ahead ? gather_heads_ahead(pool, a, n_tiles) : many;
-    const int value_units = !bf16 ? 0 : form.ahead ? 1 : hpb;       // per key unit's heads
+    const long tokens = plan->total_cached + long(plan->B) * plan->Nq;
+    const EnGatherRows rows = {a.q ? long(plan->B) * plan->Nq * a.Hq : 0, (a.v_rows ? 1 : 2) * tokens * a.Hkv};
+    const int heads = gather_heads_ahead(pool, a, rows, n_tiles);
+    const bool ahead = gather_ahead(plan, a, rows, heads);
+    if (!ahead)
+        g.a.order = nullptr;                                     // (the order is for that form)
+    const int hpb = ahead ? heads : many;
+    const int value_units = !bf16 ? 0 : ahead ? 1 : hpb;         // per key unit's heads
     // (n_q_units more units along y when the launch also prepares the queries: bf16 contexts only)
-    const dim3 grid(form.order_grid ? form.order_grid : n_tiles,
+    const dim3 grid(a.order ? int(plan->order_ints / 2) << plan->order_shift : n_tiles,
                     (a.Hkv / hpb) * (en_gather_key_units(hpb) + value_units) + (bf16 && a.q ? a.n_q_units : 0),
-                    form.order_grid ? 1 : a.B);
+                    a.order ? 1 : a.B);
     if (!bf16) {
         if (D == 64)
-            launch_gather_kernel<float, 64>(form.ahead, hpb, grid, st, g);
+            launch_gather_kernel<float, 64>(ahead, hpb, grid, st, g);
         else
-            launch_gather_kernel<float, 128>(form.ahead, hpb, grid, st, g);
+            launch_gather_kernel<float, 128>(ahead, hpb, grid, st, g);
     } else {
         if (D == 64)
-            launch_gather_kernel<bf16_t, 64>(form.ahead, hpb, grid, st, g);
+            launch_gather_kernel<bf16_t, 64>(ahead, hpb, grid, st, g);
         else
-            launch_gather_kernel<bf16_t, 128>(form.ahead, hpb, grid, st, g);
+            launch_gather_kernel<bf16_t, 128>(ahead, hpb, grid, st, g);
     }
     return (int)hipGetLastError();
 }

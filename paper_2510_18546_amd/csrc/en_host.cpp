@@ -1017,12 +1017,6 @@ static int gather_common(en_pool *pool, en_plan *plan, const void *k_new_dev, co
     a.nseg = d_nseg(plan);
     a.sel = d_sel(plan);
     a.bnd = d_bnd(plan);
-    a.order = plan->order_ints ? d_order(plan) : nullptr;
-    a.order_shift = plan->order_shift;
-    EnGatherForm form;
-    form.ahead = pool->d.dtype == EN_BF16 && pool->d.head_dim == 128 &&
-              (a.order || 2 * en_context_bytes(pool, plan) < EN_GATHER_HUGE_BYTES);
-    form.order_grid = int(plan->order_ints / 2) << plan->order_shift;
     a.B = plan->B;
     a.Hkv = pool->d.n_kv_heads;
     a.C = pool->d.capacity;
@@ -1041,6 +1035,8 @@ static int gather_common(en_pool *pool, en_plan *plan, const void *k_new_dev, co
     a.scale_log2e = softmax_scale_log2e(pool);
     a.v_rows = plan->values_from_pool ? 1 : 0;
     a.stream = gather_past_caches(pool, plan) ? 1 : 0;
+    a.order = plan->order_ints ? d_order(plan) : nullptr;
+    a.order_shift = plan->order_shift;
     if (a.v_rows && (reinterpret_cast<uintptr_t>(v_new_dev) & uintptr_t(2 * pool->d.head_dim - 1)))
         return fail(EN_ERR_INVALID_ARG, "gather_rope: with the values taken from where they are "
                     "(en_plan_values_from_pool) the new tokens' values must be aligned to a row (%d bytes)",
@@ -1053,7 +1049,7 @@ static int gather_common(en_pool *pool, en_plan *plan, const void *k_new_dev, co
         g.n_zero = int(plan->acc_off + 2 * size_t(plan->B) * (plan->Smax + 1)) - g.n_inline;
         std::memcpy(g.desc, plan->h_desc.data(), plan->h_desc.size() * sizeof(int32_t));
     }
-    const int e = en_launch_gather(pool, g, form, plan->max_ctx_len, stream);
+    const int e = en_launch_gather(plan, g, stream);
     if (e != 0) {
         if (inlined)
             plan->uploaded = false;       // the block was to be filled by this launch

@@ -133,18 +133,8 @@ struct EnGatherLaunch {
 };
 // What every workgroup reads before its tables lies in the first three lines (of 64 bytes) of the arguments: a field in
 // the fourth is one more trip before the tables' own (the gather of 64 fp32 rows 3.22 -> 3.32 us, of one agent's ragged
-// map 5.59 -> 5.71). So what the host alone needs is passed beside them.
+// map 5.59 -> 5.71). So what the host alone needs is not among them.
 static_assert(offsetof(EnGatherLaunch, desc_out) <= 192, "a field that every workgroup reads is in the fourth line");
-// The host's choices for a gather launch.
-struct EnGatherForm {
-    int order_grid = 0;     // with EnGatherArgs::order: workgroups along x
-    // a workgroup takes the keys, or the values, of several heads with the next heads' loads on their way (bf16 rows
-    // of 128 values). Gather and attention, us, without / with: 194 tiles of 8 heads 57.7 / 51.8, 390: 86.8 / 78.5, 528:
-    // 133 / 128. Not where a context of three times the last-level cache and more is gathered agent by agent: 16
-    // agents x 12 K tokens 433 / 445, 64 x 6 K 832 / 850, 64 x 16 K 2173 / 2217 (in order, see en_gather_order: 1806).
-    // Rows of 64 values: 64 agents x 16 K tokens 797 / 817.
-    bool ahead = false;
-};
 
 struct EnAttnArgs {
     const void *q, *kc, *vt;
@@ -281,7 +271,7 @@ void en_gather_order(en_plan *plan);
 size_t en_plan_block_bytes(const en_plan *plan, size_t bytes);
 
 // Kernel launchers (the .hip files). Return hipError_t as int.
-int en_launch_gather(const en_pool *pool, EnGatherLaunch &g, const EnGatherForm &form, int max_ctx_len, void *stream);
+int en_launch_gather(const en_plan *plan, EnGatherLaunch &g, void *stream);
 int en_launch_attention(const en_pool *pool, const EnAttnArgs &a, void *stream);
 int en_launch_attention_prefill(const en_pool *pool, const EnAttnArgs &a, void *stream);   // called by the former
 int en_launch_combine(const en_pool *pool, const EnAttnArgs &a, const EnMassArgs &m, void *stream);

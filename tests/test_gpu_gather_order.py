@@ -36,18 +36,47 @@ def gather(pool, sel, k_new, v_new, q, from_pool):
     return plan, kc, vt, q_prep
 
 
-# 2 x 2 bytes x 128 x heads x tokens of the agents: 900 MB and more, in order; two that share too little, agent by agent;
-# the last three below the line
-@pytest.mark.parametrize("agents,kv,groups,cap,lo,hi,picks,n_new,from_pool", [
-    (24, 8, 60, 256, 200, 256, 50, 5, False), (24, 8, 60, 256, 200, 256, 50, 130, True),
-    (40, 3, 90, 512, 300, 512, 48, 70, False), (100, 1, 80, 1000, 500, 1000, 70, 5, False),
-    (130, 8, 130, 32, 1, 32, 120, 64, False),
-    (14, 8, 700, 512, 300, 512, 42, 5, False), (60, 2, 3000, 512, 300, 512, 42, 33, True), (25, 8, 30, 70, 30, 70, 20, 129, False),
-    (4, 8, 64, 130, 60, 130, 40, 100, False), (3, 2, 40, 64, 10, 64, 33, 17, False)])
-def test_same_contexts_as_one_by_one(agents, kv, groups, cap, lo, hi, picks, n_new, from_pool):
+def n_cu():
+    import torch
+    return torch.cuda.get_device_properties(0).multi_processor_count
+
+
+def route(plan, kv, lens, sel, n_new, q_heads, from_pool):
+    """How a bf16 gather of rows of 128 values goes, by the rules of the library: in the order of the groups or not, past the
+    caches or not, heads a workgroup, with loads ahead or not."""
+    agents, tiles = len(sel), -(-plan.info.max_ctx_len // 64)
+    cached = [sum(int(lens[g]) for g in s) for s in sel]
+    tokens, used = sum(cached) + agents * n_new, np.bincount(np.concatenate(sel), minlength=len(lens))
+    size = 512 * agents * kv * plan.info.ctx_stride
+    distinct, own = lens[used > 0].sum(), agents * n_new + lens[used == 1].sum()
+    order = (size >= 768 << 20 and 3 * own <= tokens and (sum(cached) - distinct) * kv * 512 >= 400000 * (used > 0).sum() and
+             sum(cached) >= (2 if size < 1 << 30 else 1.5) * distinct)
+    stream, rows, queries = size > 256 << 20, tokens * kv * (1 if from_pool else 2), agents * n_new * q_heads
+    heads = 2 if not stream and (1 if from_pool else 2) * kv * tiles * agents > 32 * n_cu() else 8 if 6 * queries < rows else 4
+    while heads > 1 and (kv % heads or 4 * (1 if from_pool else 2) * kv * tiles * agents < 5 * heads * n_cu()):
+        heads //= 2
+    if (order or size < 768 << 20) and (heads == 1 or 2 * queries < (3 if stream else 2) * rows):
+        return order, stream, heads, True
+    heads = max(h for h in (1, 2, 4, 8) if h == 1 or kv % h == 0 and kv // h * (1 + h) * tiles * agents >= 32 * n_cu())
+    return False, stream, heads, False
+
+
+# (order, past the caches, heads, ahead) as `route` says it: contexts of 768 MB and more in order; two that share too little,
+# agent by agent; smaller ones; and launches that are mostly queries, agent by agent too
+@pytest.mark.parametrize("agents,kv,groups,cap,lo,hi,picks,n_new,from_pool,how", [
+    (24, 8, 60, 256, 200, 256, 50, 5, False, (True, True, 8, True)), (24, 8, 60, 256, 200, 256, 50, 130, True, (True, True, 8, True)),
+    (40, 3, 90, 512, 300, 512, 48, 70, False, (True, True, 1, True)), (100, 1, 80, 1000, 500, 1000, 70, 5, False, (True, True, 1, True)),
+    (130, 8, 130, 32, 1, 32, 120, 64, False, (True, True, 4, True)), (90, 2, 60, 256, 200, 256, 50, 5, False, (True, True, 2, True)),
+    (14, 8, 700, 512, 300, 512, 42, 5, False, (False, True, 8, False)), (60, 2, 3000, 512, 300, 512, 42, 33, True, (False, True, 2, False)),
+    (25, 8, 30, 70, 30, 70, 20, 129, False, (False, False, 4, True)), (4, 8, 64, 130, 60, 130, 40, 100, False, (False, False, 4, True)),
+    (3, 2, 40, 64, 10, 64, 33, 17, False, (False, False, 1, True)), (30, 8, 60, 130, 100, 130, 14, 1, False, (False, False, 2, True)),
+    (30, 8, 64, 64, 30, 64, 8, 512, False, (False, False, 1, False)), (64, 8, 64, 30, 1, 30, 2, 900, False, (False, False, 8, False)),
+    (190, 2, 64, 30, 1, 30, 2, 900, False, (False, False, 2, False)), (100, 8, 40, 64, 30, 64, 40, 500, True, (False, True, 8, False))])
+def test_same_contexts_as_one_by_one(agents, kv, groups, cap, lo, hi, picks, n_new, from_pool, how):
     import torch
     pool, lens, sel, k_new, v_new, q = make(agents, kv, groups, cap, lo, hi, picks, n_new)
     plan, kc, vt, q_prep = gather(pool, sel, k_new, v_new, q, from_pool)
+    assert route(plan, kv, lens, sel, n_new, 8 * kv, from_pool) == how
     T = plan.info.ctx_stride
     kc = kc.view(agents, kv, T, 128)
     table = vt.view(torch.int64)[:agents * kv * T].view(agents, kv, T) if from_pool else None
