@@ -45,7 +45,8 @@ __device__ __forceinline__ void rope_scale_pair(float x1, float x2, float c, flo
 // the loop around the expression, and the last bits of the context with it. The first half rounds x2's product.
 // The second half rounds x2's too or (X1_ROUNDED) x1's; either is as exact, and who writes which are the bits
 // that these contexts have always had: x1's in the 8-bit gather, in the first row that a wave of the decode
-// kernel appends, and in all heads but the last of a gather unit of four (16-bit, of eight with D = 64).
+// kernel appends, and (16-bit) in all heads but the last of four, of eight with D = 64, where gather_heads_many says
+// so many (EnGatherArgs::rope_unit; the heads that a workgroup takes with loads ahead are another number).
 template <bool X1_ROUNDED = false, typename F>
 __device__ __forceinline__ void rope_key_pair(F x1, F x2, F c, F s, F &y1, F &y2)
 {

@@ -920,9 +920,12 @@ template <int D, bool STREAM>
 static void launch_gather_q8(int hpb, dim3 grid, hipStream_t st, const EnGatherLaunch &g)
 {
     const dim3 blk(256);
-    if (hpb == 4)
-        hipLaunchKernelGGL((gather_q8_kernel<D, 4, STREAM>), grid, blk, 0, st, g);
-    else if (hpb == 2)
+    if constexpr (STREAM)
+        if (hpb == 4) {                              // (past the caches only)
+            hipLaunchKernelGGL((gather_q8_kernel<D, 4, STREAM>), grid, blk, 0, st, g);
+            return;
+        }
+    if (hpb == 2)
         hipLaunchKernelGGL((gather_q8_kernel<D, 2, STREAM>), grid, blk, 0, st, g);
     else
         hipLaunchKernelGGL((gather_q8_kernel<D, 1, STREAM>), grid, blk, 0, st, g);
