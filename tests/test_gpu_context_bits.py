@@ -1,6 +1,7 @@
 """The keys of a context, bit for bit: x1 cos - x2 sin and x1 sin + x2 cos, of each the product of x2 rounded and the
-product of x1 inside a fused multiply-add. The other way round in the second half: the 8-bit gather; a gather unit of
-four heads, all but the last (of eight too, with D = 64); the first row that a wave of the decode kernel appends. These
+product of x1 inside a fused multiply-add. The other way round in the second half: the 8-bit gather; where a 16-bit gather
+is large enough for units of four heads by 32 workgroups for each compute unit, all but the last of four (of eight too,
+with D = 64), whatever number of heads its workgroups take; the first row that a wave of the decode kernel appends. These
 are the bits that contexts have always had, whichever way the loops are unrolled."""
 import math
 
@@ -32,9 +33,10 @@ def bf16(x):
 @pytest.mark.parametrize("dtype,kv,agents,d", [
     ("f32", 1, 1, 64), ("f32", 2, 3, 128), ("bf16", 1, 1, 128), ("bf16", 3, 1, 64), ("bf16", 2, 256, 64),
     ("bf16", 4, 140, 128), ("bf16", 4, 140, 64), ("bf16", 8, 72, 128), ("bf16", 8, 72, 64), ("f32", 4, 600, 64),
-    ("bf16", 8, 3, 128), ("i8", 2, 2, 128), ("i8", 1, 2, 64)])
+    ("bf16", 8, 3, 128), ("bf16", 2, 1000, 128), ("bf16", 4, 500, 128), ("bf16", 8, 250, 128), ("i8", 2, 2, 128), ("i8", 1, 2, 64)])
 def test_rotated_keys(dtype, kv, agents, d):
-    """agents: enough for 2, 4 and 8 heads a workgroup (32 workgroups for each of 256 compute units)."""
+    """agents: enough for 2, 4 and 8 heads a unit (32 workgroups for each of 256 compute units), then for 768 MB of keys and
+    values, which are gathered in the order of the groups."""
     import torch
     rng = np.random.default_rng(agents + d)
     g_n, cap, s_n, n_new, base = 12, 96, 9, 34, 1e4
@@ -54,6 +56,7 @@ def test_rotated_keys(dtype, kv, agents, d):
         B.kv_pool_set_scales(pool, *scales)
     sel = [rng.choice(g_n, s_n, replace=False).astype(np.int32) for _ in range(agents)]
     plan = B.segment_select(pool, np.concatenate(sel), np.arange(agents + 1) * s_n, n_new)
+    assert (agents in (250, 500, 1000)) == (dtype == "bf16" and 4 * agents * kv * plan.info.ctx_stride * d >= 768 << 20)
     k_new = torch.from_numpy(rng.standard_normal((agents, n_new, kv, d)).astype(np.float32)).to(act).to(dev)
     kc, vt = B.alloc_context(pool, plan)
     B.gather_rope(pool, plan, k_new, k_new, kc, vt)

@@ -104,12 +104,12 @@ def test_same_contexts_as_one_by_one(agents, kv, groups, cap, lo, hi, picks, n_n
     plan.close()
 
 
-# 8-bit pools: contexts of 300 MB go past the caches, four, two or one heads a workgroup; the last three do not (two heads
-# for the agents together, one for each by itself)
-@pytest.mark.parametrize("agents,kv,d,cap,n_new", [(9, 8, 128, 130, 70), (17, 2, 128, 256, 1), (18, 6, 64, 200, 33),
-                                                   (25, 3, 128, 130, 70), (20, 4, 64, 200, 130),
-                                                   (2, 8, 128, 100, 40), (3, 6, 64, 130, 129), (2, 8, 64, 130, 1)])
-def test_same_contexts_from_8_bit_pools(agents, kv, d, cap, n_new):
+# 8-bit pools: contexts that go past the caches, four, two or one heads a workgroup; the others two heads for the agents
+# together, one for each by itself
+@pytest.mark.parametrize("agents,kv,d,cap,n_new,heads", [
+    (9, 8, 128, 130, 70, 4), (17, 2, 128, 256, 1, 2), (18, 6, 64, 200, 33, 2), (25, 3, 128, 130, 70, 1), (30, 4, 64, 200, 130, 4),
+    (2, 8, 128, 130, 40, 2), (4, 6, 64, 130, 129, 2), (2, 8, 64, 130, 1, 2)])
+def test_same_contexts_from_8_bit_pools(agents, kv, d, cap, n_new, heads):
     import torch
     rng = np.random.default_rng(agents)
     gen = torch.Generator(device="cuda:0").manual_seed(agents)
@@ -125,6 +125,8 @@ def test_same_contexts_from_8_bit_pools(agents, kv, d, cap, n_new):
     sel = [rng.choice(groups, 0 if b == 1 else picks - b % 3, replace=False).astype(np.int32) for b in range(agents)]
     plan, kc, vt, q_prep = gather(pool, sel, k_new, v_new, q, False)
     T = plan.info.ctx_stride
+    past = 4 * agents * kv * T * d > 256 << 20
+    assert heads == max(h for h in (1, 2, 4) if h == 1 or kv % h == 0 and (past if h == 4 else past or 2 * kv * T // 64 * agents >= 16 * n_cu()))
     kc, vt = kc.view(agents, kv, T, d), vt.view(agents, kv, d, T)
     # the values of agent 0 are code x scale in float32, rounded once; token j in the column with its bits 2 and 3 exchanged
     rows = torch.from_numpy(np.concatenate([g * cap + np.arange(lens[g]) for g in sel[0]])).cuda()
