@@ -391,8 +391,8 @@ __device__ __forceinline__ bool query_unit(const EnGatherArgs &a, int &unit)
     const int w = unit * gridDim.x + blockIdx.x, n = a.n_q_units * gridDim.x;
     if (!ORDERED || !a.order)
         prepare_queries<D>(a, w, n, blockIdx.z);
-    else if (w / a.B < n / a.B)              // one grid for all agents (n >= B: an agent has a tile at least)
-        prepare_queries<D>(a, w / a.B, n / a.B, w % a.B);
+    else if (w < n / a.B * a.B)              // one grid for all agents, one after the other (n >= B: each has a tile)
+        prepare_queries<D>(a, w % (n / a.B), n / a.B, w / (n / a.B));
     return true;
 }
 
