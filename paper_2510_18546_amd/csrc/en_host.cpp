@@ -585,18 +585,30 @@ struct EnGroupUse {
 // tokens, 6 agents a group (246 KB) 384 / 453, 4 heads, 96 tokens, 2.2 (236 KB) 379 / 403, 8 heads, 96 tokens, 1.9 (354
 // KB) 547 / 552, 4 heads, 96 tokens, 3 (393 KB) 382 / 408; 1 head, 256 tokens, 4.2 (419 KB) 410 / 343, 8 heads, 96 tokens,
 // 2.2 (472 KB) 360 / 358 and 298 / 294, 4 heads, 48 tokens, 6 (491 KB) 382 / 376, 8 heads, 256 tokens, 2.2 352 / 332.
+// With queries to prepare ten times their share of the rows more: 64 agents with 256 new tokens (0.12 of the
+// rows), 96 tokens, 3 (786 KB) 428 / 446, 256 tokens, 2.2 (1.3 MB) 429 / 429; keys only (0.23), 96 tokens, 4.2 (629 KB) 273
+// / 288, 8 (1.4 MB) 273 / 274. And keys only, which are half as long under way, not where a segment's are less than
+// EN_ORDER_MIN_KEYS bytes on average: 256 agents, 2 heads, 96 tokens (49 KB), 17 agents a group 218 / 247, 32 a group 216 /
+// 243, 256 tokens (131 KB), 32 a group 182 / 194; 64 agents, 8 heads, 96 tokens (196 KB), 4.2 208 / 190.
 // Nor for rows of 64 values: 791 / 896; nor from 8-bit pools, which are half the reading: 64 x 16 K of 4.1 1984 / 2104,
 // 16 x 14 K of 5.1 493 / 538. Plans whose tables travel in the launch's arguments stay as they are: the order would need a
 // copy of its own.
-constexpr int64_t EN_ORDER_MIN_SAVED = 400000;
-static bool gather_in_order(const en_plan *pl, std::vector<EnGroupUse> &groups)
+constexpr int64_t EN_ORDER_MIN_SAVED = 400000, EN_ORDER_MIN_KEYS = 160000;
+static bool gather_in_order(const en_plan *pl, int64_t queries, std::vector<EnGroupUse> &groups)
 {
     const en_pool *pool = pl->pool;
     const size_t bytes = 2 * en_context_bytes(pool, pl);
     const int64_t cached = pl->total_cached, all = cached + int64_t(pl->B) * pl->Nq;      // tokens
-    const int64_t saved = (cached - pl->distinct) * pool->d.n_kv_heads * 2 * 256;         // bytes of keys and values
+    const int64_t per_token = pool->d.n_kv_heads * (pl->values_from_pool ? 1 : 2);        // rows that the gather moves
+    const int64_t saved = (cached - pl->distinct) * per_token * 256;
+    const double least = double(EN_ORDER_MIN_SAVED) * (1.0 + 10.0 * double(queries) / double(all * per_token));
     if (pool->d.dtype != EN_BF16 || pool->d.head_dim != 128 || bytes < EN_GATHER_HUGE_BYTES ||
-        2 * cached < (bytes < EN_GATHER_HUGE_BYTES / 3 * 4 ? 4 : 3) * pl->distinct || saved < pl->selected * EN_ORDER_MIN_SAVED)
+        2 * cached < (bytes < EN_GATHER_HUGE_BYTES / 3 * 4 ? 4 : 3) * pl->distinct || double(saved) < double(pl->selected) * least)
+        return false;
+    int64_t segments = 0;
+    for (const int32_t n : pl->nseg)
+        segments += n;
+    if (pl->values_from_pool && cached * per_token * 256 < segments * EN_ORDER_MIN_KEYS)
         return false;
     groups.assign(size_t(pool->d.n_groups), EnGroupUse());
     for (int b = 0; b < pl->B; ++b) {
@@ -621,11 +633,12 @@ static bool gather_in_order(const en_plan *pl, std::vector<EnGroupUse> &groups)
 // 212, two of three groups of 1 - 2 K 503 / 594 / 335, 64 agents with eight of nine such groups 978 / 645 / 641.
 // These loops stand in front of the launch. They and the longer tables add to a step by itself, us: 64 agents x 64 groups
 // 18 (segments sorted, lists that grew entry by entry: 29), 130 x 120 42 (67), 512 x 60 of 1 head 138 (180).
-void en_gather_order(en_plan *pl)
+// queries: rows to prepare in the launches.
+void en_gather_order(en_plan *pl, int64_t queries)
 {
     std::vector<EnGroupUse> groups;
     pl->order_ints = 0;
-    if (!gather_in_order(pl, groups))
+    if (!gather_in_order(pl, queries, groups))
         return;
     const int sstr = std::max(pl->Smax, 1);
     int max_len = 0;
@@ -738,7 +751,7 @@ size_t en_plan_block_bytes(const en_plan *pl, size_t bytes)
 // gather kernel, which receives the image in its arguments, provided it is
 // small enough; *inlined says which way it went.
 static int plan_ensure_device(en_plan *pl, hipStream_t stream, bool inline_ok = false,
-                              bool *inlined = nullptr)
+                              bool *inlined = nullptr, int64_t queries = 0)
 {
     if (inlined)
         *inlined = false;
@@ -753,7 +766,7 @@ static int plan_ensure_device(en_plan *pl, hipStream_t stream, bool inline_ok = 
     const bool small = pl->h_desc.size() <= size_t(EN_INLINE_DESC_MAX), inline_it = inline_ok && small;
     pl->order_ints = 0;
     if (!small)
-        en_gather_order(pl);
+        en_gather_order(pl, queries);
     pl->acc_off = (pl->h_desc.size() + 1) & ~size_t(1);                   // 8-byte aligned
     const size_t n_all = pl->acc_off + 2 * size_t(pl->B) * (pl->Smax + 1);    // tables, then the accumulators
     const size_t bytes = n_all * sizeof(int32_t);
@@ -1000,7 +1013,8 @@ static int gather_common(en_pool *pool, en_plan *plan, const void *k_new_dev, co
     int rc;
     bool inlined = false;
     if ((rc = pool_ensure_device(pool)) != EN_OK ||
-        (rc = plan_ensure_device(plan, (hipStream_t)stream, true, &inlined)) != EN_OK)
+        (rc = plan_ensure_device(plan, (hipStream_t)stream, true, &inlined,
+                                 q_dev ? int64_t(plan->B) * plan->Nq * pool->d.n_q_heads : 0)) != EN_OK)
         return rc;
     EnGatherLaunch g;
     EnGatherArgs &a = g.a;

@@ -267,7 +267,7 @@ EnWsLayout en_ws_layout(const en_pool *pool, const en_plan *plan);
 EnWsLayout en_ws_layout_for(const en_pool *pool, const en_plan *plan, int n_rows, int n_splits);
 int en_attn_sub(const en_pool *pool, const en_plan *plan, int n_rows, int n_splits);
 // The order of a plan's gather, to the end of en_plan::h_desc.
-void en_gather_order(en_plan *plan);
+void en_gather_order(en_plan *plan, int64_t queries);
 size_t en_plan_block_bytes(const en_plan *plan, size_t bytes);
 
 // Kernel launchers (the .hip files). Return hipError_t as int.

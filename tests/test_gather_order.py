@@ -11,7 +11,7 @@ from paper_2510_18546_amd import binding as B
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 XCDS, TILE = 8, 64
 
-# reads: heads, groups, agents, new tokens, capacity, tokens per group, (groups, then their numbers) per agent,
+# reads: heads, query rows in all, keys only, groups, agents, new tokens, capacity, tokens per group, (groups, then their numbers) per agent,
 # -1: as the agent before
 DRIVER = '''
 #include <cstdio>
@@ -20,6 +20,7 @@ static int num() { int v = 0; if (scanf("%d", &v) != 1) v = -1; return v; }
 int main() {
     en_pool_desc d = {};
     d.n_kv_heads = d.n_q_heads = num();
+    const int queries = num(), keys_only = num();
     d.n_groups = num();
     const int agents = num(), n_new = num();
     d.capacity = num();
@@ -35,7 +36,8 @@ int main() {
     en_pool *pool = nullptr; en_plan *plan = nullptr;
     if (kv_pool_create(&d, (void *)256, (void *)256, len.data(), &pool) != EN_OK) return 1;
     if (segment_select(pool, agents, sel.data(), ptr.data(), n_new, &plan) != EN_OK) return 2;
-    en_gather_order(plan);
+    plan->values_from_pool = keys_only;
+    en_gather_order(plan, queries);
     if (plan->order_ints != plan->h_desc.size()) return 3;
     const size_t tables = plan->nseg.size() + plan->sel.size() + plan->bnd.size() + plan->hdr.size();
     printf("%d %d %zu", plan->order_ints > 0, plan->order_shift, en_plan_block_bytes(plan, 4 * (tables + plan->order_ints)));
@@ -60,8 +62,8 @@ def driver(tmp_path_factory):
     return str(exe)
 
 
-def run(driver, kv, lens, sel, n_new):
-    nums = [kv, len(lens), len(sel), n_new, max(1, int(max(lens)))] + [int(x) for x in lens]
+def run(driver, kv, lens, sel, n_new, queries=0, keys_only=0):
+    nums = [kv, queries, keys_only, len(lens), len(sel), n_new, max(1, int(max(lens)))] + [int(x) for x in lens]
     for b, s in enumerate(sel):
         nums += [-1] if b and s is sel[b - 1] else [len(s)] + [int(x) for x in s]
     out = subprocess.run([driver], input=" ".join(map(str, nums)), capture_output=True, text=True, check=True).stdout
@@ -162,7 +164,7 @@ def test_order_goes_by_the_tokens_that_agents_share(driver, agents, own, groups,
 
 def test_no_order_of_more_workgroups_than_a_launch_may_have(driver):
     """4.4 million entries of one tile where an entry is four tiles' workgroups: 17.6 million of them, 2^24 - 1 fit."""
-    nums = [1, 4000, 1100, 1, 256] + [64] * 3999 + [256] + [4000] + list(range(4000)) + [-1] * 1099
+    nums = [1, 0, 0, 4000, 1100, 1, 256] + [64] * 3999 + [256] + [4000] + list(range(4000)) + [-1] * 1099
     out = subprocess.run([driver], input=" ".join(map(str, nums)), capture_output=True, text=True, check=True).stdout
     assert out.split()[0] == "0" and len(out.split()) == 3
 
@@ -174,3 +176,15 @@ def test_a_planner_of_one_kind_of_step_allocates_its_device_block_once(driver):
     out = [run(driver, 8, lens, picks(rng, 200, 48, 30), 1) for _ in range(12)]
     assert all(o[0] for o in out) and len({len(o) for o in out}) > 3
     assert len({int(o[2]) for o in out}) == 1
+
+
+# 64 agents, 8 heads, 32 new tokens: 256 query rows of each for 4 K tokens of 2 x 8 rows are 0.12 of the rows
+@pytest.mark.parametrize("tokens,agents_a_group,queries,keys_only,want", [
+    (96, 3, 0, 0, True), (96, 2.6, 64 * 256 * 32, 0, False), (96, 8, 64 * 256 * 32, 0, True), (256, 3, 64 * 256 * 32, 0, True),
+    (48, 2.2, 0, 0, False), (96, 4.2, 0, 1, True), (96, 2.6, 0, 1, False), (256, 2.6, 64 * 256 * 32, 1, False), (64, 30, 0, 1, False),
+    (64, 30, 0, 0, True)])
+def test_the_order_has_to_save_more_beside_queries_and_of_keys_only(driver, tokens, agents_a_group, queries, keys_only, want):
+    rng = np.random.default_rng(tokens)
+    per = 4096 // tokens
+    groups = int(64 * per / agents_a_group)
+    assert run(driver, 8, [tokens] * groups, picks(rng, groups, 64, per), 32, queries, keys_only)[0] == want
