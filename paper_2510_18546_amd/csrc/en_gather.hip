@@ -480,7 +480,10 @@ __device__ __forceinline__ EnCtxLoc context_loc(const EnGatherArgs &a, const EnG
 }
 
 // The key rows of HPB heads, kv0 onwards: where the row comes from, its cosines and sines once for all of them, and
-// the codes of all of them on their way before the first are turned and stored.
+// the codes of all of them on their way before the first are turned and stored. The codes are asked for first, the cosines
+// and sines behind them (with nothing in the caches 24 agents x 2 K tokens of 2 heads of 64 values 14.0 / 13.7 us, 8 x 6 K
+// 17.1 / 16.8), of a single head of 128 values when its codes have come: 3 agents x 2 K tokens 12.2 / 11.7, one agent's
+// 24 K of 2 heads 15.1 / 14.9, 6 K of 8 heads 13.2 / 13.0, but its 0.5 K of 2 heads 4.24 / 4.36.
 template <int D, int HPB, bool STREAM>
 __device__ __forceinline__ void gather_q8_k_rows(const EnGatherArgs &a, const EnGatherTables &tabs, int b, int tok,
                                                  int kv0, int32_t *lds)
@@ -506,11 +509,19 @@ __device__ __forceinline__ void gather_q8_k_rows(const EnGatherArgs &a, const En
             store(h, 0.f, 0.f);
         return;
     }
-    const fvec cs = *reinterpret_cast<const fvec *>(a.cos_tab + (size_t)tok * (D / 2) + c * E);
-    const fvec sn = *reinterpret_cast<const fvec *>(a.sin_tab + (size_t)tok * (D / 2) + c * E);
-    if (loc.kind == 1) {
-        int8_t c1[HPB][E], c2[HPB][E];
-        float sc[HPB];
+    fvec cs, sn;
+    auto angles = [&] {
+        cs = *reinterpret_cast<const fvec *>(a.cos_tab + (size_t)tok * (D / 2) + c * E);
+        sn = *reinterpret_cast<const fvec *>(a.sin_tab + (size_t)tok * (D / 2) + c * E);
+    };
+    auto turn = [&](int h, fvec x1, fvec x2) {
+        fvec y1, y2;
+        rope_key_pair<true>(x1, x2, cs, sn, y1, y2);
+        store(h, y1, y2);
+    };
+    int8_t c1[HPB][E], c2[HPB][E];
+    float sc[HPB];
+    auto codes = [&] {
 #pragma unroll
         for (int h = 0; h < HPB; ++h) {
             const size_t row = loc.row + (size_t)h * a.C;
@@ -519,28 +530,48 @@ __device__ __forceinline__ void gather_q8_k_rows(const EnGatherArgs &a, const En
             __builtin_memcpy(c2[h], src + D / 2 + c * E, E);
             sc[h] = a.k_scale[row];
         }
+    };
+    auto scaled = [&](int h, fvec &x1, fvec &x2) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            x1[e] = (float)c1[h][e] * sc[h];
+            x2[e] = (float)c2[h][e] * sc[h];
+        }
+    };
+    auto fresh = [&](int h, fvec &x1, fvec &x2) {
+        const bf16_t *src = (const bf16_t *)a.k_new + (loc.row + h) * D;
+        x1 = __builtin_convertvector(*reinterpret_cast<const tvec *>(src + c * E), fvec);
+        x2 = __builtin_convertvector(*reinterpret_cast<const tvec *>(src + D / 2 + c * E), fvec);
+    };
+    if constexpr (HPB == 1 && D == 128) {
+        fvec x1, x2;
+        if (loc.kind == 1) {
+            codes();
+            scaled(0, x1, x2);
+        } else {
+            fresh(0, x1, x2);
+        }
+        asm volatile("" : "+v"(x1), "+v"(x2)::"memory");          // (before the angles)
+        angles();
+        turn(0, x1, x2);
+    } else if (loc.kind == 1) {
+        codes();
+        angles();
         if constexpr (HPB > 1)
             asm volatile("" ::: "memory");             // (not behind the stores)
 #pragma unroll
         for (int h = 0; h < HPB; ++h) {
-            fvec x1, x2, y1, y2;
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                x1[e] = (float)c1[h][e] * sc[h];
-                x2[e] = (float)c2[h][e] * sc[h];
-            }
-            rope_key_pair<true>(x1, x2, cs, sn, y1, y2);
-            store(h, y1, y2);
+            fvec x1, x2;
+            scaled(h, x1, x2);
+            turn(h, x1, x2);
         }
     } else {
+        angles();
 #pragma unroll
         for (int h = 0; h < HPB; ++h) {
-            const bf16_t *src = (const bf16_t *)a.k_new + (loc.row + h) * D;
-            const fvec x1 = __builtin_convertvector(*reinterpret_cast<const tvec *>(src + c * E), fvec);
-            const fvec x2 = __builtin_convertvector(*reinterpret_cast<const tvec *>(src + D / 2 + c * E), fvec);
-            fvec y1, y2;
-            rope_key_pair<true>(x1, x2, cs, sn, y1, y2);
-            store(h, y1, y2);
+            fvec x1, x2;
+            fresh(h, x1, x2);
+            turn(h, x1, x2);
         }
     }
 }
@@ -903,14 +934,17 @@ static void launch_gather_kernel(bool ahead, int hpb, dim3 grid, hipStream_t st,
 }
 
 // Heads per unit of the gather from 8-bit pools: four where the context goes past the caches and the launch is many
-// rounds of workgroups, two from 16 (tile, head) units per compute unit on (about two rounds), one below. Gather and
+// rounds of workgroups, two from 16 or 18 (tile, head) units per compute unit on (about two rounds), one below. Gather and
 // attention, us, with one / two / four / eight heads: 64 agents x 16 K tokens 2316 / 2116 / 1984 / 1976, rows of 64
 // values 1233 / 1101 / 1044 / 1011, 32 x 6 K 430 / 406 / 399 / 409, 16 x 14 K 532 / 502 / 486 / 491; kept in the
 // caches 16 x 2 K (9000 units) 138.4 / 136.1 / 138.2 / 145.0, rows of 64 values 84.0 / 80.9 / 82.5 / 83.9; 3600 units
-// 56.5 / 57.5 / 56.7 / 61.0, 2200: 90.4 / 90.7 / 92.9 / 98.9, 450: 38.1 / 39.1 / 42.6 / 49.4.
+// 56.5 / 57.5 / 56.7 / 61.0, 2200: 90.4 / 90.7 / 92.9 / 98.9, 450: 38.1 / 39.1 / 42.6 / 49.4. Rows of 128 values from 18
+// units on: the gather with nothing in the caches, one / two heads, 4096 units 25.9 / 27.2, 4800: 31.6 / 30.3; rows of
+// 64, 4096 units: 0.93 of the time with two.
 static int gather_heads_q8(const en_pool *pool, const EnGatherArgs &a, int n_tiles)
 {
-    int hpb = a.stream ? 4 : 2L * a.Hkv * n_tiles * a.B >= 16L * pool->n_cu ? 2 : 1;
+    const long line = pool->d.head_dim == 128 ? 18 : 16;
+    int hpb = a.stream ? 4 : 2L * a.Hkv * n_tiles * a.B >= line * pool->n_cu ? 2 : 1;
     while (a.Hkv % hpb)
         hpb /= 2;
     return hpb;

@@ -49,9 +49,11 @@ def route(plan, kv, lens, sel, n_new, q_heads, from_pool):
     tokens, used = sum(cached) + agents * n_new, np.bincount(np.concatenate(sel), minlength=len(lens))
     size = 512 * agents * kv * plan.info.ctx_stride
     distinct, own = lens[used > 0].sum(), agents * n_new + lens[used == 1].sum()
-    order = (size >= 768 << 20 and 3 * own <= tokens and (sum(cached) - distinct) * kv * 512 >= 400000 * (used > 0).sum() and
-             sum(cached) >= (2 if size < 1 << 30 else 1.5) * distinct)
     stream, rows, queries = size > 256 << 20, tokens * kv * (1 if from_pool else 2), agents * n_new * q_heads
+    saved = (sum(cached) - distinct) * kv * (256 if from_pool else 512)
+    order = (size >= 768 << 20 and 3 * own <= tokens and saved >= 400000 * (used > 0).sum() * (1 + 10 * queries / rows) and
+             sum(cached) >= (2 if size < 1 << 30 else 1.5) * distinct and
+             not (from_pool and sum(cached) * kv * 256 < 160000 * sum(map(len, sel))))
     heads = 2 if not stream and (1 if from_pool else 2) * kv * tiles * agents > 32 * n_cu() else 8 if 6 * queries < rows else 4
     while heads > 1 and (kv % heads or 4 * (1 if from_pool else 2) * kv * tiles * agents < 5 * heads * n_cu()):
         heads //= 2
@@ -108,7 +110,7 @@ def test_same_contexts_as_one_by_one(agents, kv, groups, cap, lo, hi, picks, n_n
 # together, one for each by itself
 @pytest.mark.parametrize("agents,kv,d,cap,n_new,heads", [
     (9, 8, 128, 130, 70, 4), (17, 2, 128, 256, 1, 2), (18, 6, 64, 200, 33, 2), (25, 3, 128, 130, 70, 1), (30, 4, 64, 200, 130, 4),
-    (2, 8, 128, 130, 40, 2), (4, 6, 64, 130, 129, 2), (2, 8, 64, 130, 1, 2)])
+    (3, 8, 128, 130, 40, 2), (4, 6, 64, 130, 129, 2), (2, 8, 64, 130, 1, 2)])
 def test_same_contexts_from_8_bit_pools(agents, kv, d, cap, n_new, heads):
     import torch
     rng = np.random.default_rng(agents)
@@ -126,7 +128,7 @@ def test_same_contexts_from_8_bit_pools(agents, kv, d, cap, n_new, heads):
     plan, kc, vt, q_prep = gather(pool, sel, k_new, v_new, q, False)
     T = plan.info.ctx_stride
     past = 4 * agents * kv * T * d > 256 << 20
-    assert heads == max(h for h in (1, 2, 4) if h == 1 or kv % h == 0 and (past if h == 4 else past or 2 * kv * T // 64 * agents >= 16 * n_cu()))
+    assert heads == max(h for h in (1, 2, 4) if h == 1 or kv % h == 0 and (past if h == 4 else past or 2 * kv * T // 64 * agents >= (18 if d == 128 else 16) * n_cu()))
     kc, vt = kc.view(agents, kv, T, d), vt.view(agents, kv, d, T)
     # the values of agent 0 are code x scale in float32, rounded once; token j in the column with its bits 2 and 3 exchanged
     rows = torch.from_numpy(np.concatenate([g * cap + np.arange(lens[g]) for g in sel[0]])).cuda()
