@@ -124,9 +124,8 @@ __device__ __forceinline__ void gather_k_rows(const EnGatherArgs &a, int b, int 
     // Four of eight at a time then (two: the ordered gather of 64 agents x 16 K tokens takes 1 % longer, that of 32
     // agents 3 %).
     constexpr int HU = AHEAD && HPB == 8 ? 4 : HPB < 2 ? HPB : 2;
-    // (without AHEAD the heads of a unit are those that en_rope_unit goes by; with it, a launch of single heads is far
-    // smaller than one that has such units)
-    const int rope_unit = !AHEAD ? en_rope_unit(sizeof(T), D, HPB) : HPB > 1 ? a.rope_unit : 0;
+    // (without AHEAD the heads of a unit are those that en_rope_unit goes by)
+    const int rope_unit = AHEAD ? a.rope_unit : en_rope_unit(sizeof(T), D, HPB);
     tvec x1[HU], x2[HU];
     auto load = [&](int h0) {
         if (ksrc) {
@@ -859,14 +858,18 @@ struct EnGatherRows {
     long queries, keys_values;
 };
 
-// Heads per unit with AHEAD: as many as leave 1.25 workgroups per compute unit. Three (of eight heads) to five fit one, so
-// where eight heads make more of them than four each, a last round of long workgroups would run alone: two heads then,
-// unless the context is so long (past the caches) that many rounds follow each other. Gather and attention, us, with one /
-// two / four / eight heads: 137 tiles (of 8 heads) 88.8 / 88.6 / 88.9 / 90.3, 194: 56.7 / 55.5 / 53.0 / 50.9, 390: 85.0 /
-// 81.0 / 79.6 / 80.1, 528: 129.2 / 125.7 / 127.3 / 129.7, 784: 130.2 / 130.7 / 133.0 / 135.2; past the caches 1300
-// tiles 233 / 228 / 217 / 214, 6200: 965 / 840 / 823 / 805. With changing inputs (nothing of the pool left in the
-// last-level cache) 136 tiles, keys only, 69.5 / 68.9 / 68.8 / 72.3, 28 tiles 32.1 / 32.1 / 32.7 / 35.6, 235: 97.0 /
-// 95.5 / 93.0 / 92.7.
+// Heads per unit with AHEAD: at most as many as leave 1.25 workgroups per compute unit, and
+// - past the caches, where many rounds of workgroups follow each other, eight: gather and attention, us, with one / two /
+//   four / eight heads, 1300 tiles (of 8 heads) 233 / 228 / 217 / 214, 6200: 965 / 840 / 823 / 805;
+// - two where eight would be more than four workgroups per compute unit (three, of eight heads, to five fit one), the last
+//   round of them alone: 528 tiles 129.2 / 125.7 / 127.3 / 129.7, 784: 130.2 / 130.7 / 133.0 / 135.2;
+// - else one for contexts of under 24 tiles, two of six agents and more with under 60, four of three agents and more:
+//   many short runs through memory gain by neither. The gather with nothing in the caches, one / two / four / eight heads:
+//   24 agents x 3 runs (9 tiles) 20.2 / 20.3 / 20.4 / 22.3, 24 x 18 tiles of 2 heads 12.4 / 14.5, of 4 heads 20.4 / 21.1 /
+//   23.3, 6 x 33 tiles 21.7 / 22.9 / 23.9 / 24.8, 12 x 32 34.8 / 32.8 / 34.3 / 34.1 (but 12 x 16 21.1 / 21.8 / 20.1 / 19.9),
+//   4 x 104: 0.96 / 0.93 / 0.97 / 1.03 of the time without loads ahead, 8 x 107 of 4 heads 49.8 / 42.7 / 41.1, one agent's
+//   201 28.1 / 24.7 / 25.0 / 24.6; in them, with the attention, 2 x 97 56.7 / 55.5 / 53.0 / 50.9, one agent's 137 88.8 / 88.6
+//   / 88.9 / 90.3.
 // With one query row to six of keys and values and more, at most four: eight heads are 132 registers, three workgroups to
 // a compute unit, four are 96 and five, and queries prepared beside them want the more. The gather, us, with eight / four:
 // 64 agents with 512 new tokens of 2.3 K, keys only (0.44 to 1) 228 / 209, with values (0.22) 318 / 310, 16 of 4.1 K, keys
@@ -876,8 +879,16 @@ static int gather_heads_ahead(const en_pool *pool, const EnGatherArgs &a, const 
 {
     int hpb = 6 * rows.queries < rows.keys_values ? 8 : 4;
     const long work = (a.v_rows ? 1L : 2L) * a.Hkv * n_tiles * a.B;                  // (tile, head), keys and values
-    if (!a.stream && work > 8 * 4L * pool->n_cu)
-        hpb = 2;
+    if (!a.stream) {
+        if (work > 8 * 4L * pool->n_cu)
+            hpb = 2;
+        else if (n_tiles < 24)
+            hpb = 1;
+        else if (a.B >= 6 && n_tiles < 60)
+            hpb = 2;
+        else if (a.B > 2)
+            hpb = 4;
+    }
     while (hpb > 1 && (a.Hkv % hpb || 4 * work < 5L * hpb * pool->n_cu))
         hpb /= 2;
     return hpb;

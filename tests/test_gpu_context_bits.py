@@ -33,11 +33,13 @@ def bf16(x):
 @pytest.mark.parametrize("dtype,kv,agents,d", [
     ("f32", 1, 1, 64), ("f32", 2, 3, 128), ("bf16", 1, 1, 128), ("bf16", 3, 1, 64), ("bf16", 2, 256, 64),
     ("bf16", 4, 140, 128), ("bf16", 4, 140, 64), ("bf16", 8, 72, 128), ("bf16", 8, 72, 64), ("f32", 4, 600, 64),
-    ("bf16", 8, 3, 128), ("bf16", 2, 1000, 128), ("bf16", 4, 500, 128), ("bf16", 8, 250, 128), ("i8", 2, 2, 128), ("i8", 1, 2, 64)])
+    ("bf16", 8, 3, 128), ("bf16", 2, 1000, 128), ("bf16", 4, 500, 128), ("bf16", 8, 250, 128), ("keys only", 4, 130, 128), ("i8", 2, 2, 128),
+    ("i8", 1, 2, 64)])
 def test_rotated_keys(dtype, kv, agents, d):
-    """agents: enough for 2, 4 and 8 heads a unit (32 workgroups for each of 256 compute units), then for 768 MB of keys and
+    """keys only: bf16, the values left in the pool, which take one head a workgroup there. agents: enough for 2, 4 and 8 heads a unit (32 workgroups for each of 256 compute units), then for 768 MB of keys and
     values, which are gathered in the order of the groups."""
     import torch
+    keys_only, dtype = dtype == "keys only", "bf16" if dtype == "keys only" else dtype
     rng = np.random.default_rng(agents + d)
     g_n, cap, s_n, n_new, base = 12, 96, 9, 34, 1e4
     dev, bits16 = "cuda:0", dtype != "f32"
@@ -57,6 +59,9 @@ def test_rotated_keys(dtype, kv, agents, d):
     sel = [rng.choice(g_n, s_n, replace=False).astype(np.int32) for _ in range(agents)]
     plan = B.segment_select(pool, np.concatenate(sel), np.arange(agents + 1) * s_n, n_new)
     assert (agents in (250, 500, 1000)) == (dtype == "bf16" and 4 * agents * kv * plan.info.ctx_stride * d >= 768 << 20)
+    if keys_only:
+        plan.values_from_pool(True)
+        assert 5 * (kv // 4) * plan.info.ctx_stride // 64 * agents >= 32 * 256 > kv * plan.info.ctx_stride // 64 * agents
     k_new = torch.from_numpy(rng.standard_normal((agents, n_new, kv, d)).astype(np.float32)).to(act).to(dev)
     kc, vt = B.alloc_context(pool, plan)
     B.gather_rope(pool, plan, k_new, k_new, kc, vt)

@@ -54,8 +54,11 @@ def route(plan, kv, lens, sel, n_new, q_heads, from_pool):
     order = (size >= 768 << 20 and 3 * own <= tokens and saved >= 400000 * (used > 0).sum() * (1 + 10 * queries / rows) and
              sum(cached) >= (2 if size < 1 << 30 else 1.5) * distinct and
              not (from_pool and sum(cached) * kv * 256 < 160000 * sum(map(len, sel))))
-    heads = 2 if not stream and (1 if from_pool else 2) * kv * tiles * agents > 32 * n_cu() else 8 if 6 * queries < rows else 4
-    while heads > 1 and (kv % heads or 4 * (1 if from_pool else 2) * kv * tiles * agents < 5 * heads * n_cu()):
+    work = (1 if from_pool else 2) * kv * tiles * agents
+    heads = 8 if 6 * queries < rows else 4
+    if not stream:
+        heads = 2 if work > 32 * n_cu() else 1 if tiles < 24 else 2 if agents >= 6 and tiles < 60 else 4 if agents > 2 else heads
+    while heads > 1 and (kv % heads or 4 * work < 5 * heads * n_cu()):
         heads //= 2
     if (order or size < 768 << 20) and (heads == 1 or 2 * queries < (3 if stream else 2) * rows):
         return order, stream, heads, True
@@ -70,9 +73,10 @@ def route(plan, kv, lens, sel, n_new, q_heads, from_pool):
     (40, 3, 90, 512, 300, 512, 48, 70, False, (True, True, 1, True)), (100, 1, 80, 1000, 500, 1000, 70, 5, False, (True, True, 1, True)),
     (130, 8, 130, 32, 1, 32, 120, 64, False, (True, True, 4, True)), (90, 2, 60, 256, 200, 256, 50, 5, False, (True, True, 2, True)),
     (14, 8, 700, 512, 300, 512, 42, 5, False, (False, True, 8, False)), (60, 2, 3000, 512, 300, 512, 42, 33, True, (False, True, 2, False)),
-    (25, 8, 30, 70, 30, 70, 20, 129, False, (False, False, 4, True)), (4, 8, 64, 130, 60, 130, 40, 100, False, (False, False, 4, True)),
+    (25, 8, 30, 70, 30, 70, 20, 129, False, (False, False, 1, True)), (4, 8, 64, 130, 60, 130, 40, 100, False, (False, False, 4, True)),
     (3, 2, 40, 64, 10, 64, 33, 17, False, (False, False, 1, True)), (30, 8, 60, 130, 100, 130, 14, 1, False, (False, False, 2, True)),
-    (30, 8, 64, 64, 30, 64, 8, 512, False, (False, False, 1, False)), (64, 8, 64, 30, 1, 30, 2, 900, False, (False, False, 8, False)),
+    (30, 8, 64, 64, 30, 64, 8, 512, False, (False, False, 1, True)), (3, 8, 40, 130, 100, 130, 30, 129, False, (False, False, 4, True)),
+    (1, 8, 170, 200, 150, 200, 160, 5, False, (False, False, 8, True)), (7, 8, 60, 130, 100, 130, 20, 1, False, (False, False, 2, True)), (64, 8, 64, 30, 1, 30, 2, 900, False, (False, False, 8, False)),
     (190, 2, 64, 30, 1, 30, 2, 900, False, (False, False, 2, False)), (100, 8, 40, 64, 30, 64, 40, 500, True, (False, True, 8, False))])
 def test_same_contexts_as_one_by_one(agents, kv, groups, cap, lo, hi, picks, n_new, from_pool, how):
     import torch
