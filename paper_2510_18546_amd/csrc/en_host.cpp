@@ -566,6 +566,7 @@ static bool gather_past_caches(const en_pool *pool, const en_plan *pl)
     return 2 * en_context_bytes(pool, pl) > EN_LAST_LEVEL_CACHE_BYTES;
 }
 
+static inline uint32_t tile_at(int32_t token) { return uint32_t(token + EN_KEY_TILE - 1) / EN_KEY_TILE; }   // first one from there on
 struct EnGroupUse {
     int32_t len = 0, agents = 0;       // tokens, agents of the plan that select it
     uint32_t first = 0;                // number of its first piece, see en_gather_order
@@ -594,7 +595,8 @@ struct EnGroupUse {
 // 16 x 14 K of 5.1 493 / 538. Plans whose tables travel in the launch's arguments stay as they are: the order would need a
 // copy of its own.
 constexpr int64_t EN_ORDER_MIN_SAVED = 400000, EN_ORDER_MIN_KEYS = 160000;
-static bool gather_in_order(const en_plan *pl, int64_t queries, std::vector<EnGroupUse> &groups)
+// (slots: tiles of the segments rounded up to one, two, four.)
+static bool gather_in_order(const en_plan *pl, int64_t queries, std::vector<EnGroupUse> &groups, size_t (&slots)[3])
 {
     const en_pool *pool = pl->pool;
     const size_t bytes = 2 * en_context_bytes(pool, pl);
@@ -613,10 +615,16 @@ static bool gather_in_order(const en_plan *pl, int64_t queries, std::vector<EnGr
     groups.assign(size_t(pool->d.n_groups), EnGroupUse());
     for (int b = 0; b < pl->B; ++b) {
         const int32_t *sel = &pl->sel[size_t(b) * std::max(pl->Smax, 1)], *bnd = &pl->bnd[size_t(b) * (pl->Smax + 2)];
+        uint32_t t0 = 0;
         for (int s = 0; s < pl->nseg[b]; ++s) {
             EnGroupUse &g = groups[sel[s]];
             g.len = bnd[s + 1] - bnd[s];
             ++g.agents;
+            const uint32_t t1 = tile_at(bnd[s + 1]), n = t1 - t0;
+            slots[0] += n;
+            slots[1] += (n + 1) & ~1u;
+            slots[2] += (n + 3) & ~3u;
+            t0 = t1;
         }
     }
     int64_t own = int64_t(pl->B) * pl->Nq;
@@ -632,21 +640,24 @@ static bool gather_in_order(const en_plan *pl, int64_t queries, std::vector<EnGr
 // us, agent by agent / whole groups on one XCD / their pieces: 128 agents that share one group of 2 K tokens 325 / 905 /
 // 212, two of three groups of 1 - 2 K 503 / 594 / 335, 64 agents with eight of nine such groups 978 / 645 / 641.
 // These loops stand in front of the launch. They and the longer tables add to a step by itself, us: 64 agents x 64 groups
-// 18 (segments sorted, lists that grew entry by entry: 29), 130 x 120 42 (67), 512 x 60 of 1 head 138 (180).
+// 20 (segments sorted, lists that grew entry by entry: 29), 130 x 120 49 (67), 512 x 60 of 1 head 150 (180).
 // queries: rows to prepare in the launches.
 void en_gather_order(en_plan *pl, int64_t queries)
 {
     std::vector<EnGroupUse> groups;
+    size_t slots[3] = {};
     pl->order_ints = 0;
-    if (!gather_in_order(pl, queries, groups))
+    if (!gather_in_order(pl, queries, groups, slots))
         return;
     const int sstr = std::max(pl->Smax, 1);
-    int max_len = 0;
-    for (const EnGroupUse &g : groups)
-        max_len = std::max(max_len, g.len);
-    const int shift = max_len > 2 * EN_KEY_TILE ? 2 : max_len > EN_KEY_TILE ? 1 : 0;
+    // An entry is a workgroup per unit for each of its `most` tiles, also for those that a segment's last entry does not
+    // have, and the idle ones are not free: the largest entries of which at most an eighth is idle, with fewer than four
+    // heads, where the workgroups are small beside the host's time for an entry, a third (the gather with nothing in the
+    // caches, agent by agent / entries by the longest group / these: 64 agents, 950 MB, 2.4 agents a group, groups of 56 -
+    // 136 tokens 299 / 465 / 262 us, 120 - 200 tokens 298 / 321 / 256, 184 - 264 301 / 264 / 258).
+    const size_t allowed = pl->pool->d.n_kv_heads < 4 ? 12 : 9;
+    const int shift = 8 * slots[2] <= allowed * slots[0] ? 2 : 8 * slots[1] <= allowed * slots[0] ? 1 : 0;
     const uint32_t most = 1u << shift;               // tiles per entry
-    const auto tile_at = [](int32_t token) { return uint32_t(token + EN_KEY_TILE - 1) / EN_KEY_TILE; };   // first one from there on
     uint32_t n_pieces = 0;
     for (EnGroupUse &g : groups) {
         g.first = n_pieces;

@@ -96,6 +96,11 @@ def busiest(lists):
     return max(tiles) * XCDS / sum(tiles)
 
 
+def idle(most, lists):
+    """Workgroups without a tile, as a share of those with one."""
+    return most * max(map(len, lists)) * XCDS / sum(k for l in lists for _, _, k in l) - 1
+
+
 def picks(rng, groups, agents, n):
     return [rng.choice(groups, n, replace=False) for _ in range(agents)]
 
@@ -163,8 +168,8 @@ def test_order_goes_by_the_tokens_that_agents_share(driver, agents, own, groups,
 
 
 def test_no_order_of_more_workgroups_than_a_launch_may_have(driver):
-    """4.4 million entries of one tile where an entry is four tiles' workgroups: 17.6 million of them, 2^24 - 1 fit."""
-    nums = [1, 0, 0, 4000, 1100, 1, 256] + [64] * 3999 + [256] + [4000] + list(range(4000)) + [-1] * 1099
+    """4.4 million entries of three tiles, four tiles' workgroups each: 17.6 million of them, 2^24 - 1 fit."""
+    nums = [1, 0, 0, 4000, 1100, 1, 192] + [192] * 4000 + [4000] + list(range(4000)) + [-1] * 1099
     out = subprocess.run([driver], input=" ".join(map(str, nums)), capture_output=True, text=True, check=True).stdout
     assert out.split()[0] == "0" and len(out.split()) == 3
 
@@ -188,3 +193,17 @@ def test_the_order_has_to_save_more_beside_queries_and_of_keys_only(driver, toke
     per = 4096 // tokens
     groups = int(64 * per / agents_a_group)
     assert run(driver, 8, [tokens] * groups, picks(rng, groups, 64, per), 32, queries, keys_only)[0] == want
+
+
+@pytest.mark.parametrize("kv,lo,hi,most", [(8, 56, 136, 1), (8, 120, 200, 1), (8, 250, 256, 4), (8, 256, 256, 4), (8, 128, 128, 2),
+                                           (2, 64, 128, 2), (2, 48, 48, 1)])
+def test_entries_leave_few_workgroups_idle(driver, kv, lo, hi, most):
+    """Also where one group is longer than most."""
+    rng = np.random.default_rng(lo)
+    per = 5000 // hi
+    lens = rng.integers(lo, hi + 1, 16 * per)
+    lens[0] = 300
+    in_order, got, lists, piece = order(driver, kv, lens, picks(rng, 16 * per, 512 // kv, per), 1)
+    assert in_order and got == most
+    check_once(lists, piece, got)
+    assert idle(got, lists) <= (0.2 if kv > 2 else 0.55)
