@@ -213,19 +213,33 @@ __device__ __forceinline__ float pair_max(float v)
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
-// Sum over the 32 lanes of each half of the wave, in every lane of the half: four steps inside the
-// rows of 16 lanes in the vector ALU (data-parallel primitives), one exchange between the two rows.
-__device__ __forceinline__ float half_sum(float v)
+// v of all lanes of a group of N = 4, 16 or 32 neighbours taken together by `op`, in each of them: steps inside the rows of
+// 16 lanes in the vector ALU (data-parallel primitives), one exchange between two rows.
+template <int N, typename F>
+__device__ __forceinline__ float lanes_reduce(float v, F op)
 {
     auto dpp = [](float x, auto ctrl) {
         return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), decltype(ctrl)::value, 0xf, 0xf, false));
     };
-    v += dpp(v, std::integral_constant<int, 0xB1>{});      // quad_perm [1, 0, 3, 2]
-    v += dpp(v, std::integral_constant<int, 0x4E>{});      // quad_perm [2, 3, 0, 1]
-    v += dpp(v, std::integral_constant<int, 0x141>{});     // row_half_mirror
-    v += dpp(v, std::integral_constant<int, 0x140>{});     // row_mirror
-    v += __shfl_xor(v, 16, 64);
+    static_assert(N == 4 || N == 16 || N == 32, "lanes of a group");
+    v = op(v, dpp(v, std::integral_constant<int, 0xB1>{}));          // quad_perm [1, 0, 3, 2]
+    v = op(v, dpp(v, std::integral_constant<int, 0x4E>{}));          // quad_perm [2, 3, 0, 1]
+    if constexpr (N >= 16) {
+        v = op(v, dpp(v, std::integral_constant<int, 0x141>{}));     // row_half_mirror
+        v = op(v, dpp(v, std::integral_constant<int, 0x140>{}));     // row_mirror
+    }
+    if constexpr (N == 32) {
+        typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+        const u32x2 x = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = op(__uint_as_float(x[0]), __uint_as_float(x[1]));
+    }
     return v;
+}
+
+// Sum over the 32 lanes of each half of the wave, in every lane of the half.
+__device__ __forceinline__ float half_sum(float v)
+{
+    return lanes_reduce<32>(v, [](float x, float y) { return x + y; });
 }
 
 __device__ __forceinline__ float wave_max(float v)

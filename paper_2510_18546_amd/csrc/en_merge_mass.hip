@@ -31,10 +31,11 @@ __host__ inline int mass_partial_blocks(const EnMassArgs &m)
 
 // With many splits (decode over a long context by few agents) G = 4, 16 or 32 neighbouring lanes
 // share a (row, 16-byte chunk): lane g takes the splits g, g + G, ... and the G partial results
-// are merged with lane shuffles, so that the chain of dependent loads is 1/G as long (with 16
+// are merged among the lanes, so that the chain of dependent loads is 1/G as long (with 16
 // lanes, up to 64 splits are one batch of loads) and the few rows of such a step make G times
-// as many workgroups.
-template <typename T, int D, int G>
+// as many workgroups. NB: splits per lane and batch, no more than there are (eight of which six are the
+// first one again: a decode step over 0.4 K tokens, 7 splits, 9.4 us with the merge, 8.2 with two; 26 splits 12.7, 11.8).
+template <typename T, int D, int G, int NB>
 __global__ __launch_bounds__(256) void combine_kernel(EnAttnArgs a, EnMassArgs m, int n_comb)
 {
     // head of the grid (these workgroups take longest: they start first): the reduced masses, where
@@ -59,7 +60,6 @@ __global__ __launch_bounds__(256) void combine_kernel(EnAttnArgs a, EnMassArgs m
     // The splits are read in batches of independent loads, (reference, sum) pairs and outputs
     // together, and merged batch by batch with a running reference: read one after the other,
     // the latencies of 2 * n_splits dependent loads are what this kernel would take.
-    constexpr int NB = G == 4 ? 8 : 4;
     float M = EN_NEG_INF, l = 0.f;
     fvec acc = 0.f;
     for (int sp0 = g; sp0 < a.n_splits; sp0 += NB * G) {
@@ -93,21 +93,18 @@ __global__ __launch_bounds__(256) void combine_kernel(EnAttnArgs a, EnMassArgs m
         }
     }
     if constexpr (G > 1) {
-        float Mall = M;
-#pragma unroll
-        for (int o = 1; o < G; o <<= 1)
-            Mall = fmaxf(Mall, __shfl_xor(Mall, o, 64));
+        // (in the vector ALU: data-parallel primitives; through the LDS crossbar the 40 exchanges of 16 lanes are a chain
+        // of four trips)
+        const float Mall = lanes_reduce<G>(M, [](float x, float y) { return fmaxf(x, y); });
         const float keep = M == EN_NEG_INF ? 0.f : fast_exp2(M - Mall);
         l *= keep;
         acc *= keep;
         M = Mall;
+        const auto plus = [](float x, float y) { return x + y; };
+        l = lanes_reduce<G>(l, plus);
 #pragma unroll
-        for (int o = 1; o < G; o <<= 1) {
-            l += __shfl_xor(l, o, 64);
-#pragma unroll
-            for (int e = 0; e < V; ++e)
-                acc[e] += __shfl_xor(acc[e], o, 64);
-        }
+        for (int e = 0; e < V; ++e)
+            acc[e] = lanes_reduce<G>(acc[e], plus);
         if (g != 0)
             return;
     }
@@ -649,16 +646,22 @@ int en_launch_combine(const en_pool *pool, const EnAttnArgs &a, const EnMassArgs
     const int n_comb = (int)((n + 255) / 256);
     const int n_part = m.red_out && !m.few ? mass_partial_blocks(m) : 0;
     const dim3 grid((unsigned)(n_comb + n_part)), blk(256);
-#define EN_COMBINE(T, DD)                                                                             \
-    do {                                                                                              \
-        if (G == 1)                                                                                   \
-            hipLaunchKernelGGL((combine_kernel<T, DD, 1>), grid, blk, 0, st, a, m, n_comb);           \
-        else if (G == 4)                                                                              \
-            hipLaunchKernelGGL((combine_kernel<T, DD, 4>), grid, blk, 0, st, a, m, n_comb);           \
-        else if (G == 16)                                                                             \
-            hipLaunchKernelGGL((combine_kernel<T, DD, 16>), grid, blk, 0, st, a, m, n_comb);          \
-        else                                                                                          \
-            hipLaunchKernelGGL((combine_kernel<T, DD, 32>), grid, blk, 0, st, a, m, n_comb);          \
+#define EN_COMBINE(T, DD)                                                                                    \
+    do {                                                                                                     \
+        if (G == 1)                                                                                          \
+            hipLaunchKernelGGL((combine_kernel<T, DD, 1, 4>), grid, blk, 0, st, a, m, n_comb);               \
+        else if (G == 4 && a.n_splits <= 8)                                                                  \
+            hipLaunchKernelGGL((combine_kernel<T, DD, 4, 2>), grid, blk, 0, st, a, m, n_comb);               \
+        else if (G == 4 && a.n_splits <= 16)                                                                 \
+            hipLaunchKernelGGL((combine_kernel<T, DD, 4, 4>), grid, blk, 0, st, a, m, n_comb);               \
+        else if (G == 4)                                                                                     \
+            hipLaunchKernelGGL((combine_kernel<T, DD, 4, 8>), grid, blk, 0, st, a, m, n_comb);               \
+        else if (G == 16 && a.n_splits <= 32)                                                                \
+            hipLaunchKernelGGL((combine_kernel<T, DD, 16, 2>), grid, blk, 0, st, a, m, n_comb);              \
+        else if (G == 16)                                                                                    \
+            hipLaunchKernelGGL((combine_kernel<T, DD, 16, 4>), grid, blk, 0, st, a, m, n_comb);              \
+        else                                                                                                 \
+            hipLaunchKernelGGL((combine_kernel<T, DD, 32, 4>), grid, blk, 0, st, a, m, n_comb);              \
     } while (0)
     if (pool->d.dtype == EN_F32) {
         if (D == 64)
