@@ -473,6 +473,425 @@ __global__ __launch_bounds__(64 * SUB) void attn_decode_kernel(EnAttnArgs a)
 }
 
 // ---------------------------------------------------------------------------
+// attn_once (bf16): the same for steps of at most 16 query rows per KV head whose (agent, KV head) pairs are so few that
+// the kernel above is bound by its start-up and its tiles one after the other (a step of one agent over 8 K tokens: 12.3
+// us for 34 MB, of which a plain read of them takes 4: what an earlier step left in the L2s is still there). Here nothing
+// comes one after the other: a workgroup is a whole split of up to five tiles, two waves a tile and 32 keys a wave, all of
+// its loads out before anything is waited for, one barrier before the products with the values, one before the waves'
+// results meet in LDS. The chain that is left is argument, header, load, two products, exchange, store: 5.7 us on average
+// for five tiles (7.1 the slowest workgroup), 3.2 for two, of which the loads' way through the vector memory path of a
+// compute unit (64 bytes a clock) is 1.5 and 0.5. Per decoded token with the merge, streaming kernel / this one: 8 K tokens
+// 16.5 / 11.8 us, 1.5 K 11.4 / 8.5, 0.25 K, with one split and no merge, 11.0 / 7.4. See once_fits for more, and for which
+// steps it takes.
+//
+// Products are 16 x 16 x 32: the 16 columns are the r * N_q rows, half the width of the kernel above, and a score product's
+// chain of dependent instructions is D / 32 long instead of D / 16. A wave takes the maximum of its own 32 keys as its rows'
+// reference, so that no row ever lacks one; the references meet with the results.
+// ---------------------------------------------------------------------------
+// The operands of a wave's score products, when all but the last NEWER of its loads have come: of k-step ks the bytes at
+// addr ^ 64 ks, and STEP further.
+template <int STEP, int NEWER>
+__device__ __forceinline__ void read_keys(bf16x8 (&fr)[4][2], uint32_t addr, std::integral_constant<int, STEP>, std::integral_constant<int, NEWER>)
+{
+    asm volatile("s_waitcnt vmcnt(%12)\n\t"
+                 "ds_read_b128 %0, %8\n\tds_read_b128 %1, %8 offset:%13\n\t"
+                 "ds_read_b128 %2, %9\n\tds_read_b128 %3, %9 offset:%13\n\t"
+                 "ds_read_b128 %4, %10\n\tds_read_b128 %5, %10 offset:%13\n\t"
+                 "ds_read_b128 %6, %11\n\tds_read_b128 %7, %11 offset:%13\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(fr[0][0]), "=&v"(fr[0][1]), "=&v"(fr[1][0]), "=&v"(fr[1][1]), "=&v"(fr[2][0]), "=&v"(fr[2][1]),
+                   "=&v"(fr[3][0]), "=&v"(fr[3][1])
+                 : "v"(addr), "v"(addr ^ 64), "v"(addr ^ 128), "v"(addr ^ 192), "n"(NEWER), "n"(STEP)
+                 : "memory");
+}
+template <int STEP, int NEWER>
+__device__ __forceinline__ void read_keys(bf16x8 (&fr)[2][2], uint32_t addr, std::integral_constant<int, STEP>, std::integral_constant<int, NEWER>)
+{
+    asm volatile("s_waitcnt vmcnt(%6)\n\t"
+                 "ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:%7\n\t"
+                 "ds_read_b128 %2, %5\n\tds_read_b128 %3, %5 offset:%7\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(fr[0][0]), "=&v"(fr[0][1]), "=&v"(fr[1][0]), "=&v"(fr[1][1])
+                 : "v"(addr), "v"(addr ^ 64), "n"(NEWER), "n"(STEP)
+                 : "memory");
+}
+
+template <int D, int TPS>
+__global__ __launch_bounds__(128 * TPS) void attn_once_kernel(EnAttnArgs a)
+{
+    constexpr int KB = 32;                       // keys per wave
+    constexpr int NKS = D / 32;                  // k-steps of a 16 x 16 score product
+    constexpr int NDT = D / 16;                  // 16-row blocks of O^T
+    constexpr int W = 2 * TPS;                   // waves
+    constexpr int ROWB = 2 * D;                  // bytes per K row
+    constexpr int KCPR = ROWB / 16;              // 16-byte chunks per K row
+    constexpr int KRPB = 1024 / ROWB;            // K rows per loader block
+    constexpr int KHALF = KB * ROWB;             // a wave's K rows
+    constexpr int KBYTES = 2 * KHALF;
+    constexpr int VROWB = EN_KEY_TILE * 2;       // bytes per V^T row of a tile
+    constexpr int VBYTES = D * VROWB;
+    constexpr int STAGE = KBYTES + VBYTES;
+    constexpr int NBK = KHALF / 1024, NBV = VBYTES / 2048;   // loader blocks per wave
+    __shared__ __attribute__((aligned(1024))) char smem[TPS * STAGE];
+
+    // (all of the arguments at once: they lie in several lines, a trip to memory each when they are asked for one by one)
+    asm volatile("" ::"s"(a.q), "s"(a.cos_tab), "s"(a.kc), "s"(a.app_k), "s"(a.hdr), "s"(a.q_first), "s"(a.ws_seg), "s"(a.scale_log2e));
+    const int sp = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+    const int lane = tid % 64;
+    const int col = lane % 16, g = lane / 16;
+    // x / n for x < 2^15, n <= 2^10 without the thirty instructions of an integer division: x + 1/2 is at least n / 2048
+    // of n away from a multiple of n, the error of the quotient is 2^-21 of itself
+    auto quotient = [](int x, int n) {
+        return __builtin_amdgcn_readfirstlane((int)(((float)x + 0.5f) * __builtin_amdgcn_rcpf((float)n)));
+    };
+    const int r = quotient(a.Hq, a.Hkv);
+    const int rows = r * a.Nq;                   // at most 16
+    const bool row_valid = col < rows;           // (the other columns compute on row 0 once more, for nobody)
+    const int hl = !row_valid || a.Nq == 1 ? (row_valid ? col : 0) : col / a.Nq;
+    const int i_row = row_valid ? col - hl * a.Nq : 0;
+    const int hq = kvh * r + hl;
+
+    const int32_t *bnd_g = a.bnd + (size_t)b * (a.Smax + 2);
+    const bool bnd_in_lanes = a.Smax + 2 <= 64;
+    int my_bnd = 0x7fffffff;
+    if (a.ws_seg && bnd_in_lanes && lane <= a.Smax + 1)
+        my_bnd = bnd_g[lane];
+    const en_table_ptr hdr = as_table(a.hdr + 4 * (size_t)b);
+    const int S = hdr[0];
+    const int Lc = hdr[1] + a.q_first;           // rows are new tokens q_first .. q_first+Nq-1
+    const int Ltot = Lc + a.Nq;
+    const int ntiles = (Ltot + EN_KEY_TILE - 1) / EN_KEY_TILE;
+    const int t_begin = quotient(sp * ntiles + a.n_splits - 1, a.n_splits);        // split_first_tile
+    const int t_end = quotient((sp + 1) * ntiles + a.n_splits - 1, a.n_splits);
+    const int key_begin = t_begin * EN_KEY_TILE, key_end = min(t_end * EN_KEY_TILE, Ltot);
+    const unsigned rows_all = (unsigned)a.B * a.Hq * a.Nq;
+    if (t_begin >= t_end) {                      // an agent with fewer tiles than splits
+        if (a.ws_ml && tid < rows) {
+            f32x2 v = {EN_NEG_INF, 0.f};
+            *reinterpret_cast<f32x2 *>(a.ws_ml + ((size_t)sp * rows_all + ((size_t)b * a.Hq + kvh * r) * a.Nq + tid) * 2) = v;
+        }
+        return;
+    }
+    const int u = wave & 1;                      // half of the tile
+    const int tile = t_begin + wave / 2;
+    const bool active = tile < t_end;            // the same for the whole wave
+    const int kb = tile * EN_KEY_TILE + u * KB;  // first key
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
+    char *const kst = smem + (wave / 2) * STAGE + u * KHALF;         // the wave's K rows
+    char *const vst = smem + (wave / 2) * STAGE + KBYTES;            // the pair's V^T tile
+
+    // ---- queries and their angles, asked for first ----
+    bf16x8 qraw[NKS];
+    f32x8 cs[NKS / 2], sn[NKS / 2];
+    if (row_valid) {                             // (lanes without a row ask for nothing: their way through the vector memory path is not free)
+        const bf16_t *qp = (const bf16_t *)a.q + (((size_t)b * a.Nq + i_row) * a.Hq + hq) * D + 8 * g;
+        const size_t pos = Lc + i_row;
+        const float *ct = a.cos_tab + pos * (D / 2) + 8 * g, *st = a.sin_tab + pos * (D / 2) + 8 * g;
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks)
+            qraw[ks] = *reinterpret_cast<const bf16x8 *>(qp + 32 * ks);
+#pragma unroll
+        for (int ks = 0; ks < NKS / 2; ++ks) {
+            cs[ks] = *reinterpret_cast<const f32x8 *>(ct + 32 * ks);
+            sn[ks] = *reinterpret_cast<const f32x8 *>(st + 32 * ks);
+        }
+    }
+    // ---- the step's own keys and values (see attn_decode_kernel): the wave whose keys they are writes them into the
+    // context and, when the tile has landed, over what this holds in their place ----
+    constexpr int APP_L = D / 2;                 // lanes that own a rotary pair
+    const int first_new = max(Lc, key_begin);
+    const int own_first = max(first_new, kb), own_end = min(key_end, kb + KB);
+    const bool owns_new = a.app_k != nullptr && active && own_first < own_end;
+    float app_cs = 0.f, app_sn = 0.f;
+    bf16_t app_k1 = (bf16_t)0.f, app_k2 = (bf16_t)0.f, app_v1 = (bf16_t)0.f, app_v2 = (bf16_t)0.f;
+    auto app_load = [&](int t) {
+        const int c = min(lane, APP_L - 1);
+        const bf16_t *kr = (const bf16_t *)a.app_k + (((size_t)b * a.Nq + t) * a.Hkv + kvh) * D;
+        const bf16_t *vr = (const bf16_t *)a.app_v + (((size_t)b * a.Nq + t) * a.Hkv + kvh) * D;
+        app_cs = a.cos_tab[(size_t)(Lc + t) * (D / 2) + c];
+        app_sn = a.sin_tab[(size_t)(Lc + t) * (D / 2) + c];
+        app_k1 = kr[c];
+        app_k2 = kr[c + D / 2];
+        app_v1 = vr[c];
+        app_v2 = vr[c + D / 2];
+    };
+    if (owns_new)
+        app_load(own_first - Lc);
+
+    // ---- the tile's loads: the wave's own K rows, half of the pair's V^T rows. Inside a row the 16-byte chunks are
+    // exchanged (XOR) so that the operand reads of 16 consecutive lanes meet distinct banks.
+    // (a wave without a tile asks for bytes past the end, which is no trip to memory: with a branch here the waits for the
+    // queries would have to be waits for everything) ----
+    {
+        typedef __attribute__((address_space(3))) char *lptr;
+        constexpr int RSRC = 0x00027000;
+        const auto kr = __builtin_amdgcn_make_buffer_rsrc((char *)const_cast<void *>(a.kc) + ((size_t)b * a.Hkv + kvh) * a.T * ROWB, 0,
+                                                          a.T * ROWB, RSRC);
+        const auto vr = __builtin_amdgcn_make_buffer_rsrc((char *)const_cast<void *>(a.vt) + ((size_t)b * a.Hkv + kvh) * a.T * ROWB, 0,
+                                                          a.T * ROWB, RSRC);
+        const int krow = lane / KCPR;            // row inside a loader block
+        const int kpat = D == 128 ? krow : (krow >> 1) & 3;
+        const uint32_t past = active ? 0u : 1u << 31;
+        const uint32_t koff = (uint32_t)(krow * ROWB + ((lane % KCPR) ^ kpat) * 16) | past;
+        static_for<NBK>([&](auto j_tag) {
+            constexpr int j = decltype(j_tag)::value;
+            constexpr int bits = D == 128 ? (j & 1) | ((j >> 1) & 2) : j >> 1;        // bits 2, 3 of the row's pattern
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, (lptr)(kst + j * 1024), 16, koff ^ (bits << 6), kb * ROWB + j * 1024, 0, 0);
+        });
+        // loader block 2 j + u is the V^T rows 16 j + 8 u ..
+        const uint32_t voff = (uint32_t)((8 * u + lane / 8) * a.T * 2 + ((lane % 8) ^ (4 * u + lane / 16)) * 16) | past;
+#pragma unroll
+        for (int j = 0; j < NBV; ++j)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, (lptr)(vst + (2 * j + u) * 1024), 16, voff,
+                                                     tile * VROWB + 16 * j * a.T * 2, 0, 0);
+    }
+
+    // ---- Q: rotate at L_c + i, scale, round to bf16 ----
+    bf16x8 qf[NKS];
+    if (row_valid) {
+#pragma unroll
+        for (int ks = 0; ks < NKS / 2; ++ks)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float x1 = (float)qraw[ks][j], x2 = (float)qraw[ks + NKS / 2][j];
+                qf[ks][j] = (bf16_t)((x1 * cs[ks][j] - x2 * sn[ks][j]) * a.scale_log2e);
+                qf[ks + NKS / 2][j] = (bf16_t)((x2 * cs[ks][j] + x1 * sn[ks][j]) * a.scale_log2e);
+            }
+    }
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks)
+        asm volatile("" : "+v"(qf[ks]));         // (here, while the tile is on its way)
+    // addresses of what is read behind the barrier.
+    // S^T: row 4 g' + e of block 0 is key 16 (g' / 2) + 4 (g' % 2) + e, of block 1 that key + 8, so that a lane's
+    // eight scores are the keys of its chunk of a V^T row (bits 2 and 3 exchanged)
+    auto k_pattern = [](int row) {
+        return D == 128 ? (row & 3) | ((row >> 2) & 1) << 2 | ((row >> 4) & 1) << 3 : ((row >> 1) & 3) | ((row >> 4) & 1) << 2;
+    };
+    const int key0 = 16 * (col >> 3) + (col & 7);
+    uint32_t kaddr = (uint32_t)(kst - smem) + (uint32_t)(key0 * ROWB + (g ^ k_pattern(key0)) * 16);
+    uint32_t vaddr = (uint32_t)(vst - smem) + (uint32_t)(col * VROWB + ((4 * u + g) ^ (col / 2)) * 16);
+    asm volatile("" : "+v"(kaddr), "+v"(vaddr));
+    const int key_g = 16 * (g >> 1) + 4 * (g & 1);               // the lane's first key
+
+    auto app_turn = [&](int pos, float &y1, float &y2) {
+        // (the rows whose products are rounded the other way: see rope_key_pair)
+        if (pos == first_new)
+            rope_key_pair<true>((float)app_k1, (float)app_k2, app_cs, app_sn, y1, y2);
+        else
+            rope_key_pair((float)app_k1, (float)app_k2, app_cs, app_sn, y1, y2);
+    };
+    if (owns_new) {
+        __builtin_amdgcn_s_waitcnt(0x0f70 | NBV);                // vmcnt(NBV): the wave's K rows have landed
+        for (int pos = own_first; pos < own_end; ++pos) {
+            if (pos > own_first)
+                app_load(pos - Lc);
+            float y1, y2;
+            app_turn(pos, y1, y2);
+            if (lane < APP_L) {
+                char *kd = kst + (pos - kb) * ROWB + lane % 8 * 2;
+                const int pat = k_pattern(pos - kb);
+                *reinterpret_cast<bf16_t *>(kd + ((lane / 8) ^ pat) * 16) = (bf16_t)y1;
+                *reinterpret_cast<bf16_t *>(kd + ((lane / 8 + D / 16) ^ pat) * 16) = (bf16_t)y2;
+            }
+        }
+    }
+    // ---- scores and probabilities, while the V^T tile is on its way. (The K operands are read in one piece of assembly:
+    // the compiler would wait for everything in flight to LDS before any of its own reads.) ----
+    float m = EN_NEG_INF, l = 0.f;
+    bf16x8 pf;
+    f32x4 pr[2];
+    if (active) {
+        f32x4 sv[2];
+        bf16x8 fr[NKS][2];
+        read_keys(fr, lds0 + kaddr, std::integral_constant<int, 8 * ROWB>{}, std::integral_constant<int, NBV>{});
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                sv[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[ks][h], qf[ks], ks == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : sv[h], 0, 0, 0);
+        if (kb + KB - 1 > Lc) {
+            const int rel = Lc + i_row - kb - key_g;             // last visible key, counted from it
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (8 * h + e > rel)
+                        sv[h][e] = EN_NEG_INF;
+        }
+        auto over_groups = [&](float v, auto op) {               // over the four lanes of a column
+            typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+            u32x2 x = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+            v = op(__uint_as_float(x[0]), __uint_as_float(x[1]));
+            x = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+            return op(__uint_as_float(x[0]), __uint_as_float(x[1]));
+        };
+        m = sv[0][0];
+#pragma unroll
+        for (int e = 1; e < 8; ++e)
+            m = fmaxf(m, sv[e / 4][e % 4]);
+        m = over_groups(m, [](float x, float y) { return fmaxf(x, y); });
+        const float ref = m == EN_NEG_INF ? 0.f : m;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            pf[e] = (bf16_t)fast_exp2(sv[e / 4][e % 4] - ref);
+            pr[e / 4][e % 4] = (float)pf[e];                     // (the sums use what the products use)
+            l += pr[e / 4][e % 4];
+        }
+        l = over_groups(l, [](float x, float y) { return x + y; });
+    }
+    __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    lds_data_ready();
+    if (owns_new)                                // (the partner's loads of these rows have landed, too)
+        for (int pos = own_first; pos < own_end; ++pos) {
+            if (own_end - own_first > 1)
+                app_load(pos - Lc);
+            float y1, y2;
+            app_turn(pos, y1, y2);
+            const int vcol = (pos & ~0xC) | ((pos & 4) << 1) | ((pos & 8) >> 1);      // bits 2 and 3 exchanged
+            if (lane < APP_L) {
+                auto vput = [&](int d, bf16_t v) {
+                    *reinterpret_cast<bf16_t *>(vst + d * VROWB + (((vcol % EN_KEY_TILE) / 8) ^ ((d / 2) & 7)) * 16 + (vcol % 8) * 2) = v;
+                };
+                vput(lane, app_v1);
+                vput(lane + D / 2, app_v2);
+                bf16_t *kd = (bf16_t *)a.kc + (((size_t)b * a.Hkv + kvh) * a.T + pos) * D;
+                bf16_t *vd = (bf16_t *)a.vt + ((size_t)b * a.Hkv + kvh) * (size_t)D * a.T + vcol;
+                kd[lane] = (bf16_t)y1;
+                kd[lane + D / 2] = (bf16_t)y2;
+                vd[(size_t)lane * a.T] = app_v1;
+                vd[(size_t)(lane + D / 2) * a.T] = app_v2;
+            }
+        }
+
+    // P of the wave's block, [col][32 keys] floats, and (reference, sum) per column: over the wave's own columns of
+    // the V^T tile, when its products have read them
+    auto p_at = [&](int w, int c, int key) {
+        const int row = 2 * c + key / 16;
+        return smem + (w / 2) * STAGE + KBYTES + row * VROWB + ((4 * (w & 1) + (key % 16) / 4) ^ (c & 7)) * 16 + key % 4 * 4;
+    };
+    auto ml_at = [&](int w, int c) {
+        return smem + (w / 2) * STAGE + KBYTES + (32 + c / 8) * VROWB + (w & 1) * 64 + c % 8 * 8;
+    };
+    // O of the wave's block, [col][D] floats, the chunks of a row rotated by the column: over its K rows
+    auto o_at = [&](int w, int c, int chunk) {
+        return smem + (w / 2) * STAGE + (w & 1) * KHALF + c * (4 * D) + ((chunk + c) & (D / 4 - 1)) * 16;
+    };
+    if (active) {
+        // ---- O^T = V^T P^T ----
+        f32x4 o[NDT];
+#pragma unroll
+        for (int d = 0; d < NDT; ++d) {
+            const bf16x8 fr = *reinterpret_cast<const bf16x8 *>(smem + vaddr + d * 16 * VROWB);
+            o[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr, pf, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        }
+        if (row_valid) {
+#pragma unroll
+            for (int d = 0; d < NDT; ++d)
+                *reinterpret_cast<f32x4 *>(o_at(wave, col, 4 * d + g)) = o[d];
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                *reinterpret_cast<f32x4 *>(p_at(wave, col, key_g + 8 * h)) = pr[h];
+            if (g == 0) {
+                f32x2 v = {m, l};
+                *reinterpret_cast<f32x2 *>(ml_at(wave, col)) = v;
+            }
+        }
+    } else if (lane < 16) {
+        f32x2 v = {EN_NEG_INF, 0.f};
+        *reinterpret_cast<f32x2 *>(ml_at(wave, lane)) = v;
+    }
+    // (LDS only: nobody waits for the stores of new tokens)
+    __builtin_amdgcn_s_waitcnt(0xc07f);          // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    lds_data_ready();
+
+    // the weights of the waves' results for row c
+    auto weights = [&](int c, float (&wt)[W], float &M, float &L) {
+        f32x2 ml[W];
+        M = EN_NEG_INF;
+        L = 0.f;
+#pragma unroll
+        for (int w = 0; w < W; ++w)
+            ml[w] = *reinterpret_cast<const f32x2 *>(ml_at(w, c));
+#pragma unroll
+        for (int w = 0; w < W; ++w)
+            M = fmaxf(M, ml[w][0]);
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            wt[w] = ml[w][0] == EN_NEG_INF ? 0.f : fast_exp2(ml[w][0] - M);
+            L += wt[w] * ml[w][1];
+        }
+    };
+    // ---- the waves' results meet: a thread takes four values of a row ----
+    for (int it = tid; it < rows * (D / 4); it += 64 * W) {
+        const int c = it / (D / 4), ch = it % (D / 4);
+        float wt[W], M, L;
+        f32x4 x[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w)
+            x[w] = *reinterpret_cast<const f32x4 *>(o_at(w, c, ch));
+        weights(c, wt, M, L);
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < W; ++w)
+            acc += wt[w] == 0.f ? f32x4{0.f, 0.f, 0.f, 0.f} : x[w] * wt[w];
+        const float inv = L > 0.f ? 1.f / L : 0.f;
+        const int h = kvh * r + (a.Nq == 1 ? c : c / a.Nq), i = a.Nq == 1 ? 0 : c % a.Nq;
+        const size_t row = ((size_t)b * a.Hq + h) * a.Nq + i;
+        bf16_t *op = (a.n_splits == 1) ? (bf16_t *)a.out + (((size_t)b * a.Nq + i) * a.Hq + h) * D
+                                       : (bf16_t *)a.ws_opart + ((size_t)sp * rows_all + row) * D;
+        *reinterpret_cast<bf16x4 *>(op + 4 * ch) = __builtin_convertvector(acc * inv, bf16x4);
+        if (a.ws_ml && ch == 0) {
+            f32x2 v = {M, L};
+            *reinterpret_cast<f32x2 *>(a.ws_ml + ((size_t)sp * rows_all + row) * 2) = v;
+        }
+    }
+    // ---- the buckets' sums: 16 lanes take a (bucket, row), from the last wave on (the first have rows to merge) ----
+    if (!a.ws_seg)
+        return;
+    auto bucket_of = [&](int tok) {
+        return bnd_in_lanes ? (int)__popcll(__ballot(lane <= S && my_bnd <= tok)) - 1 : find_bucket(as_table(bnd_g), S, tok);
+    };
+    const int s_first = bucket_of(key_begin), n_pairs = (bucket_of(key_end - 1) - s_first + 1) * rows;
+    const float per_row = 1.f / (float)rows;
+    for (int p0 = 4 * (W - 1 - wave); p0 < n_pairs; p0 += 4 * W) {
+        const int p = min(p0 + g, n_pairs - 1);
+        const int sb = (int)(((float)p + 0.5f) * per_row), c = p - sb * rows;         // p / rows (p < 2^16)
+        const int s = s_first + sb;
+        float x[2 * W];                          // this lane's keys col, col + 16, ..
+#pragma unroll
+        for (int k = 0; k < 2 * W; ++k)
+            x[k] = *reinterpret_cast<const float *>(p_at(k / 2, c, col + 16 * (k & 1)));
+        int blo, bhi;
+        if (bnd_in_lanes) {
+            blo = __shfl(my_bnd, s, 64);
+            bhi = __shfl(my_bnd, s + 1, 64);
+        } else {
+            blo = bnd_g[s];
+            bhi = bnd_g[s + 1];
+        }
+        const int lo = max(blo, key_begin) - key_begin, hi = min(bhi, key_end) - key_begin;
+        float wt[W], M, L;
+        weights(c, wt, M, L);
+        float sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const int k0 = w * KB + col, k1 = k0 + 16;
+            sum += ((k0 >= lo && k0 < hi ? x[2 * w] : 0.f) + (k1 >= lo && k1 < hi ? x[2 * w + 1] : 0.f)) * wt[w];
+        }
+        sum = lanes_reduce<16>(sum, [](float x, float y) { return x + y; });
+        if (col == 0 && p0 + g < n_pairs && bhi > blo) {
+            const int h = kvh * r + (a.Nq == 1 ? c : c / a.Nq), i = a.Nq == 1 ? 0 : c % a.Nq;
+            f32x2 v = {sum, M};
+            *reinterpret_cast<f32x2 *>(a.ws_seg + ((((size_t)sp * a.B * a.Hq + (size_t)b * a.Hq + h) * (a.Smax + 1) + s) * a.Nq + i) * 2) = v;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
 // attn_f32: attention in single precision on the fp32 matrix instruction (16 x 16 x 4, exact products,
 // fp32 sums), for small layers and short steps, which are bound by latency: the chain of a wave's trips
 // to memory and of its dependent products, not by bytes or operations.
@@ -812,6 +1231,19 @@ static void launch_f32_waves(int D, const EnAttnArgs &a, hipStream_t st)
         hipLaunchKernelGGL((attn_f32_kernel<128, WAVES>), grid, blk, 0, st, a);
 }
 
+template <int D>
+static void launch_once(const EnAttnArgs &a, hipStream_t st)
+{
+    const dim3 grid(a.n_splits, a.Hkv, a.B), blk(128 * a.once_tiles);
+    switch (a.once_tiles) {
+    case 1: hipLaunchKernelGGL((attn_once_kernel<D, 1>), grid, blk, 0, st, a); break;
+    case 2: hipLaunchKernelGGL((attn_once_kernel<D, 2>), grid, blk, 0, st, a); break;
+    case 3: hipLaunchKernelGGL((attn_once_kernel<D, 3>), grid, blk, 0, st, a); break;
+    case 4: hipLaunchKernelGGL((attn_once_kernel<D, 4>), grid, blk, 0, st, a); break;
+    default: hipLaunchKernelGGL((attn_once_kernel<D, 5>), grid, blk, 0, st, a); break;
+    }
+}
+
 // ---------------------------------------------------------------------------
 // launcher: fp32 pools, steps that fit the decode kernel, everything else
 // ---------------------------------------------------------------------------
@@ -826,6 +1258,11 @@ int en_launch_attention(const en_pool *pool, const EnAttnArgs &a, void *stream)
             launch_f32_waves<2>(D, a, st);
         else
             return (int)hipErrorInvalidValue;
+    } else if (a.decode && a.once_tiles) {
+        if (D == 64)
+            launch_once<64>(a, st);
+        else
+            launch_once<128>(a, st);
     } else if (a.decode) {
         const dim3 grid((a.total_wgs + 7) / 8 * 8), blk(64 * a.sub);
         if (a.sub != 1 && a.sub != 2)

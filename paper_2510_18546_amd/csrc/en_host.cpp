@@ -261,6 +261,47 @@ static int pool_ensure_device(en_pool *p)
 // ---------------------------------------------------------------------------
 // planner
 // ---------------------------------------------------------------------------
+// Whether attn_once_kernel takes a decode step of n splits of at most `per` tiles for each of `base` (agent, KV head)
+// pairs: where its workgroups, as many of a compute unit's as its LDS holds, come in few enough rounds. us per decoded
+// token (attention and merge), streaming kernel / this one:
+// - one round: one agent of 8 heads, 0.25 K tokens 11.0 / 7.4 (one split, no merge), 1.5 K 11.4 / 8.5, 4 K 12.9 / 9.8, 6 K
+//   14.1 / 10.3, 8 K (five tiles) 16.5 / 11.8, rows of 64 values 12.7 / 9.2; 16 agents, 2 heads, 0.4 K 11.9 / 8.3;
+// - two tiles, two workgroups to a compute unit that relieve one another, in up to six rounds: 16 agents x 0.8 K (1.75
+//   rounds) 21.7 / 17.0, x 1.6 K (3.3) 28.5 / 26.5, 16 x 6 K of 2 heads (3.1) 26.5 / 25.8; but 16 x 3 K (6.3) 41.7 / 43.0,
+//   64 x 4 K of 2 heads (8.2) 51.6 / 52.9. Rows of 64 values in up to 16: 64 x 4 K of 2 heads (3.3) 32.7 / 27.9, 64 x 2.5 K
+//   (8.4) 75.3 / 68.8, 256 x 1 K (12.8) 115.7 / 113.4; but 64 x 8 K (25) 198 / 209;
+// - three tiles, one workgroup to a compute unit, in up to two (longer contexts than 64 splits of two hold): 10 K (1.7)
+//   18.3 / 16.4; two agents x 8 K (2.7) 23.6 / 24.4; four or five tiles in one: 16 K as 52 x 5 (1.6) 22.4 / 23.3.
+static bool once_fits(const en_pool *pool, long base, int per, int n, int rounds)
+{
+    const long slots = EN_ONCE_TILES * 128 / pool->d.head_dim;       // tiles that the LDS of a compute unit holds
+    return per <= EN_ONCE_TILES && n <= EN_MAX_SPLITS && base * n <= rounds * pool->n_cu * (slots / per);
+}
+static int once_rounds(const en_pool *pool, int per)
+{
+    return per <= 2 ? (pool->d.head_dim == 64 ? 16 : 6) : per == 3 ? 2 : 1;
+}
+// KV splits for it, or 0: one where that is a whole context, else splits as short as one round allows. (Splits of one tile
+// only up to two workgroups to a compute unit: 2 agents x 2 K tokens 9.6 us with one, 9.4 with two, one agent over 1.5 K 8.5
+// either way, but 4 x 2 K, four workgroups of one tile, 13.2, with five 11.6.)
+static int once_splits(const en_pool *pool, long base, int tiles)
+{
+    const auto splits = [tiles](int per) { return (tiles + per - 1) / per; };
+    if (once_fits(pool, base, tiles, 1, 1))
+        return 1;
+    for (int per = base * tiles <= 2L * pool->n_cu ? 1 : 2; per <= EN_ONCE_TILES; ++per)
+        if (once_fits(pool, base, per, splits(per), 1)) {
+            // the fewest splits that are as short as that; but all there may be where only a few of those are, from three
+            // tiles on (see below)
+            const int most = std::min(tiles, EN_MAX_SPLITS), n_longest = tiles - (per - 1) * most;
+            return per > 2 && per == splits(most) && 8 * n_longest < most && once_fits(pool, base, per, most, 1) ? most : splits(per);
+        }
+    for (int per = 2; per <= 3; ++per)
+        if (once_fits(pool, base, per, splits(per), once_rounds(pool, per)))
+            return splits(per);
+    return 0;
+}
+
 static int choose_splits(const en_pool *pool, const en_plan *pl)
 {
     // One workgroup covers 8 (head, 32-query block) pairs of one KV head and
@@ -283,6 +324,11 @@ static int choose_splits(const en_pool *pool, const en_plan *pl)
         // 16 K tokens).
         const long base = long(pl->B) * pool->d.n_kv_heads;
         const int tiles = std::max(1, (pl->max_ctx_len + EN_KEY_TILE - 1) / EN_KEY_TILE);
+        if (pool->r * pl->Nq <= EN_ONCE_ROWS) {
+            const int n = once_splits(pool, base, tiles);
+            if (n > 0)
+                return n;
+        }
         long want = (2L * pool->n_cu + base - 1) / base;
         if (want < 2 && tiles >= 64)
             want = 2;
@@ -844,9 +890,19 @@ static bool decode_kernel_fits(const en_pool *pool, int n_rows)
 // merge of twice as many partial results must not eat the gain: see its lane groups.)
 int en_attn_sub(const en_pool *pool, const en_plan *pl, int n_rows, int n_splits)
 {
-    if (!decode_kernel_fits(pool, n_rows))
+    if (!decode_kernel_fits(pool, n_rows) || en_attn_once_tiles(pool, pl, n_rows, n_splits))
         return 1;
     return long(pl->B) * pool->d.n_kv_heads * n_splits <= 2L * pool->n_cu ? 2 : 1;
+}
+
+// EnAttnArgs::once_tiles of a step with n_splits KV splits.
+int en_attn_once_tiles(const en_pool *pool, const en_plan *pl, int n_rows, int n_splits)
+{
+    if (!computes_bf16(pool->d.dtype) || pool->r * n_rows > EN_ONCE_ROWS)
+        return 0;
+    const int tiles = std::max(1, (pl->max_ctx_len + EN_KEY_TILE - 1) / EN_KEY_TILE);
+    const int per = (tiles + n_splits - 1) / n_splits;
+    return once_fits(pool, long(pl->B) * pool->d.n_kv_heads, per, n_splits, once_rounds(pool, per)) ? per : 0;
 }
 
 // Whether the reduced masses that an attention call over n_rows query rows per head is asked for are summed by
@@ -1206,6 +1262,7 @@ static int run_attention(en_pool *pool, en_plan *plan, const void *q_dev, const 
     a.decode = decode_kernel_fits(pool, n_rows) ? 1 : 0;
     if (a.decode)
         a.n_ptiles = 1;
+    a.once_tiles = a.decode ? en_attn_once_tiles(pool, plan, n_rows, n_splits) : 0;
     if (!computes_bf16(pool->d.dtype))
         a.n_ptiles = (pool->r * n_rows + EN_F32_ROWS - 1) / EN_F32_ROWS;
     a.total_wgs = plan->B * pool->d.n_kv_heads * n_splits * a.n_ptiles;

@@ -20,6 +20,8 @@ constexpr int EN_KEY_TILE = 64;    // keys per attention tile; context rows are 
 constexpr int EN_ROWS_PER_WAVE = 32;
 constexpr int EN_WAVES = 8;          // waves per attention workgroup
 constexpr int EN_F32_ROWS = 16;      // query rows per workgroup of the fp32 attention kernel
+constexpr int EN_ONCE_ROWS = 16;     // query rows per KV head of attn_once_kernel at most
+constexpr int EN_ONCE_TILES = 5;     // key tiles of a split there at most (32 KB of LDS each with D = 128)
 
 struct en_pool {
     en_pool_desc d;
@@ -160,6 +162,8 @@ struct EnAttnArgs {
     // 256 agents x 33 keys 64.6 us with eight, 31.9 with two; x 513 keys 227, 208; 64 agents x 1025 keys 103, 98;
     // x 4097 keys 371, 372; 16 agents x 129 keys 8.1, 11.0).
     int f32_waves;
+    // decode steps, or 0: the most 64-key tiles of a split, all of them in LDS at once (attn_once_kernel)
+    int once_tiles;
     int q_prepared;    // prefill kernel: q holds prepared queries (rotated, scaled, bf16: see EnGatherArgs)
     int v_rows;        // prefill kernel: vt holds no values but the address of every context row's values
                        // (see EnGatherArgs::v_rows)
@@ -266,6 +270,7 @@ struct EnWsLayout {
 EnWsLayout en_ws_layout(const en_pool *pool, const en_plan *plan);
 EnWsLayout en_ws_layout_for(const en_pool *pool, const en_plan *plan, int n_rows, int n_splits);
 int en_attn_sub(const en_pool *pool, const en_plan *plan, int n_rows, int n_splits);
+int en_attn_once_tiles(const en_pool *pool, const en_plan *plan, int n_rows, int n_splits);
 // The order of a plan's gather, to the end of en_plan::h_desc.
 void en_gather_order(en_plan *plan, int64_t queries);
 size_t en_plan_block_bytes(const en_plan *plan, size_t bytes);

@@ -1,0 +1,102 @@
+"""Decode steps whose splits are whole in LDS (attn_once_kernel): one to five tiles a split, both head widths, rows up to
+16, segments that end anywhere in a wave's 32 keys, more of them than a wave has lanes, agents with fewer tiles than
+splits; and steps whose rows cross the borders of 32-key blocks, tiles and splits. Against the oracle, to the tolerances of
+every other bf16 case (outputs 2e-2: P and O rounded to bf16, 2^-9 each; masses 1e-2)."""
+import numpy as np
+import pytest
+
+from paper_2510_18546_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+def workload(seed, agents, r, kv, d, nq, lens, n_sel):
+    cap = max(lens)
+    cfg = I.Config("once", seed, I.BF16, agents, r * kv, kv, d, len(lens), cap, cap, cap, n_sel, nq, 500000.0)
+    w = I.make_workload(cfg)
+    w.lens[:] = lens
+    for g, n in enumerate(lens):
+        w.k_pool[g, :, n:] = w.v_pool[g, :, n:] = np.nan
+    return cfg, w
+
+
+def both(step, oracle, w, splits):
+    import torch
+    st = step.PlanningStep(w, n_splits=splits)
+    st.ws.fill_(0xFF)                            # a NaN pattern: nothing is read that was not written
+    print(f"[case] {w.cfg} splits {splits}", flush=True)
+    st.run()
+    torch.cuda.synchronize()
+    out, mass = oracle.attention(w.k_pool, w.v_pool, w.lens, w.sel, w.sel_ptr, w.q, w.k_new, w.v_new, w.cfg.rope_base)
+    assert np.abs(st.out_host() - out).max() <= 2e-2
+    assert np.abs(st.mass_host() - mass).max() <= 1e-2
+    assert np.abs(st.mass_host().sum(-1) - 1.0).max() <= 1e-4
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("total,splits", [(40, None), (64, 1), (65, 1), (160, 1), (192, 1), (193, 1), (320, 1), (321, 2), (300, 5), (640, 2),
+                                          (700, 3), (1100, None)])
+def test_tiles_per_split(oracle, total, splits, d):
+    from paper_2510_18546_amd import step
+    # one group as long as it takes, behind groups of 0, 1, 31 and 33 tokens
+    lens = [0, 1, 31, 33, total - 1 - 65 if total > 70 else 0]
+    cfg, w = workload(total, 2, 3, 2, d, 1, lens if total > 70 else [0, 1, 31, total - 33, 0], 5)
+    both(step, oracle, w, splits)
+
+
+@pytest.mark.parametrize("r,nq,d", [(16, 1, 128), (4, 4, 128), (7, 2, 64), (1, 16, 64), (1, 1, 128), (5, 3, 128)])
+def test_rows(oracle, r, nq, d):
+    from paper_2510_18546_amd import step
+    for seed, lens in ((1, [70, 3, 55]), (2, [200, 120, 129]), (3, [32, 32, 0])):
+        cfg, w = workload(10 * r + seed, 2, r, 2, d, nq, lens, 3)
+        both(step, oracle, w, None)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_many_short_segments(oracle, d):
+    """80 segments of 0 to 5 tokens: the bounds do not fit a wave's lanes; several (bucket, row) pairs for each 16 lanes."""
+    from paper_2510_18546_amd import step
+    lens = [int(x) for x in np.random.default_rng(7).integers(0, 6, 80)]
+    cfg, w = workload(31, 3, 4, 2, d, 2, lens, 80)
+    both(step, oracle, w, None)
+
+
+def test_agents_of_unequal_length(oracle):
+    """Agents of one tile beside one of eleven: most of their splits hold nothing."""
+    from paper_2510_18546_amd import step
+    cfg, w = workload(41, 3, 4, 2, 128, 1, [600, 70, 9], 3)
+    lists = [[0, 1], [2], []]
+    w.sel = np.concatenate([np.array(x, np.int32) for x in lists]).astype(np.int32)
+    w.sel_ptr = np.cumsum([0] + [len(x) for x in lists]).astype(np.int32)
+    for splits in (None, 3, 6):
+        both(step, oracle, w, splits)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("cached,steps", [(30, (1, 1, 1, 4)), (61, (2, 4, 1)), (126, (4, 4)), (318, (1, 1, 1, 4)), (637, (4, 1, 1, 2))])
+def test_steps_across_borders(oracle, cached, steps, d):
+    """Rows appended to a gathered context: outputs of every step, and the context as a gather of all rows leaves it."""
+    import torch
+    from paper_2510_18546_amd import binding as B
+    from paper_2510_18546_amd import step
+    n = sum(steps)
+    cfg, w = workload(cached, 2, 4, 2, d, n, [cached - 20, 20], 2)
+    st = step.PlanningStep(w)
+    print(f"[case] {cfg} steps {steps}", flush=True)
+    ref, _ = oracle.attention(w.k_pool, w.v_pool, w.lens, w.sel, w.sel_ptr, w.q, w.k_new, w.v_new, cfg.rope_base)
+    B.gather_rope(st.pool, st.plan, torch.zeros_like(st.k_new), torch.zeros_like(st.v_new), st.kc, st.vt)
+    q0 = 0
+    for m in steps:
+        q, k, v = (t[:, q0:q0 + m].contiguous() for t in (st.q, st.k_new, st.v_new))
+        out = torch.empty_like(q)
+        ws = torch.empty(max(B.decode_workspace_bytes(st.pool, st.plan, m), 256), dtype=torch.uint8, device="cuda:0").fill_(0xFF)
+        B.segmented_decode_step(st.pool, st.plan, q0, q, k, v, st.kc, st.vt, out, ws)
+        torch.cuda.synchronize()
+        assert np.abs(step._to_host(out) - ref[:, q0:q0 + m]).max() <= 2e-2
+        q0 += m
+    kc, vt = st.kc.clone(), st.vt.clone()
+    B.gather_rope(st.pool, st.plan, st.k_new, st.v_new, st.kc, st.vt)
+    assert torch.equal(vt, st.vt)                # values are copies
+    # rotated keys differ by which of two products is rounded, then by one rounding to bf16 of values up to 4
+    diff = kc.view(torch.bfloat16).float() - st.kc.view(torch.bfloat16).float()
+    assert diff.abs().max().item() <= 4e-2
