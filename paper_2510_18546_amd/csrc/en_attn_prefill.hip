@@ -81,34 +81,40 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_bf16_kernel(EnAttnArgs a)
     static_assert(KRPL == 1 || KRPL == 2, "row rotation");
     __shared__ __attribute__((aligned(1024))) char smem[NST * (KBYTES + VBYTES)];
 
+    // What stands in front of the first loads and behind the last product is paid by every launch, by a step of five tiles
+    // a workgroup as a third of it. Three things took time there: arguments asked for one by one (they lie in several
+    // lines, a trip to memory each), integer divisions by run-time values (EnDivisor), rows' 64-bit addresses. Loop entered
+    // 4.9 -> 3.7 us after the workgroups start, last stores issued 2.3 -> 1.9 us after it; one agent's ragged map 34.5 ->
+    // 32.9 us a step, 16 objects clustered 73.9 -> 72.3, the 8 K-token map 90.7 -> 89.3, sixteen agents 130.1 -> 128.3.
+    asm volatile("" ::"s"(a.q), "s"(a.cos_tab), "s"(a.bnd), "s"(a.ws_ml), "s"(a.ws_opart), "s"(a.B), "s"(a.Smax), "s"(a.one_Lc),
+                 "s"(a.by_ptiles.mul), "s"(a.by_splits.mul), "s"(a.by_r.mul), "s"(a.red_zero), "s"(a.n_red_zero), "s"(a.red_direct), "s"(a.red_shift));
     // ---- work decode: consecutive logical ids share K/V and map to one XCD ----
-    const int per_xcd = gridDim.x / 8;
+    const int per_xcd = (a.total_wgs + 7) / 8;
     const int logical = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
     if (logical >= a.total_wgs)
         return;
     if (logical == 0 && a.red_zero)               // start of the reduced masses that later launches add up
         for (int i = threadIdx.x; i < a.n_red_zero; i += 64 * ATT_WAVES)
             a.red_zero[i] = 0ull;
-    int t = logical;
-    const int ptile = t % a.n_ptiles;
-    t /= a.n_ptiles;
-    const int sp = t % a.n_splits;
-    t /= a.n_splits;
-    const int kvh = t % a.Hkv;
-    const int b = t / a.Hkv;
+    unsigned t = divided(logical, a.by_ptiles);
+    const int ptile = logical - t * a.n_ptiles;
+    unsigned t2 = divided(t, a.by_splits);
+    const int sp = t - t2 * a.n_splits;
+    const int b = divided(t2, a.by_hkv);
+    const int kvh = t2 - b * a.Hkv;
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
     const int lane = tid % 64;
     const int col = lane % 32, half = lane / 32;
-    const int r = a.Hq / a.Hkv;
+    const int r = a.by_r.n;
     const int nqb = (a.Nq + 31) / 32;
     const int pair = ptile * ATT_WAVES + wave;
     // A wave without a valid (head, query block) pair computes on zero queries
     // and writes nothing.
     const bool wave_valid = pair < r * nqb;
-    const int hl = wave_valid ? pair % r : 0;
-    const int qb = wave_valid ? pair / r : 0;
+    const int qb = wave_valid ? divided(pair, a.by_r) : 0;
+    const int hl = wave_valid ? pair - qb * r : 0;
     const int hq = kvh * r + hl;
     const int i_row = qb * 32 + col;
     const bool row_valid = wave_valid && i_row < a.Nq;
@@ -123,24 +129,27 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_bf16_kernel(EnAttnArgs a)
     if (bnd_in_lanes && lane <= a.Smax + 1)
         my_bnd = bnd_g[lane];
     const en_table_ptr hdr = as_table(a.hdr + 4 * (size_t)b);
-    const int S = hdr[0];
-    // the rows are new tokens q_first .. q_first+Nq-1: everything before them counts as context
-    const int Lc = hdr[1] + a.q_first;
+    int S = a.one_S, Lc = a.one_Lc;
+    if (a.B > 1) {
+        S = hdr[0];
+        Lc = hdr[1];
+    }
+    Lc += a.q_first;       // the rows are new tokens q_first .. q_first+Nq-1: everything before them counts as context
     const int Ltot = Lc + a.Nq;
     const en_table_ptr bnd = as_table(bnd_g);
     auto bound_at = [&](int s) {          // s is wave-uniform
         return bnd_in_lanes ? __builtin_amdgcn_readlane(my_bnd, s) : bnd[s];
     };
     const int ntiles = (Ltot + KT - 1) / KT;
-    const int t_begin = (int)split_first_tile(sp, ntiles, a.n_splits);
-    int t_end = (int)split_first_tile(sp + 1, ntiles, a.n_splits);
+    const int t_begin = divided(sp * ntiles + a.n_splits - 1, a.by_splits);      // split_first_tile
+    int t_end = divided((sp + 1) * ntiles + a.n_splits - 1, a.by_splits);
     const int split_key_begin = t_begin * KT;
     const int split_key_end = min(t_end * KT, Ltot);
     {
         // causal frontier of the workgroup: last key any of its rows may see.
         // Every wave walks all tiles up to it; a wave whose own frontier is
         // earlier sees only masked scores in the last ones.
-        const int qb_hi = min((ptile * ATT_WAVES + ATT_WAVES - 1) / r, nqb - 1);
+        const int qb_hi = min((int)divided(ptile * ATT_WAVES + ATT_WAVES - 1, a.by_r), nqb - 1);
         const int last_key = Lc + min(a.Nq - 1, qb_hi * 32 + 31);
         t_end = min(t_end, last_key / KT + 1);
     }
@@ -232,9 +241,6 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_bf16_kernel(EnAttnArgs a)
     const int s1 = (s0 + 1) % NST, s2 = (s0 + 2) % NST, s3 = (s0 + 3) % NST;
     if (nt > 0) {
         vrow_request(t_begin);       // (VPOOL) the first V tile waits for these: asked for first, loaded first
-        char *vz = smem + VBASE + s3 * VBYTES;     // the first product reads a zero V^T stage
-        for (int i = tid * 16; i < VBYTES; i += 64 * ATT_WAVES * 16)
-            *reinterpret_cast<uint4 *>(vz + i) = make_uint4(0, 0, 0, 0);
         if constexpr (VPOOL) {
             vrow_take();
 #pragma unroll
@@ -257,6 +263,10 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_bf16_kernel(EnAttnArgs a)
             for (int j = 0; j < VJ; ++j)
                 dma16(vg, voff[j] + job_goff, lds_w + VBASE + s0 * VBYTES + j * ATT_WAVES * 1024);
         }
+        char *vz = smem + VBASE + s3 * VBYTES + tid * 16;     // the first product reads a zero V^T stage
+#pragma unroll
+        for (int i = 0; i < VBYTES; i += 64 * ATT_WAVES * 16)
+            *reinterpret_cast<uint4 *>(vz + i) = make_uint4(0, 0, 0, 0);
     }
 
     // ---- operand read addresses inside a stage (plus immediates per step) ----
@@ -297,13 +307,11 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_bf16_kernel(EnAttnArgs a)
     // ---- Q: prepared queries are loaded as they are; else load, rotate at L_c + i, scale, round to bf16 ----
     bf16x8 qf[NKS];
     if constexpr (QPREP) {
-        const bf16_t *qp = (const bf16_t *)a.q + (((size_t)b * a.Nq + i_row) * a.Hq + hq) * D + 8 * half;
+        // (lanes without a row load the first one, see below)
+        const bf16_t *qp = (const bf16_t *)a.q + (((size_t)b * a.Nq + (row_valid ? i_row : 0)) * a.Hq + hq) * D + 8 * half;
 #pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) {
-            qf[ks] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-            if (row_valid)
-                qf[ks] = *reinterpret_cast<const bf16x8 *>(qp + 16 * ks);
-        }
+        for (int ks = 0; ks < NKS; ++ks)
+            qf[ks] = *reinterpret_cast<const bf16x8 *>(qp + 16 * ks);
     } else
     {
         // The rotary rows (cosines and sines of position L_c + i, D/2 floats each) are the same for
@@ -729,6 +737,12 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_bf16_kernel(EnAttnArgs a)
     using c3 = std::integral_constant<int, 3>;
     if (nt > 0) {
         wait_all_memory();
+        if constexpr (QPREP)
+            if (__any(!row_valid)) {           // zero queries there
+#pragma unroll
+                for (int ks = 0; ks < NKS; ++ks)
+                    qf[ks] = row_valid ? qf[ks] : bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+            }
         __builtin_amdgcn_s_barrier();
         lds_data_ready();
         // K of the third tile and V^T of the second go out behind everything that the first one waited for
@@ -871,18 +885,18 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_bf16_kernel(EnAttnArgs a)
         wait_all_memory();
         load_pairs(0);
     }
+    // (a scalar base and a lane's offset: the rows' 64-bit addresses one by one were a third of the wind-down)
+    constexpr int RPS = 64 / OCPR;               // rows per store instruction
+    const int stride = a.n_splits == 1 ? a.Hq * (2 * D) : 2 * D;            // bytes between the rows
+    char *dst = a.n_splits == 1 ? (char *)a.out + (((size_t)b * a.Nq + i_lo) * a.Hq + hq) * (2 * D)
+                                : (char *)a.ws_opart + ((size_t)sp * a.B * a.Hq * a.Nq + row_hq * a.Nq + i_lo) * (2 * D);
+    const uint32_t dst_lane = (uint32_t)((lane / OCPR) * stride + lane % OCPR * 16);
+    const char *src = stage_o + (lane / OCPR) * OSTR + lane % OCPR * 16;
+    const int left = a.Nq - i_lo - lane / OCPR;
 #pragma unroll
-    for (int k = 0; k < 32 * OCPR / 64; ++k) {
-        const int idx = k * 64 + lane;
-        const int rr = idx / OCPR, c = idx % OCPR;
-        const int i = i_lo + rr;
-        if (i < a.Nq) {
-            const uint4 val = *reinterpret_cast<const uint4 *>(stage_o + rr * OSTR + c * 16);
-            bf16_t *op = (a.n_splits == 1)
-                             ? (bf16_t *)a.out + (((size_t)b * a.Nq + i) * a.Hq + hq) * D
-                             : (bf16_t *)a.ws_opart + ((size_t)sp * a.B * a.Hq * a.Nq + row_hq * a.Nq + i) * D;
-            *reinterpret_cast<uint4 *>(op + c * 8) = val;
-        }
+    for (int k = 0; k < 32 / RPS; ++k) {
+        if (RPS * k < left)
+            *reinterpret_cast<uint4 *>(dst + (size_t)(RPS * k) * stride + dst_lane) = *reinterpret_cast<const uint4 *>(src + RPS * k * OSTR);
     }
 
     }      // wave_valid

@@ -124,6 +124,11 @@ __device__ __forceinline__ unsigned split_first_tile(unsigned sp, unsigned ntile
     return (sp * ntiles + n_splits - 1) / n_splits;
 }
 
+__device__ __forceinline__ unsigned divided(unsigned x, const EnDivisor &d)
+{
+    return (unsigned)((unsigned long long)x * d.mul >> d.shift);
+}
+
 template <typename P>
 __device__ __forceinline__ int find_bucket(P bnd, int S, int tok)
 {

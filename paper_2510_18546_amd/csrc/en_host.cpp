@@ -1266,6 +1266,12 @@ static int run_attention(en_pool *pool, en_plan *plan, const void *q_dev, const 
     if (!computes_bf16(pool->d.dtype))
         a.n_ptiles = (pool->r * n_rows + EN_F32_ROWS - 1) / EN_F32_ROWS;
     a.total_wgs = plan->B * pool->d.n_kv_heads * n_splits * a.n_ptiles;
+    a.by_ptiles = en_divisor(a.n_ptiles);
+    a.by_splits = en_divisor(n_splits);
+    a.by_hkv = en_divisor(a.Hkv);
+    a.by_r = en_divisor(pool->r);
+    a.one_S = plan->hdr[0];
+    a.one_Lc = plan->hdr[1];
     a.f32_waves = a.total_wgs >= 2 * pool->n_cu && plan->max_ctx_len <= 1024 * n_splits ? 2 : 8;
     a.scale_log2e = softmax_scale_log2e(pool);
     a.app_k = a.decode ? app_k_dev : nullptr;

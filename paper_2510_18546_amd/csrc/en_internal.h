@@ -138,6 +138,21 @@ struct EnGatherLaunch {
 // map 5.59 -> 5.71). So what the host alone needs is not among them.
 static_assert(offsetof(EnGatherLaunch, desc_out) <= 192, "a field that every workgroup reads is in the fourth line");
 
+// A divisor of the attention kernels' workgroup and split numbers. An integer division by a run-time value is some thirty
+// instructions one after the other, and eight of them stood in front of a workgroup's first load; this is three:
+// x / n = x mul >> (31 + shift) for all x < 2^31, with shift = ceil(log2 n) and mul = ceil(2^(31 + shift) / n) < 2^32: mul n
+// is less than n <= 2^shift above 2^(31 + shift), so the product is less than 1 / n of 2^(31 + shift) above x / n.
+struct EnDivisor {
+    unsigned n, mul, shift;      // (shift: 31 + ..)
+};
+inline EnDivisor en_divisor(unsigned n)
+{
+    unsigned s = 0;
+    while ((1ull << s) < n)
+        ++s;
+    return {n, unsigned(((1ull << (31 + s)) + n - 1) / n), 31 + s};
+}
+
 struct EnAttnArgs {
     const void *q, *kc, *vt;
     void *out;
@@ -151,6 +166,10 @@ struct EnAttnArgs {
     int q_first;       // the Nq query rows are new tokens q_first .. q_first+Nq-1 of the plan: every key
                        // before L_c + q_first is visible to all of them (0 for a whole prefill)
     int n_splits, n_ptiles, total_wgs;
+    // prefill kernel: n_ptiles, n_splits (of workgroup numbers and of split boundaries), Hkv, Hq / Hkv
+    EnDivisor by_ptiles, by_splits, by_hkv, by_r;
+    // the header {S, L_c} of the only agent (B == 1): one trip to memory less in front of its first load
+    int one_S, one_Lc;
     int decode;        // 1: all r*Nq query rows of a KV head fit one wave (attn_decode kernel)
     int sub;           // decode kernel: waves per (agent, KV head, split); wave w takes every sub-th 32-key
                        // block of the split's tiles and leaves its own partial results at index
