@@ -129,6 +129,17 @@ __device__ __forceinline__ unsigned divided(unsigned x, const EnDivisor &d)
     return (unsigned)((unsigned long long)x * d.mul >> d.shift);
 }
 
+// x / n for x < 2^31 and a quotient below 2^20: the estimate in single precision is off by one at most. A third of the
+// instructions of a division.
+__device__ __forceinline__ unsigned small_quotient(unsigned x, unsigned n)
+{
+    unsigned q = (unsigned)((float)x * __builtin_amdgcn_rcpf((float)n));
+    const int left = (int)(x - q * n);
+    q -= left < 0;
+    q += left >= (int)n;
+    return q;
+}
+
 template <typename P>
 __device__ __forceinline__ int find_bucket(P bnd, int S, int tok)
 {
@@ -218,24 +229,29 @@ __device__ __forceinline__ float pair_max(float v)
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
-// v of all lanes of a group of N = 4, 16 or 32 neighbours taken together by `op`, in each of them: steps inside the rows of
-// 16 lanes in the vector ALU (data-parallel primitives), one exchange between two rows.
+// v of all lanes of a group of N = 4, 16, 32 or 64 neighbours taken together by `op`, in each of them: steps inside the
+// rows of 16 lanes in the vector ALU (data-parallel primitives), then exchanges of rows there. (Through the LDS crossbar a
+// step is a trip of some sixty cycles.)
 template <int N, typename F>
 __device__ __forceinline__ float lanes_reduce(float v, F op)
 {
     auto dpp = [](float x, auto ctrl) {
         return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), decltype(ctrl)::value, 0xf, 0xf, false));
     };
-    static_assert(N == 4 || N == 16 || N == 32, "lanes of a group");
+    static_assert(N == 4 || N == 16 || N == 32 || N == 64, "lanes of a group");
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
     v = op(v, dpp(v, std::integral_constant<int, 0xB1>{}));          // quad_perm [1, 0, 3, 2]
     v = op(v, dpp(v, std::integral_constant<int, 0x4E>{}));          // quad_perm [2, 3, 0, 1]
     if constexpr (N >= 16) {
         v = op(v, dpp(v, std::integral_constant<int, 0x141>{}));     // row_half_mirror
         v = op(v, dpp(v, std::integral_constant<int, 0x140>{}));     // row_mirror
     }
-    if constexpr (N == 32) {
-        typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    if constexpr (N >= 32) {
         const u32x2 x = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = op(__uint_as_float(x[0]), __uint_as_float(x[1]));
+    }
+    if constexpr (N == 64) {
+        const u32x2 x = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
         v = op(__uint_as_float(x[0]), __uint_as_float(x[1]));
     }
     return v;
@@ -249,15 +265,9 @@ __device__ __forceinline__ float half_sum(float v)
 
 __device__ __forceinline__ float wave_max(float v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1)
-        v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
+    return lanes_reduce<64>(v, [](float x, float y) { return fmaxf(x, y); });
 }
 __device__ __forceinline__ float wave_sum(float v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1)
-        v += __shfl_xor(v, o, 64);
-    return v;
+    return lanes_reduce<64>(v, [](float x, float y) { return x + y; });
 }

@@ -1204,6 +1204,10 @@ static EnMassArgs mass_args(const en_pool *pool, const en_plan *plan, char *ws, 
     a.n_splits = n_splits;
     a.sub = en_attn_sub(pool, plan, n_rows, n_splits);
     a.q_first = q_first;
+    a.by_splits = en_divisor(n_splits);
+    a.by_groups = en_divisor((plan->Smax + 1 + EN_MASS_BG - 1) / EN_MASS_BG);
+    a.by_target = en_divisor(a.red_target);
+    a.by_chunks = en_divisor((n_rows + 63) / 64);
     return a;
 }
 
@@ -1270,6 +1274,8 @@ static int run_attention(en_pool *pool, en_plan *plan, const void *q_dev, const 
     a.by_splits = en_divisor(n_splits);
     a.by_hkv = en_divisor(a.Hkv);
     a.by_r = en_divisor(pool->r);
+    a.by_nq = en_divisor(n_rows);
+    a.by_hq = en_divisor(a.Hq);
     a.one_S = plan->hdr[0];
     a.one_Lc = plan->hdr[1];
     a.f32_waves = a.total_wgs >= 2 * pool->n_cu && plan->max_ctx_len <= 1024 * n_splits ? 2 : 8;

@@ -168,6 +168,7 @@ struct EnAttnArgs {
     int n_splits, n_ptiles, total_wgs;
     // prefill kernel: n_ptiles, n_splits (of workgroup numbers and of split boundaries), Hkv, Hq / Hkv
     EnDivisor by_ptiles, by_splits, by_hkv, by_r;
+    EnDivisor by_nq, by_hq;      // merge: Nq, Hq
     // the header {S, L_c} of the only agent (B == 1): one trip to memory less in front of its first load
     int one_S, one_Lc;
     int decode;        // 1: all r*Nq query rows of a KV head fit one wave (attn_decode kernel)
@@ -203,6 +204,7 @@ struct EnAttnArgs {
 };
 
 struct EnMassArgs {
+    EnDivisor by_splits, by_groups, by_target, by_chunks;      // n_splits; of the reduced masses' workgroup numbers
     const float *ws_ml, *ws_seg, *ws_mlfin;
     // Reduced masses [B, Smax+1], or null. Unless the step has few rows (`few`, see mass_few_rows in en_host.cpp)
     // red_target workgroups, of EN_MASS_UNITS units of 64 rows of a head each, sum a bucket's rows in fp32.
@@ -249,6 +251,7 @@ constexpr int EN_MASS_FEW_ROWS = 8;
 // beyond it the parts of many workgroups and a second launch (17 buckets: 1024 pairs 5.0 / 7.7 us, 2048 7.1 / 7.7,
 // 3072 9.3 / 7.7; 16 agents x 25 buckets: 4.7 / 8.2, 6.2 / 8.2, 7.8 / 10.0).
 constexpr int EN_MASS_FEW_PAIRS = 2048;
+constexpr int EN_MASS_BG = 8;           // buckets per workgroup of the reduced masses
 constexpr int EN_MASS_UNITS = 4;        // units of 64 query rows of a head per workgroup of the reduced masses, one per wave
 constexpr int EN_MASS_ARRIVALS = 1023;  // workgroups that may meet in one accumulator of the reduced masses (10 bits)
 constexpr int EN_MAX_SPLITS = 64;       // KV splits of a plan: the mass kernels hold one split per lane

@@ -19,7 +19,6 @@ __device__ __forceinline__ void add_reduced_mass(const EnMassArgs &a, size_t idx
 
 // A workgroup of the reduced masses takes EN_MASS_BG consecutive buckets of one agent over EN_MASS_UNITS
 // units of 64 query rows (see mass_partial_block).
-constexpr int EN_MASS_BG = 8;
 __host__ __device__ inline int mass_bucket_groups(const EnMassArgs &m)
 {
     return (m.Smax + 1 + EN_MASS_BG - 1) / EN_MASS_BG;
@@ -38,6 +37,12 @@ __host__ inline int mass_partial_blocks(const EnMassArgs &m)
 template <typename T, int D, int G, int NB>
 __global__ __launch_bounds__(256) void combine_kernel(EnAttnArgs a, EnMassArgs m, int n_comb)
 {
+    // The arguments in one batch and no integer divisions, as in attn_bf16_kernel, sums over lanes in the vector ALU: the
+    // launch without masses is 2.5 us of start and end and three trips to memory, with them these and what the set-up of
+    // the buckets takes. With masses, one agent's ragged map 7.6 -> 6.2 us, 8 K tokens 9.5 -> 8.4; a decode step's 26
+    // partial results 3.7 -> 3.4.
+    asm volatile("" ::"s"(a.out), "s"(a.ws_ml), "s"(a.ws_opart), "s"(a.ws_mlfin), "s"(a.B), "s"(a.by_nq.mul), "s"(a.by_hq.mul),
+                 "s"(m.by_splits.mul), "s"(m.ws_seg), "s"(m.red_acc), "s"(m.bnd), "s"(m.hdr), "s"(m.B), "s"(m.q_first), "s"(n_comb));
     // head of the grid (these workgroups take longest: they start first): the reduced masses, where
     // the attention call was asked for them (without: 10.1 -> 6.1 us on the 8K-context step)
     const int n_part = (int)gridDim.x - n_comb;
@@ -113,11 +118,10 @@ __global__ __launch_bounds__(256) void combine_kernel(EnAttnArgs a, EnMassArgs m
         f32x2 ml = {M, l};
         *reinterpret_cast<f32x2 *>(a.ws_mlfin + row * 2) = ml;
     }
-    // 32-bit divisions (the host refuses more rows than that): a 64-bit division by a run-time
-    // value is some hundred instructions, a third of this kernel
-    const unsigned bh = (unsigned)row / (unsigned)a.Nq;
+    // (the host refuses 2^31 rows and more)
+    const unsigned bh = divided((unsigned)row, a.by_nq);
     const unsigned i = (unsigned)row - bh * (unsigned)a.Nq;
-    const unsigned b = bh / (unsigned)a.Hq;
+    const unsigned b = divided(bh, a.by_hq);
     const unsigned hq = bh - b * (unsigned)a.Hq;
     T *op = (T *)a.out + (((size_t)b * a.Nq + i) * a.Hq + hq) * D + d0;
     *reinterpret_cast<tvec *>(op) = __builtin_convertvector(acc * inv, tvec);
@@ -178,11 +182,12 @@ struct EnSplitMap {
     unsigned long long keys;       // bit sp: split sp holds at least one tile
 };
 // whole wave, uniform arguments
-__device__ __forceinline__ EnSplitMap split_map(int n_splits, int ntiles)
+__device__ __forceinline__ EnSplitMap split_map(const EnDivisor &by_splits, int ntiles)
 {
+    const int n_splits = by_splits.n;
     const unsigned q = threadIdx.x % 64;
-    const unsigned bgn = split_first_tile(q, ntiles, n_splits);
-    const unsigned end = split_first_tile(q + 1, ntiles, n_splits);
+    const unsigned bgn = divided(q * ntiles + n_splits - 1, by_splits);           // split_first_tile
+    const unsigned end = divided((q + 1) * ntiles + n_splits - 1, by_splits);
     EnSplitMap m;
     m.end_tile = (int)q < n_splits ? (int)end : 0x7fffffff;
     m.keys = __ballot((int)q < n_splits && end != bgn);
@@ -255,10 +260,12 @@ __global__ __launch_bounds__(256) void mass_rows_kernel(EnMassArgs a)
     constexpr int PER = EN_MASS_RB / 4;          // buckets per wave
     __shared__ float tile[64][EN_MASS_RB + 1];
     const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+    asm volatile("" ::"s"(a.ws_ml), "s"(a.ws_mlfin), "s"(a.bnd), "s"(a.out), "s"(a.B), "s"(a.by_splits.mul), "s"(a.q_first));
     const int n_chunks = (a.Smax + EN_MASS_RB) / EN_MASS_RB;
-    const int i0 = blockIdx.x / n_chunks * 64, i = i0 + lane;
+    const int rows64 = __builtin_amdgcn_readfirstlane(small_quotient(blockIdx.x, n_chunks));
+    const int i0 = rows64 * 64, i = i0 + lane;
     const int hq = blockIdx.y, b = blockIdx.z;
-    const int s0 = blockIdx.x % n_chunks * EN_MASS_RB;
+    const int s0 = (blockIdx.x - rows64 * n_chunks) * EN_MASS_RB;
     const bool valid = i < a.Nq;
     const size_t rows = (size_t)a.B * a.Hq * a.Nq;
     const size_t row = ((size_t)b * a.Hq + hq) * a.Nq + (valid ? i : 0);
@@ -268,7 +275,7 @@ __global__ __launch_bounds__(256) void mass_rows_kernel(EnMassArgs a)
     const int S = hdr[0];
     const int Ltot = hdr[1] + a.q_first + a.Nq;     // end of what the rows could see
     const int ntiles = (Ltot + EN_KEY_TILE - 1) / EN_KEY_TILE;
-    const EnSplitMap map = split_map(a.n_splits, ntiles);
+    const EnSplitMap map = split_map(a.by_splits, ntiles);
     const int32_t *bnd = a.bnd + (size_t)b * (a.Smax + 2);
     int lo[PER], hi[PER];
     bool live[PER], simple = a.sub == 1;
@@ -382,10 +389,10 @@ __global__ __launch_bounds__(256) void mass_rows_few_kernel(EnMassArgs a)
 __device__ __forceinline__ void mass_partial_block(const EnMassArgs &a, int blk, float *red)
 {
     constexpr int BG = EN_MASS_BG;
-    const int ng = mass_bucket_groups(a);
-    const int s0 = (blk % ng) * BG;
-    const int wg = (blk / ng) % a.red_target;          // workgroup among those of the agent's bucket group
-    const int b = blk / (ng * a.red_target);
+    const int wgs = divided(blk, a.by_groups);
+    const int s0 = (blk - wgs * a.by_groups.n) * BG;
+    const int b = divided(wgs, a.by_target);
+    const int wg = wgs - b * a.red_target;             // workgroup among those of the agent's bucket group
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
     const int n_chunks = (a.Nq + 63) / 64;
     const int n_units = a.Hq * n_chunks;
@@ -419,9 +426,9 @@ __device__ __forceinline__ void mass_partial_block(const EnMassArgs &a, int blk,
             live_v = s0 + jl <= S && bhi > blo;
             const unsigned t_lo = live_v ? blo / EN_KEY_TILE : 0, t_hi = live_v ? (bhi - 1) / EN_KEY_TILE : 0;
             // the split that holds tile t is the largest sp whose first tile is <= t
-            const unsigned l = t_lo * n / ntiles, h = t_hi * n / ntiles;
-            const unsigned e0 = split_first_tile(l, ntiles, n), e1 = split_first_tile(l + 1, ntiles, n),
-                           e2 = split_first_tile(l + 2, ntiles, n);
+            const unsigned l = small_quotient(t_lo * n, ntiles), h = small_quotient(t_hi * n, ntiles);
+            const auto first_tile = [&](unsigned sp) { return divided(sp * ntiles + n - 1, a.by_splits); };
+            const unsigned e0 = first_tile(l), e1 = first_tile(l + 1), e2 = first_tile(l + 2);
             next_v = l + 1 < n;
             use0_v = live_v && e0 != e1;                // an agent with fewer tiles than splits leaves some empty
             use1_v = live_v && h > l && next_v && e1 != e2;
@@ -433,7 +440,7 @@ __device__ __forceinline__ void mass_partial_block(const EnMassArgs &a, int blk,
         const unsigned use0 = (unsigned)__ballot(use0_v), use1 = (unsigned)__ballot(use1_v);
         const unsigned live = (unsigned)__ballot(live_v);
         const bool simple = a.sub == 1 && __ballot(live_v && hi_v - lo_v > 1) == 0;
-        const int hq = unit / n_chunks;
+        const int hq = divided(unit, a.by_chunks);
         const int row_i = (unit - hq * n_chunks) * 64 + lane;
         const bool on = row_i < a.Nq;
         const int i = on ? row_i : 0;
@@ -459,7 +466,7 @@ __device__ __forceinline__ void mass_partial_block(const EnMassArgs &a, int blk,
                 acc[j] = part * inv;
             }
         } else {
-            const EnSplitMap map = split_map(a.n_splits, (int)ntiles);
+            const EnSplitMap map = split_map(a.by_splits, (int)ntiles);
             int lo[BG], hi[BG];
 #pragma unroll
             for (int j = 0; j < BG; ++j) {
@@ -496,6 +503,7 @@ __device__ __forceinline__ void mass_partial_block(const EnMassArgs &a, int blk,
 __global__ __launch_bounds__(256) void mass_partial_kernel(EnMassArgs a)
 {
     __shared__ float red[4 * EN_MASS_BG];
+    asm volatile("" ::"s"(a.by_splits.mul), "s"(a.ws_ml), "s"(a.parts), "s"(a.bnd), "s"(a.B), "s"(a.q_first));
     mass_partial_block(a, blockIdx.x, red);
 }
 
@@ -568,21 +576,23 @@ __global__ __launch_bounds__(256) void cluster_score_kernel(EnClusterArgs a)
     const int32_t *spans = reinterpret_cast<const int32_t *>(
         reinterpret_cast<uintptr_t>(__builtin_amdgcn_kernarg_segment_ptr()) + offsetof(EnClusterArgs, spans));
     const int lo = spans[o], hi = spans[o + 1];
+    asm volatile("" ::"s"(m.ws_ml), "s"(m.ws_mlfin), "s"(m.bnd), "s"(m.B), "s"(m.by_splits.mul), "s"(m.q_first), "s"(a.score), "s"(a.scale));
     const int n_pairs = (hi - lo) * m.Hq;
     const size_t rows = (size_t)m.B * m.Hq * m.Nq;
-    const int S = m.nseg[b];
-    const int32_t *bnd = m.bnd + (size_t)b * (m.Smax + 2);
-    const int Ltot = bnd[S] + m.q_first + m.Nq;     // end of what the rows could see
+    const en_table_ptr hdr = as_table(m.hdr + 4 * (size_t)b);
+    const int S = hdr[0];
+    const en_table_ptr bnd = as_table(m.bnd + (size_t)b * (m.Smax + 2));
+    const int Ltot = hdr[1] + m.q_first + m.Nq;     // end of what the rows could see
     const int ntiles = (Ltot + EN_KEY_TILE - 1) / EN_KEY_TILE;
     const int len = s <= S ? bnd[s + 1] - bnd[s] : 0;
     float acc = 0.f;
-    const EnSplitMap map = split_map(m.n_splits, ntiles);
+    const EnSplitMap map = split_map(m.by_splits, ntiles);
     if (len > 0) {
         int slo, shi;
         bucket_splits(map, m.n_splits, Ltot, bnd[s], bnd[s + 1], slo, shi);
         for (int idx = threadIdx.x; idx < n_pairs; idx += 256) {
             // token fastest: neighbouring lanes read neighbouring scratch entries
-            const int hq = idx / (hi - lo), i = lo + idx % (hi - lo);
+            const int hq = small_quotient(idx, hi - lo), i = lo + idx - hq * (hi - lo);
             const size_t row = ((size_t)b * m.Hq + hq) * m.Nq + i;
             float M, L;
             row_final_ml(m, rows, row, M, L);
@@ -604,10 +614,11 @@ __global__ __launch_bounds__(256) void cluster_score_kernel(EnClusterArgs a)
     }
 }
 
+// A wave per (agent, object), the lanes take the segments in turn.
 __global__ __launch_bounds__(256) void cluster_decide_kernel(EnClusterArgs a)
 {
     const EnMassArgs &m = a.m;
-    const int idx = blockIdx.x * 256 + threadIdx.x;
+    const int idx = blockIdx.x * 4 + threadIdx.x / 64, lane = threadIdx.x % 64;
     if (idx >= m.B * a.n_obj)
         return;
     const int b = idx / a.n_obj;
@@ -616,14 +627,25 @@ __global__ __launch_bounds__(256) void cluster_decide_kernel(EnClusterArgs a)
     const float *score = a.score + (size_t)idx * (m.Smax + 1);
     float best = EN_NEG_INF;
     int best_s = -1;
-    for (int s = 0; s < S; ++s) {
+    for (int s = lane; s < S; s += 64) {
         const float v = score[s] * a.scale;
         if (bnd[s + 1] > bnd[s] && v > best) {   // empty segments never win; the lowest s among equals
             best = v;
             best_s = s;
         }
     }
-    a.assign[idx] = (best_s >= 0 && best >= a.threshold) ? best_s : -1;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const float v = __shfl_xor(best, o, 64);
+        const int s = __shfl_xor(best_s, o, 64);
+        // (a lane without a segment has the largest number of all)
+        if (v > best || (v == best && (unsigned)s < (unsigned)best_s)) {
+            best = v;
+            best_s = s;
+        }
+    }
+    if (lane == 0)
+        a.assign[idx] = (best_s >= 0 && best >= a.threshold) ? best_s : -1;
 }
 
 // ---------------------------------------------------------------------------
@@ -684,7 +706,7 @@ int en_launch_cluster(const en_pool *pool, const EnClusterArgs &a, void *stream)
     const dim3 grid(a.m.Smax + 1, a.n_obj, a.m.B), blk(256);
     hipLaunchKernelGGL(cluster_score_kernel, grid, blk, 0, (hipStream_t)stream, a);
     if (a.assign) {
-        const dim3 grid2((a.m.B * a.n_obj + 255) / 256);
+        const dim3 grid2((a.m.B * a.n_obj + 3) / 4);
         hipLaunchKernelGGL(cluster_decide_kernel, grid2, blk, 0, (hipStream_t)stream, a);
     }
     return (int)hipGetLastError();
