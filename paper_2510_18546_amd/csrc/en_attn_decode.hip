@@ -924,42 +924,57 @@ __global__ __launch_bounds__(64 * WAVES) void attn_f32_kernel(EnAttnArgs a)
     __shared__ f32x2 sfirst[WAVES][F32_ROWS];        // (sum, reference) of the bucket that a wave entered midway
     __shared__ int sspan[WAVES];                     // 1: ... and that it did not leave
 
+    // (arguments and divisions: see attn_bf16_kernel)
+    asm volatile("" ::"s"(a.q), "s"(a.cos_tab), "s"(a.bnd), "s"(a.ws_ml), "s"(a.B), "s"(a.Smax), "s"(a.by_ptiles.mul),
+                 "s"(a.by_nq.mul), "s"(a.one_Lc), "s"(a.red_zero));
     if (blockIdx.x == 0 && a.red_zero)
         for (int i = threadIdx.x; i < a.n_red_zero; i += 64 * WAVES)
             a.red_zero[i] = 0ull;
-    int t = blockIdx.x;
-    const int rg = t % a.n_ptiles;
-    t /= a.n_ptiles;
-    const int sp = t % a.n_splits;
-    t /= a.n_splits;
-    const int kvh = t % a.Hkv;
-    const int b = t / a.Hkv;
+    const unsigned t = divided(blockIdx.x, a.by_ptiles);
+    const int rg = blockIdx.x - t * a.n_ptiles;
+    const unsigned t2 = divided(t, a.by_splits);
+    const int sp = t - t2 * a.n_splits;
+    const int b = divided(t2, a.by_hkv);
+    const int kvh = t2 - b * a.Hkv;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
     const int lane = tid % 64;
     const int col = lane % 16, grp = lane / 16;
-    const int r = a.Hq / a.Hkv;
+    const int r = a.by_r.n;
 
+    // all bucket bounds at once, one per lane, when they fit: a search through the table is a trip to memory per step
+    const int32_t *bnd_g = a.bnd + (size_t)b * (a.Smax + 2);
+    const bool bnd_in_lanes = a.Smax + 2 <= 64;
+    const int my_bnd = bnd_g[min(lane, a.Smax + 1)];
     const en_table_ptr hdr = as_table(a.hdr + 4 * (size_t)b);
-    const en_table_ptr bnd = as_table(a.bnd + (size_t)b * (a.Smax + 2));
-    const int S = hdr[0];
-    const int Lc = hdr[1] + a.q_first;       // rows are new tokens q_first .. q_first+Nq-1
+    const en_table_ptr bnd = as_table(bnd_g);
+    auto bound_at = [&](int s) {             // s is wave-uniform
+        return bnd_in_lanes ? __builtin_amdgcn_readlane(my_bnd, s) : bnd[s];
+    };
+    int S = a.one_S, Lc = a.one_Lc;
+    if (a.B > 1) {
+        S = hdr[0];
+        Lc = hdr[1];
+    }
+    Lc += a.q_first;                         // rows are new tokens q_first .. q_first+Nq-1
     const int Ltot = Lc + a.Nq;
     const int ntiles = (Ltot + EN_KEY_TILE - 1) / EN_KEY_TILE;
-    const int kbeg = (int)split_first_tile(sp, ntiles, a.n_splits) * EN_KEY_TILE;
-    const int kend = min((int)split_first_tile(sp + 1, ntiles, a.n_splits) * EN_KEY_TILE, Ltot);
+    const int kbeg = (int)divided(sp * ntiles + a.n_splits - 1, a.by_splits) * EN_KEY_TILE;           // split_first_tile
+    const int kend = min((int)divided((sp + 1) * ntiles + a.n_splits - 1, a.by_splits) * EN_KEY_TILE, Ltot);
 
     // the workgroup's rows, head by head: row rr is new token rr % Nq of head rr / Nq
     const int n_rows = r * a.Nq;
     const int r0 = rg * F32_ROWS, r1 = min(r0 + F32_ROWS, n_rows) - 1;
-    const int i_hi = r0 / a.Nq == r1 / a.Nq ? r1 % a.Nq : a.Nq - 1;
+    const int h1 = divided(r1, a.by_nq);
+    const int i_hi = (int)divided(r0, a.by_nq) == h1 ? r1 - h1 * a.Nq : a.Nq - 1;
     const bool row_valid = r0 + col <= r1;
     const int rr = min(r0 + col, r1);
-    const int hq = kvh * r + rr / a.Nq, i_row = rr % a.Nq;
+    const int hr = divided(rr, a.by_nq);
+    const int hq = kvh * r + hr, i_row = rr - hr * a.Nq;
     const int kvis = min(kend, Lc + i_hi + 1);           // keys that any of the rows may see
     const int n_blk = kvis > kbeg ? (kvis - kbeg + F32_KEYS - 1) / F32_KEYS : 0;
     const int per = (n_blk + WAVES - 1) / WAVES;
-    const int n_used = per > 0 ? (n_blk + per - 1) / per : 0;          // waves with keys
+    const int n_used = per > 0 ? __builtin_amdgcn_readfirstlane(small_quotient(n_blk + per - 1, per)) : 0;      // waves with keys
     const int wb = kbeg + min(wave * per, n_blk) * F32_KEYS;           // this wave's keys
     const int we = min(kbeg + min((wave + 1) * per, n_blk) * F32_KEYS, kvis);
 
@@ -1020,9 +1035,9 @@ __global__ __launch_bounds__(64 * WAVES) void attn_f32_kernel(EnAttnArgs a)
     };
     // The bucket the wave is in. One that an earlier wave began is handed over through sfirst, one that a
     // later wave goes on with stays open; the others are complete here.
-    int cur = wb < we ? find_bucket(bnd, S, wb) : 0;
-    int cur_end = wb < we ? bnd[cur + 1] : 0;
-    const bool entered = wb < we && wb > kbeg && bnd[cur] < wb;
+    int cur = wb >= we ? 0 : bnd_in_lanes ? (int)__popcll(__ballot(lane <= S && my_bnd <= wb)) - 1 : find_bucket(bnd, S, wb);
+    int cur_end = wb < we ? bound_at(cur + 1) : 0;
+    const bool entered = wb < we && wb > kbeg && bound_at(cur) < wb;
     bool first = entered, open = false;
     auto leave_bucket = [&]() {
         const float tot = row_sum(seg);
@@ -1090,10 +1105,10 @@ __global__ __launch_bounds__(64 * WAVES) void attn_f32_kernel(EnAttnArgs a)
                 seg += (in[0] + in[1]) + (in[2] + in[3]);
                 if (cur_end > ke || cur > S)
                     break;
-                if (cur_end > bnd[cur])      // (an empty bucket has no entry)
+                if (cur_end > bound_at(cur)) // (an empty bucket has no entry)
                     leave_bucket();
                 ++cur;
-                cur_end = cur <= S ? bnd[cur + 1] : 0x7fffffff;
+                cur_end = cur <= S ? bound_at(cur + 1) : 0x7fffffff;
                 lo = hi;
             }
         }
@@ -1143,12 +1158,12 @@ __global__ __launch_bounds__(64 * WAVES) void attn_f32_kernel(EnAttnArgs a)
     // ---- the waves meet ----
     float open_sum = 0.f;
     if (wb < we) {
-        open = cur <= S && cur_end > we && bnd[cur] < we && we < kvis;
+        open = cur <= S && cur_end > we && bound_at(cur) < we && we < kvis;
         if (open) {
             open_sum = row_sum(seg);
             if (first && grp == 0)
                 sfirst[wave][col] = f32x2{open_sum, m};
-        } else if (cur <= S && bnd[cur] < we && cur_end > we) {
+        } else if (cur <= S && bound_at(cur) < we && cur_end > we) {
             leave_bucket();                  // the split, or what the rows may see, ends in it
         }
         const float lt = row_sum(l);
@@ -1161,8 +1176,11 @@ __global__ __launch_bounds__(64 * WAVES) void attn_f32_kernel(EnAttnArgs a)
     }
     __syncthreads();
     float M = EN_NEG_INF;
-    for (int w = 0; w < n_used; ++w)
-        M = fmaxf(M, sml[w][col][0]);
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {        // (all read at once; what waves without keys left is not used)
+        const float x = sml[w][col][0];
+        M = w < n_used ? fmaxf(M, x) : M;
+    }
     if (wb < we) {
         const float keep = m == EN_NEG_INF ? 0.f : fast_exp2(m - M);
 #pragma unroll
@@ -1200,15 +1218,25 @@ __global__ __launch_bounds__(64 * WAVES) void attn_f32_kernel(EnAttnArgs a)
         if (row >= F32_ROWS || r0 + row > r1)
             return;
         float Mr = EN_NEG_INF, L = 0.f;
-        for (int w = 0; w < n_used; ++w)
-            Mr = fmaxf(Mr, sml[w][row][0]);
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        for (int w = 0; w < n_used; ++w) {
-            const f32x2 x = sml[w][row];
-            L += x[0] == EN_NEG_INF ? 0.f : x[1] * fast_exp2(x[0] - Mr);
-            acc += *reinterpret_cast<const f32x4 *>(&so[w][row][c4]);
+        f32x2 ml[WAVES];
+        f32x4 part[WAVES];
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            ml[w] = sml[w][row];
+            part[w] = *reinterpret_cast<const f32x4 *>(&so[w][row][c4]);
         }
-        const int h = kvh * r + (r0 + row) / a.Nq, i = (r0 + row) % a.Nq;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w)
+            Mr = w < n_used ? fmaxf(Mr, ml[w][0]) : Mr;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w)
+            if (w < n_used) {
+                L += ml[w][0] == EN_NEG_INF ? 0.f : ml[w][1] * fast_exp2(ml[w][0] - Mr);
+                acc += part[w];
+            }
+        const int ho = divided(r0 + row, a.by_nq);
+        const int h = kvh * r + ho, i = r0 + row - ho * a.Nq;
         const size_t out_row = ((size_t)b * a.Hq + h) * a.Nq + i;
         const float inv = L > 0.f ? 1.f / L : 0.f;
         if (a.ws_ml && c4 == 0) {
