@@ -481,7 +481,7 @@ __global__ __launch_bounds__(64 * SUB) void attn_decode_kernel(EnAttnArgs a)
 // results meet in LDS. The chain that is left is argument, header, load, two products, exchange, store: 5.7 us on average
 // for five tiles (7.1 the slowest workgroup), 3.2 for two, of which the loads' way through the vector memory path of a
 // compute unit (64 bytes a clock) is 1.5 and 0.5. Per decoded token with the merge, streaming kernel / this one: 8 K tokens
-// 16.5 / 11.8 us, 1.5 K 11.4 / 8.5, 0.25 K, with one split and no merge, 11.0 / 7.4. See once_fits for more, and for which
+// 16.5 / 11.4 us, 1.5 K 11.4 / 8.4, 0.25 K, with one split and no merge, 11.0 / 7.2. See once_fits for more, and for which
 // steps it takes.
 //
 // Products are 16 x 16 x 32: the 16 columns are the r * N_q rows, half the width of the kernel above, and a score product's
@@ -534,22 +534,18 @@ __global__ __launch_bounds__(128 * TPS) void attn_once_kernel(EnAttnArgs a)
     constexpr int NBK = KHALF / 1024, NBV = VBYTES / 2048;   // loader blocks per wave
     __shared__ __attribute__((aligned(1024))) char smem[TPS * STAGE];
 
-    // (all of the arguments at once: they lie in several lines, a trip to memory each when they are asked for one by one)
-    asm volatile("" ::"s"(a.q), "s"(a.cos_tab), "s"(a.kc), "s"(a.app_k), "s"(a.hdr), "s"(a.q_first), "s"(a.ws_seg), "s"(a.scale_log2e));
+    // (arguments and divisions: see attn_bf16_kernel)
+    asm volatile("" ::"s"(a.q), "s"(a.cos_tab), "s"(a.kc), "s"(a.bnd), "s"(a.ws_ml), "s"(a.app_k), "s"(a.app_v), "s"(a.hdr), "s"(a.B),
+                 "s"(a.by_splits.mul), "s"(a.by_r.n), "s"(a.by_nq.mul), "s"(a.one_Lc), "s"(a.scale_log2e));
     const int sp = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
     const int lane = tid % 64;
     const int col = lane % 16, g = lane / 16;
-    // x / n for x < 2^15, n <= 2^10 without the thirty instructions of an integer division: x + 1/2 is at least n / 2048
-    // of n away from a multiple of n, the error of the quotient is 2^-21 of itself
-    auto quotient = [](int x, int n) {
-        return __builtin_amdgcn_readfirstlane((int)(((float)x + 0.5f) * __builtin_amdgcn_rcpf((float)n)));
-    };
-    const int r = quotient(a.Hq, a.Hkv);
+    const int r = a.by_r.n;
     const int rows = r * a.Nq;                   // at most 16
     const bool row_valid = col < rows;           // (the other columns compute on row 0 once more, for nobody)
-    const int hl = !row_valid || a.Nq == 1 ? (row_valid ? col : 0) : col / a.Nq;
+    const int hl = row_valid ? divided(col, a.by_nq) : 0;
     const int i_row = row_valid ? col - hl * a.Nq : 0;
     const int hq = kvh * r + hl;
 
@@ -559,12 +555,16 @@ __global__ __launch_bounds__(128 * TPS) void attn_once_kernel(EnAttnArgs a)
     if (a.ws_seg && bnd_in_lanes && lane <= a.Smax + 1)
         my_bnd = bnd_g[lane];
     const en_table_ptr hdr = as_table(a.hdr + 4 * (size_t)b);
-    const int S = hdr[0];
-    const int Lc = hdr[1] + a.q_first;           // rows are new tokens q_first .. q_first+Nq-1
+    int S = a.one_S, Lc = a.one_Lc;
+    if (a.B > 1) {
+        S = hdr[0];
+        Lc = hdr[1];
+    }
+    Lc += a.q_first;                             // rows are new tokens q_first .. q_first+Nq-1
     const int Ltot = Lc + a.Nq;
     const int ntiles = (Ltot + EN_KEY_TILE - 1) / EN_KEY_TILE;
-    const int t_begin = quotient(sp * ntiles + a.n_splits - 1, a.n_splits);        // split_first_tile
-    const int t_end = quotient((sp + 1) * ntiles + a.n_splits - 1, a.n_splits);
+    const int t_begin = divided(sp * ntiles + a.n_splits - 1, a.by_splits);        // split_first_tile
+    const int t_end = divided((sp + 1) * ntiles + a.n_splits - 1, a.by_splits);
     const int key_begin = t_begin * EN_KEY_TILE, key_end = min(t_end * EN_KEY_TILE, Ltot);
     const unsigned rows_all = (unsigned)a.B * a.Hq * a.Nq;
     if (t_begin >= t_end) {                      // an agent with fewer tiles than splits
@@ -839,7 +839,7 @@ __global__ __launch_bounds__(128 * TPS) void attn_once_kernel(EnAttnArgs a)
         for (int w = 0; w < W; ++w)
             acc += wt[w] == 0.f ? f32x4{0.f, 0.f, 0.f, 0.f} : x[w] * wt[w];
         const float inv = L > 0.f ? 1.f / L : 0.f;
-        const int h = kvh * r + (a.Nq == 1 ? c : c / a.Nq), i = a.Nq == 1 ? 0 : c % a.Nq;
+        const int ho = divided(c, a.by_nq), h = kvh * r + ho, i = c - ho * a.Nq;
         const size_t row = ((size_t)b * a.Hq + h) * a.Nq + i;
         bf16_t *op = (a.n_splits == 1) ? (bf16_t *)a.out + (((size_t)b * a.Nq + i) * a.Hq + h) * D
                                        : (bf16_t *)a.ws_opart + ((size_t)sp * rows_all + row) * D;
@@ -856,10 +856,9 @@ __global__ __launch_bounds__(128 * TPS) void attn_once_kernel(EnAttnArgs a)
         return bnd_in_lanes ? (int)__popcll(__ballot(lane <= S && my_bnd <= tok)) - 1 : find_bucket(as_table(bnd_g), S, tok);
     };
     const int s_first = bucket_of(key_begin), n_pairs = (bucket_of(key_end - 1) - s_first + 1) * rows;
-    const float per_row = 1.f / (float)rows;
     for (int p0 = 4 * (W - 1 - wave); p0 < n_pairs; p0 += 4 * W) {
         const int p = min(p0 + g, n_pairs - 1);
-        const int sb = (int)(((float)p + 0.5f) * per_row), c = p - sb * rows;         // p / rows (p < 2^16)
+        const int sb = small_quotient(p, rows), c = p - sb * rows;
         const int s = s_first + sb;
         float x[2 * W];                          // this lane's keys col, col + 16, ..
 #pragma unroll
@@ -884,7 +883,7 @@ __global__ __launch_bounds__(128 * TPS) void attn_once_kernel(EnAttnArgs a)
         }
         sum = lanes_reduce<16>(sum, [](float x, float y) { return x + y; });
         if (col == 0 && p0 + g < n_pairs && bhi > blo) {
-            const int h = kvh * r + (a.Nq == 1 ? c : c / a.Nq), i = a.Nq == 1 ? 0 : c % a.Nq;
+            const int ho = divided(c, a.by_nq), h = kvh * r + ho, i = c - ho * a.Nq;
             f32x2 v = {sum, M};
             *reinterpret_cast<f32x2 *>(a.ws_seg + ((((size_t)sp * a.B * a.Hq + (size_t)b * a.Hq + h) * (a.Smax + 1) + s) * a.Nq + i) * 2) = v;
         }
