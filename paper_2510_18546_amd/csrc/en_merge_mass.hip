@@ -660,7 +660,9 @@ int en_launch_combine(const en_pool *pool, const EnAttnArgs &a, const EnMassArgs
     // results per lane (each a dependent step of the running merge), not the number of workgroups:
     // about four per lane is best. Per decoded token, same box: 128 partial results by 16 / 32 / 64
     // lanes 18.0 / 17.5 / 17.9 us; 74 by 16 / 32 / 64 lanes 12.1 / 11.5 / 11.6; 32 (four agents) by
-    // 4 / 16 lanes 14.0 / 13.1. A prefill's many rows fill the chip without that.
+    // 4 / 16 lanes 14.0 / 13.1. A prefill's many rows fill the chip without that. What a lane asks for at once beyond the
+    // splits there are is the last split's again, so the batch is the one that holds them: plans of two splits by batches
+    // of two and of four, passes of a ragged map 30.98 / 31.3 us, of an int8 map 75.1 / 75.6.
     int G = a.n_splits > 32 ? 16 : (a.n_splits > 8 ? 4 : 1);
     if ((size_t)a.B * a.Hq * a.Nq * (D / vec) <= 16384)
         G = a.n_splits > 64 ? 32 : (a.n_splits > 16 ? 16 : (a.n_splits > 4 ? 4 : 1));
@@ -670,7 +672,9 @@ int en_launch_combine(const en_pool *pool, const EnAttnArgs &a, const EnMassArgs
     const dim3 grid((unsigned)(n_comb + n_part)), blk(256);
 #define EN_COMBINE(T, DD)                                                                                    \
     do {                                                                                                     \
-        if (G == 1)                                                                                          \
+        if (G == 1 && a.n_splits == 2)                                                                       \
+            hipLaunchKernelGGL((combine_kernel<T, DD, 1, 2>), grid, blk, 0, st, a, m, n_comb);               \
+        else if (G == 1)                                                                                     \
             hipLaunchKernelGGL((combine_kernel<T, DD, 1, 4>), grid, blk, 0, st, a, m, n_comb);               \
         else if (G == 4 && a.n_splits <= 8)                                                                  \
             hipLaunchKernelGGL((combine_kernel<T, DD, 4, 2>), grid, blk, 0, st, a, m, n_comb);               \
