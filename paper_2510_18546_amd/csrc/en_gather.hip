@@ -11,24 +11,44 @@
 //   append / append_q8     new objects' K/V rows join their group's block
 #include "en_device.h"
 
-// The bucket bounds and the selected groups of an agent, staged in LDS for the searches of a
-// gather block: a binary search over the table in global memory is six dependent trips to memory
-// per row, the group number a seventh (about 3 us before a block that moves 16 KB can issue its
-// first load); over LDS it is a few hundred cycles. All threads of the block call stage_tables;
-// staged = false: the tables do not fit and are read where they are.
+// The bucket bounds and the selected groups of an agent. Up to 62 segments, every wave holds both tables in its lanes
+// and finds its tokens' groups without a memory access (see context_row). More are staged in LDS: a binary search over the
+// table in global memory is six dependent trips to memory per row, the group number a seventh (about 3 us before a block
+// that moves 16 KB can issue its first load); over LDS it is a few hundred cycles. Tables that do not fit there either are
+// read where they are. All threads of the block call open_tables. Tables in lanes and the arguments asked for together,
+// against tables in LDS and arguments one by one: one agent's 4 K tokens 5.96 / 6.22 us, its 8.7 K 15.6 / 16.1, from 8-bit
+// codes 4 x 3.2 K 16.9 / 18.4.
 constexpr int EN_GATHER_TAB_LDS = 256;          // entries of either table
 struct EnGatherTables {
     const int32_t *bnd, *sel;                   // the agent's bounds [Smax + 2] and groups [Smax]
-    bool staged;
+    int S, Lc, Ltot;                            // segments, gathered tokens, all tokens
+    int my_bnd, my_sel;                         // entry `lane` of either
+    bool in_lanes, staged;
 };
-__device__ __forceinline__ EnGatherTables stage_tables(const EnGatherArgs &a, int b, int32_t *lds)
+__device__ __forceinline__ EnGatherTables open_tables(const EnGatherArgs &a, int b, int32_t *lds)
 {
     const int nb = a.Smax + 2;
     const int sstr = a.Smax > 0 ? a.Smax : 1;
     EnGatherTables t;
     t.bnd = a.bnd + (size_t)b * nb;
     t.sel = a.sel + (size_t)b * sstr;
+    t.in_lanes = nb <= 64;
     t.staged = nb <= EN_GATHER_TAB_LDS;
+    t.my_bnd = t.my_sel = 0;
+    if (t.in_lanes) {
+        const int lane = threadIdx.x % 64;
+        if (lane < nb)
+            t.my_bnd = t.bnd[lane];
+        if (lane < a.Smax)
+            t.my_sel = t.sel[lane];
+        t.S = as_table(a.nseg)[b];
+        t.Lc = __builtin_amdgcn_readlane(t.my_bnd, t.S);
+        t.Ltot = __builtin_amdgcn_readlane(t.my_bnd, t.S + 1);
+        return t;
+    }
+    t.S = as_table(a.nseg)[b];
+    t.Lc = as_table(t.bnd)[t.S];
+    t.Ltot = as_table(t.bnd)[t.S + 1];
     if (t.staged) {
         for (int i = threadIdx.x; i < nb; i += 256)
             lds[i] = t.bnd[i];
@@ -37,6 +57,40 @@ __device__ __forceinline__ EnGatherTables stage_tables(const EnGatherArgs &a, in
         __syncthreads();
     }
     return t;
+}
+
+// Group and row in its block of context token `tok` (below L_c; anything for others). The whole wave calls, its tokens
+// ascending from lane to lane: the segments of the first and the last one are two counts of bounds, and a lane goes
+// through the few between them.
+__device__ __forceinline__ void context_row(const EnGatherTables &t, const int32_t *lds, int tok, int &group, int &row)
+{
+    if (t.in_lanes) {
+        const int lane = threadIdx.x % 64;
+        auto bucket = [&](int x) { return (int)__popcll(__ballot(lane <= t.S && t.my_bnd <= x)) - 1; };
+        const int s0 = bucket(__builtin_amdgcn_readfirstlane(tok));
+        const int s1 = bucket(min(__builtin_amdgcn_readlane(tok, 63), t.Lc - 1));
+        int start = __builtin_amdgcn_readlane(t.my_bnd, s0);
+        group = __builtin_amdgcn_readlane(t.my_sel, s0);
+        for (int s = s0 + 1; s <= s1; ++s) {
+            const int from = __builtin_amdgcn_readlane(t.my_bnd, s), g = __builtin_amdgcn_readlane(t.my_sel, s);
+            start = tok >= from ? from : start;
+            group = tok >= from ? g : group;
+        }
+        row = tok - start;
+        return;
+    }
+    group = row = 0;
+    if (tok >= t.Lc)
+        return;
+    if (t.staged) {
+        const int s = find_bucket(lds, t.S, tok);
+        group = lds[EN_GATHER_TAB_LDS + s];
+        row = tok - lds[s];
+    } else {
+        const int s = find_bucket(t.bnd, t.S, tok);
+        group = t.sel[s];
+        row = tok - t.bnd[s];
+    }
 }
 
 // The tables of a descriptor block, one behind the other.
@@ -68,22 +122,17 @@ __host__ __device__ constexpr int en_rope_unit(int elem, int d, int many)
 {
     return elem == 2 && (many == 4 || (many == 8 && d == 64)) ? many : 0;
 }
-// Source row of context token `tok` for (agent b, KV head kvh); nullptr for
-// padding rows at or beyond L_c + N_q. `bnd` and `sel` are the agent's tables
-// (global or staged), S its number of segments.
-template <typename T, int D, typename P>
-__device__ __forceinline__ const T *context_src(const EnGatherArgs &a, P bnd, P sel, int S, const T *pool,
-                                               const T *fresh, int b, int kvh, int tok)
+// Source row of context token `tok` for (agent b, KV head kvh), in `group` at `row` if it is a gathered one; nullptr for
+// padding rows at or beyond L_c + N_q.
+template <typename T, int D>
+__device__ __forceinline__ const T *context_src(const EnGatherArgs &a, const EnGatherTables &t, const void *pool,
+                                               const void *fresh, int b, int kvh, int tok, int group, int row)
 {
-    const int Lc = bnd[S];
-    const int Ltot = bnd[S + 1];
-    if (tok >= Ltot)
+    if (tok >= t.Ltot)
         return nullptr;
-    if (tok >= Lc)
-        return fresh + (((size_t)b * a.Nq + (tok - Lc)) * a.Hkv + kvh) * D;
-    const int s = find_bucket(bnd, S, tok);
-    const int g = sel[s];
-    return pool + (((size_t)g * a.Hkv + kvh) * a.C + (tok - bnd[s])) * D;
+    if (tok >= t.Lc)
+        return (const T *)fresh + (((size_t)b * a.Nq + (tok - t.Lc)) * a.Hkv + kvh) * D;
+    return (const T *)pool + (((size_t)group * a.Hkv + kvh) * a.C + row) * D;
 }
 
 // ---------------------------------------------------------------------------
@@ -97,23 +146,25 @@ __device__ __forceinline__ const T *context_src(const EnGatherArgs &a, P bnd, P 
 // per head, 0.73 ms without the table, which is what the value half takes).
 // 256 threads, 32 rows per pass.
 // ---------------------------------------------------------------------------
-template <typename T, int D, bool COPY_V, int HPB, bool STREAM, bool AHEAD, typename P>
-__device__ __forceinline__ void gather_k_rows(const EnGatherArgs &a, int b, int tok, int kv0, P bnd, P sel, int S)
+template <typename T, int D, bool COPY_V, int HPB, bool STREAM, bool AHEAD>
+__device__ __forceinline__ void gather_k_rows(const EnGatherArgs &a, const EnGatherTables &t, const int32_t *lds, int b,
+                                              int tok, int kv0)
 {
     constexpr int E = D / 16;
     const int c = threadIdx.x % 8;
-    const int Ltot = bnd[S + 1];
-    const int Lpad = (Ltot + EN_KEY_TILE - 1) / EN_KEY_TILE * EN_KEY_TILE;
+    int group, row;
+    context_row(t, lds, tok, group, row);
+    const int Lpad = (t.Ltot + EN_KEY_TILE - 1) / EN_KEY_TILE * EN_KEY_TILE;
     if (tok >= Lpad)
         return;
     typedef T tvec __attribute__((ext_vector_type(E)));
     typedef float fvec __attribute__((ext_vector_type(E)));
     // the rows of head kv0; head kv0 + h is h * hstride elements further, keys and values alike
-    const T *ksrc = context_src<T, D>(a, bnd, sel, S, (const T *)a.k_pool, (const T *)a.k_new, b, kv0, tok);
+    const T *ksrc = context_src<T, D>(a, t, a.k_pool, a.k_new, b, kv0, tok, group, row);
     const T *vsrc = nullptr;
     if constexpr (COPY_V)
-        vsrc = context_src<T, D>(a, bnd, sel, S, (const T *)a.v_pool, (const T *)a.v_new, b, kv0, tok);
-    const size_t hstride = tok >= bnd[S] ? (size_t)D : (size_t)a.C * D;      // new tokens [.., Hkv, D], pool [.., Hkv, C, D]
+        vsrc = context_src<T, D>(a, t, a.v_pool, a.v_new, b, kv0, tok, group, row);
+    const size_t hstride = tok >= t.Lc ? (size_t)D : (size_t)a.C * D;      // new tokens [.., Hkv, D], pool [.., Hkv, C, D]
     fvec cs = 0.f, sn = 0.f;
     if (ksrc) {
         cs = *reinterpret_cast<const fvec *>(a.cos_tab + (size_t)tok * (D / 2) + c * E);
@@ -190,17 +241,10 @@ template <typename T, int D, bool COPY_V, int HPB, bool STREAM, bool AHEAD>
 __device__ __forceinline__ void gather_k_block(const EnGatherArgs &a, int b, int tile, int first, int last, int kv0,
                                                int32_t *lbnd)
 {
-    const int S = a.nseg[b];
-    const EnGatherTables t = stage_tables(a, b, lbnd);
+    const EnGatherTables t = open_tables(a, b, lbnd);
 #pragma unroll 1
-    for (int half = first; half <= last; ++half) {
-        const int tok = tile * EN_KEY_TILE + half * 32 + threadIdx.x / 8;
-        if (t.staged)
-            gather_k_rows<T, D, COPY_V, HPB, STREAM, AHEAD>(a, b, tok, kv0, (const int32_t *)lbnd,
-                                                            (const int32_t *)lbnd + EN_GATHER_TAB_LDS, S);
-        else
-            gather_k_rows<T, D, COPY_V, HPB, STREAM, AHEAD>(a, b, tok, kv0, t.bnd, t.sel, S);
-    }
+    for (int half = first; half <= last; ++half)
+        gather_k_rows<T, D, COPY_V, HPB, STREAM, AHEAD>(a, t, lbnd, b, tile * EN_KEY_TILE + half * 32 + threadIdx.x / 8, kv0);
 }
 
 // ---------------------------------------------------------------------------
@@ -216,20 +260,17 @@ __device__ __forceinline__ void gather_vt_block(const EnGatherArgs &a, int b, in
     __shared__ uint16_t tile[EN_KEY_TILE * STR];
     __shared__ const uint16_t *srcs[EN_KEY_TILE];
     const int t0 = bx * EN_KEY_TILE;
-    const int S = a.nseg[b];
-    const EnGatherTables t = stage_tables(a, b, lbnd);
-    const int32_t *lsel = lbnd + EN_GATHER_TAB_LDS;
-    const int Lc = t.staged ? lbnd[S] : t.bnd[S];
-    const int Ltot = t.staged ? lbnd[S + 1] : t.bnd[S + 1];
-    if (t0 >= Ltot)                            // the same for the whole block
+    const EnGatherTables t = open_tables(a, b, lbnd);
+    const int Lc = t.Lc;
+    if (t0 >= t.Ltot)                            // the same for the whole block
         return;
     // head kv0 + h is h * stride elements further: new tokens [.., Hkv, D], pool [.., Hkv, C, D]
     auto head_stride = [&](bool fresh) { return fresh ? (size_t)D : (size_t)a.C * D; };
     const uint16_t *src = nullptr;
     if (threadIdx.x < EN_KEY_TILE) {
-        const uint16_t *vp = (const uint16_t *)a.v_pool, *vn = (const uint16_t *)a.v_new;
-        src = t.staged ? context_src<uint16_t, D>(a, (const int32_t *)lbnd, lsel, S, vp, vn, b, kv0, t0 + threadIdx.x)
-                       : context_src<uint16_t, D>(a, t.bnd, t.sel, S, vp, vn, b, kv0, t0 + threadIdx.x);
+        int group, row;
+        context_row(t, lbnd, t0 + threadIdx.x, group, row);
+        src = context_src<uint16_t, D>(a, t, a.v_pool, a.v_new, b, kv0, t0 + threadIdx.x, group, row);
     }
     if (a.v_rows) {
         // the values stay where they are: the tile's 64 row addresses instead (padding rows: the row of zeros)
@@ -320,6 +361,14 @@ __device__ __forceinline__ void gather_vt_block(const EnGatherArgs &a, int b, in
     }
 }
 
+// The first three lines of the arguments at once: a trip to memory each when the code asks for them one by one.
+__device__ __forceinline__ void ask_arguments(const EnGatherLaunch &g)
+{
+    const EnGatherArgs &a = g.a;
+    asm volatile("" ::"s"(a.k_pool), "s"(a.k_new), "s"(a.kc), "s"(a.cos_tab), "s"(a.nseg), "s"(a.bnd), "s"(a.C), "s"(a.q),
+                 "s"(a.n_q_units), "s"(a.order), "s"(g.n_inline), "s"(g.n_zero));
+}
+
 // One launch for the whole gather. Grid (64-token tiles, units, agents); the units, head group
 // by head group: the key units (the tile's key rows of HPB heads, which also copy fp32 values),
 // then, for bf16, the value units (the same heads' transposed tiles: one unit with AHEAD, else one each). Workgroups are dispatched
@@ -348,8 +397,8 @@ template <int D>
 __device__ __forceinline__ void prepare_queries(const EnGatherArgs &a, int part, int n_parts, int b)
 {
     constexpr int TPR = D / 8;                     // threads per row
-    const int S = a.nseg[b];
-    const int Lc = a.bnd[(size_t)b * (a.Smax + 2) + S];
+    const int S = as_table(a.nseg)[b];
+    const int Lc = as_table(a.bnd)[b * (a.Smax + 2) + S];
     const int rows = a.Nq * a.Hq;
     const int per = (rows + n_parts - 1) / n_parts;
     const int r1 = min(rows, (part + 1) * per);
@@ -414,9 +463,18 @@ __device__ __forceinline__ bool gather_where(const EnGatherArgs &a, int &tile, i
     return true;
 }
 
-template <typename T, int D, int HPB, bool STREAM, bool AHEAD>
-__global__ __launch_bounds__(256) void gather_kernel(EnGatherLaunch g)
+// Workgroups of eight heads ahead: three on a compute unit, not the four that their registers allow. The streams of a
+// fourth cost more than its loads hide: 64 agents x 16 K tokens 1054 / 1065 us (two: 1093), 16 x 14 K 264 / 270 (268),
+// 32 x 4 K 171 / 174 (167).
+constexpr int en_gather_waves(int hpb, bool ahead)
 {
+    return ahead && hpb == 8 ? 3 : 8;
+}
+
+template <typename T, int D, int HPB, bool STREAM, bool AHEAD>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, en_gather_waves(HPB, AHEAD)))) void gather_kernel(EnGatherLaunch g)
+{
+    ask_arguments(g);
     EnGatherArgs a = g.a;
     if (g.n_inline > 0) {
         const int32_t *img = reinterpret_cast<const int32_t *>(
@@ -460,22 +518,16 @@ struct EnCtxLoc {
     int kind;        // 0 padding, 1 row of the pool, 2 row of the new tokens
     size_t row;      // index of the row, in rows of D elements
 };
-// the tables staged in LDS (at lds and lds + EN_GATHER_TAB_LDS) or where they are, see stage_tables
 __device__ __forceinline__ EnCtxLoc context_loc(const EnGatherArgs &a, const EnGatherTables &t, const int32_t *lds,
                                                int b, int kvh, int tok)
 {
-    const int32_t *bnd = t.staged ? lds : t.bnd;
-    const int32_t *sel = t.staged ? lds + EN_GATHER_TAB_LDS : t.sel;
-    const int S = a.nseg[b];
-    const int Lc = bnd[S];
-    const int Ltot = bnd[S + 1];
-    if (tok >= Ltot)
+    int group, row;
+    context_row(t, lds, tok, group, row);
+    if (tok >= t.Ltot)
         return {0, 0};
-    if (tok >= Lc)
-        return {2, ((size_t)b * a.Nq + (tok - Lc)) * a.Hkv + kvh};
-    const int s = find_bucket(bnd, S, tok);
-    const int g = sel[s];
-    return {1, ((size_t)g * a.Hkv + kvh) * a.C + (tok - bnd[s])};
+    if (tok >= t.Lc)
+        return {2, ((size_t)b * a.Nq + (tok - t.Lc)) * a.Hkv + kvh};
+    return {1, ((size_t)group * a.Hkv + kvh) * a.C + row};
 }
 
 // The key rows of HPB heads, kv0 onwards: where the row comes from, its cosines and sines once for all of them, and
@@ -489,9 +541,8 @@ __device__ __forceinline__ void gather_q8_k_rows(const EnGatherArgs &a, const En
 {
     constexpr int E = D / 16;
     const int c = threadIdx.x % 8;
-    const int S = a.nseg[b];
-    const int Ltot = tabs.staged ? lds[S + 1] : tabs.bnd[S + 1];
-    const int Lpad = (Ltot + EN_KEY_TILE - 1) / EN_KEY_TILE * EN_KEY_TILE;
+    const EnCtxLoc loc = context_loc(a, tabs, lds, b, kv0, tok);
+    const int Lpad = (tabs.Ltot + EN_KEY_TILE - 1) / EN_KEY_TILE * EN_KEY_TILE;
     if (tok >= Lpad)
         return;
     typedef bf16_t tvec __attribute__((ext_vector_type(E)));
@@ -501,7 +552,6 @@ __device__ __forceinline__ void gather_q8_k_rows(const EnGatherArgs &a, const En
         store_context<STREAM>(dst + c * E, __builtin_convertvector(y1, tvec));
         store_context<STREAM>(dst + D / 2 + c * E, __builtin_convertvector(y2, tvec));
     };
-    const EnCtxLoc loc = context_loc(a, tabs, lds, b, kv0, tok);
     if (loc.kind == 0) {
 #pragma unroll
         for (int h = 0; h < HPB; ++h)
@@ -578,7 +628,7 @@ __device__ __forceinline__ void gather_q8_k_rows(const EnGatherArgs &a, const En
 template <int D, int HPB, bool STREAM>
 __device__ __forceinline__ void gather_q8_k_block(const EnGatherArgs &a, int b, int tile, int kv0, int32_t *lds)
 {
-    const EnGatherTables tabs = stage_tables(a, b, lds);
+    const EnGatherTables tabs = open_tables(a, b, lds);
 #pragma unroll 1
     for (int half = 0; half < 2; ++half)
         gather_q8_k_rows<D, HPB, STREAM>(a, tabs, b, tile * EN_KEY_TILE + half * 32 + threadIdx.x / 8, kv0, lds);
@@ -594,10 +644,8 @@ __device__ __forceinline__ void gather_q8_vt_block(const EnGatherArgs &a, int b,
     __shared__ size_t rows[EN_KEY_TILE];
     __shared__ int kinds[EN_KEY_TILE];
     const int t0 = bx * EN_KEY_TILE;
-    const int S = a.nseg[b];
-    const EnGatherTables tabs = stage_tables(a, b, lds);
-    const int Ltot = tabs.staged ? lds[S + 1] : tabs.bnd[S + 1];
-    if (t0 >= Ltot)                            // the same for the whole block
+    const EnGatherTables tabs = open_tables(a, b, lds);
+    if (t0 >= tabs.Ltot)                            // the same for the whole block
         return;
     if (threadIdx.x < EN_KEY_TILE) {
         const EnCtxLoc loc = context_loc(a, tabs, lds, b, kv0, t0 + threadIdx.x);
@@ -689,6 +737,7 @@ __device__ __forceinline__ void gather_q8_vt_block(const EnGatherArgs &a, int b,
 template <int D, int HPB, bool STREAM>
 __global__ __launch_bounds__(256) void gather_q8_kernel(EnGatherLaunch g)
 {
+    ask_arguments(g);
     EnGatherArgs a = g.a;
     if (g.n_inline > 0) {
         const int32_t *img = reinterpret_cast<const int32_t *>(
