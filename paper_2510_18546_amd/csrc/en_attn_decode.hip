@@ -1,6 +1,6 @@
-// attn_decode: the same attention for steps of few query rows (the decode phase
-// of a planning step, Section 3.2), bound by reading the context once; and
-// attn_f32, the fp32 matrix-core path of small configurations.
+// attn_decode, attn_once: the same attention for steps of few query rows (the decode phase
+// of a planning step, Section 3.2): contexts streamed through, bound by reading them once, and
+// those that fit the chip's LDS in a round or a few, bound by latency; and attn_f32, the fp32 matrix-core path of small configurations.
 #include "en_device.h"
 
 // ---------------------------------------------------------------------------

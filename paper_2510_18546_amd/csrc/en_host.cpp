@@ -264,8 +264,8 @@ static int pool_ensure_device(en_pool *p)
 // Whether attn_once_kernel takes a decode step of n splits of at most `per` tiles for each of `base` (agent, KV head)
 // pairs: where its workgroups, as many of a compute unit's as its LDS holds, come in few enough rounds. us per decoded
 // token (attention and merge), streaming kernel / this one:
-// - one round: one agent of 8 heads, 0.25 K tokens 11.0 / 7.4 (one split, no merge), 1.5 K 11.4 / 8.5, 4 K 12.9 / 9.8, 6 K
-//   14.1 / 10.3, 8 K (five tiles) 16.5 / 11.8, rows of 64 values 12.7 / 9.2; 16 agents, 2 heads, 0.4 K 11.9 / 8.3;
+// - one round: one agent of 8 heads, 0.25 K tokens 11.0 / 7.2 (one split, no merge), 1.5 K 11.4 / 8.4, 4 K 12.9 / 9.7, 6 K
+//   14.1 / 10.2, 8 K (five tiles) 16.5 / 11.4, rows of 64 values 12.7 / 9.2; 16 agents, 2 heads, 0.4 K 11.9 / 8.3;
 // - two tiles, two workgroups to a compute unit that relieve one another, in up to six rounds: 16 agents x 0.8 K (1.75
 //   rounds) 21.7 / 17.0, x 1.6 K (3.3) 28.5 / 26.5, 16 x 6 K of 2 heads (3.1) 26.5 / 25.8; but 16 x 3 K (6.3) 41.7 / 43.0,
 //   64 x 4 K of 2 heads (8.2) 51.6 / 52.9. Rows of 64 values in up to 16: 64 x 4 K of 2 heads (3.3) 32.7 / 27.9, 64 x 2.5 K
@@ -302,7 +302,8 @@ static int once_splits(const en_pool *pool, long base, int tiles)
     return 0;
 }
 
-static int choose_splits(const en_pool *pool, const en_plan *pl)
+// (once: decode steps may have the splits of attn_once_kernel, of which there are more where they come in several rounds)
+static int choose_splits(const en_pool *pool, const en_plan *pl, bool once = true)
 {
     // One workgroup covers 8 (head, 32-query block) pairs of one KV head and
     // fills a compute unit. The key range is split so that the rounds of
@@ -311,7 +312,8 @@ static int choose_splits(const en_pool *pool, const en_plan *pl)
     // tiles), is shortest; at least four key tiles per split.
     const int r = pool->r;
     if (computes_bf16(pool->d.dtype) && r * pl->Nq <= EN_ROWS_PER_WAVE) {
-        // decode path: one wave per (agent, KV head, split); the two LDS stages
+        // decode path, where attn_once_kernel does not take it (once_splits):
+        // one wave per (agent, KV head, split); the two LDS stages
         // of a wave let two waves share a compute unit, and a wave takes about
         // 2 us per 64-key tile whatever the load: as many splits as give every
         // compute unit its two waves (measured on 1 and 4 agents x 8 K tokens:
@@ -324,7 +326,7 @@ static int choose_splits(const en_pool *pool, const en_plan *pl)
         // 16 K tokens).
         const long base = long(pl->B) * pool->d.n_kv_heads;
         const int tiles = std::max(1, (pl->max_ctx_len + EN_KEY_TILE - 1) / EN_KEY_TILE);
-        if (pool->r * pl->Nq <= EN_ONCE_ROWS) {
+        if (once && pool->r * pl->Nq <= EN_ONCE_ROWS) {
             const int n = once_splits(pool, base, tiles);
             if (n > 0)
                 return n;
@@ -549,6 +551,7 @@ static int en_plan_set_splits_impl(en_plan *plan, int32_t n_splits)
         return fail(EN_ERR_INVALID_ARG, "en_plan_set_splits: null plan or n_splits < 1");
     const int tiles = std::max(1, (plan->max_ctx_len + EN_KEY_TILE - 1) / EN_KEY_TILE);
     plan->n_splits = std::min(std::min(n_splits, tiles), EN_MAX_SPLITS);
+    plan->splits_set = true;
     return EN_OK;
 }
 extern "C" int en_plan_set_splits(en_plan *plan, int32_t n_splits)
@@ -878,7 +881,8 @@ static bool decode_kernel_fits(const en_pool *pool, int n_rows)
     return computes_bf16(pool->d.dtype) && pool->r * n_rows <= EN_ROWS_PER_WAVE;
 }
 
-// Waves per (agent, KV head, split) in the decode attention kernel. One wave alone on its SIMD
+// Waves per (agent, KV head, split) in the streaming decode kernel (attn_once_kernel leaves one partial result whatever
+// its waves, and takes most of the steps below; the figures are from before it did). One wave alone on its SIMD
 // takes about 2 us per 64-key tile whatever the load, and the kernel's LDS stages leave room for
 // two workgroups per compute unit: when a step has no more units than that, two waves share each
 // unit's tiles, each takes every other 32-key block and leaves partial results of its own (the
@@ -1340,6 +1344,22 @@ static int run_attention(en_pool *pool, en_plan *plan, const void *q_dev, const 
     return EN_OK;
 }
 
+// KV splits for a step of n_rows query rows (same rule as for a whole plan).
+static int step_splits(const en_pool *pool, const en_plan *plan, int n_rows, bool once = true)
+{
+    en_plan tmp;
+    tmp.pool = pool;
+    tmp.B = plan->B;
+    tmp.Nq = n_rows;
+    tmp.max_ctx_len = plan->max_ctx_len;
+    return choose_splits(pool, &tmp, once);
+}
+// ... that brings no scratch: none where the streaming decode kernel needs none.
+static int splits_without_scratch(const en_pool *pool, const en_plan *plan, int n_rows, int n_splits)
+{
+    return n_splits > 1 && step_splits(pool, plan, n_rows, false) == 1 ? 1 : n_splits;
+}
+
 static int segmented_prefill_attention_impl(en_pool *pool, en_plan *plan, const void *q_dev,
                                            const void *kc_dev, const void *vt_dev, void *out_dev,
                                            void *ws_dev, size_t ws_bytes, void *stream)
@@ -1348,8 +1368,9 @@ static int segmented_prefill_attention_impl(en_pool *pool, en_plan *plan, const 
         return fail(EN_ERR_INVALID_ARG, "segmented_prefill_attention: null argument");
     if (plan->pool != pool)
         return fail(EN_ERR_INVALID_ARG, "segmented_prefill_attention: plan belongs to another pool");
+    const int n_splits = ws_dev || plan->splits_set ? plan->n_splits : splits_without_scratch(pool, plan, plan->Nq, plan->n_splits);
     return run_attention(pool, plan, q_dev, kc_dev, vt_dev, out_dev, ws_dev, ws_bytes, stream, 0, plan->Nq,
-                         plan->n_splits, false, "segmented_prefill_attention");
+                         n_splits, false, "segmented_prefill_attention");
 }
 extern "C" int segmented_prefill_attention(en_pool *pool, en_plan *plan, const void *q_dev,
                                            const void *kc_dev, const void *vt_dev, void *out_dev,
@@ -1392,21 +1413,10 @@ extern "C" int segmented_prefill_attention_prepared(en_pool *pool, en_plan *plan
                                                          mass_red_out_dev, ws_dev, ws_bytes, stream));
 }
 
-// KV splits for a step of n_rows query rows (same rule as for a whole plan).
 static int cluster_assign(en_pool *pool, en_plan *plan, int q_first, int n_rows, int n_splits, void *ws_dev,
                           int32_t n_obj, const int32_t *span_ptr_host, int32_t per_key, int32_t accumulate,
                           float scale, float threshold, float *score_dev, int32_t *assign_dev, void *stream,
                           const char *who);
-
-static int step_splits(const en_pool *pool, const en_plan *plan, int n_rows)
-{
-    en_plan tmp;
-    tmp.pool = pool;
-    tmp.B = plan->B;
-    tmp.Nq = n_rows;
-    tmp.max_ctx_len = plan->max_ctx_len;
-    return choose_splits(pool, &tmp);
-}
 
 extern "C" size_t en_decode_workspace_bytes(const en_pool *pool, const en_plan *plan, int32_t n_rows)
 {
@@ -1418,7 +1428,7 @@ extern "C" size_t en_decode_workspace_bytes(const en_pool *pool, const en_plan *
 static int segmented_decode_step_impl(en_pool *pool, en_plan *plan, int32_t q_first, int32_t n_rows,
                                      const void *q_dev, const void *k_rows_dev, const void *v_rows_dev,
                                      void *kc_dev, void *vt_dev, void *out_dev, float *mass_out_dev,
-                                     void *ws_dev, size_t ws_bytes, void *stream)
+                                     void *ws_dev, size_t ws_bytes, void *stream, int n_splits = 0)
 {
     if (!pool || !plan || !q_dev || !k_rows_dev || !v_rows_dev || !kc_dev || !vt_dev || !out_dev)
         return fail(EN_ERR_INVALID_ARG, "segmented_decode_step: null argument");
@@ -1457,7 +1467,10 @@ static int segmented_decode_step_impl(en_pool *pool, en_plan *plan, int32_t q_fi
     if (e != 0)
         return hip_fail((hipError_t)e, "segmented_decode_step context append");
     // 2. attention of the step's rows over everything before and including them
-    const int n_splits = step_splits(pool, plan, n_rows);
+    if (n_splits == 0)
+        n_splits = step_splits(pool, plan, n_rows);
+    if (!ws_dev)
+        n_splits = splits_without_scratch(pool, plan, n_rows, n_splits);
     if ((rc = run_attention(pool, plan, q_dev, kc_dev, vt_dev, out_dev, ws_dev, ws_bytes, stream, q_first, n_rows,
                             n_splits, true, "segmented_decode_step", fused ? k_rows_dev : nullptr,
                             fused ? v_rows_dev : nullptr)) != EN_OK)
@@ -1494,7 +1507,14 @@ static int segmented_decode_step_static_impl(en_pool *pool, en_plan *plan, int32
         return fail(EN_ERR_INVALID_ARG, "segmented_decode_step_static: plan belongs to another pool");
     if (n_rows <= 0)
         return fail(EN_ERR_OUT_OF_RANGE, "segmented_decode_step_static: n_rows = %d", n_rows);
-    const size_t need = en_ws_layout_for(pool, plan, n_rows, step_splits(pool, plan, n_rows)).parts_off;
+    // the partial results of a step in several rounds of attn_once_kernel can take more than the array holds where those
+    // of the streaming kernel do not
+    int n_splits = step_splits(pool, plan, n_rows);
+    size_t need = en_ws_layout_for(pool, plan, n_rows, n_splits).parts_off;
+    if (need > EN_STATIC_SCRATCH_BYTES) {
+        n_splits = step_splits(pool, plan, n_rows, false);
+        need = en_ws_layout_for(pool, plan, n_rows, n_splits).parts_off;
+    }
     if (need > EN_STATIC_SCRATCH_BYTES)
         return fail(EN_ERR_CAPACITY, "segmented_decode_step_static: the step needs %zu bytes of scratch, the static "
                     "scratch holds %zu; use segmented_decode_step with a workspace of the caller's", need,
@@ -1508,7 +1528,7 @@ static int segmented_decode_step_static_impl(en_pool *pool, en_plan *plan, int32
     if (e != 0)
         return hip_fail((hipError_t)e, "segmented_decode_step_static: address of the static scratch");
     return segmented_decode_step_impl(pool, plan, q_first, n_rows, q_dev, k_rows_dev, v_rows_dev, kc_dev, vt_dev,
-                                      out_dev, mass_out_dev, ws, ws_bytes, stream);
+                                      out_dev, mass_out_dev, ws, ws_bytes, stream, n_splits);
 }
 extern "C" int segmented_decode_step_static(en_pool *pool, en_plan *plan, int32_t q_first, int32_t n_rows,
                                             const void *q_dev, const void *k_rows_dev, const void *v_rows_dev,

@@ -49,6 +49,7 @@ struct en_plan {
     const en_pool *pool = nullptr;
     int B = 0, Nq = 0, Smax = 0;
     int ctx_stride = 0, max_ctx_len = 0, n_splits = 1;
+    bool splits_set = false;      // by en_plan_set_splits
     int64_t total_pairs = 0, total_cached = 0;
     int64_t selected = 0, distinct = 0;      // groups that at least one agent selects, their tokens
     // host descriptors (uniform stride per agent)
@@ -166,9 +167,9 @@ struct EnAttnArgs {
     int q_first;       // the Nq query rows are new tokens q_first .. q_first+Nq-1 of the plan: every key
                        // before L_c + q_first is visible to all of them (0 for a whole prefill)
     int n_splits, n_ptiles, total_wgs;
-    // prefill kernel: n_ptiles, n_splits (of workgroup numbers and of split boundaries), Hkv, Hq / Hkv
+    // attention kernels: n_ptiles, n_splits (of workgroup numbers and of split boundaries), Hkv, Hq / Hkv
     EnDivisor by_ptiles, by_splits, by_hkv, by_r;
-    EnDivisor by_nq, by_hq;      // merge: Nq, Hq
+    EnDivisor by_nq, by_hq;      // merge, attn_once_kernel: Nq, Hq
     // the header {S, L_c} of the only agent (B == 1): one trip to memory less in front of its first load
     int one_S, one_Lc;
     int decode;        // 1: all r*Nq query rows of a KV head fit one wave (attn_decode kernel)

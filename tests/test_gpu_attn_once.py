@@ -100,3 +100,30 @@ def test_steps_across_borders(oracle, cached, steps, d):
     # rotated keys differ by which of two products is rounded, then by one rounding to bf16 of values up to 4
     diff = kc.view(torch.bfloat16).float() - st.kc.view(torch.bfloat16).float()
     assert diff.abs().max().item() <= 4e-2
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_no_scratch_for_many_short_contexts(oracle, d):
+    """So many agents of three tiles that the kernel would rather have two splits: one, which needs no scratch, still does
+    for a call that brings none."""
+    import torch
+    from paper_2510_18546_amd import binding as B
+    from paper_2510_18546_amd import step
+    agents = 300 * 128 // d
+    cfg, w = workload(51, agents, 2, 2, d, 2, [100, 70], 2)
+    print(f"[case] {cfg}", flush=True)
+    st = step.PlanningStep(w)
+    assert st.plan.info.n_splits == 2
+    ref, _ = oracle.attention(w.k_pool, w.v_pool, w.lens, w.sel, w.sel_ptr, w.q, w.k_new, w.v_new, cfg.rope_base)
+    st.gather()
+    B.segmented_prefill_attention(st.pool, st.plan, st.q, st.kc, st.vt, st.out, None)
+    torch.cuda.synchronize()
+    assert np.abs(st.out_host() - ref).max() <= 2e-2
+    q, k, v = (t[:, :1].contiguous() for t in (st.q, st.k_new, st.v_new))
+    out = torch.empty_like(q)
+    B.segmented_decode_step(st.pool, st.plan, 0, q, k, v, st.kc, st.vt, out, None)
+    torch.cuda.synchronize()
+    assert np.abs(step._to_host(out) - ref[:, :1]).max() <= 2e-2
+    st.plan.set_splits(2)
+    with pytest.raises(B.EnError, match="workspace required"):
+        B.segmented_prefill_attention(st.pool, st.plan, st.q, st.kc, st.vt, st.out, None)
