@@ -110,8 +110,8 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_bf16_kernel(EnAttnArgs a)
     const int r = a.by_r.n;
     const int nqb = (a.Nq + 31) / 32;
     const int pair = ptile * ATT_WAVES + wave;
-    // A wave without a valid (head, query block) pair computes on zero queries
-    // and writes nothing.
+    // A wave without a valid (head, query block) pair loads its share of the tiles
+    // and computes and writes nothing.
     const bool wave_valid = pair < r * nqb;
     const int qb = wave_valid ? divided(pair, a.by_r) : 0;
     const int hl = wave_valid ? pair - qb * r : 0;
@@ -620,48 +620,50 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_bf16_kernel(EnAttnArgs a)
                 return;
             }
         }
-        const bool odd_row = overflow || pend_mask != 0;
+        const bool first = PAR == 0 && kb == split_key_begin;
         const int ke = min(kb + KB, split_key_end);
         mask_block(kb + KB, s_nxt);
         // ---- reference check: the wave recomputes the scores of the block,
         // moves the affected rows to their current maximum, rescales what
-        // they have accumulated and redoes the exponentials ----
-        if (odd_row) {
-            f32x16 sv;
-            block_scores(ST * KBYTES + PAR * KB * ROWB, sv);
-            mask_block(kb, sv);
-            float mx = sv[0];
+        // they have accumulated and redoes the exponentials. The first block has its references (they were taken before
+        // the loop) and its exponentials; the next block's scores were taken without them. ----
+        if (first || overflow || pend_mask != 0) {
+            float delta = m_ref;
+            if (!first) {
+                f32x16 sv;
+                block_scores(ST * KBYTES + PAR * KB * ROWB, sv);
+                mask_block(kb, sv);
+                float mx = sv[0];
 #pragma unroll
-            for (int e = 1; e < 16; ++e)
-                mx = fmaxf(mx, sv[e]);
-            mx = pair_max(mx);
-            // both lanes of a row must take the same decision
-            const float want = (pending || !(rs < BIG)) ? 1.f : 0.f;
-            const bool fix = pair_max(want) > 0.f && mx > EN_NEG_INF;
-            const float delta = fix ? mx : 0.f;
-            const float alpha = fix ? (has_ref ? fast_exp2(-delta) : 0.f) : 1.f;
+                for (int e = 1; e < 16; ++e)
+                    mx = fmaxf(mx, sv[e]);
+                mx = pair_max(mx);
+                // both lanes of a row must take the same decision
+                const float want = (pending || !(rs < BIG)) ? 1.f : 0.f;
+                const bool fix = pair_max(want) > 0.f && mx > EN_NEG_INF;
+                delta = fix ? mx : 0.f;
+                const float alpha = fix ? (has_ref ? fast_exp2(-delta) : 0.f) : 1.f;
 #pragma unroll
-            for (int d = 0; d < NDB; ++d)
+                for (int d = 0; d < NDB; ++d)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e)
+                        o[d][e] *= alpha;
+                l_part *= alpha;
+                seg_part *= alpha;
+                m_ref += delta;
+                has_ref = has_ref || fix;
+                pending = pending && !fix;
+                pend_mask = __builtin_amdgcn_ballot_w64(pending);
 #pragma unroll
                 for (int e = 0; e < 16; ++e)
-                    o[d][e] *= alpha;
-            l_part *= alpha;
-            seg_part *= alpha;
-            m_ref += delta;
-            has_ref = has_ref || fix;
-            pending = pending && !fix;
-            pend_mask = __builtin_amdgcn_ballot_w64(pending);
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                negm[e] = -m_ref;
-                s_nxt[e] -= delta;            // the next block was taken against the old reference
+                    pbuf[PAR][e / 8][e % 8] = (bf16_t)fast_exp2(sv[e] - delta);
             }
             rs = 0.f;
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                const bf16_t pb = (bf16_t)fast_exp2(sv[e] - delta);
-                pbuf[PAR][e / 8][e % 8] = pb;
-                rs += (float)pb;
+                negm[e] = -m_ref;
+                s_nxt[e] -= delta;            // the next block was taken against the old reference
+                rs += (float)pbuf[PAR][e / 8][e % 8];
             }
         }
         l_part += rs;
@@ -806,11 +808,9 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_bf16_kernel(EnAttnArgs a)
             pending = pending && !has_ref;
             pend_mask = __builtin_amdgcn_ballot_w64(pending);
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                negm[e] = -m_ref;
+            for (int e = 0; e < 16; ++e)
                 sbuf[0][e] -= m_ref;
-            }
-            calm = calm_limit();
+            calm = -1;                         // (the first phase finishes this)
         }
         // first operands of the first phase: K keys 32..63 of the first tile, the zero V^T stage
 #pragma unroll
