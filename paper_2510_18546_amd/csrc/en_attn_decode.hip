@@ -808,8 +808,9 @@ __global__ __launch_bounds__(128 * TPS) void attn_once_kernel(EnAttnArgs a)
     __builtin_amdgcn_s_barrier();
     lds_data_ready();
 
-    // the weights of the waves' results for row c
-    auto weights = [&](int c, float (&wt)[W], float &M, float &L) {
+    // the weights of the waves' results for row c; `none`: the wave has no key that the row sees (its sum is 0, with any key
+    // it is 1 at least or NaN). By the bits: without NaN compares a row of NaN could pass for one without keys.
+    auto weights = [&](int c, float (&wt)[W], bool (&none)[W], float &M, float &L) {
         f32x2 ml[W];
         M = EN_NEG_INF;
         L = 0.f;
@@ -821,7 +822,8 @@ __global__ __launch_bounds__(128 * TPS) void attn_once_kernel(EnAttnArgs a)
             M = fmaxf(M, ml[w][0]);
 #pragma unroll
         for (int w = 0; w < W; ++w) {
-            wt[w] = ml[w][0] == EN_NEG_INF ? 0.f : fast_exp2(ml[w][0] - M);
+            none[w] = __float_as_uint(ml[w][1]) == 0u;
+            wt[w] = none[w] ? 0.f : fast_exp2(ml[w][0] - M);
             L += wt[w] * ml[w][1];
         }
     };
@@ -829,15 +831,16 @@ __global__ __launch_bounds__(128 * TPS) void attn_once_kernel(EnAttnArgs a)
     for (int it = tid; it < rows * (D / 4); it += 64 * W) {
         const int c = it / (D / 4), ch = it % (D / 4);
         float wt[W], M, L;
+        bool none[W];
         f32x4 x[W];
 #pragma unroll
         for (int w = 0; w < W; ++w)
             x[w] = *reinterpret_cast<const f32x4 *>(o_at(w, c, ch));
-        weights(c, wt, M, L);
+        weights(c, wt, none, M, L);
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int w = 0; w < W; ++w)
-            acc += wt[w] == 0.f ? f32x4{0.f, 0.f, 0.f, 0.f} : x[w] * wt[w];
+            acc += none[w] ? f32x4{0.f, 0.f, 0.f, 0.f} : x[w] * wt[w];      // (a wave without a tile left nothing)
         const float inv = L > 0.f ? 1.f / L : 0.f;
         const int ho = divided(c, a.by_nq), h = kvh * r + ho, i = c - ho * a.Nq;
         const size_t row = ((size_t)b * a.Hq + h) * a.Nq + i;
@@ -874,7 +877,8 @@ __global__ __launch_bounds__(128 * TPS) void attn_once_kernel(EnAttnArgs a)
         }
         const int lo = max(blo, key_begin) - key_begin, hi = min(bhi, key_end) - key_begin;
         float wt[W], M, L;
-        weights(c, wt, M, L);
+        bool none[W];
+        weights(c, wt, none, M, L);
         float sum = 0.f;
 #pragma unroll
         for (int w = 0; w < W; ++w) {

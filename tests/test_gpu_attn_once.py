@@ -127,3 +127,61 @@ def test_no_scratch_for_many_short_contexts(oracle, d):
     st.plan.set_splits(2)
     with pytest.raises(B.EnError, match="workspace required"):
         B.segmented_prefill_attention(st.pool, st.plan, st.q, st.kc, st.vt, st.out, None)
+
+
+def _run(step, w, splits):
+    import torch
+    st = step.PlanningStep(w, n_splits=splits)
+    st.ws.fill_(0xFF)
+    st.run()
+    torch.cuda.synchronize()
+    return st.out_host(), st.mass_host()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("splits", [1, 3])
+def test_not_finite(oracle, splits, d):
+    """NaN and infinity stay in what is computed from them: a query's in its row, a key's in the rows of its KV head, a
+    value's in its element of them, whatever the key's weight is. Everything else has the bits of the clean run."""
+    from paper_2510_18546_amd import step
+    cfg, w = workload(61, 2, 3, 2, d, 1, [150, 149], 2)
+    print(f"[case] {cfg} splits {splits}", flush=True)
+    out0, mass0 = _run(step, w, splits)
+    assert np.isfinite(out0).all() and np.isfinite(mass0).all()
+
+    q = w.q.copy()
+    w.q[1, 0, 4, 5] = np.nan
+    out, mass = _run(step, w, splits)
+    assert np.isnan(out[1, 0, 4]).all() and np.isnan(mass[1, 0, 4]).all()
+    out[1, 0, 4], mass[1, 0, 4] = out0[1, 0, 4], mass0[1, 0, 4]
+    assert np.array_equal(out, out0) and np.array_equal(mass, mass0)
+    w.q[:] = q
+
+    # a key of a group that both agents hold, in KV head 1
+    for bad in (np.nan, np.inf):
+        k = w.k_pool.copy()
+        w.k_pool[0, 1, 40, 7] = bad
+        out, mass = _run(step, w, splits)
+        rows = slice(3, 6)
+        # (an infinite key is turned: infinite in two dimensions; a row's score is either infinity or NaN)
+        low = ~np.isnan(out[:, :, rows]).any(-1)
+        assert not low.any() or (bad == np.inf and np.isfinite(out[:, :, rows][low]).all())
+        assert low.mean() < 1.0
+        assert np.array_equal(out[:, :, :3], out0[:, :, :3]) and np.array_equal(mass[:, :, :3], mass0[:, :, :3])
+        w.k_pool[:] = k
+
+    # a value, under its key's usual weight and under a weight that underflows
+    for bad in (np.nan, np.inf):
+        for far in (False, True):
+            k, v = w.k_pool.copy(), w.v_pool.copy()
+            if far:                                  # (towards no row's query: the slowest pair, against every query)
+                w.q[..., d // 2 - 1] = 8.0
+                w.k_pool[0, 1, 40] = 0
+                w.k_pool[0, 1, 40, d // 2 - 1] = -3000.0
+            base, mbase = _run(step, w, splits)
+            w.v_pool[0, 1, 40, 9] = bad
+            out, mass = _run(step, w, splits)
+            assert not np.isfinite(out[:, :, 3:6, 9]).any(), (bad, far)
+            out[:, :, 3:6, 9] = base[:, :, 3:6, 9]
+            assert np.array_equal(out, base) and np.array_equal(mass, mbase), (bad, far)
+            w.q[:], w.k_pool[:], w.v_pool[:] = q, k, v
