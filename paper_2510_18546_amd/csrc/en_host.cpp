@@ -302,6 +302,41 @@ static int once_splits(const en_pool *pool, long base, int tiles)
     return 0;
 }
 
+// KV splits of a decode step in the streaming kernel: one wave per (agent, KV head, split); the two LDS stages
+// of a wave let two waves share a compute unit, and a wave takes about
+// 2 us per 64-key tile whatever the load: as many splits as give every
+// compute unit its two waves (measured on 1 and 4 agents x 8 K tokens:
+// more waves than that only add start-up and merge work), down to one
+// tile per split (one agent over 1.7 K tokens: 18.9 us per step with at
+// least four tiles per split, 15.0 with two, 12.8 with one: the waves run
+// side by side and the merge costs the same launch either way).
+// Long contexts of many agents are the exception: two
+// splits measured faster than one (0.73 against 0.78 ms on 64 agents x
+// 16 K tokens).
+static int streaming_splits(const en_pool *pool, long base, int tiles)
+{
+    long want = (2L * pool->n_cu + base - 1) / base;
+    if (want < 2 && tiles >= 64)
+        want = 2;
+    want = std::max<long>(1, std::min<long>(std::min<long>(want, tiles), EN_MAX_SPLITS));
+    // The fewest splits that keep the longest split as short do with fewer units and merges:
+    // 97 tiles are two for some of 64 splits and two for nearly all of 49 (one agent, 6 K
+    // tokens: 14.7 -> 13.9 us per step; 137 tiles as 46 x 3 instead of 64 x 2 or 3: 17.5 ->
+    // 17.1). Not when only a few splits are three tiles or longer: those then run while the
+    // others have finished, and making all of them as long costs more than it saves (65 tiles
+    // of two agents as 22 x 3 instead of 32 splits: 16.1 -> 16.6 us).
+    const long longest = (tiles + want - 1) / want;
+    const long n_longest = tiles - (longest - 1) * want;       // splits of that length
+    if (longest <= 2 || 8 * n_longest >= want)
+        want = (tiles + longest - 1) / longest;
+    return int(want);
+}
+// Waves per (agent, KV head, split) there, each with partial results of its own: see en_attn_sub.
+static int streaming_sub(const en_pool *pool, long base, int n_splits)
+{
+    return base * n_splits <= 2L * pool->n_cu ? 2 : 1;
+}
+
 // (once: decode steps may have the splits of attn_once_kernel, of which there are more where they come in several rounds)
 static int choose_splits(const en_pool *pool, const en_plan *pl, bool once = true)
 {
@@ -312,40 +347,18 @@ static int choose_splits(const en_pool *pool, const en_plan *pl, bool once = tru
     // tiles), is shortest; at least four key tiles per split.
     const int r = pool->r;
     if (computes_bf16(pool->d.dtype) && r * pl->Nq <= EN_ROWS_PER_WAVE) {
-        // decode path, where attn_once_kernel does not take it (once_splits):
-        // one wave per (agent, KV head, split); the two LDS stages
-        // of a wave let two waves share a compute unit, and a wave takes about
-        // 2 us per 64-key tile whatever the load: as many splits as give every
-        // compute unit its two waves (measured on 1 and 4 agents x 8 K tokens:
-        // more waves than that only add start-up and merge work), down to one
-        // tile per split (one agent over 1.7 K tokens: 18.9 us per step with at
-        // least four tiles per split, 15.0 with two, 12.8 with one: the waves run
-        // side by side and the merge costs the same launch either way).
-        // Long contexts of many agents are the exception: two
-        // splits measured faster than one (0.73 against 0.78 ms on 64 agents x
-        // 16 K tokens).
         const long base = long(pl->B) * pool->d.n_kv_heads;
         const int tiles = std::max(1, (pl->max_ctx_len + EN_KEY_TILE - 1) / EN_KEY_TILE);
-        if (once && pool->r * pl->Nq <= EN_ONCE_ROWS) {
+        const int streaming = streaming_splits(pool, base, tiles);
+        if (once && r * pl->Nq <= EN_ONCE_ROWS) {
             const int n = once_splits(pool, base, tiles);
-            if (n > 0)
+            // A step that the streaming kernel writes out directly, from sums in fp32, is not split: its partial results
+            // would be rounded to bf16 on the way. (That costs 20 - 50 % of the time of more than 512 pairs over 0.2 -
+            // 0.6 K tokens: 75 agents x 8 heads, 0.6 K, 38.7 us with five splits, 65.2 with one.)
+            if (n == 1 || (n > 0 && streaming * streaming_sub(pool, base, streaming) > 1))
                 return n;
         }
-        long want = (2L * pool->n_cu + base - 1) / base;
-        if (want < 2 && tiles >= 64)
-            want = 2;
-        want = std::max<long>(1, std::min<long>(std::min<long>(want, tiles), EN_MAX_SPLITS));
-        // The fewest splits that keep the longest split as short do with fewer units and merges:
-        // 97 tiles are two for some of 64 splits and two for nearly all of 49 (one agent, 6 K
-        // tokens: 14.7 -> 13.9 us per step; 137 tiles as 46 x 3 instead of 64 x 2 or 3: 17.5 ->
-        // 17.1). Not when only a few splits are three tiles or longer: those then run while the
-        // others have finished, and making all of them as long costs more than it saves (65 tiles
-        // of two agents as 22 x 3 instead of 32 splits: 16.1 -> 16.6 us).
-        const long longest = (tiles + want - 1) / want;
-        const long n_longest = tiles - (longest - 1) * want;       // splits of that length
-        if (longest <= 2 || 8 * n_longest >= want)
-            want = (tiles + longest - 1) / longest;
-        return int(want);
+        return streaming;
     }
     if (!computes_bf16(pool->d.dtype)) {
         // fp32: a workgroup takes 16 rows, its eight waves share the split's keys 16 at a time, one block
@@ -896,7 +909,7 @@ int en_attn_sub(const en_pool *pool, const en_plan *pl, int n_rows, int n_splits
 {
     if (!decode_kernel_fits(pool, n_rows) || en_attn_once_tiles(pool, pl, n_rows, n_splits))
         return 1;
-    return long(pl->B) * pool->d.n_kv_heads * n_splits <= 2L * pool->n_cu ? 2 : 1;
+    return streaming_sub(pool, long(pl->B) * pool->d.n_kv_heads, n_splits);
 }
 
 // EnAttnArgs::once_tiles of a step with n_splits KV splits.
