@@ -347,9 +347,8 @@ int segmented_decode_step(en_pool *pool, en_plan *plan, int32_t q_first, int32_t
  * library: the pool and the plan must already have been through gather_rope
  * (which is where the rotary table and the plan's descriptor block are created;
  * a decode step follows a gather anyway), else INVALID_ARG.
- * A step whose scratch exceeds the static array (en_decode_workspace_bytes, or
- * what the fewer splits of the streaming decode kernel need, which the step then
- * takes) is refused with CAPACITY: one agent over 8.7 K tokens needs 0.5 MB, 64 agents over
+ * A step whose scratch (en_decode_workspace_bytes) exceeds the static array is
+ * refused with CAPACITY: one agent over 8.7 K tokens needs 0.5 MB, 64 agents over
  * 16 K tokens 3.2 MB.
  * All calls on one GPU share that GPU's array, which keeps what the last call
  * left in it (the kernels write every entry they later read; nothing relies on

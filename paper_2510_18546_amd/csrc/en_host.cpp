@@ -281,23 +281,24 @@ static int once_rounds(const en_pool *pool, int per)
 {
     return per <= 2 ? (pool->d.head_dim == 64 ? 16 : 6) : per == 3 ? 2 : 1;
 }
-// KV splits for it, or 0: one where that is a whole context, else splits as short as one round allows. (Splits of one tile
-// only up to two workgroups to a compute unit: 2 agents x 2 K tokens 9.6 us with one, 9.4 with two, one agent over 1.5 K 8.5
-// either way, but 4 x 2 K, four workgroups of one tile, 13.2, with five 11.6.)
-static int once_splits(const en_pool *pool, long base, int tiles)
+// KV splits for it, at most n_max, or 0: one where that is a whole context, else splits as short as one round allows. (Splits
+// of one tile only up to two workgroups to a compute unit: 2 agents x 2 K tokens 9.6 us with one, 9.4 with two, one agent
+// over 1.5 K 8.5 either way, but 4 x 2 K, four workgroups of one tile, 13.2, with five 11.6.)
+static int once_splits(const en_pool *pool, long base, int tiles, int n_max)
 {
     const auto splits = [tiles](int per) { return (tiles + per - 1) / per; };
-    if (once_fits(pool, base, tiles, 1, 1))
+    const auto fits = [&](int per, int n, int rounds) { return n <= n_max && once_fits(pool, base, per, n, rounds); };
+    if (fits(tiles, 1, 1))
         return 1;
     for (int per = base * tiles <= 2L * pool->n_cu ? 1 : 2; per <= EN_ONCE_TILES; ++per)
-        if (once_fits(pool, base, per, splits(per), 1)) {
+        if (fits(per, splits(per), 1)) {
             // the fewest splits that are as short as that; but all there may be where only a few of those are, from three
             // tiles on (see below)
-            const int most = std::min(tiles, EN_MAX_SPLITS), n_longest = tiles - (per - 1) * most;
-            return per > 2 && per == splits(most) && 8 * n_longest < most && once_fits(pool, base, per, most, 1) ? most : splits(per);
+            const int most = std::min(tiles, n_max), n_longest = tiles - (per - 1) * most;
+            return per > 2 && per == splits(most) && 8 * n_longest < most && fits(per, most, 1) ? most : splits(per);
         }
     for (int per = 2; per <= 3; ++per)
-        if (once_fits(pool, base, per, splits(per), once_rounds(pool, per)))
+        if (fits(per, splits(per), once_rounds(pool, per)))
             return splits(per);
     return 0;
 }
@@ -337,7 +338,7 @@ static int streaming_sub(const en_pool *pool, long base, int n_splits)
     return base * n_splits <= 2L * pool->n_cu ? 2 : 1;
 }
 
-// (once: decode steps may have the splits of attn_once_kernel, of which there are more where they come in several rounds)
+// (once: decode steps may have the splits of attn_once_kernel)
 static int choose_splits(const en_pool *pool, const en_plan *pl, bool once = true)
 {
     // One workgroup covers 8 (head, 32-query block) pairs of one KV head and
@@ -351,11 +352,14 @@ static int choose_splits(const en_pool *pool, const en_plan *pl, bool once = tru
         const int tiles = std::max(1, (pl->max_ctx_len + EN_KEY_TILE - 1) / EN_KEY_TILE);
         const int streaming = streaming_splits(pool, base, tiles);
         if (once && r * pl->Nq <= EN_ONCE_ROWS) {
-            const int n = once_splits(pool, base, tiles);
-            // A step that the streaming kernel writes out directly, from sums in fp32, is not split: its partial results
-            // would be rounded to bf16 on the way. (That costs 20 - 50 % of the time of more than 512 pairs over 0.2 -
-            // 0.6 K tokens: 75 agents x 8 heads, 0.6 K, 38.7 us with five splits, 65.2 with one.)
-            if (n == 1 || (n > 0 && streaming * streaming_sub(pool, base, streaming) > 1))
+            // No more partial results than the streaming kernel leaves: scratch that holds a step of that kernel holds it
+            // either way, and a step that it writes out directly, from sums in fp32, is not rounded to bf16 on the way.
+            // (More would mostly be faster, with up to 155 times the scratch. us with this limit / without, the context where
+            // the last step left it and, in parentheses, from HBM: 16 agents x 8 heads, 1.6 K tokens, 8 / 13 partial results,
+            // 26.4 / 25.7 (32.7 / 29.6), rows of 64 values, 1.3 K, 16.3 / 13.9 (18.6 / 15.8); 64 x 8, 0.5 K, 31.6 / 32.1
+            // (40.3 / 36.8), of 64 values 23.7 / 18.4 (25.7 / 21.1); 75 x 8, 0.6 K, 1 / 5, 65.4 / 38.5 (71.2 / 48.9).)
+            const int n = once_splits(pool, base, tiles, std::min(EN_MAX_SPLITS, streaming * streaming_sub(pool, base, streaming)));
+            if (n > 0)
                 return n;
         }
         return streaming;
@@ -1441,7 +1445,7 @@ extern "C" size_t en_decode_workspace_bytes(const en_pool *pool, const en_plan *
 static int segmented_decode_step_impl(en_pool *pool, en_plan *plan, int32_t q_first, int32_t n_rows,
                                      const void *q_dev, const void *k_rows_dev, const void *v_rows_dev,
                                      void *kc_dev, void *vt_dev, void *out_dev, float *mass_out_dev,
-                                     void *ws_dev, size_t ws_bytes, void *stream, int n_splits = 0)
+                                     void *ws_dev, size_t ws_bytes, void *stream)
 {
     if (!pool || !plan || !q_dev || !k_rows_dev || !v_rows_dev || !kc_dev || !vt_dev || !out_dev)
         return fail(EN_ERR_INVALID_ARG, "segmented_decode_step: null argument");
@@ -1480,8 +1484,7 @@ static int segmented_decode_step_impl(en_pool *pool, en_plan *plan, int32_t q_fi
     if (e != 0)
         return hip_fail((hipError_t)e, "segmented_decode_step context append");
     // 2. attention of the step's rows over everything before and including them
-    if (n_splits == 0)
-        n_splits = step_splits(pool, plan, n_rows);
+    int n_splits = step_splits(pool, plan, n_rows);
     if (!ws_dev)
         n_splits = splits_without_scratch(pool, plan, n_rows, n_splits);
     if ((rc = run_attention(pool, plan, q_dev, kc_dev, vt_dev, out_dev, ws_dev, ws_bytes, stream, q_first, n_rows,
@@ -1520,14 +1523,7 @@ static int segmented_decode_step_static_impl(en_pool *pool, en_plan *plan, int32
         return fail(EN_ERR_INVALID_ARG, "segmented_decode_step_static: plan belongs to another pool");
     if (n_rows <= 0)
         return fail(EN_ERR_OUT_OF_RANGE, "segmented_decode_step_static: n_rows = %d", n_rows);
-    // the partial results of a step in several rounds of attn_once_kernel can take more than the array holds where those
-    // of the streaming kernel do not
-    int n_splits = step_splits(pool, plan, n_rows);
-    size_t need = en_ws_layout_for(pool, plan, n_rows, n_splits).parts_off;
-    if (need > EN_STATIC_SCRATCH_BYTES) {
-        n_splits = step_splits(pool, plan, n_rows, false);
-        need = en_ws_layout_for(pool, plan, n_rows, n_splits).parts_off;
-    }
+    const size_t need = en_ws_layout_for(pool, plan, n_rows, step_splits(pool, plan, n_rows)).parts_off;
     if (need > EN_STATIC_SCRATCH_BYTES)
         return fail(EN_ERR_CAPACITY, "segmented_decode_step_static: the step needs %zu bytes of scratch, the static "
                     "scratch holds %zu; use segmented_decode_step with a workspace of the caller's", need,
@@ -1541,7 +1537,7 @@ static int segmented_decode_step_static_impl(en_pool *pool, en_plan *plan, int32
     if (e != 0)
         return hip_fail((hipError_t)e, "segmented_decode_step_static: address of the static scratch");
     return segmented_decode_step_impl(pool, plan, q_first, n_rows, q_dev, k_rows_dev, v_rows_dev, kc_dev, vt_dev,
-                                      out_dev, mass_out_dev, ws, ws_bytes, stream, n_splits);
+                                      out_dev, mass_out_dev, ws, ws_bytes, stream);
 }
 extern "C" int segmented_decode_step_static(en_pool *pool, en_plan *plan, int32_t q_first, int32_t n_rows,
                                             const void *q_dev, const void *k_rows_dev, const void *v_rows_dev,

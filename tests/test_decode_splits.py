@@ -43,3 +43,28 @@ def test_steps_written_out_directly_stay_so():
             met += 1
             assert plan.info.n_splits == 1, (agents, kv, r, d, n_new, tiles)
     assert met > 20
+
+
+def align(n):
+    return -(-n // 256) * 256
+
+
+def scratch(agents, heads, rows, segments, d, partial):
+    """Bytes of a step's scratch with `partial` results per row: (reference, sum) pairs of the row and of its buckets,
+    accumulators of the reduced masses, and what more than one result needs: the merged pair, the outputs in bf16."""
+    n = agents * heads * rows
+    at = align(align(partial * n * 8) + partial * n * (segments + 1) * 8)
+    at = align(at + agents * (segments + 1) * 8)
+    return align(align(at + n * 8) + partial * n * d * 2) if partial > 1 else at
+
+
+def test_no_more_scratch_than_the_streaming_kernel_needs():
+    """Scratch sized for a step of the streaming kernel holds the step whichever kernel takes it, the plan's own workspace
+    holds its steps of a row where it held those, and so does the static array."""
+    less = 0
+    for pool, plan, agents, kv, r, d, n_new, base, tiles in plans(2, 600):
+        before = scratch(agents, kv * r, 1, plan.info.max_segments, d, streaming(base, tiles)[1])
+        now = B.decode_workspace_bytes(pool, plan, 1)
+        assert now <= before, (agents, kv, r, d, n_new, tiles)
+        less += now < before
+    assert less > 100
