@@ -623,7 +623,8 @@ __global__ __launch_bounds__(128 * TPS) void attn_once_kernel(EnAttnArgs a)
     // ---- the tile's loads: the wave's own K rows, half of the pair's V^T rows. Inside a row the 16-byte chunks are
     // exchanged (XOR) so that the operand reads of 16 consecutive lanes meet distinct banks.
     // (a wave without a tile asks for bytes past the end, which is no trip to memory: with a branch here the waits for the
-    // queries would have to be waits for everything) ----
+    // queries would have to be waits for everything. Its vector offset alone puts them there: a scalar offset beyond the
+    // buffer may be taken from the buffer's length before the comparison) ----
     {
         typedef __attribute__((address_space(3))) char *lptr;
         constexpr int RSRC = 0x00027000;
@@ -634,18 +635,19 @@ __global__ __launch_bounds__(128 * TPS) void attn_once_kernel(EnAttnArgs a)
         const int krow = lane / KCPR;            // row inside a loader block
         const int kpat = D == 128 ? krow : (krow >> 1) & 3;
         const uint32_t past = active ? 0u : 1u << 31;
+        const int kat = active ? kb * ROWB : 0, vat = active ? tile * VROWB : 0;
         const uint32_t koff = (uint32_t)(krow * ROWB + ((lane % KCPR) ^ kpat) * 16) | past;
         static_for<NBK>([&](auto j_tag) {
             constexpr int j = decltype(j_tag)::value;
             constexpr int bits = D == 128 ? (j & 1) | ((j >> 1) & 2) : j >> 1;        // bits 2, 3 of the row's pattern
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, (lptr)(kst + j * 1024), 16, koff ^ (bits << 6), kb * ROWB + j * 1024, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, (lptr)(kst + j * 1024), 16, koff ^ (bits << 6), kat + j * 1024, 0, 0);
         });
         // loader block 2 j + u is the V^T rows 16 j + 8 u ..
         const uint32_t voff = (uint32_t)((8 * u + lane / 8) * a.T * 2 + ((lane % 8) ^ (4 * u + lane / 16)) * 16) | past;
 #pragma unroll
         for (int j = 0; j < NBV; ++j)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, (lptr)(vst + (2 * j + u) * 1024), 16, voff,
-                                                     tile * VROWB + 16 * j * a.T * 2, 0, 0);
+                                                     vat + 16 * j * a.T * 2, 0, 0);
     }
 
     // ---- Q: rotate at L_c + i, scale, round to bf16 ----
