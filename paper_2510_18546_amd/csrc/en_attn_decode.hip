@@ -544,7 +544,7 @@ __global__ __launch_bounds__(128 * TPS) void attn_once_kernel(EnAttnArgs a)
     const int col = lane % 16, g = lane / 16;
     const int r = a.by_r.n;
     const int rows = r * a.Nq;                   // at most 16
-    const bool row_valid = col < rows;           // (the other columns compute on row 0 once more, for nobody)
+    const bool row_valid = col < rows;           // (the other columns compute on zero queries, for nobody)
     const int hl = row_valid ? divided(col, a.by_nq) : 0;
     const int i_row = row_valid ? col - hl * a.Nq : 0;
     const int hq = kvh * r + hl;
@@ -661,6 +661,10 @@ __global__ __launch_bounds__(128 * TPS) void attn_once_kernel(EnAttnArgs a)
                 qf[ks][j] = (bf16_t)((x1 * cs[ks][j] - x2 * sn[ks][j]) * a.scale_log2e);
                 qf[ks + NKS / 2][j] = (bf16_t)((x2 * cs[ks][j] + x1 * sn[ks][j]) * a.scale_log2e);
             }
+    } else {
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks)
+            qf[ks] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
     }
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks)
