@@ -100,6 +100,12 @@ static int kv_pool_create_impl(const en_pool_desc *desc, void *k_dev, void *v_de
         return fail(EN_ERR_CAPACITY, "kv_pool_create: out of host memory for %d group lengths", desc->n_groups);
     }
     p->r = desc->n_q_heads / desc->n_kv_heads;
+    // Once and for all: splits, scratch layouts and kernels are chosen by it, some when a plan is made and some when a call
+    // comes, and have to agree. (256 where there is no device, for the planner by itself.)
+    int dev = 0, n_cu = 0;
+    if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+        n_cu > 0)
+        p->n_cu = n_cu;
     *out = p;
     return EN_OK;
 }
@@ -245,11 +251,6 @@ static int pool_ensure_device(en_pool *p)
         return hip_fail(e, "hipMemcpy(rotary table)");
     if ((e = hipMemcpy(p->d_sin, s.data(), n * sizeof(float), hipMemcpyHostToDevice)) != hipSuccess)
         return hip_fail(e, "hipMemcpy(rotary table)");
-    int dev = 0;
-    hipDeviceProp_t prop;
-    if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess &&
-        prop.multiProcessorCount > 0)
-        p->n_cu = prop.multiProcessorCount;
     // set-up is also where this device's address of the static scratch is looked up, so that
     // segmented_decode_step_static finds it ready (it asks again by itself if this failed)
     void *sp = nullptr;

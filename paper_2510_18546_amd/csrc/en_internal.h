@@ -34,7 +34,7 @@ struct en_pool {
     // device side, created on first GPU use
     float *d_cos = nullptr;       // [max_ctx, D/2]
     float *d_sin = nullptr;
-    int n_cu = 256;
+    int n_cu = 256;               // compute units, from the pool's creation on
     // descriptor blocks of destroyed plans, kept for reuse (bytes, pointer)
     mutable std::vector<std::pair<size_t, int32_t *>> desc_cache;
     // plans made on this pool and not yet destroyed: a pool that is destroyed
