@@ -564,7 +564,7 @@ __global__ __launch_bounds__(256) void mass_few_rows_kernel(EnMassArgs a)
 // cluster: score of every (object, segment) pair and the join / new-group
 // decision of Section 3.3. Scores: grid (Smax+1, n_obj, B), 256 threads, the
 // block sums the masses that the object's (token, head) pairs put on one bucket.
-// Decision: one thread per (agent, object) walks that object's scores.
+// Decision: one wave per (agent, object), its lanes take that object's scores in turn.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void cluster_score_kernel(EnClusterArgs a)
 {

@@ -20,9 +20,18 @@ def workload(seed, agents, r, kv, d, nq, lens, n_sel):
     return cfg, w
 
 
-def both(step, oracle, w, splits):
+def tiles_of(st, n_rows=None):
+    """Key tiles a split of the plan's step in attn_once_kernel, 0: the streaming kernel."""
+    import ctypes as C
+    from paper_2510_18546_amd import binding as B
+    rule = B.load()["_Z18en_attn_once_tilesPK7en_poolPK7en_planii"]
+    return rule(st.pool.handle, st.plan.handle, C.c_int(n_rows or st.cfg.n_new), C.c_int(st.plan.info.n_splits))
+
+
+def both(step, oracle, w, splits, tiles=None):
     import torch
     st = step.PlanningStep(w, n_splits=splits)
+    assert tiles_of(st) == tiles if tiles else tiles_of(st) > 0
     st.ws.fill_(0xFF)                            # a NaN pattern: nothing is read that was not written
     print(f"[case] {w.cfg} splits {splits}", flush=True)
     st.run()
@@ -59,6 +68,27 @@ def test_many_short_segments(oracle, d):
     lens = [int(x) for x in np.random.default_rng(7).integers(0, 6, 80)]
     cfg, w = workload(31, 3, 4, 2, d, 2, lens, 80)
     both(step, oracle, w, None)
+
+
+@pytest.mark.parametrize("agents,kv,d,tokens,splits,tiles", [
+    (64, 4, 128, 820, 7, 2),       # 3.5 rounds of two workgroups a compute unit
+    (128, 4, 128, 240, 2, 2),      # two
+    (32, 4, 128, 560, 3, 3),       # 1.5 rounds of one
+    (150, 4, 128, 100, 1, 2),      # one split, 1.2 rounds, written out directly
+    (256, 4, 64, 240, 2, 2),       # 1.6 rounds of five
+    (200, 4, 64, 170, 1, 3),       # 1.04 rounds of three
+    (96, 4, 64, 560, 3, 3),        # 1.5
+])
+def test_several_rounds(oracle, agents, kv, d, tokens, splits, tiles):
+    """More workgroups than the chip holds at once, agents of unequal length among them: outputs, masses, merge."""
+    from paper_2510_18546_amd import step
+    lens = [tokens - 70, 37, 33, 0]
+    cfg, w = workload(agents, agents, 2, kv, d, 1, lens, 4)
+    lists = [[0, 1, 2, 3], [3, 1], [2], [1, 0], []]
+    lists = [np.array(lists[b % 5], np.int32) for b in range(agents)]
+    w.sel = np.concatenate(lists)
+    w.sel_ptr = np.cumsum([0] + [len(x) for x in lists]).astype(np.int32)
+    both(step, oracle, w, splits, tiles)
 
 
 def test_agents_of_unequal_length(oracle):
