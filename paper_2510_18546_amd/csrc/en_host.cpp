@@ -264,15 +264,23 @@ static int pool_ensure_device(en_pool *p)
 // ---------------------------------------------------------------------------
 // Whether attn_once_kernel takes a decode step of n splits of at most `per` tiles for each of `base` (agent, KV head)
 // pairs: where its workgroups, as many of a compute unit's as its LDS holds, come in few enough rounds. us per decoded
-// token (attention and merge), streaming kernel / this one:
-// - one round: one agent of 8 heads, 0.25 K tokens 11.0 / 7.2 (one split, no merge), 1.5 K 11.4 / 8.4, 4 K 12.9 / 9.7, 6 K
-//   14.1 / 10.2, 8 K (five tiles) 16.5 / 11.4, rows of 64 values 12.7 / 9.2; 16 agents, 2 heads, 0.4 K 11.9 / 8.3;
-// - two tiles, two workgroups to a compute unit that relieve one another, in up to six rounds: 16 agents x 0.8 K (1.75
-//   rounds) 21.7 / 17.0, x 1.6 K (3.3) 28.5 / 26.5, 16 x 6 K of 2 heads (3.1) 26.5 / 25.8; but 16 x 3 K (6.3) 41.7 / 43.0,
-//   64 x 4 K of 2 heads (8.2) 51.6 / 52.9. Rows of 64 values in up to 16: 64 x 4 K of 2 heads (3.3) 32.7 / 27.9, 64 x 2.5 K
-//   (8.4) 75.3 / 68.8, 256 x 1 K (12.8) 115.7 / 113.4; but 64 x 8 K (25) 198 / 209;
-// - three tiles, one workgroup to a compute unit, in up to two (longer contexts than 64 splits of two hold): 10 K (1.7)
-//   18.3 / 16.4; two agents x 8 K (2.7) 23.6 / 24.4; four or five tiles in one: 16 K as 52 x 5 (1.6) 22.4 / 23.3.
+// token (attention and merge), streaming kernel / this one, over a context that the last token left in the caches and, in
+// parentheses, over one from HBM, as a model of many layers finds it:
+// - one round, either with its own splits: one agent of 8 heads, 0.25 K tokens 12.1 / 6.5 (14.1 / 8.2; one split, no
+//   merge), 1.5 K 11.6 / 7.9 (13.8 / 9.6), 4 K 12.5 / 8.7 (16.0 / 12.0), 8 K 15.4 / 10.3 (18.5 / 14.1), 9.6 K 17.0 / 12.7
+//   (19.7 / 15.4), rows of 64 values, 4 K, 11.3 / 7.9 (13.7 / 10.2); 4 agents x 0.4 K 12.1 / 8.0 (14.2 / 9.9);
+// - two tiles, two workgroups to a compute unit that relieve one another (five with rows of 64 values), the same splits in
+//   both: 16 agents x 8 heads, 13 splits (3.25 rounds) 41.5 / 25.3 (44.6 / 28.8), 24 (6) 61.7 / 40.1 (67.0 / 46.0), 64 x 8,
+//   6 (6) 70.3 / 38.9 (75.3 / 47.7), rows of 64 values, 33 (13.2) 128.3 / 107.4 (128.8 / 107.7), 128 x 8, 20 (16) 161.9 /
+//   136.3 (162.2 / 136.6); one split of one or two: 384 x 8 (6 rounds) 95.8 / 40.8 (101.2 / 47.5), of 64 values, 2560 x 8
+//   (16) 264.9 / 130.7 (265.9 / 131.2). With its own splits of that length, no more results than the other's (see
+//   choose_splits): 16 x 8, 0.8 K (1.75 rounds) 21.7 / 16.6 (24.8 / 19.0), 32 x 8, 0.5 K (2) 21.5 / 20.3 (26.6 / 22.9), 8 x
+//   8, 2 K (2) 21.6 / 19.0 (25.3 / 21.5);
+// - three tiles, one workgroup to a compute unit (three with rows of 64 values), the same splits: one agent, 64 splits (2
+//   rounds) 18.7 / 17.1 (21.1 / 19.4), 16 x 8, 4 (2) 19.8 / 16.8 (21.8 / 18.9), of 64 values, 12 (2) 25.0 / 19.5 (27.9 /
+//   22.4). Two agents x 8 K with its own (2.7 rounds) 23.6 / 24.4; four or five tiles in more than one: 16 K as 52 x 5 (1.6)
+//   22.4 / 23.3.
+// Rounds beyond these are not measured.
 static bool once_fits(const en_pool *pool, long base, int per, int n, int rounds)
 {
     const long slots = EN_ONCE_TILES * 128 / pool->d.head_dim;       // tiles that the LDS of a compute unit holds
@@ -900,16 +908,16 @@ static bool decode_kernel_fits(const en_pool *pool, int n_rows)
 }
 
 // Waves per (agent, KV head, split) in the streaming decode kernel (attn_once_kernel leaves one partial result whatever
-// its waves, and takes most of the steps below; the figures are from before it did). One wave alone on its SIMD
+// its waves). One wave alone on its SIMD
 // takes about 2 us per 64-key tile whatever the load, and the kernel's LDS stages leave room for
 // two workgroups per compute unit: when a step has no more units than that, two waves share each
 // unit's tiles, each takes every other 32-key block and leaves partial results of its own (the
 // scratch then holds n_splits * 2 of them per row; the units' key ranges stay whole tiles).
-// Measured per decoded token with 8 KV heads, two waves against one: 10.9 / 12.4 us (1 agent,
-// 25 splits), 11.3 / 12.5 (2 agents, 17 splits), 12.6 / 13.9 (2 agents, 32 splits), 13.1 / 14.0
-// (4 agents, 16 splits), 12.9 / 13.0 (1 agent, 4K tokens, 64 splits), 17.5 / 18.0 (1 agent, 8.7K
-// tokens, 64 splits); the attention launch itself 9.6 / 10.0 us in the last but one case. (The
-// merge of twice as many partial results must not eat the gain: see its lane groups.)
+// Of what attn_once_kernel leaves to it, per decoded token of 8 KV heads, two waves against one, the context in the caches
+// and, in parentheses, from HBM: one agent x 16 K tokens 20.8 / 22.1 us (24.2 / 25.0), two 33.2 / 34.0 (36.3 / 36.9), 8
+// 102.0 / 103.9 (102.3 / 104.1), 16 x 1.6 K 26.1 / 28.1 (30.8 / 31.7), 16 x 8 K 135.9 / 136.6 (136.0 / 136.6), 64 x 0.6 K
+// 35.0 / 38.2 (42.0 / 43.2), of 64 values 26.2 / 27.8 (28.0 / 29.3). Steps of 32 rows a head, whose partial results are as
+// many more for the merge, would do with one: 1 x 8 K 21.6 / 19.2 (23.3 / 21.3), 16 x 0.8 K 25.2 / 23.4 (27.3 / 25.6).
 int en_attn_sub(const en_pool *pool, const en_plan *pl, int n_rows, int n_splits)
 {
     if (!decode_kernel_fits(pool, n_rows) || en_attn_once_tiles(pool, pl, n_rows, n_splits))
