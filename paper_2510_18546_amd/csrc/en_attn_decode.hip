@@ -480,9 +480,9 @@ __global__ __launch_bounds__(64 * SUB) void attn_decode_kernel(EnAttnArgs a)
 // its loads out before anything is waited for, one barrier before the products with the values, one before the waves'
 // results meet in LDS. The chain that is left is argument, header, load, two products, exchange, store: 5.7 us on average
 // for five tiles (7.1 the slowest workgroup), 3.2 for two, of which the loads' way through the vector memory path of a
-// compute unit (64 bytes a clock) is 1.5 and 0.5. Per decoded token with the merge, streaming kernel / this one: 8 K tokens
-// 16.5 / 11.4 us, 1.5 K 11.4 / 8.4, 0.25 K, with one split and no merge, 11.0 / 7.2. See once_fits for more, and for which
-// steps it takes.
+// compute unit (64 bytes a clock) is 1.5 and 0.5. Per decoded token with the merge, streaming kernel / this one, in
+// parentheses over a context from HBM: 8 K tokens 15.4 / 10.3 us (18.5 / 14.1), 1.5 K 11.6 / 7.9 (13.8 / 9.6), 0.25 K, with
+// one split and no merge, 12.1 / 6.5 (14.1 / 8.2). See once_fits for more, and for which steps it takes.
 //
 // Products are 16 x 16 x 32: the 16 columns are the r * N_q rows, half the width of the kernel above, and a score product's
 // chain of dependent instructions is D / 32 long instead of D / 16. A wave takes the maximum of its own 32 keys as its rows'
